@@ -1,82 +1,343 @@
-// Generic fp32-FMA GEMM with element strides:  C(m,n) = sum_k A(m,k) · B(n,k).
-// Serves the ATP_F32 storage path (true fp32 arithmetic, 1e-4 parity) and every
-// shape or alignment the MFMA kernel does not cover.  64×64 block tile, 16-deep
-// k slices staged k-major in LDS, 4×4 register tile per thread.
+// GEMM with element strides on the matrix cores:  C(m,n) = sum_k A(m,k) · B(n,k).
+// Serves the ATP_F32 storage path (v_mfma_f32_32x32x2f32: fp32 products, fp32 accumulation) and, on the
+// bf16 path, every shape or alignment the asynchronous kernel of gemm_mfma.hip does not cover.
+//
+// A tile goes global -> registers -> LDS, because only this way can an operand be turned, widened, added to its lo
+// plane, masked at a ragged edge and read at any alignment.  Tile kt is multiplied out of one of two LDS buffers
+// while tile kt+1 waits in registers and tile kt+2 is on its way: what bounds these products at the sizes they
+// meet is the latency of a few k-tiles, not the arithmetic.  An operand may be contiguous along k or along its rows (a
+// transposed operand needs no pass of its own); LDS always holds rows of k, padded by 16 bytes, so a fragment read is
+// one conflict-free 16-byte access.
+//
+// Tile choice.  The fp32 matrix cores do 256 flop per clock and compute unit, so what counts is that the 256 compute
+// units have work: 128×128 tiles when at least 192 of them exist, else 64×64, else 32×32 with four waves that share
+// the tile and split k (their sums meet in LDS at the end).
+// Measured on one MI355X against a scalar-FMA kernel with 64×64 tiles: four products (512×768)·(768×128) 151 -> 14 µs, their
+// Gram matrices (128×128, k = 512) 103 -> 10 µs, the block at that shape 5.08 -> 1.47 ms.
 #include "common.h"
+
+#include <type_traits>
 
 namespace atp {
 namespace {
 
-template <typename T> __device__ __forceinline__ float ldf(const T* p);
-template <> __device__ __forceinline__ float ldf<float>(const float* p) { return *p; }
-template <> __device__ __forceinline__ float ldf<bf16_t>(const bf16_t* p) { return bf2f(*p); }
-
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + expf(-x)); }
 
-constexpr int SB = 64, SK = 16;
+__device__ __forceinline__ bf16x8 u4_bf16x8(const uint4& u) {
+    union { uint4 u; bf16x8 b; } c;
+    c.u = u;
+    return c.b;
+}
 
-template <typename TA, typename TB, bool SWIGLU>
-__global__ void __launch_bounds__(256) gemm_simt_kernel(SimtArgs p) {
-    __shared__ float As[SK][SB + 1];
-    __shared__ float Bs[SWIGLU ? 2 : 1][SK][SB + 1];
-    const int bz = blockIdx.z;
-    const TA* A = reinterpret_cast<const TA*>(p.A) + (int64_t)bz * p.sA;
-    const TB* B = reinterpret_cast<const TB*>(p.B) + (int64_t)bz * p.sB;
-    const TA* Alo = p.A_lo ? reinterpret_cast<const TA*>(p.A_lo) + (int64_t)bz * p.sA : nullptr;
-    const TB* Blo = p.B_lo ? reinterpret_cast<const TB*>(p.B_lo) + (int64_t)bz * p.sB : nullptr;
-    const int m0 = blockIdx.y * SB, n0 = blockIdx.x * SB;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    float acc[4][4] = {}, acc2[4][4] = {};
-    for (int k0 = 0; k0 < p.K; k0 += SK) {
-        for (int e = tid; e < SB * SK; e += 256) {
-            int row, kk;
-            // pick the loop order that walks memory contiguously
-            if (p.a_cs == 1) { row = e / SK; kk = e % SK; } else { kk = e / SB; row = e % SB; }
-            const int gm = m0 + row, gk = k0 + kk;
-            float av = 0.f;
-            if (gm < p.M && gk < p.K) {
-                const int64_t o = (int64_t)gm * p.a_rs + (int64_t)gk * p.a_cs;
-                av = ldf<TA>(A + o);
-                if (Alo) av += ldf<TA>(Alo + o);
-            }
-            As[kk][row] = av;
+// One operand: element (row, k) at p[row·rs + k·cs], optional lo plane added to it.
+// mode 0: contiguous along k (cs == 1), 1: contiguous along the rows (rs == 1), 2: neither.
+struct Operand {
+    const void* p;
+    const void* lo;
+    int64_t rs, cs;
+    int rows, K;
+    int mode;
+    int vec;   // elements a load may take at once along the contiguous direction: 8 / 4 (whole pieces), 2, 1
+};
+
+template <typename T> __device__ __forceinline__ float widen(T x);
+template <> __device__ __forceinline__ float widen<float>(float x) { return x; }
+template <> __device__ __forceinline__ float widen<bf16_t>(bf16_t x) { return bf2f(x); }
+
+// ---- fp32 tiles: ROWS × BK floats in LDS, pitch BK + 4; a piece is four elements along the contiguous direction --
+template <typename T, int ROWS, int BK, int NT>
+struct LoadF32 {
+    static constexpr int P = BK + 4, N = ROWS * BK / 4 / NT, WORDS = ROWS * P;
+    static_assert(ROWS * BK % (4 * NT) == 0, "tile / threads mismatch");
+    f32x4 v[N];
+    static __device__ __forceinline__ f32x4 piece(const T* q) {
+        if constexpr (sizeof(T) == 4) return *reinterpret_cast<const f32x4*>(q);
+        else {
+            const uint2 u = *reinterpret_cast<const uint2*>(q);
+            return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                         __uint_as_float(u.y & 0xffff0000u)};
         }
-        for (int e = tid; e < SB * SK; e += 256) {
-            int row, kk;
-            if (p.b_cs == 1) { row = e / SK; kk = e % SK; } else { kk = e / SB; row = e % SB; }
-            const int gn = n0 + row, gk = k0 + kk;
-            const bool ok = gn < p.N && gk < p.K;
-            float bv = 0.f;
-            if (ok) {
-                const int64_t o = (int64_t)gn * p.b_rs + (int64_t)gk * p.b_cs;
-                bv = ldf<TB>(B + o);
-                if (Blo) bv += ldf<TB>(Blo + o);
-            }
-            Bs[0][kk][row] = bv;
-            if constexpr (SWIGLU)
-                Bs[1][kk][row] = ok ? ldf<TB>(B + (int64_t)(gn + p.N) * p.b_rs + (int64_t)gk * p.b_cs) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < SK; ++kk) {
-            float a[4], b[4], b2[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                b[j] = Bs[0][kk][tx * 4 + j];
-                if constexpr (SWIGLU) b2[j] = Bs[1][kk][tx * 4 + j];
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-                    if constexpr (SWIGLU) acc2[i][j] = fmaf(a[i], b2[j], acc2[i][j]);
-                }
-        }
-        __syncthreads();
     }
+    __device__ __forceinline__ void load(const Operand& o, int row0, int k0, int tid) {
+        const T* hi = reinterpret_cast<const T*>(o.p);
+        const T* lo = reinterpret_cast<const T*>(o.lo);
+        // whole pieces: one past the end of K reads the last valid piece and becomes zero, rows past the end read a
+        // valid row and are never stored
+        if (o.mode == 0 && o.vec >= 4) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = i * NT + tid, row = c / (BK / 4), k = k0 + 4 * (c % (BK / 4));
+                const int64_t off = (int64_t)min(row0 + row, o.rows - 1) * o.rs + min(k, o.K - 4);
+                v[i] = piece(hi + off);
+                if (lo) v[i] += piece(lo + off);
+                if (k >= o.K) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        } else if (o.mode == 1 && o.vec >= 4) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = i * NT + tid, k = k0 + c / (ROWS / 4), rq = c % (ROWS / 4);
+                const int64_t off = (int64_t)min(k, o.K - 1) * o.cs + min(row0 + 4 * rq, o.rows - 4);
+                v[i] = piece(hi + off);
+                if (lo) v[i] += piece(lo + off);
+                if (k >= o.K) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = i * NT + tid;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int row = row0 + (o.mode == 1 ? 4 * (c % (ROWS / 4)) + e : c / (BK / 4));
+                    const int k = k0 + (o.mode == 1 ? c / (ROWS / 4) : 4 * (c % (BK / 4)) + e);
+                    float x = 0.f;
+                    if (row < o.rows && k < o.K) {
+                        const int64_t off = (int64_t)row * o.rs + (int64_t)k * o.cs;
+                        x = widen<T>(hi[off]);
+                        if (lo) x += widen<T>(lo[off]);
+                    }
+                    v[i][e] = x;
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float* lds, int mode, int tid) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int c = i * NT + tid;
+            if (mode == 1) {
+                const int k = c / (ROWS / 4), rq = c % (ROWS / 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) lds[(4 * rq + e) * P + k] = v[i][e];
+            } else {
+                *reinterpret_cast<f32x4*>(lds + (c / (BK / 4)) * P + 4 * (c % (BK / 4))) = v[i];
+            }
+        }
+    }
+};
+
+// ---- bf16 tiles: ROWS × BK bf16 in LDS, pitch BK + 8; a piece is 8 elements along k, or 2 (k) × 8 (rows) ---------
+template <int ROWS, int BK, int NT>
+struct LoadBF16 {
+    static constexpr int P = BK + 8, N = ROWS * BK / 8 / NT, WORDS = ROWS * P / 2;
+    static_assert(ROWS * BK % (16 * NT) == 0, "tile / threads mismatch");
+    uint4 v[N];
+    __device__ __forceinline__ void load(const Operand& o, int row0, int k0, int tid) {
+        const bf16_t* hi = reinterpret_cast<const bf16_t*>(o.p);
+        const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+        if (o.mode == 0 && o.vec >= 8) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = i * NT + tid, row = c / (BK / 8), k = k0 + 8 * (c % (BK / 8));
+                v[i] = *reinterpret_cast<const uint4*>(hi + (int64_t)min(row0 + row, o.rows - 1) * o.rs + min(k, o.K - 8));
+                if (k >= o.K) v[i] = zero;
+            }
+        } else if (o.mode == 1 && o.vec >= 8) {
+#pragma unroll
+            for (int i = 0; i < N / 2; ++i) {
+                const int c = i * NT + tid, k = k0 + 2 * (c / (ROWS / 8)), rq = c % (ROWS / 8);
+                const bf16_t* q = hi + min(row0 + 8 * rq, o.rows - 8);
+                v[2 * i] = *reinterpret_cast<const uint4*>(q + (int64_t)min(k, o.K - 1) * o.cs);
+                v[2 * i + 1] = *reinterpret_cast<const uint4*>(q + (int64_t)min(k + 1, o.K - 1) * o.cs);
+                if (k >= o.K) v[2 * i] = zero;
+                if (k + 1 >= o.K) v[2 * i + 1] = zero;
+            }
+        } else if (o.mode == 0 && o.vec >= 2) {   // 4-byte loads; K is even, so a pair is inside or outside as a whole
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = i * NT + tid, row = c / (BK / 8), k = k0 + 8 * (c % (BK / 8));
+                const bf16_t* q = hi + (int64_t)min(row0 + row, o.rows - 1) * o.rs;
+                uint32_t w[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = (k + 2 * e < o.K) ? *reinterpret_cast<const uint32_t*>(q + k + 2 * e) : 0u;
+                v[i] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                uint32_t w[4];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    int row, k;
+                    if (o.mode == 1) {
+                        const int c = (i / 2) * NT + tid;
+                        row = row0 + 8 * (c % (ROWS / 8)) + e;
+                        k = k0 + 2 * (c / (ROWS / 8)) + (i & 1);
+                    } else {
+                        const int c = i * NT + tid;
+                        row = row0 + c / (BK / 8);
+                        k = k0 + 8 * (c % (BK / 8)) + e;
+                    }
+                    uint32_t x = 0u;
+                    if (row < o.rows && k < o.K) x = hi[(int64_t)row * o.rs + (int64_t)k * o.cs];
+                    if (e & 1) w[e / 2] |= x << 16; else w[e / 2] = x;
+                }
+                v[i] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
+    }
+    __device__ __forceinline__ void store(float* lds_f, int mode, int tid) const {
+        bf16_t* lds = reinterpret_cast<bf16_t*>(lds_f);
+        if (mode == 1) {
+#pragma unroll
+            for (int i = 0; i < N / 2; ++i) {
+                const int c = i * NT + tid, k = 2 * (c / (ROWS / 8)), rq = c % (ROWS / 8);
+                const uint32_t* a = reinterpret_cast<const uint32_t*>(&v[2 * i]);
+                const uint32_t* b = reinterpret_cast<const uint32_t*>(&v[2 * i + 1]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    *reinterpret_cast<uint32_t*>(lds + (8 * rq + 2 * e) * P + k) = (a[e] & 0xffffu) | (b[e] << 16);
+                    *reinterpret_cast<uint32_t*>(lds + (8 * rq + 2 * e + 1) * P + k) = (a[e] >> 16) | (b[e] & 0xffff0000u);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                const int c = i * NT + tid;
+                *reinterpret_cast<uint4*>(lds + (c / (BK / 8)) * P + 8 * (c % (BK / 8))) = v[i];
+            }
+        }
+    }
+};
+
+// BM×BN block tile, waves of (32·TM)×(32·TN); KW waves share a wave tile and take every KW-th k-step.
+// BF: operands stay bf16 (v_mfma_f32_32x32x16_bf16: exact products, fp32 accumulation), else everything is fp32.
+template <typename TA, typename TB, bool BF, int BM, int BN, int TM, int TN, int KW, int BK, bool SWIGLU>
+__global__ void __launch_bounds__((BM / (32 * TM)) * (BN / (32 * TN)) * KW * 64)
+gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) {
+    constexpr int NWN = BN / (32 * TN), NWT = (BM / (32 * TM)) * NWN, NT = NWT * KW * 64;
+    using LA = std::conditional_t<BF, LoadBF16<BM, BK, NT>, LoadF32<TA, BM, BK, NT>>;
+    using LB = std::conditional_t<BF, LoadBF16<BN, BK, NT>, LoadF32<TB, BN, BK, NT>>;
+    constexpr int NB2 = SWIGLU ? 2 : 1;
+    constexpr int STAGE = LA::WORDS + NB2 * LB::WORDS;
+    static_assert(KW == 1 || (KW - 1) * NWT * TM * TN * NB2 * 1024 <= 2 * STAGE, "the partial sums meet in the stages");
+    __shared__ __align__(16) float lds[2 * STAGE];
+    // consecutive workgroup ids go to the 8 XCDs in turn: each XCD gets a contiguous run of the tile list (tile column
+    // fastest), so the tiles that share rows of A share an L2
+    int id = blockIdx.x;
+    if ((gridDim.x & 7) == 0) id = (id & 7) * (gridDim.x >> 3) + (id >> 3);
+    const int bz = id / (tilesM * tilesN), m0 = id / tilesN % tilesM * BM, n0 = id % tilesN * BN;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int kw = wave / NWT, wt = wave % NWT, wm = wt / NWN, wn = wt % NWN;
+    const int l32 = lane & 31, lh = lane >> 5;
+    oa.p = reinterpret_cast<const TA*>(oa.p) + (int64_t)bz * p.sA;
+    if (oa.lo) oa.lo = reinterpret_cast<const TA*>(oa.lo) + (int64_t)bz * p.sA;
+    ob.p = reinterpret_cast<const TB*>(ob.p) + (int64_t)bz * p.sB;
+    if (ob.lo) ob.lo = reinterpret_cast<const TB*>(ob.lo) + (int64_t)bz * p.sB;
+    Operand ob2 = ob;   // SWIGLU: the up rows, N rows further on
+    if constexpr (SWIGLU) ob2.p = reinterpret_cast<const TB*>(ob.p) + (int64_t)p.N * ob.rs;
+
+    f32x16 acc[NB2][TM][TN];
+#pragma unroll
+    for (int h = 0; h < NB2; ++h)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[h][i][j][v] = 0.f;
+
+    struct Regs { LA a; LB b, b2; };
+    auto load = [&](Regs& r, int kt) {
+        r.a.load(oa, m0, kt * BK, tid);
+        r.b.load(ob, n0, kt * BK, tid);
+        if constexpr (SWIGLU) r.b2.load(ob2, n0, kt * BK, tid);
+    };
+    auto store = [&](const Regs& r, int buf) {
+        r.a.store(lds + buf * STAGE, oa.mode, tid);
+        r.b.store(lds + buf * STAGE + LA::WORDS, ob.mode, tid);
+        if constexpr (SWIGLU) r.b2.store(lds + buf * STAGE + LA::WORDS + LB::WORDS, ob.mode, tid);
+    };
+    auto compute = [&](int buf) {
+        const float* sa = lds + buf * STAGE;
+        const float* sb = sa + LA::WORDS;
+        if constexpr (BF) {
+            const bf16_t* ha = reinterpret_cast<const bf16_t*>(sa);
+#pragma unroll
+            for (int s = 0; s < BK / 16 / KW; ++s) {
+                const int k = 16 * (s * KW + kw) + 8 * lh;
+                bf16x8 a[TM];
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    a[i] = u4_bf16x8(*reinterpret_cast<const uint4*>(ha + (32 * (wm * TM + i) + l32) * LA::P + k));
+#pragma unroll
+                for (int h = 0; h < NB2; ++h)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const bf16_t* hb = reinterpret_cast<const bf16_t*>(sb + h * LB::WORDS);
+                        const bf16x8 b = u4_bf16x8(*reinterpret_cast<const uint4*>(hb + (32 * (wn * TN + j) + l32) * LB::P + k));
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b, acc[h][i][j], 0, 0, 0);
+                    }
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < BK / 8 / KW; ++s) {
+                // lanes of half lh take k = +4·lh .. +3: one 16-byte read per operand feeds four MFMAs
+                const int k = 8 * (s * KW + kw) + 4 * lh;
+                f32x4 a[TM];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const f32x4*>(sa + (32 * (wm * TM + i) + l32) * LA::P + k);
+#pragma unroll
+                for (int h = 0; h < NB2; ++h)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const f32x4 b = *reinterpret_cast<const f32x4*>(sb + h * LB::WORDS + (32 * (wn * TN + j) + l32) * LB::P + k);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+#pragma unroll
+                            for (int i = 0; i < TM; ++i) acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[e], acc[h][i][j], 0, 0, 0);
+                    }
+            }
+        }
+    };
+
+    const int nkt = (p.K + BK - 1) / BK;
+    // tile kt is in LDS, tile kt+1 in registers, tile kt+2 on its way
+    Regs r0, r1;
+    load(r0, 0);
+    if (nkt > 1) load(r1, 1);
+    store(r0, 0);
+    for (int kt = 0; kt < nkt; kt += 2) {
+        if (kt + 2 < nkt) load(r0, kt + 2);
+        __syncthreads();   // tile kt is in its buffer, and nobody reads the other one any more
+        compute(0);
+        if (kt + 1 >= nkt) break;
+        store(r1, 1);
+        if (kt + 3 < nkt) load(r1, kt + 3);
+        __syncthreads();
+        compute(1);
+        if (kt + 2 < nkt) store(r0, 0);
+    }
+    if constexpr (KW > 1) {   // the waves' shares meet in LDS, added in a fixed order
+        __syncthreads();
+        constexpr int PER = NB2 * TM * TN * 1024;
+        if (kw > 0) {
+            float* d = lds + ((kw - 1) * NWT + wt) * PER + lane;
+#pragma unroll
+            for (int h = 0; h < NB2; ++h)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) d[(((h * TM + i) * TN + j) * 16 + v) * 64] = acc[h][i][j][v];
+        }
+        __syncthreads();
+        if (kw > 0) return;
+#pragma unroll
+        for (int q = 0; q < KW - 1; ++q) {
+            const float* d = lds + (q * NWT + wt) * PER + lane;
+#pragma unroll
+            for (int h = 0; h < NB2; ++h)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[h][i][j][v] += d[(((h * TM + i) * TN + j) * 16 + v) * 64];
+        }
+    }
+
     float* C32 = p.C32 ? p.C32 + (int64_t)bz * p.sC : nullptr;
     bf16_t* C16 = p.C16 ? p.C16 + (int64_t)bz * p.sC : nullptr;
     float* CT32 = p.CT32 ? p.CT32 + (int64_t)bz * p.sCT : nullptr;
@@ -84,44 +345,78 @@ __global__ void __launch_bounds__(256) gemm_simt_kernel(SimtArgs p) {
     bf16_t* C16lo = p.C16lo ? p.C16lo + (int64_t)bz * p.sC : nullptr;
     bf16_t* CT16lo = p.CT16lo ? p.CT16lo + (int64_t)bz * p.sCT : nullptr;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int row = m0 + ty * 4 + i, col = n0 + tx * 4 + j;
-            if (row < p.M && col < p.N) {
-                float o = acc[i][j];
-                if constexpr (SWIGLU) o = silu_f(o) * acc2[i][j];
-                if (C32) C32[(int64_t)row * p.ldc + col] = o;
-                const bf16_t h = f2bf(o);
-                const bf16_t l = f2bf(o - bf2f(h));
-                if (C16) C16[(int64_t)row * p.ldc + col] = h;
-                if (C16lo) C16lo[(int64_t)row * p.ldc + col] = l;
-                if (CT32) CT32[(int64_t)col * p.ldct + row] = o;
-                if (CT16) CT16[(int64_t)col * p.ldct + row] = h;
-                if (CT16lo) CT16lo[(int64_t)col * p.ldct + row] = l;
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = m0 + 32 * (wm * TM + i) + 8 * (v >> 2) + 4 * lh + (v & 3), col = n0 + 32 * (wn * TN + j) + l32;
+                if (row < p.M && col < p.N) {
+                    float o = acc[0][i][j][v];
+                    if constexpr (SWIGLU) o = silu_f(o) * acc[NB2 - 1][i][j][v];
+                    if (C32) C32[(int64_t)row * p.ldc + col] = o;
+                    const bf16_t h = f2bf(o);
+                    const bf16_t l = f2bf(o - bf2f(h));
+                    if (C16) C16[(int64_t)row * p.ldc + col] = h;
+                    if (C16lo) C16lo[(int64_t)row * p.ldc + col] = l;
+                    if (CT32) CT32[(int64_t)col * p.ldct + row] = o;
+                    if (CT16) CT16[(int64_t)col * p.ldct + row] = h;
+                    if (CT16lo) CT16lo[(int64_t)col * p.ldct + row] = l;
+                }
             }
-        }
 }
 
-template <typename TA, typename TB>
-hipError_t launch_simt(hipStream_t st, const SimtArgs& g) {
-    dim3 grid((g.N + SB - 1) / SB, (g.M + SB - 1) / SB, g.batch);
-    if (g.swiglu)
-        hipLaunchKernelGGL((gemm_simt_kernel<TA, TB, true>), grid, dim3(256), 0, st, g);
-    else
-        hipLaunchKernelGGL((gemm_simt_kernel<TA, TB, false>), grid, dim3(256), 0, st, g);
+// how the loads of an operand may be widened: `piece` elements at once need 16-byte (8-byte when bf16 is widened to
+// fp32) pieces at aligned addresses that are inside or outside the matrix as a whole
+Operand operand(const void* ptr, const void* lo, int64_t rs, int64_t cs, int64_t sbatch, int rows, int K, int es, int piece) {
+    Operand o;
+    o.p = ptr; o.lo = lo; o.rs = rs; o.cs = cs; o.rows = rows; o.K = K;
+    o.mode = cs == 1 ? 0 : (rs == 1 ? 1 : 2);
+    const int64_t ld = o.mode == 0 ? rs : cs;
+    const auto fits = [&](int n) {
+        return o.mode != 2 && ld % n == 0 && sbatch % n == 0 && (((uintptr_t)ptr | (uintptr_t)lo) % (size_t)(n * es)) == 0 &&
+               ((o.mode == 0 ? K : rows) % n == 0);
+    };
+    o.vec = fits(piece) ? piece : (es == 2 && o.mode == 0 && K % 2 == 0 && fits(2) ? 2 : 1);
+    return o;
+}
+
+template <typename TA, typename TB, bool BF, int BM, int BN, int TM, int TN, int KW, int BK, bool SWIGLU>
+hipError_t launch_tile(hipStream_t st, const SimtArgs& g, const Operand& oa, const Operand& ob) {
+    const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
+    const int64_t tiles = (int64_t)tm * tn * g.batch;
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    constexpr int NT = (BM / (32 * TM)) * (BN / (32 * TN)) * KW * 64;
+    hipLaunchKernelGGL((gemm_strided_kernel<TA, TB, BF, BM, BN, TM, TN, KW, BK, SWIGLU>), dim3((unsigned)tiles), dim3(NT), 0, st, g, oa, ob, tm, tn);
     return hipGetLastError();
+}
+
+template <typename TA, typename TB, bool BF, bool SWIGLU>
+hipError_t launch_strided(hipStream_t st, const SimtArgs& g) {
+    constexpr int piece = BF ? 8 : 4;
+    const Operand oa = operand(g.A, g.A_lo, g.a_rs, g.a_cs, g.sA, g.M, g.K, sizeof(TA), piece);
+    const Operand ob = operand(g.B, g.B_lo, g.b_rs, g.b_cs, g.sB, g.N, g.K, sizeof(TB), piece);
+    const auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.batch; };
+    constexpr int BK = BF ? 64 : 32;
+    if (tiles(128) >= 192) return launch_tile<TA, TB, BF, 128, SWIGLU ? 64 : 128, 2, SWIGLU ? 1 : 2, 1, BK, SWIGLU>(st, g, oa, ob);
+    if (tiles(64) >= 192) return launch_tile<TA, TB, BF, 64, 64, 1, 1, 1, BK, SWIGLU>(st, g, oa, ob);
+    return launch_tile<TA, TB, BF, 32, 32, 1, 1, 4, 128, SWIGLU>(st, g, oa, ob);
 }
 
 }  // namespace
 
 hipError_t gemm_simt(hipStream_t st, OperandType ta, OperandType tb, const SimtArgs& g) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
-    if (g.batch > 65535 || (g.M + SB - 1) / SB > 65535) return hipErrorInvalidValue;
-    if (ta == OP_F32 && tb == OP_F32) return launch_simt<float, float>(st, g);
-    if (ta == OP_BF16 && tb == OP_BF16) return launch_simt<bf16_t, bf16_t>(st, g);
-    if (ta == OP_BF16 && tb == OP_F32) return launch_simt<bf16_t, float>(st, g);
-    return launch_simt<float, bf16_t>(st, g);
+    if (ta == OP_F32 && tb == OP_F32)
+        return g.swiglu ? launch_strided<float, float, false, true>(st, g) : launch_strided<float, float, false, false>(st, g);
+    if (ta == OP_BF16 && tb == OP_BF16) {
+        // operands with a lo plane carry more than bf16: they are widened and multiplied in fp32
+        if (g.A_lo || g.B_lo) return g.swiglu ? hipErrorInvalidValue : launch_strided<bf16_t, bf16_t, false, false>(st, g);
+        return g.swiglu ? launch_strided<bf16_t, bf16_t, true, true>(st, g) : launch_strided<bf16_t, bf16_t, true, false>(st, g);
+    }
+    if (g.swiglu) return hipErrorInvalidValue;
+    if (ta == OP_BF16) return launch_strided<bf16_t, float, false, false>(st, g);
+    return launch_strided<float, bf16_t, false, false>(st, g);
 }
 
 }  // namespace atp

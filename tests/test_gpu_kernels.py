@@ -1,0 +1,50 @@
+"""Kernels at the sizes where their tiling can go wrong: edges of tiles, remainders, the ends of a dispatch range.
+Compared with the float64 oracle on the rounded inputs.
+
+Tolerances.  fp32: a sum of K products carries at most about sqrt(K)·2^-24 relative error for inputs of random sign
+(K = 4096: 4e-6).  bf16: the products are exact and the sums fp32, so the output rounding is what remains; with 8
+significant bits half a unit in the last place is at most 2^-8 of an entry (a value just above a power of two)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+from util import rel_fro, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+F32_TOL, BF16_TOL = 1e-5, 2.0 ** -8 * 1.05
+
+
+@pytest.fixture(scope="module")
+def atp():
+    import paper_2403_02352_amd as m
+    return m
+
+
+def rnd(shape, seed, scale=1.0):
+    return np.random.default_rng(seed).standard_normal(shape) * scale
+
+
+# (batch, m, k, n): single elements, one short of / one past the 32-, 64- and 128-wide tiles and the k-tiles, K odd,
+# even (4-byte pieces), a multiple of 4 and of 8, and one shape per tile size of the strided kernel
+STRIDED = [(1, 1, 1, 1), (2, 31, 33, 65), (1, 33, 130, 31), (3, 64, 250, 96), (1, 127, 129, 128), (2, 128, 36, 132),
+           (1, 300, 127, 260), (1, 1000, 62, 900), (2, 1100, 72, 1990)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("epilogue", ["none", "swiglu"])
+@pytest.mark.parametrize("case", STRIDED)
+def test_strided_products(atp, dtype, layout, epilogue, case):
+    batch, m, k, n = case
+    n *= 2 if epilogue == "swiglu" else 1
+    B = wl.round_to_dtype(rnd((batch, m, k), 1), dtype)
+    W = wl.round_to_dtype(rnd((k, n), 2, 1 / np.sqrt(k)), dtype)
+    ref = np.stack([oracle.lowrank_linear(B[b], W, *(["swiglu"] if epilogue == "swiglu" else [])) for b in range(batch)])
+    Wd = to_dev(W if layout == "kn" else W.T, dtype)
+    out = atp.lowrank_linear(to_dev(B, dtype), Wd, atp.ATP_W_KN if layout == "kn" else atp.ATP_W_NK,
+                             atp.ATP_EPI_SWIGLU if epilogue == "swiglu" else atp.ATP_EPI_NONE)
+    torch.cuda.synchronize()
+    assert rel_fro(to_host(out), ref) <= (F32_TOL if dtype == "f32" else BF16_TOL)
