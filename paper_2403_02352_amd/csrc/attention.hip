@@ -283,87 +283,195 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
 }
 
 // ---------------------------------------------------------------------------
-// fp32 storage path: one wave per query row, features spread over the lanes,
-// scalar online softmax over the keys.  True fp32 arithmetic throughout.
+// fp32 storage path: same scheme on v_mfma_f32_32x32x2f32 (fp32 products and sums, expf).  A wave owns 32 queries and sees the
+// scores transposed, one query per lane.  Accumulator register v of lane half lh belongs to key 8·(v/4) + 4·lh + v%4, so register v
+// is at once the B operand of a k-step of Oᵀ += V'ᵀ·Pᵀ over the two keys of its halves: probabilities go from one product to the
+// next without moving, and V' is read in its natural layout.
+// KS = waves that share a query block, each with every KS-th tile of 32 keys (their sums meet in LDS): 1 when there are enough
+// query blocks for the chip, else 4.  DP = head width padded to 64, 128 or 256 (zeros).
+// Bound by the fp32 matrix cores (256 flop per clock and compute unit).  With one wave per query and scalar products this
+// kernel took 358 µs of the 1.47 ms of a block of 4 × 512 × 768 with r = 128 (12 heads of 64); the block now takes 1.15 ms.
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) attn_f32_kernel(AttnArgs a, int dh) {
+template <int DP, int KS, bool LIN>
+__global__ void __launch_bounds__(256, 1) attn_f32_kernel(AttnArgs a, int dh, int vec) {
+    constexpr int PK = DP + 4, PV = DP + 8;   // LDS row pitches: conflict-free 16-byte rows of K', 4 rows of V' half a bank span apart
+    constexpr int TK = 32 * KS;               // keys per stage
+    constexpr int NCT = DP / 32, NL = TK * DP / 4 / 256;
+    constexpr int NQ = 4 / KS;
+    __shared__ __align__(16) float sK[TK * PK];
+    __shared__ __align__(16) float sV[TK * PV];
     const int b = blockIdx.z, h = blockIdx.y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int q = blockIdx.x * 4 + wave;
-    if (q >= a.L) return;
-    const float* Qp = reinterpret_cast<const float*>(a.Q) + ((int64_t)b * a.L + q) * a.dq + h * dh;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lh = lane >> 5;
+    const int kw = wave / NQ;
+    const int q = (blockIdx.x * NQ + wave % NQ) * 32 + l32;
+    const float* Qp = reinterpret_cast<const float*>(a.Q) + ((int64_t)b * a.L + min(q, a.L - 1)) * a.dq + h * dh;
     const float* Kp = reinterpret_cast<const float*>(a.K) + ((int64_t)b * a.nk) * a.dq + h * dh;
     const float* Vp = reinterpret_cast<const float*>(a.V) + ((int64_t)b * a.nk) * a.dq + h * dh;
-    float qv[4], ov[4];
+    const float* csum = LIN ? a.colsum + (int64_t)b * a.nk_pad : nullptr;
+    // four features of a row; zeros past the end of the head
+    const auto quad = [&](const float* row, int c) {
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+        if (vec) { if (c < dh) v = *reinterpret_cast<const f32x4*>(row + c); }
+        else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = lane + 64 * i;
-        qv[i] = (c < dh) ? Qp[c] * a.scale : 0.f;
-        ov[i] = 0.f;
-    }
+            for (int e = 0; e < 4; ++e) if (c + e < dh) v[e] = row[c + e];
+        }
+        return v;
+    };
+    f32x4 qf[DP / 8];   // features 8s + 4·lh .. +3, scaled
+#pragma unroll
+    for (int s = 0; s < DP / 8; ++s) qf[s] = quad(Qp, 8 * s + 4 * lh) * a.scale;
+    f32x4 kr[NL], vr[NL];
+    const auto load = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < NL; ++i) {
+            const int c = i * 256 + tid, key = k0 + c / (DP / 4), f = 4 * (c % (DP / 4));
+            const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+            kr[i] = key < a.nk ? quad(Kp + (int64_t)key * a.dq, f) : zero;
+            vr[i] = key < a.nk ? quad(Vp + (int64_t)key * a.dq, f) : zero;
+        }
+    };
+    f32x16 o[NCT];
+#pragma unroll
+    for (int i = 0; i < NCT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[i][v] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;
-    if (a.linearised) {
-        // first-order variant (Eq.8): weight (1·U)_j + scale·<q, k_j>
-        const float* csum = a.colsum + (int64_t)b * a.nk_pad;
-        for (int j = 0; j < a.nk; ++j) {
-            const float* kr = Kp + (int64_t)j * a.dq;
-            float s = 0.f;
+    load(0);
+    for (int k0 = 0; k0 < a.nk; k0 += TK) {
+        __syncthreads();
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = lane + 64 * i;
-                if (c < dh) s = fmaf(qv[i], kr[c], s);
+        for (int i = 0; i < NL; ++i) {
+            const int c = i * 256 + tid, row = c / (DP / 4), f = 4 * (c % (DP / 4));
+            *reinterpret_cast<f32x4*>(sK + row * PK + f) = kr[i];
+            *reinterpret_cast<f32x4*>(sV + row * PV + f) = vr[i];
+        }
+        __syncthreads();
+        if (k0 + TK < a.nk) load(k0 + TK);
+        const int kb = k0 + 32 * kw;
+        if (kb >= a.nk) continue;
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int t = 0; t < DP / 8; ++t) {
+            const f32x4 kf = *reinterpret_cast<const f32x4*>(sK + (32 * kw + l32) * PK + 8 * t + 4 * lh);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], qf[t][e], s, 0, 0, 0);
+        }
+        if constexpr (LIN) {
+            // first-order variant (Eq.8): weight (1·U)_j + <q, k_j>·scale; keys past the end weigh nothing
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int key = kb + 8 * (v >> 2) + 4 * lh + (v & 3);
+                const bool live = key < a.nk;
+                const float cj = csum[key];   // padded with zeros to a multiple of 64 keys
+                const float pv = live ? cj + s[v] : 0.f;
+                l_run += a.norm_rowsum ? pv : (live ? s[v] * cj : 0.f);
+                s[v] = pv;
+            }
+        } else {
+            float mloc = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                if (kb + 8 * (v >> 2) + 4 * lh + (v & 3) >= a.nk) s[v] = -INFINITY;
+                mloc = fmaxf(mloc, s[v]);
+            }
+            mloc = fmaxf(mloc, __shfl_xor(mloc, 32));
+            const float m_new = fmaxf(m_run, mloc);
+            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {   // the factor is exactly 1 otherwise
+                const float alpha = m_new > m_run ? expf(m_run - m_new) : 1.f;
+                l_run *= alpha;
+#pragma unroll
+                for (int i = 0; i < NCT; ++i)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
+                m_run = m_new;
             }
 #pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-            const float cj = csum[j];
-            const float p = cj + s;
-            l_run += a.norm_rowsum ? p : s * cj;
-            const float* vr = Vp + (int64_t)j * a.dq;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = lane + 64 * i;
-                if (c < dh) ov[i] = fmaf(p, vr[c], ov[i]);
+            for (int v = 0; v < 16; ++v) {
+                s[v] = expf(s[v] - m_run);
+                l_run += s[v];
             }
         }
-        if (!a.norm_rowsum) l_run += a.n_tokens;
-        float* Ol = reinterpret_cast<float*>(a.O) + ((int64_t)b * a.L + q) * a.dq + h * dh;
-        const float invl = 1.0f / l_run;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = lane + 64 * i;
-            if (c < dh) Ol[c] = ov[i] * invl;
-        }
-        return;
-    }
-    for (int j = 0; j < a.nk; ++j) {
-        const float* kr = Kp + (int64_t)j * a.dq;
-        float s = 0.f;
+        for (int v = 0; v < 16; ++v) {
+            const float* vrow = sV + (32 * kw + 8 * (v >> 2) + 4 * lh + (v & 3)) * PV + l32;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = lane + 64 * i;
-            if (c < dh) s = fmaf(qv[i], kr[c], s);
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-        const float m_new = fmaxf(m_run, s);
-        const float alpha = expf(m_run - m_new);
-        const float p = expf(s - m_new);
-        l_run = l_run * alpha + p;
-        m_run = m_new;
-        const float* vr = Vp + (int64_t)j * a.dq;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = lane + 64 * i;
-            if (c < dh) ov[i] = fmaf(p, vr[c], ov[i] * alpha);
+            for (int i = 0; i < NCT; ++i) o[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(vrow[32 * i], s[v], o[i], 0, 0, 0);
         }
     }
+    if constexpr (KS > 1) {   // wave 0 adds the other waves' shares, in order, at the common maximum
+        constexpr int PER = (NCT * 16 + 2) * 64;
+        static_assert((KS - 1) * PER <= TK * (PK + PV) && PER <= TK * PK, "shares fit the stages");
+        __syncthreads();
+        float* share = wave == 1 ? sK : wave == 2 ? sV : sV + PER;
+        if (wave) {
+#pragma unroll
+            for (int i = 0; i < NCT; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) share[(16 * i + v) * 64 + lane] = o[i][v];
+            share[NCT * 16 * 64 + lane] = m_run;
+            share[(NCT * 16 + 1) * 64 + lane] = l_run;
+        }
+        __syncthreads();
+        if (wave) return;
+        float f[KS];
+        if constexpr (LIN) {
+#pragma unroll
+            for (int w = 0; w < KS; ++w) f[w] = 1.f;
+        } else {
+            float m_all = m_run;
+#pragma unroll
+            for (int w = 1; w < KS; ++w) {
+                f[w] = (w == 1 ? sK : w == 2 ? sV : sV + PER)[NCT * 16 * 64 + lane];
+                m_all = fmaxf(m_all, f[w]);
+            }
+            f[0] = expf(m_run - m_all);
+#pragma unroll
+            for (int w = 1; w < KS; ++w) f[w] = expf(f[w] - m_all);
+        }
+        l_run *= f[0];
+#pragma unroll
+        for (int i = 0; i < NCT; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[i][v] *= f[0];
+#pragma unroll
+        for (int w = 1; w < KS; ++w) {
+            const float* p = w == 1 ? sK : w == 2 ? sV : sV + PER;
+#pragma unroll
+            for (int i = 0; i < NCT; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[i][v] = fmaf(p[(16 * i + v) * 64 + lane], f[w], o[i][v]);
+            l_run = fmaf(p[(NCT * 16 + 1) * 64 + lane], f[w], l_run);
+        }
+    }
+    float l_tot = l_run + __shfl_xor(l_run, 32);
+    if (LIN && !a.norm_rowsum) l_tot += a.n_tokens;
+    const float inv = 1.0f / l_tot;
+    if (q >= a.L) return;
     float* Op = reinterpret_cast<float*>(a.O) + ((int64_t)b * a.L + q) * a.dq + h * dh;
-    const float inv = 1.0f / l_run;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = lane + 64 * i;
-        if (c < dh) Op[c] = ov[i] * inv;
-    }
+    for (int i = 0; i < NCT; ++i)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int c = 32 * i + 8 * g + 4 * lh;
+            const f32x4 v = {o[i][4 * g] * inv, o[i][4 * g + 1] * inv, o[i][4 * g + 2] * inv, o[i][4 * g + 3] * inv};
+            if (vec) { if (c < dh) *reinterpret_cast<f32x4*>(Op + c) = v; }
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) if (c + e < dh) Op[c + e] = v[e];
+            }
+        }
+}
+
+template <int DP, int KS>
+hipError_t launch_attn_f32(hipStream_t st, const AttnArgs& a, int dh) {
+    const dim3 grid((a.L + 128 / KS - 1) / (128 / KS), a.heads, a.batch);
+    const int vec = dh % 4 == 0;   // bases are 16-byte aligned, rows and heads then start at multiples of 16 bytes
+    if (a.linearised) hipLaunchKernelGGL((attn_f32_kernel<DP, KS, true>), grid, dim3(256), 0, st, a, dh, vec);
+    else hipLaunchKernelGGL((attn_f32_kernel<DP, KS, false>), grid, dim3(256), 0, st, a, dh, vec);
+    return hipGetLastError();
 }
 
 // out[b][j] = sum over the L rows of U[b][:, j]; one workgroup per (64 columns, item): thread (ry, cx)
@@ -423,11 +531,12 @@ hipError_t attention_bf16(hipStream_t st, const AttnArgs& a) {
 
 hipError_t attention_f32(hipStream_t st, const AttnArgs& a) {
     const int dh = a.dq / a.heads;
-    if (dh > 256) return hipErrorInvalidValue;
-    dim3 grid((a.L + 3) / 4, a.heads, a.batch);
-    if (grid.y > 65535 || grid.z > 65535) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(attn_f32_kernel, grid, dim3(256), 0, st, a, dh);
-    return hipGetLastError();
+    if (dh > 256 || a.heads > 65535 || a.batch > 65535) return hipErrorInvalidValue;
+    // 128 queries per workgroup once that gives every second compute unit one, else 32 with the keys dealt to four waves
+    const bool wide = (int64_t)((a.L + 127) / 128) * a.heads * a.batch >= 128 || a.nk <= 32;
+    if (dh <= 64) return wide ? launch_attn_f32<64, 1>(st, a, dh) : launch_attn_f32<64, 4>(st, a, dh);
+    if (dh <= 128) return wide ? launch_attn_f32<128, 1>(st, a, dh) : launch_attn_f32<128, 4>(st, a, dh);
+    return launch_attn_f32<256, 1>(st, a, dh);   // (four shares of 256 features do not fit the LDS)
 }
 
 }  // namespace atp

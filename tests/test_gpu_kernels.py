@@ -48,3 +48,34 @@ def test_strided_products(atp, dtype, layout, epilogue, case):
                              atp.ATP_EPI_SWIGLU if epilogue == "swiglu" else atp.ATP_EPI_NONE)
     torch.cuda.synchronize()
     assert rel_fro(to_host(out), ref) <= (F32_TOL if dtype == "f32" else BF16_TOL)
+
+
+# (batch, L, r, dq, heads): fp32 attention with 128 queries per workgroup and with the keys dealt to four waves; heads of every
+# padded width (64, 128, 256), widths that are no multiple of 4 (scalar loads); one short of / past the 32-key tile and the
+# 128-key stage; a single key and a single query
+F32_ATTENTION = [(1, 1, 1, 5, 1), (1, 33, 31, 64, 1), (2, 129, 33, 130, 2), (1, 127, 127, 128, 1), (1, 65, 129, 256, 2),
+                 (1, 40, 300, 96, 1), (1, 130, 65, 200, 1), (1, 100, 257, 512, 2), (4, 500, 97, 640, 10), (3, 260, 129, 1408, 22),
+                 (2, 512, 96, 8192, 64)]
+
+
+@pytest.mark.parametrize("variant", ["softmax", "taylor", "rowsum"])
+@pytest.mark.parametrize("case", F32_ATTENTION)
+def test_attention_f32(atp, case, variant):
+    """The score sums carry sqrt(d_h)·2^-24 of their terms' size, which the exponential passes on: below 1e-5."""
+    batch, L, r, dq, heads = case
+    Q, K, V = (rnd((batch, n, dq), s).astype(np.float32) for s, n in ((3, L), (4, r), (5, r)))
+    if variant == "softmax":
+        ref = np.stack([oracle.attention(Q[b], K[b], V[b], heads) for b in range(batch)])
+        out = atp.attention(to_dev(Q, "f32"), to_dev(K, "f32"), to_dev(V, "f32"), heads)
+    else:
+        # column sums c_j of about 0.8·sqrt(L) and scores s_j of about 0.1: Σ s_j·c_j is 0.08·sqrt(L·r) or less, a fraction of L, so
+        # neither denominator (L + Σ s_j·c_j, Σ c_j + s_j) cancels and its relative error stays that of the sums
+        U = (np.abs(rnd((batch, L, r), 6)) / np.sqrt(L)).astype(np.float32)
+        Q *= np.float32(0.1)
+        ref = np.stack([oracle.linearised_attention(Q[b], K[b], V[b], U[b], heads, norm=variant) for b in range(batch)])
+        norm = atp.ATP_NORM_TAYLOR if variant == "taylor" else atp.ATP_NORM_ROWSUM
+        out = atp.attention_linearised(to_dev(Q, "f32"), to_dev(K, "f32"), to_dev(V, "f32"), to_dev(U, "f32"), heads, norm=norm)
+    torch.cuda.synchronize()
+    err = rel_fro(to_host(out), ref)
+    print(case, variant, err, flush=True)
+    assert err <= F32_TOL
