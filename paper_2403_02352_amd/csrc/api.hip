@@ -664,10 +664,10 @@ atp_status atp_rayleigh_ritz(const void* U_r, const void* B_r, int64_t batch, in
     const int ib = (int)batch, iL = (int)L, id = (int)d, ir = (int)r;
     const int64_t rp = (r + 63) / 64 * 64;
     Carver c(workspace);
-    float* T0 = (float*)c.take((size_t)batch * r * r * 4);
-    float* T1 = (float*)c.take((size_t)batch * r * r * 4);
-    float* R0 = (float*)c.take((size_t)batch * r * r * 4);
-    float* R1 = (float*)c.take((size_t)batch * r * r * 4);
+    float* T = (float*)c.take((size_t)batch * r * r * 4);
+    float* R = (float*)c.take((size_t)batch * r * r * 4);
+    // products of rotations: batch·ceil(r/64)·4096 floats, which 2·r² per item hold for every r > 64
+    float* W = (float*)c.take(2 * align_up((size_t)batch * r * r * 4));
     float* RsT = (float*)c.take((size_t)batch * r * r * 4);
     float* cs = (float*)c.take((size_t)batch * rp * 4);
     int* rank = (int*)c.take((size_t)batch * r * 4);
@@ -678,15 +678,14 @@ atp_status atp_rayleigh_ritz(const void* U_r, const void* B_r, int64_t batch, in
         SimtArgs g;
         g.A = B_r; g.B = B_r; g.a_rs = d; g.a_cs = 1; g.b_rs = d; g.b_cs = 1; g.sA = r * d; g.sB = r * d;
         g.M = ir; g.N = ir; g.K = id; g.batch = ib;
-        g.C32 = T0; g.ldc = r; g.sC = r * r;
+        g.C32 = T; g.ldc = r; g.sC = r * r;
         ProfScope ps(st, ATP_K_GEMM_SIMT, 2.0 * batch * r * r * d, (double)batch * r * d * esize(t));
         ATP_HIP(gemm_simt(st, ot, ot, g));
     }
-    float *Tf = nullptr, *Rf = nullptr;
-    ATP_HIP(ritz_jacobi(st, T0, T1, R0, R1, ir, ib, sweeps, &Tf, &Rf));
+    ATP_HIP(ritz_jacobi(st, T, R, W, ir, ib, sweeps));
     ATP_HIP(column_sums(st, U_r, cs, iL, ir, rp, ib, (int)esize(t)));
     const float zero_tol = (t == ATP_BF16 ? 2e-4f : 1e-5f) * sqrtf((float)L);
-    ATP_HIP(ritz_order(st, Tf, Rf, cs, rp, rank, RsT, sigma, zsum, ir, ib, zero_tol));
+    ATP_HIP(ritz_order(st, T, R, cs, rp, rank, RsT, sigma, zsum, ir, ib, zero_tol));
     {   // U_out = U_r·Rs
         SimtArgs g;
         g.A = U_r; g.B = RsT; g.a_rs = r; g.a_cs = 1; g.b_rs = r; g.b_cs = 1; g.sA = L * r; g.sB = r * r;
@@ -706,7 +705,7 @@ atp_status atp_rayleigh_ritz(const void* U_r, const void* B_r, int64_t batch, in
         ATP_HIP(gemm_simt(st, OP_F32, ot, g));
     }
     ATP_HIP(ritz_fallback_sign(st, U_out, B_out, zsum, iL, id, ir, ib, (int)esize(t)));
-    if (diagnostics) ATP_HIP(ritz_diagnostics(st, Tf, sigma, ir, ib, diagnostics));
+    if (diagnostics) ATP_HIP(ritz_diagnostics(st, T, sigma, ir, ib, R, diagnostics));
     return ATP_OK;
 }
 

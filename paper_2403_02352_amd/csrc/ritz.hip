@@ -4,91 +4,197 @@
 // so that 1ᵀ·u_i ≥ 0.  Also the diagnostics the paper uses to choose r: captured energy (Fig.5) and
 // the SVD-entropy low-rankness ⌈2^μ⌉ (Eq.4) of the estimated singular values.
 //
-// Jacobi: one launch per round of n/2 disjoint rotations (round-robin pairing, n-1 rounds per
-// sweep).  A workgroup owns one index pair (p, q): it rotates rows p, q of T (and of Rᵀ, whose rows
-// are the eigenvector estimates) and applies the column rotations of every other pair to its two
-// rows; the angles of all pairs come from the previous buffer (ping-pong), so a round has no
-// internal dependencies.
+// Jacobi in blocks of 32 indices.  A round pairs the blocks (round-robin) and runs two launches: jacobi_pair_kernel
+// takes the 64×64 diagonal sub-matrix of every block pair into LDS and annihilates each of its cross entries once, 32
+// steps of 32 disjoint rotations, keeping their product W; jacobi_apply_kernel carries the W of all pairs to T (W_P·T_PQ·W_Qᵀ) and
+// to the eigenvector rows (W_P·R_P) with fp32 MFMA.  The first round of a sweep also annihilates the entries inside the blocks, so a
+// sweep still visits every index pair exactly once.  r <= 64 is one pair and one launch.
+//
+// What bounds it: the chain of r-1 dependent steps per sweep, each at best an LDS round trip plus the rotation formula (about 0.5 µs).
+// A launch per step instead, with every step a pass over T and R, cost 7.4 µs per step: at r = 512, ten sweeps, 37.8 ms for the whole
+// call against 7.2 ms.
 #include "common.h"
-
-#include <algorithm>
 
 namespace atp {
 namespace {
 
-// partner of index x in round k of the round-robin schedule over n (even) indices
-__device__ __forceinline__ int rr_partner(int x, int k, int n) {
-    const int m = n - 1;
-    if (x == m) return k;
-    if (x == k) return m;
-    int y = 2 * k - x;
-    y %= m;
-    if (y < 0) y += m;
-    return y;
-}
+constexpr int JB = 32;            // block size
+constexpr int JW = 2 * JB;        // indices of a block pair
+constexpr int JP = 96;            // LDS row pitch: rows of opposite parity start in opposite halves of the 64 banks
 
-// rotation that annihilates T[p][q]: c, s with J = [[c, s], [-s, c]] on (p, q); identity when the pair
-// reaches past r (padding index) or the entry is already zero
-__device__ __forceinline__ void jacobi_cs(const float* __restrict__ T, int n_ld, int r, int p, int q, float& c, float& s) {
-    c = 1.f; s = 0.f;
-    if (p >= r || q >= r) return;
-    const float apq = T[(int64_t)p * n_ld + q];
-    if (apq == 0.f) return;
-    const float app = T[(int64_t)p * n_ld + p], aqq = T[(int64_t)q * n_ld + q];
+// blocks of pair i in round k of the round-robin schedule over nb (even) blocks; first < second
+__device__ __forceinline__ void block_pair(int i, int k, int nb, int& first, int& second) {
+    const int m = nb - 1;
+    const int x = i == 0 ? m : (k + i) % m, y = i == 0 ? k : (k - i + m) % m;
+    first = min(x, y); second = max(x, y);
+}
+// matrix index of local index l (0 .. 63) of a block pair
+__device__ __forceinline__ int pair_index(int l, int first, int second) { return (l < JB ? first : second - 1) * JB + l; }
+
+// rotation that annihilates the entry pq of [[pp, pq], [pq, qq]]: J = [[c, s], [-s, c]] as s and u = s/(1 + c); identity when the
+// entry is zero (as it is for padding indices, whose rows and columns are zero)
+__device__ __forceinline__ void jacobi_su(float app, float aqq, float apq, float& s, float& u) {
     const float tau = (aqq - app) / (2.f * apq);
     const float t = (tau >= 0.f ? 1.f : -1.f) / (fabsf(tau) + sqrtf(1.f + tau * tau));
-    c = 1.0f / sqrtf(1.f + t * t);
+    const float c = 1.0f / sqrtf(1.f + t * t);
     s = t * c;
+    u = s * __builtin_amdgcn_rcpf(1.f + c);
+    if (apq == 0.f) { s = 0.f; u = 0.f; }
+}
+// (x, y) <- (c·x - s·y, s·x + c·y) with c = 1 - s·u never rounded to fp32: near convergence a rounded c is too large by up to
+// half a unit on average, which scaled the whole spectrum up by 6e-5 in ten sweeps at r = 512 (3e-6 this way)
+__device__ __forceinline__ void rotate(float s, float u, float x, float y, float& xr, float& yr) {
+    xr = fmaf(-s, fmaf(u, x, y), x);
+    yr = fmaf(s, fmaf(-u, y, x), y);
 }
 
-// One round.  Tin/Tout [batch][r][r], Rin/Rout [batch][r][r] (rows = eigenvector estimates).
-__global__ void __launch_bounds__(256) jacobi_round_kernel(const float* __restrict__ Tin, float* __restrict__ Tout,
-                                                           const float* __restrict__ Rin, float* __restrict__ Rout, int r,
-                                                           int n, int k) {
-    extern __shared__ float lds[];   // a[n], b[n]: rows p, q after the row rotation
-    float* ra = lds;
-    float* rb = lds + n;
-    const int b = blockIdx.y;
-    const float* T = Tin + (int64_t)b * r * r;
-    const float* R = Rin + (int64_t)b * r * r;
-    float* To = Tout + (int64_t)b * r * r;
-    float* Ro = Rout + (int64_t)b * r * r;
-    // pair of this workgroup: x = blockIdx.x runs over the "first" members
-    const int m = n - 1;
-    int p, q;
-    {
-        const int i = blockIdx.x;  // 0 .. n/2-1
-        int x, y;
-        if (i == 0) { x = m; y = k; }
-        else { x = (k + i) % m; y = (k - i + m) % m; }
-        p = min(x, y); q = max(x, y);
-    }
-    float c, s;
-    jacobi_cs(T, r, r, p, q, c, s);
-    const bool live_p = p < r, live_q = q < r;
-    for (int j = threadIdx.x; j < n; j += 256) {
-        const float tp = (live_p && j < r) ? T[(int64_t)p * r + j] : 0.f;
-        const float tq = (live_q && j < r) ? T[(int64_t)q * r + j] : 0.f;
-        ra[j] = c * tp - s * tq;
-        rb[j] = s * tp + c * tq;
-        if (j < r) {   // eigenvector rows: Rᵀ ← Jᵀ·Rᵀ
-            const float rp = live_p ? R[(int64_t)p * r + j] : 0.f;
-            const float rq = live_q ? R[(int64_t)q * r + j] : 0.f;
-            if (live_p) Ro[(int64_t)p * r + j] = c * rp - s * rq;
-            if (live_q) Ro[(int64_t)q * r + j] = s * rp + c * rq;
+// indices (p < q) of rotation i (0 .. 31) in step k: the 32 cross pairs of two blocks (32 steps), or 16 pairs inside each
+// block (31 steps of a round-robin over 32)
+template <bool CROSS>
+__device__ __forceinline__ void step_pair(int i, int k, int& p, int& q) {
+    if constexpr (CROSS) { p = i; q = JB + ((i + k) & (JB - 1)); }
+    else {
+        int e = i & 15, a = JB - 1, b = k;
+        if (e) {
+            a = k + e; if (a >= JB - 1) a -= JB - 1;
+            b = k - e; if (b < 0) b += JB - 1;
         }
+        p = min(a, b) + (i >> 4) * JB; q = max(a, b) + (i >> 4) * JB;
+    }
+}
+
+// One step: A0 -> A1 = J·A0·Jᵀ (every thread one 2×2 block of the 32×32 grid of rotation pairs), W <- J·W in place.
+// Lane l of every wave derives rotation l % 32, so the step needs a single barrier.
+template <bool CROSS>
+__device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W, int k, int wave, int lane) {
+    const int j = lane & 31;
+    int pi, qi, pj, qj;
+    step_pair<CROSS>(2 * wave + (lane >> 5), k, pi, qi);
+    step_pair<CROSS>(j, k, pj, qj);
+    const float b00 = A0[pi * JP + pj], b01 = A0[pi * JP + qj], b10 = A0[qi * JP + pj], b11 = A0[qi * JP + qj];
+    const float w00 = W[pi * JP + j], w01 = W[pi * JP + j + 32], w10 = W[qi * JP + j], w11 = W[qi * JP + j + 32];
+    float sj, uj;
+    jacobi_su(A0[pj * JP + pj], A0[qj * JP + qj], A0[pj * JP + qj], sj, uj);
+    const auto lane_of = [](float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
+    const float s0 = lane_of(sj, 2 * wave), s1 = lane_of(sj, 2 * wave + 1), u0 = lane_of(uj, 2 * wave), u1 = lane_of(uj, 2 * wave + 1);
+    const float si = lane < 32 ? s0 : s1, ui = lane < 32 ? u0 : u1;
+    float r00, r01, r10, r11, x, y;
+    rotate(si, ui, b00, b10, r00, r10);
+    rotate(si, ui, b01, b11, r01, r11);
+    rotate(sj, uj, r00, r01, x, y);
+    A1[pi * JP + pj] = x;
+    A1[pi * JP + qj] = y;
+    rotate(sj, uj, r10, r11, x, y);
+    A1[qi * JP + pj] = x;
+    A1[qi * JP + qj] = y;
+    rotate(si, ui, w00, w10, x, y);
+    W[pi * JP + j] = x;
+    W[qi * JP + j] = y;
+    rotate(si, ui, w01, w11, x, y);
+    W[pi * JP + j + 32] = x;
+    W[qi * JP + j + 32] = y;
+    __syncthreads();
+}
+
+// One workgroup per (block pair of round k, item): the rotations of the pair's 64×64 sub-matrix of T.  Their product goes to
+// Wout[item][pair][64][64].  With a single pair (nb == 2) all `sweeps` sweeps run here; T and the product (then all of R) are the results.
+__global__ void __launch_bounds__(1024) jacobi_pair_kernel(float* __restrict__ T, float* __restrict__ Wout, int64_t w_stride, int w_rows,
+                                                           int r, int nb, int k, int sweeps) {
+    __shared__ float A[2][JW * JP];
+    __shared__ float W[JW * JP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int fb, sb;
+    block_pair(blockIdx.x, k, nb, fb, sb);
+    float* Tb = T + (int64_t)blockIdx.y * r * r;
+    for (int e = tid; e < JW * JW; e += 1024) {
+        const int i = e >> 6, j = e & 63, gi = pair_index(i, fb, sb), gj = pair_index(j, fb, sb);
+        A[0][i * JP + j] = (gi < r && gj < r) ? Tb[(int64_t)gi * r + gj] : 0.f;
+        W[i * JP + j] = i == j ? 1.f : 0.f;
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < r; j += 256) {
-        const int jp = rr_partner(j, k, n);
-        const int pj = min(j, jp), qj = max(j, jp);
-        float cj, sj;
-        jacobi_cs(T, r, r, pj, qj, cj, sj);
-        float op, oq;
-        if (j == pj) { op = cj * ra[pj] - sj * ra[qj]; oq = cj * rb[pj] - sj * rb[qj]; }
-        else { op = sj * ra[pj] + cj * ra[qj]; oq = sj * rb[pj] + cj * rb[qj]; }
-        if (live_p) To[(int64_t)p * r + j] = op;
-        if (live_q) To[(int64_t)q * r + j] = oq;
+    int buf = 0;
+    for (int sw = 0; sw < sweeps; ++sw) {
+        if (k == 0)
+            for (int t = 0; t < JB - 1; ++t, buf ^= 1) jacobi_step<false>(A[buf], A[buf ^ 1], W, t, wave, lane);
+        for (int t = 0; t < JB; ++t, buf ^= 1) jacobi_step<true>(A[buf], A[buf ^ 1], W, t, wave, lane);
+    }
+    float* Wb = Wout + (int64_t)blockIdx.y * w_stride + (int64_t)blockIdx.x * JW * JW;
+    for (int e = tid; e < JW * JW; e += 1024) {
+        const int i = e >> 6, j = e & 63;
+        if (i < w_rows && j < w_rows) Wb[i * w_rows + j] = W[i * JP + j];
+        if (nb == 2 && i < r && j < r) Tb[(int64_t)i * r + j] = A[buf][i * JP + j];
+    }
+}
+
+// acc (the wave's 16×16 piece, rows 16·(wave/4), columns 16·(wave%4)) = A·B of two 64×64 LDS matrices (pitch LP); B is read as
+// B[k][n], or as B[n][k] when NT
+constexpr int LP = JW + 4;
+template <bool NT>
+__device__ __forceinline__ f32x4 tile_product(const float* A, const float* B, int wave, int lane) {
+    const int row = 16 * (wave >> 2) + (lane & 15), col = 16 * (wave & 3) + (lane & 15), kq = lane >> 4;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < JW; k += 4) {
+        const float b = NT ? B[col * LP + k + kq] : B[(k + kq) * LP + col];
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(A[row * LP + k + kq], b, acc, 0, 0, 0);
+    }
+    return acc;
+}
+
+// One workgroup per 64×64 tile: tiles (P, Q <= P) of the symmetric T (the mirror tile is written from the same values), then
+// tiles of 64 columns of the eigenvector rows of pair P.  Every tile is read and written by its own workgroup only, so both
+// updates are in place.  Two 64³ products per tile are 2 µs of matrix-core time; 36 + 64 workgroups at r = 512.
+__global__ void __launch_bounds__(1024) jacobi_apply_kernel(float* __restrict__ T, float* __restrict__ R, const float* __restrict__ Wall,
+                                                            int r, int nb, int k) {
+    __shared__ float WP[JW * LP], WQ[JW * LP], X[JW * LP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int np = nb / 2, ntri = np * (np + 1) / 2;
+    const bool on_T = (int)blockIdx.x < ntri;
+    int P, Q;
+    if (on_T) {
+        const int t = blockIdx.x;
+        P = (int)((sqrtf(8.f * t + 1.f) - 1.f) * 0.5f);
+        while ((P + 1) * (P + 2) / 2 <= t) ++P;
+        while (P * (P + 1) / 2 > t) --P;
+        Q = t - P * (P + 1) / 2;
+    } else {
+        P = (blockIdx.x - ntri) % np;
+        Q = (blockIdx.x - ntri) / np;   // 64-column tile
+    }
+    int fp, sp, fq = 0, sq = 0;
+    block_pair(P, k, nb, fp, sp);
+    if (on_T) block_pair(Q, k, nb, fq, sq);
+    float* M = (on_T ? T : R) + (int64_t)blockIdx.y * r * r;
+    const float* Wb = Wall + (int64_t)blockIdx.y * np * JW * JW;
+    for (int e = tid; e < JW * JW; e += 1024) {
+        const int i = e >> 6, j = e & 63, gi = pair_index(i, fp, sp), gj = on_T ? pair_index(j, fq, sq) : Q * JW + j;
+        WP[i * LP + j] = Wb[(int64_t)P * JW * JW + e];
+        if (on_T) WQ[i * LP + j] = Wb[(int64_t)Q * JW * JW + e];
+        X[i * LP + j] = (gi < r && gj < r) ? M[(int64_t)gi * r + gj] : 0.f;
+    }
+    __syncthreads();
+    f32x4 acc = tile_product<false>(WP, X, wave, lane);
+    const int row = 16 * (wave >> 2) + 4 * (lane >> 4), col = 16 * (wave & 3) + (lane & 15);
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) X[(row + v) * LP + col] = acc[v];
+    __syncthreads();
+    if (on_T) {
+        acc = tile_product<true>(X, WQ, wave, lane);
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) X[(row + v) * LP + col] = acc[v];
+        __syncthreads();
+    }
+    for (int e = tid; e < JW * JW; e += 1024) {
+        const int i = e >> 6, j = e & 63;
+        const int gi = pair_index(i, fp, sp), gj = on_T ? pair_index(j, fq, sq) : Q * JW + j;
+        // the lower triangle of a diagonal tile stands for both halves: T stays exactly symmetric
+        if (gi < r && gj < r) M[(int64_t)gi * r + gj] = (on_T && P == Q && j > i) ? X[j * LP + i] : X[i * LP + j];
+        if (on_T && P != Q) {
+            const int hi = pair_index(j, fp, sp), hj = pair_index(i, fq, sq);   // (lane varies the row of X: the mirror row is contiguous)
+            if (hi < r && hj < r) M[(int64_t)hj * r + hi] = X[j * LP + i];
+        }
     }
 }
 
@@ -97,15 +203,19 @@ __global__ void __launch_bounds__(256) ritz_identity_kernel(float* __restrict__ 
     if (j < r) R[((int64_t)b * r + i) * r + j] = (i == j) ? 1.f : 0.f;
 }
 
-// rank of eigenvalue i in descending order (ties: lower index first); lam = diag(T)
+// rank of eigenvalue i in descending order (ties: lower index first); lam = diag(T), gathered into LDS first (r <= 4096)
 __global__ void __launch_bounds__(256) ritz_rank_kernel(const float* __restrict__ T, int r, int* __restrict__ rank) {
+    __shared__ float lam[4096];
     const int b = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= r) return;
     const float* Tb = T + (int64_t)b * r * r;
-    const float li = Tb[(int64_t)i * r + i];
+    for (int j = threadIdx.x; j < r; j += 256) lam[j] = Tb[(int64_t)j * r + j];
+    __syncthreads();
+    if (i >= r) return;
+    const float li = lam[i];
     int cnt = 0;
+#pragma unroll 8
     for (int j = 0; j < r; ++j) {
-        const float lj = Tb[(int64_t)j * r + j];
+        const float lj = lam[j];
         cnt += (lj > li || (lj == li && j < i)) ? 1 : 0;
     }
     rank[(int64_t)b * r + i] = cnt;
@@ -175,19 +285,30 @@ __global__ void __launch_bounds__(256) ritz_fallback_sign_kernel(T* __restrict__
     }
 }
 
+// part[b][i] = { max_{j≠i} |T_ij|, |T_ii| }: one wave per row
+__global__ void __launch_bounds__(256) ritz_rowmax_kernel(const float* __restrict__ T, int r, float2* __restrict__ part) {
+    const int b = blockIdx.y, lane = threadIdx.x & 63, i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= r) return;
+    const float* row = T + ((int64_t)b * r + i) * r;
+    float off = 0.f, lam = 0.f;
+    for (int j = lane; j < r; j += 64) {
+        const float v = fabsf(row[j]);
+        if (i == j) lam = v; else off = fmaxf(off, v);
+    }
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) { off = fmaxf(off, __shfl_xor(off, s)); lam = fmaxf(lam, __shfl_xor(lam, s)); }
+    if (lane == 0) part[(int64_t)b * r + i] = make_float2(off, lam);
+}
+
 // diag[b] = { Σ λ (= ‖B_r‖²_F), max_{i≠j} |T_ij| / max_i λ_i, μ = -log2 Σ (σ_i/Σσ)², ⌈2^μ⌉ }
-__global__ void __launch_bounds__(256) ritz_diag_kernel(const float* __restrict__ T, const float* __restrict__ sigma, int r,
+__global__ void __launch_bounds__(256) ritz_diag_kernel(const float2* __restrict__ part, const float* __restrict__ sigma, int r,
                                                         float* __restrict__ diag) {
     __shared__ float sh[4][256];
     const int b = blockIdx.x, tid = threadIdx.x;
-    const float* Tb = T + (int64_t)b * r * r;
     float off = 0.f, lmax = 0.f, s1 = 0.f, s2 = 0.f;
-    for (int64_t e = tid; e < (int64_t)r * r; e += 256) {
-        const int i = (int)(e / r), j = (int)(e % r);
-        const float v = Tb[e];
-        if (i == j) lmax = fmaxf(lmax, fabsf(v)); else off = fmaxf(off, fabsf(v));
-    }
     for (int i = tid; i < r; i += 256) {
+        const float2 m = part[(int64_t)b * r + i];
+        off = fmaxf(off, m.x); lmax = fmaxf(lmax, m.y);
         const float s = sigma[(int64_t)b * r + i];
         s1 += s; s2 += s * s;
     }
@@ -214,22 +335,18 @@ __global__ void __launch_bounds__(256) ritz_diag_kernel(const float* __restrict_
 
 }  // namespace
 
-hipError_t ritz_jacobi(hipStream_t st, float* T0, float* T1, float* R0, float* R1, int r, int batch, int sweeps,
-                       float** T_final, float** R_final) {
-    const int n = (r + 1) & ~1;
-    hipLaunchKernelGGL(ritz_identity_kernel, dim3((r + 255) / 256, r, batch), dim3(256), 0, st, R0, r);
-    float *Ti = T0, *To = T1, *Ri = R0, *Ro = R1;
-    if (n >= 2) {
-        const size_t lds = (size_t)2 * n * sizeof(float);
-        for (int sw = 0; sw < sweeps; ++sw)
-            for (int k = 0; k < n - 1; ++k) {
-                hipLaunchKernelGGL(jacobi_round_kernel, dim3(n / 2, batch), dim3(256), lds, st, Ti, To, Ri, Ro, r, n, k);
-                std::swap(Ti, To);
-                std::swap(Ri, Ro);
-            }
+hipError_t ritz_jacobi(hipStream_t st, float* T, float* R, float* W, int r, int batch, int sweeps) {
+    const int nb = 2 * ((r + JW - 1) / JW), np = nb / 2;
+    if (nb == 2) {
+        hipLaunchKernelGGL(jacobi_pair_kernel, dim3(1, batch), dim3(1024), 0, st, T, R, (int64_t)r * r, r, r, nb, 0, sweeps);
+        return hipGetLastError();
     }
-    *T_final = Ti;
-    *R_final = Ri;
+    hipLaunchKernelGGL(ritz_identity_kernel, dim3((r + 255) / 256, r, batch), dim3(256), 0, st, R, r);
+    for (int sw = 0; sw < sweeps; ++sw)
+        for (int k = 0; k < nb - 1; ++k) {
+            hipLaunchKernelGGL(jacobi_pair_kernel, dim3(np, batch), dim3(1024), 0, st, T, W, (int64_t)np * JW * JW, JW, r, nb, k, 1);
+            hipLaunchKernelGGL(jacobi_apply_kernel, dim3(np * (np + 1) / 2 + np * ((r + JW - 1) / JW), batch), dim3(1024), 0, st, T, R, W, r, nb, k);
+        }
     return hipGetLastError();
 }
 
@@ -252,8 +369,9 @@ hipError_t ritz_fallback_sign(hipStream_t st, void* U, void* B, const int* zero_
     return hipGetLastError();
 }
 
-hipError_t ritz_diagnostics(hipStream_t st, const float* T, const float* sigma, int r, int batch, float* diag) {
-    hipLaunchKernelGGL(ritz_diag_kernel, dim3(batch), dim3(256), 0, st, T, sigma, r, diag);
+hipError_t ritz_diagnostics(hipStream_t st, const float* T, const float* sigma, int r, int batch, float* part, float* diag) {
+    hipLaunchKernelGGL(ritz_rowmax_kernel, dim3((r + 3) / 4, batch), dim3(256), 0, st, T, r, (float2*)part);
+    hipLaunchKernelGGL(ritz_diag_kernel, dim3(batch), dim3(256), 0, st, (const float2*)part, sigma, r, diag);
     return hipGetLastError();
 }
 

@@ -79,3 +79,31 @@ def test_attention_f32(atp, case, variant):
     err = rel_fro(to_host(out), ref)
     print(case, variant, err, flush=True)
     assert err <= F32_TOL
+
+
+# r: one index, an odd one, one short of / at / past one block pair (64), block counts with padding blocks, several pairs
+@pytest.mark.parametrize("r", [1, 2, 33, 63, 64, 65, 96, 97, 128, 129, 200])
+def test_rayleigh_ritz_block_edges(atp, r):
+    """sigma from 1 to 1/2: eigenvalues of T lie 0.5/r apart or more, so the fp32 rounding of T (a few 2^-24) turns its
+    eigenvectors by a few 2^-24·2r."""
+    batch, L, d = 2, 210, 230
+    rng = np.random.default_rng(77 + r)
+    U, B = np.empty((batch, L, r), np.float32), np.empty((batch, r, d), np.float32)
+    for b in range(batch):
+        M = np.linalg.qr(rng.standard_normal((r, r)))[0]
+        U[b] = np.linalg.qr(rng.standard_normal((L, r)) + 0.2)[0] @ M
+        B[b] = M.T @ (np.linspace(1.0, 0.5, r)[:, None] * np.linalg.qr(rng.standard_normal((d, r)))[0].T)
+    Uo, Bo, sig, diag = atp.rayleigh_ritz(to_dev(U, "f32"), to_dev(B, "f32"), 10)
+    torch.cuda.synchronize()
+    tol = 20 * 2.0 ** -24 * 2 * r + 2e-6
+    for b in range(batch):
+        Ur, Br, sr = oracle.rayleigh_ritz(U[b].astype(np.float64), B[b].astype(np.float64))
+        assert np.abs(sig[b].cpu().numpy() - sr).max() <= 5e-6
+        # a column sum near zero leaves its sign to rounding
+        clear = np.abs(Ur.sum(0)) > 1e-3
+        eu, eb = rel_fro(to_host(Uo[b])[:, clear], Ur[:, clear]), rel_fro(to_host(Bo[b])[clear], Br[clear])
+        orth = np.abs(to_host(Uo[b]).T @ to_host(Uo[b]) - np.eye(r)).max()
+        print(r, b, eu, eb, orth, float(diag[b, 1]), flush=True)
+        assert eu <= tol and eb <= tol and orth <= 2e-5
+        assert float(diag[b, 1]) <= 1e-5
+        assert abs(float(diag[b, 0]) - (sr ** 2).sum()) <= 1e-5 * (sr ** 2).sum()
