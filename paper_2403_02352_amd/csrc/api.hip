@@ -118,25 +118,40 @@ struct Carver {
 // Workspace layout of atp_principal_bases (shared by the query and the call).
 constexpr int KSPLIT_MAX = 8;
 constexpr int NUM_CU = 256;  // compute units of an MI355X
+// The extraction works on padded extents: Lp, dp, rp >= L, d, r are the lengths of its internal rows, filled up with zeros, so that every
+// product runs on the asynchronous bf16 kernel (K a multiple of 64, of 32 with lo planes, rows aligned to 16 bytes) whatever L, d and r
+// are; zero columns of Ω carry through as zero columns of every iterate.  Extents that this kernel takes as they are stay as they are
+// (r when it is a multiple of 32, L and d when multiples of 64).  The fp32 path pads to 4, for 16-byte loads.
+// Measured at 2 × 1003 × 1536, r = 250: whole block 4.32 ms with the products in the strided kernel, 1.71 ms padded.
+struct BasesDims {
+    int64_t Lp, dp, rp;
+};
+BasesDims bases_dims(int64_t L, int64_t d, int64_t r, atp_dtype t) {
+    const auto up = [](int64_t x, int64_t n) { return (x + n - 1) / n * n; };
+    if (t == ATP_BF16) return {up(L, 64), up(d, 64), r % 32 ? up(r, 64) : r};
+    return {up(L, 4), up(d, 4), up(r, 4)};
+}
+
 struct BasesWs {
-    void* XT;        // [batch, d, L]  type t
+    void* XT;        // [batch, d, Lp]  type t
+    void* Xp;        // [batch, L, dp]  type t, only when dp != d
     float* Om;       // [d, r]   generated start block (only when Omega == NULL)
-    float* OmT;      // [r, d]   fp32
-    bf16_t* OmT16;   // [r, d]   bf16 (bf16 path)
-    float* ZL[2];    // [batch, L, r]
-    float* ZLT[2];   // [batch, r, L]
-    float* ZD[2];    // [batch, d, r]
-    float* ZDT[2];   // [batch, r, d]
-    void* TL;        // [batch, r, L]  type t: transposed twin of the current U (finally of the returned U_r)
-    void* TD;        // [batch, r, d]  type t: transposed twin of the current V
-    float* Spart;    // [KSPLIT_MAX, batch, r, r] split-K partial Gram matrices
-    float* S;        // [batch, r, r]
-    float* Lf;       // [batch, r, r]
-    float* Y;        // [batch, r, r]
-    float* Linv;     // [batch, r, r]
-    float* dinv;     // [batch, r]
+    void* OmT;       // [rp, dp] type t
+    float* ZL[2];    // [batch, L, rp]
+    float* ZLT[2];   // [batch, rp, Lp]
+    float* ZD[2];    // [batch, d, rp]
+    float* ZDT[2];   // [batch, rp, dp]
+    void* TL;        // [batch, rp, Lp]  type t: transposed twin of the current U (finally of the returned U_r)
+    void* TD;        // [batch, rp, dp]  type t: transposed twin of the current V
+    float* Spart;    // [KSPLIT_MAX, batch, rp, rp] split-K partial Gram matrices
+    float* S;        // [batch, rp, rp]
+    float* Lf;       // [batch, rp, rp]
+    float* Y;        // [batch, rp, rp]
+    float* Linv;     // [batch, rp, rp]
+    float* dinv;     // [batch, rp]
     int32_t* info;   // [batch]
     unsigned* flags; // hand-over flags of the single-launch factorisation
+    BasesDims dim;
     size_t total;
 };
 
@@ -144,24 +159,26 @@ BasesWs carve_bases(void* ws, int64_t batch, int64_t L, int64_t d, int64_t r, at
     Carver c(ws);
     BasesWs w;
     const size_t es = esize(t);
-    w.XT = c.take((size_t)batch * d * L * es);
+    w.dim = bases_dims(L, d, r, t);
+    const int64_t Lp = w.dim.Lp, dp = w.dim.dp, rp = w.dim.rp;
+    w.XT = c.take((size_t)batch * d * Lp * es);
+    w.Xp = dp != d ? c.take((size_t)batch * L * dp * es) : nullptr;
     w.Om = (float*)c.take((size_t)d * r * 4);
-    w.OmT = (float*)c.take((size_t)d * r * 4);
-    w.OmT16 = (bf16_t*)c.take((size_t)d * r * 2);
+    w.OmT = c.take((size_t)dp * rp * es);
     for (int i = 0; i < 2; ++i) {
-        w.ZL[i] = (float*)c.take((size_t)batch * L * r * 4);
-        w.ZLT[i] = (float*)c.take((size_t)batch * L * r * 4);
-        w.ZD[i] = (float*)c.take((size_t)batch * d * r * 4);
-        w.ZDT[i] = (float*)c.take((size_t)batch * d * r * 4);
+        w.ZL[i] = (float*)c.take((size_t)batch * L * rp * 4);
+        w.ZLT[i] = (float*)c.take((size_t)batch * Lp * rp * 4);
+        w.ZD[i] = (float*)c.take((size_t)batch * d * rp * 4);
+        w.ZDT[i] = (float*)c.take((size_t)batch * dp * rp * 4);
     }
-    w.TL = c.take((size_t)batch * r * L * es);
-    w.TD = c.take((size_t)batch * r * d * es);
-    w.Spart = (float*)c.take((size_t)KSPLIT_MAX * batch * r * r * 4);
-    w.S = (float*)c.take((size_t)batch * r * r * 4);
-    w.Lf = (float*)c.take((size_t)batch * r * r * 4);
-    w.Y = (float*)c.take((size_t)batch * r * r * 4);
-    w.Linv = (float*)c.take((size_t)batch * r * r * 4);
-    w.dinv = (float*)c.take((size_t)batch * r * 4);
+    w.TL = c.take((size_t)batch * rp * Lp * es);
+    w.TD = c.take((size_t)batch * rp * dp * es);
+    w.Spart = (float*)c.take((size_t)KSPLIT_MAX * batch * rp * rp * 4);
+    w.S = (float*)c.take((size_t)batch * rp * rp * 4);
+    w.Lf = (float*)c.take((size_t)batch * rp * rp * 4);
+    w.Y = (float*)c.take((size_t)batch * rp * rp * 4);
+    w.Linv = (float*)c.take((size_t)batch * rp * rp * 4);
+    w.dinv = (float*)c.take((size_t)batch * rp * 4);
     w.info = (int32_t*)c.take((size_t)batch * 4);
     w.flags = (unsigned*)c.take(factor_dataflow_flag_bytes((int)batch));
     w.total = c.off;
@@ -302,7 +319,8 @@ hipError_t pipe_after(void* vctx, int j) {
     return err;
 }
 
-// Orthonormalise the columns of Z (n×r, fp32, with transposed twin ZT) by `passes` rounds of
+// Orthonormalise the columns of Z (n×r, fp32, with transposed twin ZT whose rows have length n_pad; r includes the padding
+// columns, r_true does not) by `passes` rounds of
 // (Gram, Jacobi scaling + shift, Cholesky with inverse, apply).  Every round multiplies from the
 // right by an upper-triangular matrix with positive diagonal, so the result is the Q factor of
 // the positive-diagonal QR of Z.  Buffers ping-pong between slot `cur` and 1-cur; the last round
@@ -317,7 +335,7 @@ hipError_t pipe_after(void* vctx, int j) {
 // (bf16 path, r a multiple of 256) the last round issues it itself, block by block behind the
 // factorisation, and sets follow->done; otherwise the caller issues it.
 atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, int passes, float shift, Work Z[2], Work ZT[2],
-                       int& cur, int n, int r, int batch, BasesWs& w, int32_t* info, const QrOut* out,
+                       int& cur, int n, int n_pad, int r, int r_true, int batch, BasesWs& w, int32_t* info, const QrOut* out,
                        Follow* follow = nullptr) {
     Work linv;
     linv.base = w.Linv; linv.elems = (int64_t)batch * r * r;
@@ -326,8 +344,8 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
         const bool certify = last && final_qr;
         GemmArgs g;
         set_A(g, mfma, ZT[cur]); set_B(g, mfma, ZT[cur]);
-        g.lda = n; g.ldb = n; g.sA = (int64_t)r * n; g.sB = (int64_t)r * n;
-        g.M = r; g.N = r; g.K = n; g.batch = batch;
+        g.lda = n_pad; g.ldb = n_pad; g.sA = (int64_t)r * n_pad; g.sB = (int64_t)r * n_pad;
+        g.M = r; g.N = r; g.K = n_pad; g.batch = batch;
         g.C32 = w.Spart; g.ldc = r; g.sC = (int64_t)r * r;
         g.symmetric = 1;
         if (mfma && !certify && (g_cond_gram_single >= 2 || (g_cond_gram_single == 1 && middle))) {
@@ -345,8 +363,8 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
             // chip.  Cost model in units of one 32-deep k-tile per workgroup: rounds of workgroups
             // (one per compute unit) × (k-tiles per slice + the epilogue, worth about 8 k-tiles).
             const int64_t ntri = (int64_t)((r + 255) / 256) * ((r + 255) / 256 + 1) / 2 * batch;
-            const int kt = std::max(1, n / 32);
-            const int np_max = std::max(1, std::min(KSPLIT_MAX, n / 256));
+            const int kt = std::max(1, n_pad / 32);
+            const int np_max = std::max(1, std::min(KSPLIT_MAX, n_pad / 256));
             double best = 0.0;
             for (int np = 1; np <= np_max; ++np) {
                 const double rounds = (double)((ntri * np + NUM_CU - 1) / NUM_CU);
@@ -363,19 +381,20 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
         set_A(a, mfma, Z[cur]); set_B(a, mfma, linv);
         a.lda = r; a.ldb = r; a.sA = (int64_t)n * r; a.sB = (int64_t)r * r;
         a.M = n; a.N = r; a.K = r; a.batch = batch;
-        a.ldc = r; a.sC = (int64_t)n * r; a.ldct = n; a.sCT = (int64_t)n * r;
+        a.ldc = r; a.sC = (int64_t)n * r; a.ldct = n_pad; a.sCT = (int64_t)r * n_pad;
         a.b_lower = 1;
         const bool apply_mfma = mfma && gemm_nt_mfma_ok(a);
         const int zero_all = !apply_mfma;
         if (last && out) {
             a.C32 = out->C32; a.C16 = out->C16;
             a.CT32 = out->CT32; a.CT16 = out->CT16;
+            if (out->C32 || out->C16) { a.N = r_true; a.ldc = r_true; a.sC = (int64_t)n * r_true; }   // a result: no padding columns
         } else {
             set_C(a, mfma, Z[1 - cur], ZT[1 - cur]);
         }
         // pipelined round: blocks of Z·R^-1 (and of the follow-up product) run on the side stream
         // behind the factorisation
-        const bool pipe = g_overlap && apply_mfma && (r % PIECE == 0) && (r >= 2 * PIECE) && side_ready();
+        const bool pipe = g_overlap && apply_mfma && r == r_true && (r % PIECE == 0) && (r >= 2 * PIECE) && side_ready();
         Follow* fol = (last && follow && follow->slice != FOLLOW_NONE && gemm_nt_mfma_ok(follow->g)) ? follow : nullptr;
         PipeCtx pc;
         pc.st = st; pc.apply = a; pc.follow = fol; pc.r = r;
@@ -384,7 +403,7 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
             ProfScope ps(st, ATP_K_CHOLESKY, (double)batch * r * r * r * (2.0 / 3.0), (double)batch * r * r * 16.0);
             const bool dataflow = g_factor_mode >= 1 && !pipe && factor_dataflow_ok(r, batch, g_factor_mode == 1);
             ATP_HIP(gram_prepare(st, w.Spart, nparts, (int64_t)batch * r * r, w.S, w.dinv, w.Y, mfma ? nullptr : w.Linv,
-                                 mfma ? linv.hi() : nullptr, mfma ? linv.lo() : nullptr, r, certify ? 0.f : shift, zero_all, batch,
+                                 mfma ? linv.hi() : nullptr, mfma ? linv.lo() : nullptr, r, r_true, certify ? 0.f : shift, zero_all, batch,
                                  dataflow ? w.flags : nullptr));
             if (dataflow)
                 ATP_HIP(factor_inverse_dataflow(st, w.S, w.Lf, w.Y, w.dinv, mfma ? nullptr : w.Linv, mfma ? linv.hi() : nullptr,
@@ -497,34 +516,41 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
     const int iL = (int)L, id = (int)d, ir = (int)r, ib = (int)batch;
     const float shift = mfma ? 1e-4f : 1e-5f;
     int32_t* inf = info ? info : w.info;
-    ATP_HIP(fill_zero_i32(st, inf, batch));
+    const int64_t Lp = w.dim.Lp, dp = w.dim.dp, rp = w.dim.rp;
+    const int iLp = (int)Lp, idp = (int)dp, irp = (int)rp, es = (int)esize(t);
 
-    // operand twins: Xᵀ and Ωᵀ
+    // operand twins: Xᵀ and Ωᵀ (and X itself when its rows have to be filled up)
     {
         ProfScope ps(st, ATP_K_STREAM, 0.0, 2.0 * (double)batch * L * d * esize(t));
-        ATP_HIP(transpose_batched(st, X, w.XT, iL, id, L, L * d, L * d, ib, (int)esize(t), 0));
+        ATP_HIP(transpose_batched(st, X, w.XT, iL, id, Lp, L * d, Lp * d, ib, es, Lp != L));
+        if (w.Xp) ATP_HIP(pad_rows(st, X, w.Xp, batch * L, id, idp, es));
     }
+    const void* Xk = w.Xp ? w.Xp : X;
     const float* Om = Omega;
     if (!Om) {
         ATP_HIP(fill_gaussian(st, w.Om, d * r, seed));
         Om = w.Om;
     }
-    ATP_HIP(transpose_batched(st, Om, w.OmT, id, ir, d, 0, 0, 1, 4, 0));
-    if (mfma) ATP_HIP(cast_f32_to_bf16(st, w.OmT, w.OmT16, d * r));
+    ATP_HIP(start_block_twin(st, Om, w.OmT, id, ir, idp, irp, es, inf, ib));
 
     // Z = X·Ω
     int curL = 0, curD = 0;
     Work ZL[2], ZLT[2], ZD[2], ZDT[2];
     for (int i = 0; i < 2; ++i) {
-        ZL[i].base = w.ZL[i]; ZLT[i].base = w.ZLT[i]; ZL[i].elems = ZLT[i].elems = batch * L * r;
-        ZD[i].base = w.ZD[i]; ZDT[i].base = w.ZDT[i]; ZD[i].elems = ZDT[i].elems = batch * d * r;
+        ZL[i].base = w.ZL[i]; ZL[i].elems = batch * L * rp; ZLT[i].base = w.ZLT[i]; ZLT[i].elems = batch * Lp * rp;
+        ZD[i].base = w.ZD[i]; ZD[i].elems = batch * d * rp; ZDT[i].base = w.ZDT[i]; ZDT[i].elems = batch * dp * rp;
+    }
+    {   // the ends of twin rows, which no product writes (both planes of a bf16 twin are rows of one matrix)
+        const int64_t nz = batch * rp * (mfma ? 2 : 1);
+        ATP_HIP(zero_columns(st, {w.ZLT[0], w.ZLT[1], w.TL}, {nz, nz, batch * rp}, {es, es, es}, iL, iLp));
+        if (iters > 0) ATP_HIP(zero_columns(st, {w.ZDT[0], w.ZDT[1], w.TD}, {nz, nz, batch * rp}, {es, es, es}, id, idp));
     }
     {
         GemmArgs g;
-        g.A = X; g.B = mfma ? (const void*)w.OmT16 : (const void*)w.OmT;
-        g.lda = d; g.ldb = d; g.sA = L * d; g.sB = 0;
-        g.M = iL; g.N = ir; g.K = id; g.batch = ib;
-        g.ldc = r; g.sC = L * r; g.ldct = L; g.sCT = L * r;
+        g.A = Xk; g.B = w.OmT;
+        g.lda = dp; g.ldb = dp; g.sA = L * dp; g.sB = 0;
+        g.M = iL; g.N = irp; g.K = idp; g.batch = ib;
+        g.ldc = rp; g.sC = L * rp; g.ldct = Lp; g.sCT = Lp * rp;
         set_C(g, mfma, ZL[0], ZLT[0]);
         ATP_HIP(nt_product(st, mfma, g));
     }
@@ -544,36 +570,36 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
     // the three products that consume an orthonormalised iterate
     auto prod_w = [&]() {  // W = Xᵀ·U      (d×r)
         GemmArgs g;
-        g.A = w.XT; g.B = w.TL; g.lda = L; g.ldb = L; g.sA = L * d; g.sB = L * r;
-        g.M = id; g.N = ir; g.K = iL; g.batch = ib;
-        g.ldc = r; g.sC = d * r; g.ldct = d; g.sCT = d * r;
+        g.A = w.XT; g.B = w.TL; g.lda = Lp; g.ldb = Lp; g.sA = d * Lp; g.sB = rp * Lp;
+        g.M = id; g.N = irp; g.K = iLp; g.batch = ib;
+        g.ldc = rp; g.sC = d * rp; g.ldct = dp; g.sCT = rp * dp;
         set_C(g, mfma, ZD[0], ZDT[0]);
         return g;
     };
     auto prod_z = [&]() {  // Z = X·V       (L×r)
         GemmArgs h;
-        h.A = X; h.B = w.TD; h.lda = d; h.ldb = d; h.sA = L * d; h.sB = d * r;
-        h.M = iL; h.N = ir; h.K = id; h.batch = ib;
-        h.ldc = r; h.sC = L * r; h.ldct = L; h.sCT = L * r;
+        h.A = Xk; h.B = w.TD; h.lda = dp; h.ldb = dp; h.sA = L * dp; h.sB = rp * dp;
+        h.M = iL; h.N = irp; h.K = idp; h.batch = ib;
+        h.ldc = rp; h.sC = L * rp; h.ldct = Lp; h.sCT = rp * Lp;
         set_C(h, mfma, ZL[0], ZLT[0]);
         return h;
     };
     auto prod_b = [&]() {  // B_r = U_rᵀ·X  (r×d) with the returned (rounded) U_r
         GemmArgs g;
-        g.A = w.TL; g.B = w.XT; g.lda = L; g.ldb = L; g.sA = r * L; g.sB = d * L;
-        g.M = ir; g.N = id; g.K = iL; g.batch = ib;
+        g.A = w.TL; g.B = w.XT; g.lda = Lp; g.ldb = Lp; g.sA = rp * Lp; g.sB = d * Lp;
+        g.M = ir; g.N = id; g.K = iLp; g.batch = ib;
         g.ldc = d; g.sC = r * d;
         if (t == ATP_BF16) g.C16 = (bf16_t*)B_r; else g.C32 = (float*)B_r;
         return g;
     };
     // an orthonormalisation followed by the product that consumes it (issued here unless the
     // orthonormalisation has already issued it block by block)
-    auto qr_then = [&](bool final_qr, bool middle, int passes, Work* Zw, Work* ZTw, int& cur, int n, const QrOut* out, GemmArgs next,
-                       FollowSlice how) -> atp_status {
+    auto qr_then = [&](bool final_qr, bool middle, int passes, Work* Zw, Work* ZTw, int& cur, int n, int n_pad, const QrOut* out,
+                       GemmArgs next, FollowSlice how) -> atp_status {
         Follow f;
         f.g = next;
         f.slice = how;
-        const atp_status s = cholesky_qr(st, mfma, final_qr, middle, passes, shift, Zw, ZTw, cur, n, ir, ib, w, inf, out, &f);
+        const atp_status s = cholesky_qr(st, mfma, final_qr, middle, passes, shift, Zw, ZTw, cur, n, n_pad, irp, ir, ib, w, inf, out, &f);
         if (s != ATP_OK) return s;
         if (final_qr && t == ATP_F32 && U_master)
             ATP_HIP(hipMemcpyAsync(U_master, U_r, (size_t)batch * L * r * 4, hipMemcpyDeviceToDevice, st));
@@ -583,20 +609,20 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
 
     atp_status s;
     if (iters == 0) {
-        s = qr_then(true, false, g_passes_last, ZL, ZLT, curL, iL, &fin, prod_b(), FOLLOW_M);
+        s = qr_then(true, false, g_passes_last, ZL, ZLT, curL, iL, iLp, &fin, prod_b(), FOLLOW_M);
         if (s != ATP_OK) return s;
     } else {
-        s = qr_then(false, false, g_passes_first, ZL, ZLT, curL, iL, &midL, prod_w(), FOLLOW_N);
+        s = qr_then(false, false, g_passes_first, ZL, ZLT, curL, iL, iLp, &midL, prod_w(), FOLLOW_N);
         if (s != ATP_OK) return s;
     }
     for (int it = 0; it < iters; ++it) {
         curD = 0;
-        s = qr_then(false, true, g_passes_middle, ZD, ZDT, curD, id, &midD, prod_z(), FOLLOW_N);
+        s = qr_then(false, true, g_passes_middle, ZD, ZDT, curD, id, idp, &midD, prod_z(), FOLLOW_N);
         if (s != ATP_OK) return s;
         curL = 0;
         const bool lastit = (it == iters - 1);
-        if (lastit) s = qr_then(true, false, g_passes_last, ZL, ZLT, curL, iL, &fin, prod_b(), FOLLOW_M);
-        else s = qr_then(false, true, g_passes_middle, ZL, ZLT, curL, iL, &midL, prod_w(), FOLLOW_N);
+        if (lastit) s = qr_then(true, false, g_passes_last, ZL, ZLT, curL, iL, iLp, &fin, prod_b(), FOLLOW_M);
+        else s = qr_then(false, true, g_passes_middle, ZL, ZLT, curL, iL, iLp, &midL, prod_w(), FOLLOW_N);
         if (s != ATP_OK) return s;
     }
     return ATP_OK;

@@ -124,6 +124,13 @@ hipError_t transpose_batched(hipStream_t st, const void* in, void* out, int rows
 // Omega generator: out[d*r] fp32 N(0,1), counter-based
 hipError_t fill_gaussian(hipStream_t st, float* out, int64_t n, uint64_t seed);
 hipError_t fill_zero_i32(hipStream_t st, int32_t* p, int64_t n);
+// out[cols_out][rows_out] (bf16 or fp32) = transpose of the fp32 matrix in[rows][cols], zeros outside it; also clears zero[0 .. n_zero)
+hipError_t start_block_twin(hipStream_t st, const float* in, void* out, int rows, int cols, int rows_out, int cols_out, int elem_bytes,
+                            int32_t* zero, int n_zero);
+// out[b][i][0 .. ld_out) = in[b][i][0 .. cols) followed by zeros
+hipError_t pad_rows(hipStream_t st, const void* in, void* out, int64_t rows, int cols, int ld_out, int elem_bytes);
+// columns from .. ld-1 of `rows` rows of three matrices set to zero (null or rows == 0: skipped)
+hipError_t zero_columns(hipStream_t st, void* const (&m)[3], const int64_t (&rows)[3], const int (&elem_bytes)[3], int from, int ld);
 hipError_t cast_f32_to_bf16(hipStream_t st, const float* in, bf16_t* out, int64_t n);
 // rotary position encoding of the rows of in [batch][L][dq] (heads of width dh, half-split pairs); in == out allowed
 hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L, int dq, int dh, float base, int pos0,
@@ -142,13 +149,15 @@ hipError_t norm_basis(hipStream_t st, const void* P, const float* PM, void* Pn, 
 // ---------------------------------------------------------------------------
 // r×r pieces of the CholeskyQR (fp32, batched)
 // ---------------------------------------------------------------------------
+// (in all of these r is a multiple of 4; the caller pads the matrix)
 // Sum `nparts` partial Gram matrices (stride `pstride` elements; only their lower 64×64-tile
 // triangle is read), scale to unit diagonal (dinv_j = 1/sqrt(S_jj), 1 if S_jj is not positive and
-// finite), add `shift` to the diagonal; also sets Y = I on its upper tile triangle and zeroes the
+// finite), add `shift` to the diagonal; rows and columns r_true .. r-1 become those of the identity.  Also sets Y = I
+// on its upper tile triangle (not for the single-launch factorisation, which is named by passing its flags) and zeroes the
 // part of Binv that factor_inverse leaves unwritten (all of its strict upper tile triangle when
 // zero_all is set, else only inside the 256-wide diagonal blocks).
 hipError_t gram_prepare(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* S, float* dinv,
-                        float* Y, float* Binv, bf16_t* Bh, bf16_t* Bl, int r, float shift, int zero_all, int batch,
+                        float* Y, float* Binv, bf16_t* Bh, bf16_t* Bl, int r, int r_true, float shift, int zero_all, int batch,
                         unsigned* flags = nullptr);
 // Cholesky S = L·Lᵀ (S is overwritten with intermediate trailing blocks, L goes to Lf) and Binv[n][k] = (L^-1)[n][k]·dinv[k] (lower triangular).
 // info[b] receives the first column (1-based) whose pivot is below `flag_below` (kept if already

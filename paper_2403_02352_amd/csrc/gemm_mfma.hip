@@ -47,7 +47,7 @@ constexpr int WBUF = 64 * WPITCH;     // elements per wave
 struct EpiPtrs {
     float* C32;
     bf16_t *C16, *C16lo, *CT16, *CT16lo;
-    bool vecC, vecT;  // 16-byte stores allowed (extents and leading dimensions multiples of 8, aligned bases)
+    bool vecC, vecT;  // 16-byte stores allowed (leading dimensions and, for C, N multiples of 8, aligned bases)
 };
 
 template <int IH, int JH, int TM, int TN>
@@ -126,7 +126,10 @@ __device__ __forceinline__ void store_piece(const GemmArgs& p, const EpiPtrs& e,
                 const int c = it * 64 + lane, cc = c >> 3, part = c & 7;
                 const uint4 q = *reinterpret_cast<const uint4*>(wbuf + cc * WPITCH + part * 8);
                 const int col = pcol + cc, row = prow + part * 8;
-                if (row < p.M && col < p.N) *reinterpret_cast<uint4*>(dst + (int64_t)col * p.ldct + row) = q;
+                if (col >= p.N) continue;
+                if (row + 8 <= p.M) *reinterpret_cast<uint4*>(dst + (int64_t)col * p.ldct + row) = q;
+                else   // the piece across the last row; what lies beyond keeps its value (zeros of a padded twin)
+                    for (int t = 0; row + t < p.M; ++t) dst[(int64_t)col * p.ldct + row + t] = wbuf[cc * WPITCH + part * 8 + t];
             }
         } else {
             for (int c = lane; c < 64 * 64; c += 64) {
@@ -156,7 +159,7 @@ __device__ __forceinline__ void store_outputs(const GemmArgs& p, const f32x16 (&
     e.CT16lo = p.CT16lo ? p.CT16lo + (int64_t)bz * p.sCT : nullptr;
     e.vecC = (p.N % 8 == 0) && (p.ldc % 8 == 0) && (p.sC % 8 == 0) &&
              ((((uintptr_t)p.C16) | ((uintptr_t)p.C16lo)) & 15) == 0;
-    e.vecT = (p.M % 8 == 0) && (p.ldct % 8 == 0) && (p.sCT % 8 == 0) &&
+    e.vecT = (p.ldct % 8 == 0) && (p.sCT % 8 == 0) &&
              ((((uintptr_t)p.CT16) | ((uintptr_t)p.CT16lo)) & 15) == 0;
     store_pieces<TM, TN>(std::make_integer_sequence<int, (TM / 2) * (TN / 2)>{}, p, e, acc, wbuf, row0, col0, lane);
 }

@@ -1,6 +1,7 @@
 // r×r pieces of the CholeskyQR orthonormalisation (fp32, batched over sequences).
 // The orthonormal factor they lead to is the U of Eq.5 (UᵀU = I, text after Eq.8).
 //
+//  (r below is padded to a multiple of 4 by the caller, see prepare_kernel)
 //  1. gram_prepare: sum the split-K partial Gram matrices, Jacobi-scale them to unit diagonal
 //     (S' = D·S·D, D = diag(S)^-1/2), add the shift, and initialise the work matrices.
 //  2. factor_inverse: blocked right-looking Cholesky of S' = L·Lᵀ carried out on the augmented
@@ -35,94 +36,96 @@ __device__ long long g_df_trace[1024];
 #endif
 
 // ---------------------------------------------------------------------------
-// dinv[j] = 1/sqrt(sum_p Spart[p][j][j])   (1 if the diagonal entry is not positive and finite)
-// Also clears the item's hand-over flags of the single-launch factorisation (flags may be null) and arms
-// its exchange slots (wx: the first wx_fill_words words of every item's wx_stride_words are set to the
-// "not written yet" pattern).
-__global__ void diag_rsqrt_kernel(const float* __restrict__ Sp, int nparts, int64_t pstride, float* __restrict__ dinv,
-                                  int r, unsigned* __restrict__ flags, int flag_words, uint4* __restrict__ wx,
-                                  int wx_stride_words, int wx_fill_words) {
-    const int b = blockIdx.y;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (flags) {
-        for (int e = j; e < flag_words; e += gridDim.x * blockDim.x) flags[(int64_t)b * flag_words + e] = 0u;
-        const uint4 unset = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-        for (int e = j; e < wx_fill_words / 4; e += gridDim.x * blockDim.x) wx[(int64_t)b * (wx_stride_words / 4) + e] = unset;
-    }
-    if (j >= r) return;
-    float s = 0.f;
-    for (int p = 0; p < nparts; ++p) s += Sp[(int64_t)p * pstride + (int64_t)b * r * r + (int64_t)j * r + j];
-    const bool ok = (s > 0.f) && (s < 3.0e38f);
-    dinv[(int64_t)b * r + j] = ok ? 1.0f / sqrtf(s) : 1.0f;
-}
-
-// Initialises the work matrices of one factorisation, touching only what the factorisation and the
-// product Z·R^-1 read afterwards (64×64 tile granularity, ti = i/64, tj = j/64):
+// Set-up of one factorisation, one workgroup per 64×64 tile (ti, tj); r is a multiple of 4 (the caller pads to it), of which the
+// first r_true rows and columns belong to the matrix:
+//   dinv[j] = 1/sqrt(sum_p Spart[p][j][j])   (1 if the diagonal entry is not positive and finite)
 //   S'[i][j] = (sum_p Spart[p][i][j])·dinv[i]·dinv[j] (+ shift on the diagonal)   for tj <= ti
-//              (the Gram kernel fills the lower 256×256 tiles of the partial sums only);
-//   Y = I on the tiles with tj >= ti (the factorisation builds L^-T there);
-//   Binv = 0 where the factorisation never writes but the product reads: tj > ti, and, unless
+//              (the Gram kernel fills the lower 256×256 tiles of the partial sums only); padding is a unit diagonal, which leaves
+//              the factorisation of the rest as it is and never raises `info`;
+//   Y = I on the tiles with tj >= ti (null: the single-launch factorisation needs no start value);
+//   Binv = 0 where the factorisation never writes but the product Z·R^-1 reads: tj > ti, and, unless
 //   zero_all is set, only inside the 256-wide diagonal block (the MFMA product stops its K loop at
 //   the end of the diagonal block of a triangular operand).
-__global__ void prepare_kernel(const float* __restrict__ Sp, int nparts, int64_t pstride, float* __restrict__ S,
-                               const float* __restrict__ dinv, float* __restrict__ Y, float* __restrict__ Binv,
-                               bf16_t* __restrict__ Bh, bf16_t* __restrict__ Bl, int r, float shift, int zero_all) {
-    const int b = blockIdx.z;
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int i = blockIdx.y;
-    if (j >= r) return;
-    const int ti = i >> 6, tj = j >> 6;
-    const int64_t o = (int64_t)b * r * r + (int64_t)i * r + j;
-    if (tj <= ti) {
-        float s = 0.f;
-        for (int p = 0; p < nparts; ++p) s += Sp[(int64_t)p * pstride + o];
-        const float* db = dinv + (int64_t)b * r;
-        const float v = s * db[i] * db[j];
-        S[o] = (i == j) ? v + shift : v;
+// Also clears the item's hand-over flags of the single-launch factorisation (flags may be null) and arms its exchange slots (wx: the
+// first wx_fill_words words of every item's wx_stride_words are set to the "not written yet" pattern).
+// HBM-bound (nparts reads of the lower triangle).  Every tile forms the 128 scale factors it needs itself: the 128·nparts diagonal
+// loads travel with the tile's own and come from L2, where a launch of its own for dinv cost 5 µs per factorisation.
+// NP = number of partial sums, a constant so that all loads of a thread are in flight together.
+template <int NP>
+__global__ void __launch_bounds__(256) prepare_kernel(const float* __restrict__ Sp, int64_t pstride, float* __restrict__ S,
+                                                      float* __restrict__ dinv, float* __restrict__ Y, float* __restrict__ Binv,
+                                                      bf16_t* __restrict__ Bh, bf16_t* __restrict__ Bl, int r, int r_true, float shift,
+                                                      int zero_all, unsigned* __restrict__ flags, int flag_words, uint4* __restrict__ wx,
+                                                      int wx_stride_words, int wx_fill_words) {
+    __shared__ float sc[2][NB];
+    const int b = blockIdx.z, ti = blockIdx.y, tj = blockIdx.x, tid = threadIdx.x;
+    const int64_t base = (int64_t)b * r * r;
+    if (flags) {
+        const int first = (ti * gridDim.x + tj) * 256 + tid, step = gridDim.x * gridDim.y * 256;
+        for (int e = first; e < flag_words; e += step) flags[(int64_t)b * flag_words + e] = 0u;
+        const uint4 unset = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
+        for (int e = first; e < wx_fill_words / 4; e += step) wx[(int64_t)b * (wx_stride_words / 4) + e] = unset;
     }
-    if (tj >= ti) Y[o] = (i == j) ? 1.f : 0.f;
-    if (tj > ti && (zero_all || (i >> 8) == (j >> 8))) {
-        if (Binv) Binv[o] = 0.f;
-        if (Bh) { Bh[o] = 0; Bl[o] = 0; }
-    }
-}
-
-// Same for r a multiple of 4: a thread handles four consecutive columns (they lie in one 64-wide tile)
-// with 16-byte accesses.
-__global__ void prepare4_kernel(const float* __restrict__ Sp, int nparts, int64_t pstride, float* __restrict__ S,
-                                const float* __restrict__ dinv, float* __restrict__ Y, float* __restrict__ Binv,
-                                bf16_t* __restrict__ Bh, bf16_t* __restrict__ Bl, int r, float shift, int zero_all) {
-    const int b = blockIdx.z;
-    const int j = (blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    const int i = blockIdx.y;
-    if (j >= r) return;
-    const int ti = i >> 6, tj = j >> 6;
-    const int64_t o = (int64_t)b * r * r + (int64_t)i * r + j;
+    const int j = tj * NB + (tid & 15) * 4;
     if (tj <= ti) {
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < nparts; ++p) s += *reinterpret_cast<const f32x4*>(Sp + (int64_t)p * pstride + o);
-        const float* db = dinv + (int64_t)b * r;
-        const float di = db[i];
-        const f32x4 dj = *reinterpret_cast<const f32x4*>(db + j);
-        f32x4 v;
+        f32x4 s[4], part[NP][4];
+        float dg = 0.f, dpart[NP];
+        const int k = (tid < NB ? ti : tj) * NB + (tid & 63);   // diagonal entry of the first 128 threads
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const float* src = Sp + (int64_t)p * pstride + base;
+            dpart[p] = (tid < 2 * NB && k < r) ? src[(int64_t)k * r + k] : 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = ti * NB + (tid >> 4) + 16 * q;
+                part[p][q] = (i < r && j < r) ? *reinterpret_cast<const f32x4*>(src + (int64_t)i * r + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] = part[0][q];
+        dg = dpart[0];
+#pragma unroll
+        for (int p = 1; p < NP; ++p) {
+            dg += dpart[p];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) s[q] += part[p][q];
+        }
+        if (tid < 2 * NB) {
+            const float di = (dg > 0.f && dg < 3.0e38f) ? 1.0f / sqrtf(dg) : 1.0f;
+            sc[tid >> 6][tid & 63] = di;
+            if (ti == tj && tid < NB && k < r) dinv[(int64_t)b * r + k] = di;
+        }
+        __syncthreads();
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            v[q] = s[q] * di * dj[q];
-            if (i == j + q) v[q] += shift;
-        }
-        *reinterpret_cast<f32x4*>(S + o) = v;
-    }
-    if (tj >= ti) {
-        f32x4 e;
+            const int li = (tid >> 4) + 16 * q, i = ti * NB + li;
+            if (i >= r || j >= r) continue;
+            f32x4 v;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) e[q] = (i == j + q) ? 1.f : 0.f;
-        *reinterpret_cast<f32x4*>(Y + o) = e;
+            for (int e = 0; e < 4; ++e) {
+                v[e] = s[q][e] * sc[0][li] * sc[1][(tid & 15) * 4 + e];
+                if (i == j + e) v[e] = (i < r_true ? v[e] : 1.f) + shift;
+            }
+            *reinterpret_cast<f32x4*>(S + base + (int64_t)i * r + j) = v;
+        }
     }
-    if (tj > ti && (zero_all || (i >> 8) == (j >> 8))) {
-        if (Binv) *reinterpret_cast<f32x4*>(Binv + o) = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (Bh) {
-            *reinterpret_cast<uint2*>(Bh + o) = make_uint2(0u, 0u);
-            *reinterpret_cast<uint2*>(Bl + o) = make_uint2(0u, 0u);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = ti * NB + (tid >> 4) + 16 * q;
+        if (i >= r || j >= r) continue;
+        const int64_t o = base + (int64_t)i * r + j;
+        if (Y && tj >= ti) {
+            f32x4 e;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) e[v] = (i == j + v) ? 1.f : 0.f;
+            *reinterpret_cast<f32x4*>(Y + o) = e;
+        }
+        if (tj > ti && (zero_all || (i >> 8) == (j >> 8))) {
+            if (Binv) *reinterpret_cast<f32x4*>(Binv + o) = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (Bh) {
+                *reinterpret_cast<uint2*>(Bh + o) = make_uint2(0u, 0u);
+                *reinterpret_cast<uint2*>(Bl + o) = make_uint2(0u, 0u);
+            }
         }
     }
 }
@@ -357,23 +360,12 @@ constexpr int LP = NB + 4;  // padded row length of the MFMA operand tiles (16-b
 // 64×64 tile -> LDS (row-major, padded), optionally negated; rows/cols past r read as zero
 __device__ __forceinline__ void tile_to_lds(float (*dst)[LP], const float* __restrict__ src, int r, int row0, int col0,
                                             float sign, bool enable, int tid) {
-    const bool vec = ((r & 3) == 0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int row = (tid >> 4) + 16 * q, c4 = (tid & 15) * 4;
         const int gr = row0 + row, gc = col0 + c4;
         float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (enable && gr < r) {
-            const float* ptr = src + (int64_t)gr * r + gc;
-            if (vec && gc + 3 < r) {
-                v = *reinterpret_cast<const float4*>(ptr);
-            } else {
-                if (gc + 0 < r) v.x = ptr[0];
-                if (gc + 1 < r) v.y = ptr[1];
-                if (gc + 2 < r) v.z = ptr[2];
-                if (gc + 3 < r) v.w = ptr[3];
-            }
-        }
+        if (enable && gr < r && gc < r) v = *reinterpret_cast<const float4*>(src + (int64_t)gr * r + gc);
         *reinterpret_cast<float4*>(&dst[row][c4]) = make_float4(sign * v.x, sign * v.y, sign * v.z, sign * v.w);
     }
 }
@@ -538,45 +530,27 @@ __global__ void __launch_bounds__(256, 2) factor_step_kernel(float* S, float* Lf
     // ---- store ---------------------------------------------------------------------------------------
     if (!ykind) {
         const bool diag = (rb == j);
-        if ((r & 3) == 0) {   // 16-byte row pieces
-            for (int e = tid; e < NB * NB / 4; e += 256) {
-                const int row = e >> 4, col = (e & 15) * 4;
-                const int gr = r0 + row, gc = c0 + col;
-                if (gr < r && gc < r) {
-                    f32x4 v;
+        // 16-byte row pieces
+        for (int e = tid; e < NB * NB / 4; e += 256) {
+            const int row = e >> 4, col = (e & 15) * 4;
+            const int gr = r0 + row, gc = c0 + col;
+            if (gr < r && gc < r) {
+                f32x4 v;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = diag ? ((row >= col + q) ? Bs[row][col + q] : 0.f) : As[row][col + q];
-                    *reinterpret_cast<f32x4*>(Lb + (int64_t)gr * r + gc) = v;
-                }
-            }
-        } else {
-            for (int e = tid; e < NB * NB; e += 256) {
-                const int row = e >> 6, col = e & 63;
-                const int gr = r0 + row, gc = c0 + col;
-                if (gr < r && gc < r) {
-                    float v = diag ? ((row >= col) ? Bs[row][col] : 0.f) : As[row][col];
-                    Lb[(int64_t)gr * r + gc] = v;
-                }
+                for (int q = 0; q < 4; ++q) v[q] = diag ? ((row >= col + q) ? Bs[row][col + q] : 0.f) : As[row][col + q];
+                *reinterpret_cast<f32x4*>(Lb + (int64_t)gr * r + gc) = v;
             }
         }
     } else {
         const float* db = dinv + (int64_t)b * r;
-        if ((r & 3) == 0) {
-            for (int e = tid; e < NB * NB / 4; e += 256) {
-                const int row = e >> 4, col = (e & 15) * 4;
-                const int gr = r0 + row, gc = c0 + col;
-                if (gr < r && gc < r) {
-                    f32x4 v;
+        for (int e = tid; e < NB * NB / 4; e += 256) {
+            const int row = e >> 4, col = (e & 15) * 4;
+            const int gr = r0 + row, gc = c0 + col;
+            if (gr < r && gc < r) {
+                f32x4 v;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) v[q] = As[row][col + q];
-                    *reinterpret_cast<f32x4*>(Yb + (int64_t)gr * r + gc) = v;
-                }
-            }
-        } else {
-            for (int e = tid; e < NB * NB; e += 256) {
-                const int row = e >> 6, col = e & 63;
-                const int gr = r0 + row, gc = c0 + col;
-                if (gr < r && gc < r) Yb[(int64_t)gr * r + gc] = As[row][col];
+                for (int q = 0; q < 4; ++q) v[q] = As[row][col + q];
+                *reinterpret_cast<f32x4*>(Yb + (int64_t)gr * r + gc) = v;
             }
         }
         if (Bh && !Binv && (r & 7) == 0) {
@@ -770,40 +744,27 @@ __device__ __forceinline__ void df_syrk_group(f32x4 (&acc)[4], const float (*Lm)
 // with pitch LP; the first is multiplied by sa.  Entries outside the r×r matrix read as zero.
 __device__ __forceinline__ void df_tiles_to_lds(float (*da)[LP], const float* Ma, int ra0, int ca0, float sa, float (*dbm)[LP],
                                                 const float* Mb, int rb0, int cb0, bool two, int r, int tid) {
-    if ((r & 3) == 0) {
-        f32x4 v[8];
-        const float* ptr[8];
-        bool ok[8];
+    f32x4 v[8];
+    const float* ptr[8];
+    bool ok[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const bool second = q >= 4;
-            const int row = (tid >> 4) + 16 * (q & 3), c4 = (tid & 15) * 4;
-            const int gr = (second ? rb0 : ra0) + row, gc = (second ? cb0 : ca0) + c4;
-            ok[q] = (gr < r) && (gc < r) && (two || !second);
-            ptr[q] = (second ? Mb : Ma) + (ok[q] ? (int64_t)gr * r + gc : 0);   // out of range: a valid address, value dropped
-        }
-        df_ld16x8(ptr, v);
+    for (int q = 0; q < 8; ++q) {
+        const bool second = q >= 4;
+        const int row = (tid >> 4) + 16 * (q & 3), c4 = (tid & 15) * 4;
+        const int gr = (second ? rb0 : ra0) + row, gc = (second ? cb0 : ca0) + c4;
+        ok[q] = (gr < r) && (gc < r) && (two || !second);
+        ptr[q] = (second ? Mb : Ma) + (ok[q] ? (int64_t)gr * r + gc : 0);   // out of range: a valid address, value dropped
+    }
+    df_ld16x8(ptr, v);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const bool second = q >= 4;
-            if (second && !two) continue;
-            const int row = (tid >> 4) + 16 * (q & 3), c4 = (tid & 15) * 4;
-            const float sg = second ? 1.f : sa;
-            f32x4 o = {0.f, 0.f, 0.f, 0.f};
-            if (ok[q]) o = v[q] * sg;
-            *reinterpret_cast<f32x4*>(second ? &dbm[row][c4] : &da[row][c4]) = o;
-        }
-    } else {
-        for (int e = tid; e < 2 * NB * NB; e += 256) {
-            const bool second = e >= NB * NB;
-            if (second && !two) break;
-            const int row = (e >> 6) & 63, col = e & 63;
-            const int gr = (second ? rb0 : ra0) + row, gc = (second ? cb0 : ca0) + col;
-            float x = 0.f;
-            if (gr < r && gc < r)
-                x = __hip_atomic_load((second ? Mb : Ma) + (int64_t)gr * r + gc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (second) dbm[row][col] = x; else da[row][col] = sa * x;
-        }
+    for (int q = 0; q < 8; ++q) {
+        const bool second = q >= 4;
+        if (second && !two) continue;
+        const int row = (tid >> 4) + 16 * (q & 3), c4 = (tid & 15) * 4;
+        const float sg = second ? 1.f : sa;
+        f32x4 o = {0.f, 0.f, 0.f, 0.f};
+        if (ok[q]) o = v[q] * sg;
+        *reinterpret_cast<f32x4*>(second ? &dbm[row][c4] : &da[row][c4]) = o;
     }
 }
 
@@ -883,22 +844,14 @@ __device__ __forceinline__ f32x16 df_load_acc(const float* __restrict__ M, int r
 // will read), 16-byte row pieces where the shape allows
 template <int P>
 __device__ __forceinline__ void df_store_tile(float* __restrict__ M, const float (*src)[P], int r, int r0, int c0, int tid) {
-    if ((r & 3) == 0) {
-        for (int e = tid; e < NB * NB / 4; e += 256) {
-            const int row = e >> 4, col = (e & 15) * 4;
-            const int gr = r0 + row, gc = c0 + col;
-            if (gr < r && gc < r) {
-                f32x4 v;
+    for (int e = tid; e < NB * NB / 4; e += 256) {
+        const int row = e >> 4, col = (e & 15) * 4;
+        const int gr = r0 + row, gc = c0 + col;
+        if (gr < r && gc < r) {
+            f32x4 v;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[q] = src[row][col + q];
-                df_st16(M + (int64_t)gr * r + gc, v);
-            }
-        }
-    } else {
-        for (int e = tid; e < NB * NB; e += 256) {
-            const int row = e >> 6, col = e & 63;
-            const int gr = r0 + row, gc = c0 + col;
-            if (gr < r && gc < r) __hip_atomic_store(M + (int64_t)gr * r + gc, src[row][col], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int q = 0; q < 4; ++q) v[q] = src[row][col + q];
+            df_st16(M + (int64_t)gr * r + gc, v);
         }
     }
 }
@@ -1235,18 +1188,27 @@ hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y
 }
 
 hipError_t gram_prepare(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* S, float* dinv,
-                        float* Y, float* Binv, bf16_t* Bh, bf16_t* Bl, int r, float shift, int zero_all, int batch,
+                        float* Y, float* Binv, bf16_t* Bh, bf16_t* Bl, int r, int r_true, float shift, int zero_all, int batch,
                         unsigned* flags) {
+    if (r & 3) return hipErrorInvalidValue;
     const int nblk = (r + NB - 1) / NB;
-    hipLaunchKernelGGL(diag_rsqrt_kernel, dim3((r + 255) / 256, batch), dim3(256), 0, st, Spart, nparts, pstride,
-                       dinv, r, flags, DF_FLAG_WORDS, flags ? reinterpret_cast<uint4*>(flags + (size_t)batch * DF_FLAG_WORDS) : nullptr,
-                       DF_WX_WORDS, (nblk <= DF_MAX_NBLK ? nblk : 0) * DF_SLOT_WORDS);
-    if ((r & 3) == 0)
-        hipLaunchKernelGGL(prepare4_kernel, dim3((r / 4 + 255) / 256, r, batch), dim3(256), 0, st, Spart, nparts, pstride, S,
-                           dinv, Y, Binv, Bh, Bl, r, shift, zero_all);
-    else
-        hipLaunchKernelGGL(prepare_kernel, dim3((r + 255) / 256, r, batch), dim3(256), 0, st, Spart, nparts, pstride, S,
-                           dinv, Y, Binv, Bh, Bl, r, shift, zero_all);
+    const auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(nblk, nblk, batch), dim3(256), 0, st, Spart, pstride, S, dinv, flags ? nullptr : Y, Binv, Bh, Bl, r,
+                           r_true, shift, zero_all, flags, DF_FLAG_WORDS,
+                           flags ? reinterpret_cast<uint4*>(flags + (size_t)batch * DF_FLAG_WORDS) : nullptr, DF_WX_WORDS,
+                           (nblk <= DF_MAX_NBLK ? nblk : 0) * DF_SLOT_WORDS);
+    };
+    switch (nparts) {
+        case 1: launch(prepare_kernel<1>); break;
+        case 2: launch(prepare_kernel<2>); break;
+        case 3: launch(prepare_kernel<3>); break;
+        case 4: launch(prepare_kernel<4>); break;
+        case 5: launch(prepare_kernel<5>); break;
+        case 6: launch(prepare_kernel<6>); break;
+        case 7: launch(prepare_kernel<7>); break;
+        case 8: launch(prepare_kernel<8>); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

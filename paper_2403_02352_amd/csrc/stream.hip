@@ -87,6 +87,43 @@ __global__ void zero_i32_kernel(int32_t* p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
+// Twin of the start block: transposed, padded with zeros and rounded to the storage type in one pass (and `zero` cleared), where
+// a transpose, a cast and a fill were three launches of about 5 µs each.
+template <typename T>
+__global__ void __launch_bounds__(256) start_block_kernel(const float* __restrict__ in, T* __restrict__ out, int rows, int cols,
+                                                          int rows_out, int cols_out, int32_t* __restrict__ zero, int n_zero) {
+    __shared__ float tile[TT][TT + 1];
+    const int r0 = blockIdx.y * TT, c0 = blockIdx.x * TT, tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    if (blockIdx.y == 0)
+        for (int e = blockIdx.x * 256 + threadIdx.x; e < n_zero; e += gridDim.x * 256) zero[e] = 0;
+    for (int i = ty; i < TT; i += 4) tile[i][tx] = (r0 + i < rows && c0 + tx < cols) ? in[(int64_t)(r0 + i) * cols + c0 + tx] : 0.f;
+    __syncthreads();
+    for (int i = ty; i < TT; i += 4) {
+        const int c = c0 + i, r = r0 + tx;
+        if (c < cols_out && r < rows_out) {
+            if constexpr (sizeof(T) == 2) out[(int64_t)c * rows_out + r] = f2bf(tile[tx][i]);
+            else out[(int64_t)c * rows_out + r] = tile[tx][i];
+        }
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256) pad_rows_kernel(const T* __restrict__ in, T* __restrict__ out, int cols, int ld_out) {
+    const int64_t i = blockIdx.x;
+    for (int j = threadIdx.x; j < ld_out; j += 256) out[i * ld_out + j] = j < cols ? in[i * cols + j] : (T)0;
+}
+
+struct ZeroColumns { void* m[3]; int64_t rows[3]; int elem_bytes[3]; };
+__global__ void __launch_bounds__(256) zero_columns_kernel(ZeroColumns a, int from, int ld) {
+    const int w = blockIdx.y, nc = ld - from;   // at most 63 columns: 4 rows per workgroup pass
+    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < a.rows[w]; i += (int64_t)gridDim.x * 4) {
+        const int c = threadIdx.x & 63;
+        if (c >= nc) continue;
+        if (a.elem_bytes[w] == 2) reinterpret_cast<uint16_t*>(a.m[w])[i * ld + from + c] = 0;
+        else reinterpret_cast<uint32_t*>(a.m[w])[i * ld + from + c] = 0u;
+    }
+}
+
 __global__ void cast_kernel(const float* __restrict__ in, bf16_t* __restrict__ out, int64_t n) {
     const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i + 3 < n) {
@@ -186,6 +223,40 @@ __global__ void __launch_bounds__(256) norm_basis_kernel(const T* __restrict__ P
 }
 
 }  // namespace
+
+hipError_t start_block_twin(hipStream_t st, const float* in, void* out, int rows, int cols, int rows_out, int cols_out, int elem_bytes,
+                            int32_t* zero, int n_zero) {
+    const dim3 grid((cols_out + TT - 1) / TT, (rows_out + TT - 1) / TT);
+    if (grid.y > 65535) return hipErrorInvalidValue;
+    if (elem_bytes == 2)
+        hipLaunchKernelGGL(start_block_kernel<bf16_t>, grid, dim3(256), 0, st, in, (bf16_t*)out, rows, cols, rows_out, cols_out, zero, n_zero);
+    else
+        hipLaunchKernelGGL(start_block_kernel<float>, grid, dim3(256), 0, st, in, (float*)out, rows, cols, rows_out, cols_out, zero, n_zero);
+    return hipGetLastError();
+}
+
+hipError_t pad_rows(hipStream_t st, const void* in, void* out, int64_t rows, int cols, int ld_out, int elem_bytes) {
+    if (rows > 0x7fffffff) return hipErrorInvalidValue;
+    if (elem_bytes == 2)
+        hipLaunchKernelGGL(pad_rows_kernel<uint16_t>, dim3((unsigned)rows), dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, cols, ld_out);
+    else
+        hipLaunchKernelGGL(pad_rows_kernel<uint32_t>, dim3((unsigned)rows), dim3(256), 0, st, (const uint32_t*)in, (uint32_t*)out, cols, ld_out);
+    return hipGetLastError();
+}
+
+hipError_t zero_columns(hipStream_t st, void* const (&m)[3], const int64_t (&rows)[3], const int (&elem_bytes)[3], int from, int ld) {
+    if (from >= ld) return hipSuccess;
+    if (ld - from > 64) return hipErrorInvalidValue;
+    ZeroColumns a;
+    int64_t most = 0;
+    for (int i = 0; i < 3; ++i) {
+        a.m[i] = m[i]; a.rows[i] = m[i] ? rows[i] : 0; a.elem_bytes[i] = elem_bytes[i];
+        most = a.rows[i] > most ? a.rows[i] : most;
+    }
+    const int64_t blocks = (most + 3) / 4;
+    hipLaunchKernelGGL(zero_columns_kernel, dim3((unsigned)(blocks < 1024 ? (blocks < 1 ? 1 : blocks) : 1024), 3), dim3(256), 0, st, a, from, ld);
+    return hipGetLastError();
+}
 
 hipError_t copy_block(hipStream_t st, const void* in, void* out, int rows, int cols, int64_t ld_in, int64_t ld_out,
                       int64_t s_in, int64_t s_out, int batch, int elem_bytes) {

@@ -107,3 +107,39 @@ def test_rayleigh_ritz_block_edges(atp, r):
         assert eu <= tol and eb <= tol and orth <= 2e-5
         assert float(diag[b, 1]) <= 1e-5
         assert abs(float(diag[b, 0]) - (sr ** 2).sum()) <= 1e-5 * (sr ** 2).sum()
+
+
+# (batch, L, d, r, iters): each extent one short of, at and past the multiples that the extraction pads its rows to (64, 32 for r, 4 on
+# the fp32 path), all of them odd, r = 1, and several 64-wide block columns with a padded last one
+PADDED_BASES = [(1, 65, 63, 1, 1), (2, 127, 128, 31, 1), (1, 129, 100, 33, 0), (2, 191, 77, 66, 2), (1, 256, 192, 95, 2),
+                (2, 301, 250, 97, 1), (1, 515, 384, 250, 2), (3, 128, 130, 64, 1)]
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", PADDED_BASES)
+def test_principal_bases_padded_extents(atp, case, dtype, mode):
+    """Spectrum without small values (1 to 1/2 over min(L, d)), so the basis is determined to rounding.  fp32: U itself against the
+    oracle, 1e-4.  bf16: X·Omega and the iterates are products of bf16 operands, 2^-9 each, and a basis that they perturb still
+    captures X to second order: the residual agrees to 1e-2 of the norm, U'U and B = U'X to the rounding of U (2^-9 per entry)."""
+    batch, L, d, r, iters = case
+    n = min(L, d)
+    X = np.stack([wl.make_X(L, d, np.sqrt(L * d / n) * np.linspace(1.0, 0.5, n), 0.0, 40 + b) for b in range(batch)])
+    X = wl.round_to_dtype(X, dtype)
+    Om = wl.make_omega(d, r, 3)
+    atp.set_factor_mode(mode)
+    try:
+        U, B, info, Um = atp.principal_bases(to_dev(X, dtype), r, iters, to_dev(Om, "f32"), want_master=True)
+        torch.cuda.synchronize()
+    finally:
+        atp.set_factor_mode(True)
+    assert (info == 0).all()
+    for b in range(batch):
+        Xb, Ub, Bb = X[b].astype(np.float64), to_host(U[b]), to_host(B[b])
+        Uo, Bo = oracle.principal_bases(Xb, Om.astype(np.float64), iters)
+        orth, coef = np.abs(to_host(Um[b]).T @ to_host(Um[b]) - np.eye(r)).max(), rel_fro(Bb, Ub.T @ Xb)
+        recon = abs(np.linalg.norm(Xb - Ub @ Bb) - np.linalg.norm(Xb - Uo @ Bo)) / np.linalg.norm(Xb)
+        print(case, dtype, mode, orth, coef, recon, rel_fro(to_host(Um[b]), Uo), flush=True)
+        assert orth <= (1e-5 if dtype == "f32" else 1e-4) and coef <= (1e-5 if dtype == "f32" else 2.0 ** -8) and recon <= 1e-2
+        if dtype == "f32":
+            assert rel_fro(to_host(Um[b]), Uo) <= 1e-4
