@@ -12,7 +12,7 @@
 //
 // What bounds it: the chain of r-1 dependent steps per sweep, each at best an LDS round trip plus the rotation formula (about 0.5 µs).
 // A launch per step instead, with every step a pass over T and R, cost 7.4 µs per step: at r = 512, ten sweeps, 37.8 ms for the whole
-// call against 7.2 ms.
+// call against 6.5 ms.
 #include "common.h"
 
 namespace atp {
@@ -32,14 +32,17 @@ __device__ __forceinline__ void block_pair(int i, int k, int nb, int& first, int
 __device__ __forceinline__ int pair_index(int l, int first, int second) { return (l < JB ? first : second - 1) * JB + l; }
 
 // rotation that annihilates the entry pq of [[pp, pq], [pq, qq]]: J = [[c, s], [-s, c]] as s and u = s/(1 + c); identity when the
-// entry is zero (as it is for padding indices, whose rows and columns are zero)
+// entry is zero (as it is for padding indices, whose rows and columns are zero) or has no reciprocal.
+// Hardware reciprocals and roots (1 unit in the last place): an angle that is off by 1e-7 leaves 1e-7 of the entry, and what keeps the
+// rotation orthogonal is u against s, where the same error counts s²/2 at most.  Every wave derives all 32 rotations of a step, so
+// these instructions count: 37.6 -> 32.7 µs per launch of jacobi_pair_kernel (34 steps on average) against correctly rounded divisions.
 __device__ __forceinline__ void jacobi_su(float app, float aqq, float apq, float& s, float& u) {
-    const float tau = (aqq - app) / (2.f * apq);
-    const float t = (tau >= 0.f ? 1.f : -1.f) / (fabsf(tau) + sqrtf(1.f + tau * tau));
-    const float c = 1.0f / sqrtf(1.f + t * t);
+    const float tau = 0.5f * (aqq - app) * __builtin_amdgcn_rcpf(apq);
+    const float t = __builtin_copysignf(__builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.f))), tau);
+    const float c = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f));
     s = t * c;
     u = s * __builtin_amdgcn_rcpf(1.f + c);
-    if (apq == 0.f) { s = 0.f; u = 0.f; }
+    if (fabsf(apq) < 1e-37f) { s = 0.f; u = 0.f; }
 }
 // (x, y) <- (c·x - s·y, s·x + c·y) with c = 1 - s·u never rounded to fp32: near convergence a rounded c is too large by up to
 // half a unit on average, which scaled the whole spectrum up by 6e-5 in ten sweeps at r = 512 (3e-6 this way)
@@ -63,42 +66,47 @@ __device__ __forceinline__ void step_pair(int i, int k, int& p, int& q) {
     }
 }
 
-// One step: A0 -> A1 = J·A0·Jᵀ (every thread one 2×2 block of the 32×32 grid of rotation pairs), W <- J·W in place.
+// One step: A0 -> A1 = J·A0·Jᵀ (every thread two 2×2 blocks of the 32×32 grid of rotation pairs), W <- J·W in place.
 // Lane l of every wave derives rotation l % 32, so the step needs a single barrier.
 template <bool CROSS>
 __device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W, int k, int wave, int lane) {
     const int j = lane & 31;
-    int pi, qi, pj, qj;
-    step_pair<CROSS>(2 * wave + (lane >> 5), k, pi, qi);
+    int pj, qj;
     step_pair<CROSS>(j, k, pj, qj);
-    const float b00 = A0[pi * JP + pj], b01 = A0[pi * JP + qj], b10 = A0[qi * JP + pj], b11 = A0[qi * JP + qj];
-    const float w00 = W[pi * JP + j], w01 = W[pi * JP + j + 32], w10 = W[qi * JP + j], w11 = W[qi * JP + j + 32];
     float sj, uj;
     jacobi_su(A0[pj * JP + pj], A0[qj * JP + qj], A0[pj * JP + qj], sj, uj);
     const auto lane_of = [](float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
-    const float s0 = lane_of(sj, 2 * wave), s1 = lane_of(sj, 2 * wave + 1), u0 = lane_of(uj, 2 * wave), u1 = lane_of(uj, 2 * wave + 1);
-    const float si = lane < 32 ? s0 : s1, ui = lane < 32 ? u0 : u1;
-    float r00, r01, r10, r11, x, y;
-    rotate(si, ui, b00, b10, r00, r10);
-    rotate(si, ui, b01, b11, r01, r11);
-    rotate(sj, uj, r00, r01, x, y);
-    A1[pi * JP + pj] = x;
-    A1[pi * JP + qj] = y;
-    rotate(sj, uj, r10, r11, x, y);
-    A1[qi * JP + pj] = x;
-    A1[qi * JP + qj] = y;
-    rotate(si, ui, w00, w10, x, y);
-    W[pi * JP + j] = x;
-    W[qi * JP + j] = y;
-    rotate(si, ui, w01, w11, x, y);
-    W[pi * JP + j + 32] = x;
-    W[qi * JP + j + 32] = y;
+#pragma unroll
+    for (int h = 0; h < 32; h += 16) {
+        int pi, qi;
+        step_pair<CROSS>(2 * wave + (lane >> 5) + h, k, pi, qi);
+        const float b00 = A0[pi * JP + pj], b01 = A0[pi * JP + qj], b10 = A0[qi * JP + pj], b11 = A0[qi * JP + qj];
+        const float w00 = W[pi * JP + j], w01 = W[pi * JP + j + 32], w10 = W[qi * JP + j], w11 = W[qi * JP + j + 32];
+        const float s0 = lane_of(sj, 2 * wave + h), s1 = lane_of(sj, 2 * wave + h + 1);
+        const float u0 = lane_of(uj, 2 * wave + h), u1 = lane_of(uj, 2 * wave + h + 1);
+        const float si = lane < 32 ? s0 : s1, ui = lane < 32 ? u0 : u1;
+        float r00, r01, r10, r11, x, y;
+        rotate(si, ui, b00, b10, r00, r10);
+        rotate(si, ui, b01, b11, r01, r11);
+        rotate(sj, uj, r00, r01, x, y);
+        A1[pi * JP + pj] = x;
+        A1[pi * JP + qj] = y;
+        rotate(sj, uj, r10, r11, x, y);
+        A1[qi * JP + pj] = x;
+        A1[qi * JP + qj] = y;
+        rotate(si, ui, w00, w10, x, y);
+        W[pi * JP + j] = x;
+        W[qi * JP + j] = y;
+        rotate(si, ui, w01, w11, x, y);
+        W[pi * JP + j + 32] = x;
+        W[qi * JP + j + 32] = y;
+    }
     __syncthreads();
 }
 
 // One workgroup per (block pair of round k, item): the rotations of the pair's 64×64 sub-matrix of T.  Their product goes to
 // Wout[item][pair][64][64].  With a single pair (nb == 2) all `sweeps` sweeps run here; T and the product (then all of R) are the results.
-__global__ void __launch_bounds__(1024) jacobi_pair_kernel(float* __restrict__ T, float* __restrict__ Wout, int64_t w_stride, int w_rows,
+__global__ void __launch_bounds__(512) jacobi_pair_kernel(float* __restrict__ T, float* __restrict__ Wout, int64_t w_stride, int w_rows,
                                                            int r, int nb, int k, int sweeps) {
     __shared__ float A[2][JW * JP];
     __shared__ float W[JW * JP];
@@ -106,7 +114,7 @@ __global__ void __launch_bounds__(1024) jacobi_pair_kernel(float* __restrict__ T
     int fb, sb;
     block_pair(blockIdx.x, k, nb, fb, sb);
     float* Tb = T + (int64_t)blockIdx.y * r * r;
-    for (int e = tid; e < JW * JW; e += 1024) {
+    for (int e = tid; e < JW * JW; e += 512) {
         const int i = e >> 6, j = e & 63, gi = pair_index(i, fb, sb), gj = pair_index(j, fb, sb);
         A[0][i * JP + j] = (gi < r && gj < r) ? Tb[(int64_t)gi * r + gj] : 0.f;
         W[i * JP + j] = i == j ? 1.f : 0.f;
@@ -119,7 +127,7 @@ __global__ void __launch_bounds__(1024) jacobi_pair_kernel(float* __restrict__ T
         for (int t = 0; t < JB; ++t, buf ^= 1) jacobi_step<true>(A[buf], A[buf ^ 1], W, t, wave, lane);
     }
     float* Wb = Wout + (int64_t)blockIdx.y * w_stride + (int64_t)blockIdx.x * JW * JW;
-    for (int e = tid; e < JW * JW; e += 1024) {
+    for (int e = tid; e < JW * JW; e += 512) {
         const int i = e >> 6, j = e & 63;
         if (i < w_rows && j < w_rows) Wb[i * w_rows + j] = W[i * JP + j];
         if (nb == 2 && i < r && j < r) Tb[(int64_t)i * r + j] = A[buf][i * JP + j];
@@ -338,13 +346,13 @@ __global__ void __launch_bounds__(256) ritz_diag_kernel(const float2* __restrict
 hipError_t ritz_jacobi(hipStream_t st, float* T, float* R, float* W, int r, int batch, int sweeps) {
     const int nb = 2 * ((r + JW - 1) / JW), np = nb / 2;
     if (nb == 2) {
-        hipLaunchKernelGGL(jacobi_pair_kernel, dim3(1, batch), dim3(1024), 0, st, T, R, (int64_t)r * r, r, r, nb, 0, sweeps);
+        hipLaunchKernelGGL(jacobi_pair_kernel, dim3(1, batch), dim3(512), 0, st, T, R, (int64_t)r * r, r, r, nb, 0, sweeps);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(ritz_identity_kernel, dim3((r + 255) / 256, r, batch), dim3(256), 0, st, R, r);
     for (int sw = 0; sw < sweeps; ++sw)
         for (int k = 0; k < nb - 1; ++k) {
-            hipLaunchKernelGGL(jacobi_pair_kernel, dim3(np, batch), dim3(1024), 0, st, T, W, (int64_t)np * JW * JW, JW, r, nb, k, 1);
+            hipLaunchKernelGGL(jacobi_pair_kernel, dim3(np, batch), dim3(512), 0, st, T, W, (int64_t)np * JW * JW, JW, r, nb, k, 1);
             hipLaunchKernelGGL(jacobi_apply_kernel, dim3(np * (np + 1) / 2 + np * ((r + JW - 1) / JW), batch), dim3(1024), 0, st, T, R, W, r, nb, k);
         }
     return hipGetLastError();
