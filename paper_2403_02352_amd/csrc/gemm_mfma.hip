@@ -21,6 +21,7 @@
 // in groups of 8 tile rows.
 #include "common.h"
 
+#include <algorithm>
 #include <utility>
 
 namespace atp {
@@ -476,11 +477,34 @@ hipError_t launch_async(hipStream_t st, const GemmArgs& g) {
 
 }  // namespace
 
+namespace {
+
+// Tile of a plain product.  A CU holds one workgroup of 256×256, two of 128×128 or three of 128×64, so the chip holds 256, 512
+// or 768.  Cost of a round of workgroups per 64-deep k-tile, measured in µs on products from 500×1536×1536 to 4096×2048×32768
+// (epilogues included): 256×256 1.65 whether or not the round is full, 128×128 1.0 for two on a CU and 0.61 for one alone; rounds of
+// 128×128 overlap, so their number is no whole number, with 0.2 for the uneven end.
+// 256×256 is ahead from about 190 of its tiles: 4096×4096×4096 (256 tiles) 109 µs against 133 with 128×128; behind below:
+// 4096×2048×32768 (128 tiles) 752 against 511, 512×4096×11008 (32) 200 against 105.  128×64 is ahead while 128×128 leaves every
+// second CU idle (96 against 105 µs there, 500×1536×1536 12.8 against 14.4) and behind once it does not (2048×2048×4096,
+// 256 tiles of 128×128: 50 against 44).
+enum Tile { TILE_256, TILE_128, TILE_128x64 };
+Tile plain_tile(const GemmArgs& g) {
+    const auto tiles = [&](int bm, int bn) { return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch; };
+    const int half = g.swiglu ? 2 : 1;   // a tile has half the output columns with the gated epilogue
+    const int64_t t256 = tiles(256, 256 / half), t128 = tiles(128, 128 / half);
+    const double c256 = 1.65 * (double)((t256 + 255) / 256);
+    const double c128 = t128 <= 256 ? 0.61 : std::max(1.0, (double)t128 / 512 + 0.2);
+    if (c256 < c128) return TILE_256;
+    return t128 <= 128 && !g.swiglu ? TILE_128x64 : TILE_128;
+}
+
+}  // namespace
+
+// with a lo plane, from 128 tiles of 256×256 up
 bool gemm_nt_mfma_big(const GemmArgs& g) {
-    const int bn = g.swiglu ? 128 : 256;  // output columns per 256-wide tile
-    const int64_t tiles =
-        (int64_t)((g.M + 255) / 256) * ((g.N + bn - 1) / bn) * g.batch * (g.ksplit > 1 ? g.ksplit : 1);
-    return tiles >= 128 && g.M >= 256 && g.N >= bn;
+    if (!g.A_lo && !g.symmetric) return plain_tile(g) == TILE_256;
+    const int64_t tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256) * g.batch * (g.ksplit > 1 ? g.ksplit : 1);
+    return tiles >= 128 && g.M >= 256 && g.N >= 256;
 }
 
 bool gemm_nt_mfma_ok(const GemmArgs& g) {
@@ -513,6 +537,7 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g) {
         return launch_async<128, 128, 64, 64, 1, true>(st, g);
     }
     if (big) return launch_async<256, 256, 128, 64, 1, false>(st, g);
+    if (!g.symmetric && g.ksplit <= 1 && plain_tile(g) == TILE_128x64) return launch_async<128, 64, 64, 64, 1, false>(st, g);
     return launch_async<128, 128, 64, 64, 1, false>(st, g);
 }
 

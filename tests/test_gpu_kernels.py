@@ -50,6 +50,29 @@ def test_strided_products(atp, dtype, layout, epilogue, case):
     assert rel_fro(to_host(out), ref) <= (F32_TOL if dtype == "f32" else BF16_TOL)
 
 
+# (batch, m, k, n): one shape per tile of the asynchronous kernel (128×64, 128×128, 256×256), one past and one short of the tiles,
+# columns a multiple of 8 and not, one k-tile, an odd and an even number of them
+ASYNC = [(1, 1, 64, 8), (1, 129, 128, 63), (3, 127, 192, 72), (1, 1100, 256, 1032), (2, 1025, 64, 1031), (1, 4097, 192, 3080),
+         (1, 4100, 128, 3101)]
+
+
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("epilogue", ["none", "swiglu"])
+@pytest.mark.parametrize("case", ASYNC)
+def test_async_products(atp, layout, epilogue, case):
+    batch, m, k, n = case
+    n *= 2 if epilogue == "swiglu" else 1
+    B = wl.round_to_dtype(rnd((batch, m, k), 1), "bf16")
+    shared = epilogue == "swiglu"   # without the gate every sequence has weights of its own
+    W = wl.round_to_dtype(rnd((1 if shared else batch, k, n), 2, 1 / np.sqrt(k)), "bf16")
+    ref = np.stack([oracle.lowrank_linear(B[b], W[0 if shared else b], *(["swiglu"] if shared else [])) for b in range(batch)])
+    Wd = W if layout == "kn" else W.transpose(0, 2, 1)
+    out = atp.lowrank_linear(to_dev(B, "bf16"), to_dev(np.ascontiguousarray(Wd[0] if shared else Wd), "bf16"),
+                             atp.ATP_W_KN if layout == "kn" else atp.ATP_W_NK, atp.ATP_EPI_SWIGLU if shared else atp.ATP_EPI_NONE)
+    torch.cuda.synchronize()
+    assert rel_fro(to_host(out), ref) <= BF16_TOL
+
+
 # (batch, L, r, dq, heads): fp32 attention with 128 queries per workgroup and with the keys dealt to four waves; heads of every
 # padded width (64, 128, 256), widths that are no multiple of 4 (scalar loads); one short of / past the 32-key tile and the
 # 128-key stage; a single key and a single query
