@@ -217,7 +217,7 @@ hipError_t nt_product(hipStream_t st, bool mfma, const GemmArgs& g) {
     ProfScope ps(st, ATP_K_GEMM_SIMT, flops, bytes);
     SimtArgs s;
     s.A = g.A; s.A_lo = g.A_lo; s.B = g.B; s.B_lo = g.B_lo;
-    s.a_rs = g.lda; s.a_cs = 1; s.b_rs = g.ldb; s.b_cs = 1;
+    s.a_rs = g.a_cols ? 1 : g.lda; s.a_cs = g.a_cols ? g.lda : 1; s.b_rs = g.b_cols ? 1 : g.ldb; s.b_cs = g.b_cols ? g.ldb : 1;
     s.sA = g.sA; s.sB = g.sB;
     s.M = g.M; s.N = g.N; s.K = g.K; s.batch = g.batch;
     s.C32 = g.C32; s.C16 = g.C16; s.C16lo = g.C16lo; s.ldc = g.ldc; s.sC = g.sC;
@@ -772,18 +772,21 @@ atp_status atp_project_onto_bases(const void* U_r, const void* Y, void* out, int
         ATP_HIP(gemm_simt(st, OP_F32, OP_F32, s));
         return ATP_OK;
     }
-    Carver c(workspace);
-    void* UT = c.take((size_t)batch * r * L * 2);
-    void* YT = c.take((size_t)batch * dq * L * 2);
-    {
+    GemmArgs g;
+    g.A = U_r; g.B = Y; g.lda = r; g.ldb = dq; g.sA = L * r; g.sB = L * dq;
+    g.M = (int)r; g.N = (int)dq; g.K = (int)L; g.batch = (int)batch;
+    g.a_cols = 1; g.b_cols = 1;
+    g.C16 = (bf16_t*)out; g.ldc = dq; g.sC = r * dq;
+    // both operands are multiplied as they lie, unless their rows start at no multiples of 16 bytes
+    if (!gemm_nt_mfma_ok(g) && (r % 8 || dq % 8)) {
+        Carver c(workspace);
+        void* UT = c.take((size_t)batch * r * L * 2);
+        void* YT = c.take((size_t)batch * dq * L * 2);
         ProfScope ps(st, ATP_K_STREAM, 0.0, 4.0 * (double)batch * L * (r + dq));
         ATP_HIP(transpose_batched(st, U_r, UT, (int)L, (int)r, L, L * r, r * L, (int)batch, 2, 0));
         ATP_HIP(transpose_batched(st, Y, YT, (int)L, (int)dq, L, L * dq, dq * L, (int)batch, 2, 0));
+        g.A = UT; g.B = YT; g.lda = L; g.ldb = L; g.a_cols = 0; g.b_cols = 0;
     }
-    GemmArgs g;
-    g.A = UT; g.B = YT; g.lda = L; g.ldb = L; g.sA = r * L; g.sB = dq * L;
-    g.M = (int)r; g.N = (int)dq; g.K = (int)L; g.batch = (int)batch;
-    g.C16 = (bf16_t*)out; g.ldc = dq; g.sC = r * dq;
     ATP_HIP(nt_product(st, true, g));
     return ATP_OK;
 }
@@ -900,21 +903,24 @@ atp_status atp_lowrank_linear(const void* B, const void* W, void* out, int64_t b
         ATP_HIP(gemm_simt(st, OP_F32, OP_F32, s));
         return ATP_OK;
     }
-    const void* Wnk = W;
-    int64_t sW = w_stride;
-    if (w_layout == ATP_W_KN) {
-        const int nb = w_stride ? (int)batch : 1;
-        ProfScope ps(st, ATP_K_STREAM, 0.0, 4.0 * (double)nb * k * n);
-        ATP_HIP(transpose_batched(st, W, workspace, (int)k, (int)n, k, w_stride, k * n, nb, 2, 0));
-        Wnk = workspace;
-        sW = w_stride ? k * n : 0;
-    }
     GemmArgs g;
-    g.A = B; g.B = Wnk; g.lda = k; g.ldb = k; g.sA = m * k; g.sB = sW;
+    g.A = B; g.B = W; g.lda = k; g.ldb = k; g.sA = m * k; g.sB = w_stride;
     g.M = (int)m; g.N = (int)nout; g.K = (int)k; g.batch = (int)batch;
     g.C16 = (bf16_t*)out; g.ldc = nout; g.sC = m * nout;
     g.swiglu = swiglu;
-    if (sW == 0 && batch > 1 && batch * m < (1ll << 30)) {
+    if (w_layout == ATP_W_KN) {
+        // W is multiplied as it lies, by the asynchronous kernel or else by the strided one.  Only where its rows do not start at
+        // multiples of 16 bytes is it turned first: the asynchronous kernel may then take it, and the strided one would load single elements.
+        g.b_cols = 1; g.ldb = n;
+        if (!gemm_nt_mfma_ok(g) && (nout % 8 || w_stride % 8)) {
+            const int nb = w_stride ? (int)batch : 1;
+            ProfScope ps(st, ATP_K_STREAM, 0.0, 4.0 * (double)nb * k * n);
+            ATP_HIP(transpose_batched(st, W, workspace, (int)k, (int)n, k, w_stride, k * n, nb, 2, 0));
+            g.B = workspace; g.b_cols = 0; g.ldb = k;
+            g.sB = w_stride ? k * n : 0;
+        }
+    }
+    if (g.sB == 0 && batch > 1 && batch * m < (1ll << 30)) {
         // shared weights: the batch is one tall matrix [batch·m, k]; as a single product every pass over a
         // block of W serves the rows of all sequences
         GemmArgs f = g;

@@ -44,9 +44,39 @@ __device__ __forceinline__ void copy16_untracked(const void* base, unsigned off_
 }
 #pragma clang diagnostic pop
 
+// Fragments of an operand that lies in LDS as it lies in memory, rows of k by columns, come from the transposing LDS read: each
+// of 16 lanes names four consecutive 16-bit elements of a row (lanes 4i .. 4i+3 the 16 columns of row i) and lane c receives
+// column c of the four rows.  Position p of a row of W elements holds 16-byte chunk p ^ column_swz<W>(row), which puts the four
+// rows that 32 lanes take at once in different 64-byte spans of the banks.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+template <int W>
+__device__ __forceinline__ int column_swz(int row) {
+    static_assert(W == 64 || W % 128 == 0, "row width");
+    return W == 64 ? ((row >> 1) & 1) << 2 : (row & 3) << 2;
+}
+
+// byte offset, from the first of 16 rows, of what this lane names for the 32 columns from `col` (a multiple of 32) on
+template <int W>
+__device__ __forceinline__ int column_frag_offset(int lane, int col) {
+    const int row = 8 * (lane >> 5) + ((lane & 15) >> 2);
+    return row * W * 2 + (((col >> 3) ^ column_swz<W>(row)) + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) * 16 + (lane & 1) * 8;
+}
+
+// 8 consecutive rows of one column: the A or B operand of a 32x32x16 product (column lane % 32, rows 8·(lane / 32) .. +7)
+template <int W>
+__device__ __forceinline__ bf16x8 read_column_frag(const uint4* base, int ofs) {
+    const unsigned at = (unsigned)(uintptr_t)(lds_void*)base + (unsigned)ofs;
+    union { s16x4 h[2]; bf16x8 b; } u;
+    u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)at);
+    u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(at + 4 * W * 2));
+    return u.b;
+}
+
 // ---------------------------------------------------------------------------
 // C = A · Bᵀ  with both operands K-contiguous ("NT" product), batched.
-//   A[M,K] (lda), B[N,K] (ldb); fp32 accumulate.
+//   A[M,K] (lda), B[N,K] (ldb); fp32 accumulate.  With a_cols (b_cols) the operand is stored as A[K,M] (B[K,N]) instead.
 // MFMA path: operands are bf16.  A value that needs more than bf16 precision is held as a
 // hi + lo pair of bf16 planes (hi = bf16(x), lo = bf16(x - hi), ≈16 mantissa bits); when both
 // operands carry a lo plane the product is formed from three MFMA products (hi·hi, hi·lo,
@@ -63,6 +93,7 @@ struct GemmArgs {
     const void* B_lo = nullptr;
     int64_t lda = 0, ldb = 0, sA = 0, sB = 0;  // leading dims, batch strides (elements)
     int M = 0, N = 0, K = 0, batch = 1;
+    int a_cols = 0, b_cols = 0;
     float* C32 = nullptr;
     bf16_t* C16 = nullptr;
     bf16_t* C16lo = nullptr;
@@ -87,7 +118,8 @@ struct GemmArgs {
 enum OperandType { OP_BF16 = 0, OP_F32 = 1 };
 
 // MFMA path (bf16 operands, optional lo planes).  Requirements: K % 64 == 0 (K % 32 == 0 with lo
-// planes), lda/ldb/sA/sB % 8 == 0, pointers 16-byte aligned.
+// planes), lda/ldb/sA/sB % 8 == 0, pointers 16-byte aligned; a_cols only with b_cols, both only for plain operands with
+// M % 8 == 0 (a_cols) and N % 8 == 0 (b_cols).
 hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g);
 bool gemm_nt_mfma_ok(const GemmArgs& g);
 bool gemm_nt_mfma_big(const GemmArgs& g);  // true when the 256×256 tile configuration is chosen

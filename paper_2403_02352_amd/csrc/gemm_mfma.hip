@@ -236,7 +236,11 @@ __device__ __forceinline__ int b_global_row(int b_row, int n0, int N, bool& ok) 
 
 
 // NP = 1: plain bf16 operands, BK = 64.  NP = 2: hi+lo planes, BK = 32, three products.
-template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU>
+// AC / BC: A is stored [K, M] / B is stored [K, N] (plain operands only).  A tile of it is staged as BK rows of columns, and its
+// fragments come from transposing LDS reads, which cost the same (within 5 % on products of 500×1536×1536 to 32768×4096×2048): a
+// pass that turned W, U or Y first, and its launch, are gone.  Gated feed-forward of 512 rows, k = 4096, f = 11008: the passes
+// moved 540 MB and took 156 of 360 µs.
+template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC, bool BC>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     constexpr int BK = 64 / NP;
@@ -249,7 +253,7 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     constexpr int PA = BM * CPR, PB = BN * CPR;            // plane sizes (uint4)
     constexpr int STAGE = NP * (PA + PB);
     static_assert((BM / RPI) % NW == 0 && (BN / RPI) % NW == 0, "tile/waves mismatch");
-    static_assert(!SWIGLU || NP == 1, "swiglu epilogue only for plain operands");
+    static_assert((!SWIGLU && !AC && !BC) || NP == 1, "swiglu epilogue and operands stored by columns only for plain operands");
 
     // two statically distinct stages: copies into one do not alias fragment reads from the other
     __shared__ __align__(16) uint4 stage0[STAGE];
@@ -306,6 +310,10 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
         const int kc = (lane % CPR) ^ sw;
         const int gr = min(m0 + row, p.M - 1);  // rows past M: any valid row, never stored
         a_off[i] = (unsigned)(((int64_t)gr * p.lda + kc * 8) * 2);
+        if constexpr (AC) {   // columns past M: any valid chunk, never stored
+            const int slot = g * 64 + lane, kr = slot / (BM / 8), col = m0 + 8 * ((slot % (BM / 8)) ^ column_swz<BM>(kr));
+            a_off[i] = (unsigned)((kr * p.lda + min(col, p.M - 8)) * 2);
+        }
     }
 #pragma unroll
     for (int i = 0; i < GB; ++i) {
@@ -317,6 +325,11 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
         int gr = b_global_row<WN, SWIGLU>(row, n0, p.N, rok);
         if (!rok) gr = 0;
         b_off[i] = (unsigned)(((int64_t)gr * p.ldb + kc * 8) * 2);
+        if constexpr (BC) {   // a chunk is all gate, all up or all past the end
+            const int slot = g * 64 + lane, kr = slot / (BN / 8);
+            const int col = b_global_row<WN, SWIGLU>(8 * ((slot % (BN / 8)) ^ column_swz<BN>(kr)), n0, p.N, rok);
+            b_off[i] = (unsigned)((kr * p.ldb + (rok ? col : 0)) * 2);
+        }
     }
     const bf16_t* Ah = reinterpret_cast<const bf16_t*>(p.A) + offA;
     const bf16_t* Al = reinterpret_cast<const bf16_t*>(p.A_lo) + offA;
@@ -328,17 +341,17 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     const unsigned lds_stage1 = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_void*)stage1) + wave_s * 1024u;
     // (every wait for these copies is explicit below)
     auto issue = [&](int kt, const uint4* stp) {
-        const int k0 = kt * BK;
+        const int64_t ka = (int64_t)kt * BK * (AC ? p.lda : 1), kb = (int64_t)kt * BK * (BC ? p.ldb : 1);
         const unsigned st = (stp == stage0) ? lds_stage0 : lds_stage1;
 #pragma unroll
         for (int i = 0; i < GA; ++i) {
-            copy16_untracked(Ah + k0, a_off[i], st + (unsigned)(i * NW * 64) * 16u);
-            if constexpr (NP == 2) copy16_untracked(Al + k0, a_off[i], st + (unsigned)(PA + i * NW * 64) * 16u);
+            copy16_untracked(Ah + ka, a_off[i], st + (unsigned)(i * NW * 64) * 16u);
+            if constexpr (NP == 2) copy16_untracked(Al + ka, a_off[i], st + (unsigned)(PA + i * NW * 64) * 16u);
         }
 #pragma unroll
         for (int i = 0; i < GB; ++i) {
-            copy16_untracked(Bh + k0, b_off[i], st + (unsigned)(NP * PA + i * NW * 64) * 16u);
-            if constexpr (NP == 2) copy16_untracked(Bl + k0, b_off[i], st + (unsigned)(NP * PA + PB + i * NW * 64) * 16u);
+            copy16_untracked(Bh + kb, b_off[i], st + (unsigned)(NP * PA + i * NW * 64) * 16u);
+            if constexpr (NP == 2) copy16_untracked(Bl + kb, b_off[i], st + (unsigned)(NP * PA + PB + i * NW * 64) * 16u);
         }
     };
 
@@ -357,16 +370,23 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) kofs[ks] = (2 * ks + lh) ^ xs;
     constexpr int KS = BK / 16;  // k-steps per tile
+    int a_col[TM], b_col[TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) a_col[i] = AC ? column_frag_offset<BM>(lane, wm * WM + 32 * i) : 0;
+#pragma unroll
+    for (int j = 0; j < TN; ++j) b_col[j] = BC ? NP * PA * 16 + column_frag_offset<BN>(lane, wn * WN + 32 * j) : 0;
     struct Frag { bf16x8 ah[TM], bh[TN], al[TM], bl[TN]; };
     auto read_frags = [&](const uint4* st, int ks, Frag& f) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            f.ah[i] = as_bf16x8(st[rowA + i * 32 * CPR + kofs[ks]]);
+            if constexpr (AC) f.ah[i] = read_column_frag<BM>(st, a_col[i] + ks * 32 * BM);
+            else f.ah[i] = as_bf16x8(st[rowA + i * 32 * CPR + kofs[ks]]);
             if constexpr (NP == 2) f.al[i] = as_bf16x8(st[PA + rowA + i * 32 * CPR + kofs[ks]]);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-            f.bh[j] = as_bf16x8(st[rowB + j * 32 * CPR + kofs[ks]]);
+            if constexpr (BC) f.bh[j] = read_column_frag<BN>(st, b_col[j] + ks * 32 * BN);
+            else f.bh[j] = as_bf16x8(st[rowB + j * 32 * CPR + kofs[ks]]);
             if constexpr (NP == 2) f.bl[j] = as_bf16x8(st[PB + rowB + j * 32 * CPR + kofs[ks]]);
         }
     };
@@ -463,10 +483,10 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     }
 }
 
-template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU>
+template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC = false, bool BC = false>
 hipError_t launch_async(hipStream_t st, const GemmArgs& g) {
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
-    auto kern = gemm_bf16_async_kernel<BM, BN, WM, WN, NP, SWIGLU>;
+    auto kern = gemm_bf16_async_kernel<BM, BN, WM, WN, NP, SWIGLU, AC, BC>;
     const int tilesM = (g.M + BM - 1) / BM;
     const int tilesN = (g.N + (SWIGLU ? BN / 2 : BN) - 1) / (SWIGLU ? BN / 2 : BN);
     dim3 grid(tilesM * tilesN * g.batch, 1, g.ksplit > 1 ? g.ksplit : 1);
@@ -516,8 +536,12 @@ bool gemm_nt_mfma_ok(const GemmArgs& g) {
         return false;
     if (g.symmetric && g.M != g.N) return false;
     if (g.CT32) return false;  // fp32 transposed output: only the SIMT kernel writes it
-    // copies address an operand as a base plus a 32-bit byte offset within the batch item
-    if ((int64_t)g.M * g.lda * 2 >= (1ll << 31) || (int64_t)g.N * (g.swiglu ? 2 : 1) * g.ldb * 2 >= (1ll << 31)) return false;
+    if (g.a_cols && (!g.b_cols || g.swiglu || g.M % 8)) return false;
+    if (g.b_cols && (split || g.symmetric || g.b_lower || g.ksplit > 1 || g.N % 8)) return false;
+    // copies address an operand as a base plus a 32-bit byte offset within the batch item (within 64 rows of one stored by columns)
+    const int64_t reach_a = g.a_cols ? 64 * g.lda : (int64_t)g.M * g.lda;
+    const int64_t reach_b = g.b_cols ? 64 * g.ldb : (int64_t)g.N * (g.swiglu ? 2 : 1) * g.ldb;
+    if (reach_a * 2 >= (1ll << 31) || reach_b * 2 >= (1ll << 31)) return false;
     if (g.ksplit > 1 && (g.C16 || g.CT16)) return false;
     return true;
 }
@@ -532,13 +556,21 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g) {
         if (big) return launch_async<256, 256, 128, 64, 2, false>(st, g);
         return launch_async<128, 128, 64, 64, 2, false>(st, g);
     }
+    const bool small = !g.symmetric && g.ksplit <= 1 && plain_tile(g) == TILE_128x64;
     if (g.swiglu) {
-        if (big) return launch_async<256, 256, 128, 64, 1, true>(st, g);
-        return launch_async<128, 128, 64, 64, 1, true>(st, g);
+        if (g.b_cols) return big ? launch_async<256, 256, 128, 64, 1, true, false, true>(st, g) : launch_async<128, 128, 64, 64, 1, true, false, true>(st, g);
+        return big ? launch_async<256, 256, 128, 64, 1, true>(st, g) : launch_async<128, 128, 64, 64, 1, true>(st, g);
+    }
+    if (g.a_cols) {
+        if (big) return launch_async<256, 256, 128, 64, 1, false, true, true>(st, g);
+        return small ? launch_async<128, 64, 64, 64, 1, false, true, true>(st, g) : launch_async<128, 128, 64, 64, 1, false, true, true>(st, g);
+    }
+    if (g.b_cols) {
+        if (big) return launch_async<256, 256, 128, 64, 1, false, false, true>(st, g);
+        return small ? launch_async<128, 64, 64, 64, 1, false, false, true>(st, g) : launch_async<128, 128, 64, 64, 1, false, false, true>(st, g);
     }
     if (big) return launch_async<256, 256, 128, 64, 1, false>(st, g);
-    if (!g.symmetric && g.ksplit <= 1 && plain_tile(g) == TILE_128x64) return launch_async<128, 64, 64, 64, 1, false>(st, g);
-    return launch_async<128, 128, 64, 64, 1, false>(st, g);
+    return small ? launch_async<128, 64, 64, 64, 1, false>(st, g) : launch_async<128, 128, 64, 64, 1, false>(st, g);
 }
 
 }  // namespace atp

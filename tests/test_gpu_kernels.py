@@ -73,6 +73,20 @@ def test_async_products(atp, layout, epilogue, case):
     assert rel_fro(to_host(out), ref) <= BF16_TOL
 
 
+# (batch, L, r, dq): both operands stored by columns in the asynchronous kernel (L a multiple of 64; its three tiles), in the strided
+# one, and turned first (columns no multiple of 8)
+PROJECTED = [(1, 64, 8, 64), (2, 192, 72, 264), (1, 128, 1032, 1096), (1, 64, 3080, 4104), (2, 100, 40, 136), (1, 256, 33, 130), (1, 77, 9, 70)]
+
+
+@pytest.mark.parametrize("case", PROJECTED)
+def test_projection_onto_bases(atp, case):
+    batch, L, r, dq = case
+    U, Y = wl.round_to_dtype(rnd((batch, L, r), 3), "bf16"), wl.round_to_dtype(rnd((batch, L, dq), 4), "bf16")
+    out = atp.project_onto_bases(to_dev(U, "bf16"), to_dev(Y, "bf16"))
+    torch.cuda.synchronize()
+    assert rel_fro(to_host(out), np.stack([oracle.project_onto_bases(U[b], Y[b]) for b in range(batch)])) <= BF16_TOL
+
+
 # (batch, L, r, dq, heads): fp32 attention with 128 queries per workgroup and with the keys dealt to four waves; heads of every
 # padded width (64, 128, 256), widths that are no multiple of 4 (scalar loads); one short of / past the 32-key tile and the
 # 128-key stage; a single key and a single query
