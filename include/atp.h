@@ -44,7 +44,7 @@ typedef enum {
     ATP_ERR_WORKSPACE = 3,   /* workspace missing or smaller than the query says */
     ATP_ERR_UNSUPPORTED = 4, /* shape the kernels do not cover (e.g. head width) */
     ATP_ERR_DEVICE = 5,      /* a HIP call failed (launch error) */
-    ATP_ERR_SCRATCH_LIMIT = 6 /* atp_attention_static: input needs more than ATP_STATIC_SCRATCH_BYTES */
+    ATP_ERR_SCRATCH_LIMIT = 6 /* atp_attention_static: input above the limit of that entry point */
 } atp_status;
 
 typedef enum { ATP_F32 = 0, ATP_BF16 = 1 } atp_dtype;
@@ -65,9 +65,8 @@ const char* atp_status_string(atp_status s);
 /* Library / build identification (static string). */
 const char* atp_version(void);
 
-/* Optional one-time set-up on the current device, outside any stream capture: resolves the device
- * address of the built-in scratch buffer of atp_attention_static and creates the stream and events
- * the overlap option uses.  Every entry point also works without it (the set-up then happens inside
+/* Optional one-time set-up on the current device, outside any stream capture: creates the stream and
+ * events the overlap option uses.  Every entry point also works without it (the set-up then happens inside
  * the first call that needs it).  Returns ATP_ERR_DEVICE if a HIP call fails. */
 atp_status atp_init(void);
 
@@ -237,7 +236,7 @@ atp_status atp_rayleigh_ritz(const void* U_r, const void* B_r, int64_t batch, in
  *                 [batch, m, n/2] for ATP_EPI_SWIGLU (gate columns first, then
  *                 up columns, in W: the gated feed-forward applied to the bases)
  *  workspace      device; needed only for (ATP_BF16, ATP_W_KN): the call
- *                 transposes W there first.  May be NULL when the query
+ *                 may transpose W there first.  May be NULL when the query
  *                 returns 0.
  *
  * Errors: ATP_ERR_INVALID_ARG (null pointer, size < 1, n odd with SWIGLU, bad
@@ -263,7 +262,7 @@ atp_status atp_lowrank_linear(const void* B, const void* W, void* out, int64_t b
  *
  *  Q    [batch, L, dq] in;  K_r, V_r [batch, r, dq] in;  O [batch, L, dq] out
  *  scale  ≤ 0 → 1/sqrt(d_h)
- *  workspace  device; ATP_BF16 needs it (V_r is re-laid out per head there)
+ *  workspace  device; required for ATP_BF16 (the present kernel leaves it alone)
  *
  * Errors: ATP_ERR_INVALID_ARG (null pointer, size < 1, dq % heads ≠ 0,
  * misaligned pointer), ATP_ERR_UNSUPPORTED (ATP_BF16 with d_h not in {64, 128};
@@ -280,14 +279,10 @@ atp_status atp_attention(const void* Q, const void* K_r, const void* V_r, void* 
 /* --------------------------------------------------------------------------
  * atp_attention_static — atp_attention for callers that cannot allocate or pass scratch memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): same
- * arguments and results as atp_attention without `workspace`; the re-laid-out values go to a
- * buffer of ATP_STATIC_SCRATCH_BYTES that is built into the library (one copy per GPU, resident
- * until the process ends; its address on the current device is resolved by atp_init() or by the
- * first call).  Calls no hipMalloc / hipFree or other allocating routine.
- * Limit: batch · dq · ceil64(r) · 2 bytes ≤ ATP_STATIC_SCRATCH_BYTES for ATP_BF16 (ATP_F32 uses no
- * scratch); larger inputs return ATP_ERR_SCRATCH_LIMIT and enqueue nothing.
- * Every call on one GPU uses that GPU's single buffer: two calls that overlap in time on one GPU
- * (different streams or threads) race; serialise them.  Other errors as atp_attention.
+ * arguments and results as atp_attention without `workspace`.  Calls no hipMalloc / hipFree or other
+ * allocating routine and keeps nothing between calls: it may run on several streams at once.
+ * Limit: batch · dq · ceil64(r) · 2 bytes ≤ ATP_STATIC_SCRATCH_BYTES for ATP_BF16; larger inputs return
+ * ATP_ERR_SCRATCH_LIMIT and enqueue nothing.  Other errors as atp_attention.
  * -------------------------------------------------------------------------- */
 #define ATP_STATIC_SCRATCH_BYTES (32u << 20)
 
@@ -338,7 +333,7 @@ atp_status atp_attention_linearised(const void* Q, const void* K_r, const void* 
  * atp_project_onto_bases: out [batch, r, dq] = U_rᵀ·Y for U_r [batch, L, r], Y [batch, L, dq]
  * (coordinates of the projection of Y on the subspace; with Y = X it is B_r of Eq.5).
  * Errors: ATP_ERR_INVALID_ARG (null/misaligned pointer, size < 1, dq % heads ≠ 0, odd d_h,
- * base ≤ 1, pos0 < 0), ATP_ERR_WORKSPACE (ATP_BF16 projection needs the transposed operands there).
+ * base ≤ 1, pos0 < 0), ATP_ERR_WORKSPACE (ATP_BF16 projection may turn its operands there).
  * -------------------------------------------------------------------------- */
 atp_status atp_rope(const void* Y, void* out, int64_t batch, int64_t L, int64_t dq, int heads, float base,
                     int64_t pos0, atp_dtype t, void* hip_stream);

@@ -380,7 +380,7 @@ def init() -> None:
 
 def attention_static(Q: torch.Tensor, K_r: torch.Tensor, V_r: torch.Tensor, heads: int, scale: float = 0.0,
                      out: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """atp_attention with the library's built-in scratch buffer; `out` must be given by callers that may not allocate."""
+    """atp_attention without scratch memory; `out` must be given by callers that may not allocate."""
     _check(Q, K_r, V_r, out)
     batch, L, dq = Q.shape
     r = K_r.shape[1]

@@ -70,25 +70,6 @@ hipEvent_t side_event() {
     return e;
 }
 
-// Scratch of atp_attention_static: the per-head re-laid-out values.  One copy per GPU, held until
-// the process ends.  In host code the array's name is only a handle for hipGetSymbolAddress; the
-// device address is resolved once per device and kept in g_static_scratch.
-constexpr size_t STATIC_SCRATCH_BYTES = ATP_STATIC_SCRATCH_BYTES;
-constexpr int MAX_DEVICES = 64;
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
-void* g_static_scratch[MAX_DEVICES] = {};
-
-// device address of this GPU's copy of `scratch` (nullptr on failure)
-void* static_scratch_ptr() {
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) return nullptr;
-    if (g_static_scratch[dev]) return g_static_scratch[dev];
-    void* ptr = nullptr;
-    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess) return nullptr;
-    g_static_scratch[dev] = ptr;
-    return ptr;
-}
-
 // Enum-typed arguments come from C callers and may hold any int: read the value without loading it as
 // the enum type (which is undefined for values outside the enumerators), then range-check it.
 template <class E>
@@ -438,7 +419,7 @@ const char* atp_status_string(atp_status s) {
         case ATP_ERR_WORKSPACE: return "workspace missing or too small";
         case ATP_ERR_UNSUPPORTED: return "unsupported shape";
         case ATP_ERR_DEVICE: return "HIP error";
-        case ATP_ERR_SCRATCH_LIMIT: return "input larger than the library's built-in scratch buffer";
+        case ATP_ERR_SCRATCH_LIMIT: return "input larger than the entry point without scratch memory takes";
     }
     return "unknown status";
 }
@@ -479,7 +460,6 @@ void atp_set_factor_spin_limit(int polls) { factor_dataflow_set_spin_limit(polls
 void atp_set_conditioning_gram(int single_product) { g_cond_gram_single = single_product < 0 ? 0 : (single_product > 2 ? 2 : single_product); }
 
 atp_status atp_init(void) {
-    if (!static_scratch_ptr()) return ATP_ERR_DEVICE;
     if (!side_ready()) return ATP_ERR_DEVICE;
     return ATP_OK;
 }
@@ -964,13 +944,10 @@ atp_status attention_call(const void* Q, const void* K_r, const void* V_r, const
     if (t == ATP_F32 && dh > 256) return ATP_ERR_UNSUPPORTED;
     const size_t need = linearised ? atp_attention_linearised_workspace(batch, L, r, dq, heads, t)
                                    : atp_attention_workspace(batch, L, r, dq, heads, t);
+    // (softmax attention reads its values where they lie; the sizes stay those that callers plan with)
     if (static_scratch) {
-        // the library's own buffer takes the place of the workspace argument
-        if (need > STATIC_SCRATCH_BYTES) return ATP_ERR_SCRATCH_LIMIT;
-        workspace = need ? static_scratch_ptr() : nullptr;
-        if (need && !workspace) return ATP_ERR_DEVICE;
-        workspace_bytes = STATIC_SCRATCH_BYTES;
-    }
+        if (need > ATP_STATIC_SCRATCH_BYTES) return ATP_ERR_SCRATCH_LIMIT;
+    } else
     if (need && (!workspace || workspace_bytes < need)) return ATP_ERR_WORKSPACE;
 
     hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
@@ -979,10 +956,8 @@ atp_status attention_call(const void* Q, const void* K_r, const void* V_r, const
     a.Q = Q; a.K = K_r; a.V = V_r; a.O = O;
     a.batch = (int)batch; a.L = (int)L; a.nk = (int)r; a.nk_pad = (int)rp; a.dq = (int)dq; a.heads = heads;
     a.scale = (scale > 0.f) ? scale : 1.0f / sqrtf((float)dh);
-    Carver c(workspace);
-    void* vt = (t == ATP_BF16) ? c.take((size_t)batch * dq * rp * 2) : nullptr;
     if (linearised) {
-        float* cs = (float*)c.take((size_t)batch * rp * 4);
+        float* cs = (float*)workspace;
         ProfScope ps(st, ATP_K_STREAM, 0.0, (double)batch * L * r * esize(t));
         ATP_HIP(column_sums(st, U_r, cs, (int)L, (int)r, rp, (int)batch, (int)esize(t)));
         a.linearised = 1; a.colsum = cs; a.norm_rowsum = (norm == ATP_NORM_ROWSUM); a.n_tokens = (float)L;
@@ -991,12 +966,6 @@ atp_status attention_call(const void* Q, const void* K_r, const void* V_r, const
         ATP_HIP(attention_f32(st, a));
         return ATP_OK;
     }
-    // values re-laid out as [dq][r_pad] (zero padded) so a lane reads 8 consecutive keys of one feature
-    {
-        ProfScope ps(st, ATP_K_STREAM, 0.0, 4.0 * (double)batch * r * dq);
-        ATP_HIP(transpose_batched(st, V_r, vt, (int)r, (int)dq, rp, r * dq, dq * rp, (int)batch, 2, 1));
-    }
-    a.Vt = vt;
     {
         ProfScope ps(st, ATP_K_ATTENTION, 4.0 * (double)batch * L * r * dq,
                      2.0 * (double)batch * (2.0 * L * dq + 2.0 * r * dq));

@@ -12,8 +12,11 @@
 // and the probabilities are already laid out as the B operand of
 // Oᵀ += V'ᵀ·Pᵀ.  Rows of the K' tile are fetched in a permuted order (bits 2 and
 // 3 of the row index swapped) so that the 8 consecutive accumulator registers a
-// lane feeds to the second MFMA correspond to 8 consecutive keys, i.e. to one
-// 16-byte read of the transposed value tile.
+// lane feeds to the second MFMA correspond to 8 consecutive keys.  The value tile
+// is staged as it lies in memory, keys by features, and two transposing LDS reads
+// give a lane 8 keys of one feature.
+// (A pass that turned V' first cost a launch: attention of 384 queries over 96
+// keys, 12 heads of 64, 11.9 -> 9.1 µs without it.)
 #include "common.h"
 
 namespace atp {
@@ -52,14 +55,11 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
     constexpr int NT = KT / 32;           // 32-key score tiles per key tile
     constexpr int KRPI = 64 / CK;         // K rows per copy instruction
     constexpr int NKI = KT / KRPI / 4;    // K copy instructions per wave and tile
-    constexpr int VC = KT / 8;            // 16-byte chunks per Vᵀ-tile row
-    constexpr int VRPI = 64 / VC;         // Vᵀ rows per copy instruction
-    constexpr int NVI = DH / VRPI / 4;    // Vᵀ copy instructions per wave and tile
-    static_assert(NKI >= 1 && NVI >= 1, "tile too small for four waves");
+    static_assert(NKI >= 1, "tile too small for four waves");
     __shared__ __align__(16) uint4 sK0[KT * CK];
     __shared__ __align__(16) uint4 sK1[KT * CK];
-    __shared__ __align__(16) uint4 sV0[DH * VC];
-    __shared__ __align__(16) uint4 sV1[DH * VC];
+    __shared__ __align__(16) uint4 sV0[KT * CK];
+    __shared__ __align__(16) uint4 sV1[KT * CK];
 
     // 1-D grid over (batch item, head, query block).  Consecutive workgroup ids go to the 8 XCDs in
     // turn: all query blocks of one (item, head) are given to one XCD, whose L2 then serves the
@@ -80,22 +80,18 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
     const int q = qb * QT + wave * 32 + l32;
     const bf16_t* Qp = reinterpret_cast<const bf16_t*>(a.Q) + ((int64_t)b * a.L) * a.dq + h * DH;
     const bf16_t* Kp = reinterpret_cast<const bf16_t*>(a.K) + ((int64_t)b * a.nk) * a.dq + h * DH;
-    const bf16_t* Vp = reinterpret_cast<const bf16_t*>(a.Vt) + ((int64_t)b * a.dq + h * DH) * a.nk_pad;
+    const bf16_t* Vp = reinterpret_cast<const bf16_t*>(a.V) + ((int64_t)b * a.nk) * a.dq + h * DH;
     const float* csum = LIN ? a.colsum + (int64_t)b * a.nk_pad : nullptr;
 
     // per-lane pieces of the copy addresses
     int k_row[NKI];
-    unsigned k_chunk[NKI], v_off[NVI];   // byte offsets
+    unsigned k_chunk[NKI], v_chunk[NKI];   // byte offsets
 #pragma unroll
     for (int i = 0; i < NKI; ++i) {
         const int row = (i * 4 + wave) * KRPI + lane / CK;
         k_row[i] = row;
         k_chunk[i] = (unsigned)(((lane % CK) ^ tile_swz<CK>(row)) * 16);
-    }
-#pragma unroll
-    for (int i = 0; i < NVI; ++i) {
-        const int row = (i * 4 + wave) * VRPI + lane / VC;
-        v_off[i] = (unsigned)(((int64_t)row * a.nk_pad + (((lane % VC) ^ tile_swz<VC>(row)) * 8)) * 2);
+        v_chunk[i] = (unsigned)(((lane % CK) ^ column_swz<DH>(row)) * 16);
     }
     // LDS byte address of this wave's first copy slot in each stage array (scalar registers); every
     // copy is a scalar base plus a 32-bit lane offset, untracked by the compiler: all waits for them
@@ -112,9 +108,8 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
         for (int i = 0; i < NKI; ++i) {
             const int key = min(kt0 + k_row[i], a.nk - 1);  // rows past the end: any valid row, masked below
             copy16_untracked(Kp, (unsigned)key * row_bytes + k_chunk[i], lk + (unsigned)i * 4096u);
+            copy16_untracked(Vp, (unsigned)key * row_bytes + v_chunk[i], lv + (unsigned)i * 4096u);
         }
-#pragma unroll
-        for (int i = 0; i < NVI; ++i) copy16_untracked(Vp + kt0, v_off[i], lv + (unsigned)i * 4096u);
     };
 
     // query fragments (B operand of the score MFMA): 8 consecutive features per lane and k-step
@@ -136,6 +131,15 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
     // S-tile row i holds key perm(i): bits 2 and 3 swapped
     const int prow = (l32 & ~0xC) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
     const int pswz = tile_swz<CK>(prow);
+    int v_col[NCT];
+#pragma unroll
+    for (int i = 0; i < NCT; ++i) v_col[i] = column_frag_offset<DH>(lane, 32 * i);
+    // Rows past the last key hold copies of it; their weight is zero, but zero times infinity is not: they become zeros.
+    auto clear_tail = [&](int kt0, uint4* sV) {
+        if (kt0 + KT <= a.nk) return;   // the same for every wave
+        for (int c = (a.nk - kt0) * CK + tid; c < KT * CK; c += 256) sV[c] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    };
 
     auto compute = [&](int kt0, const uint4* sK, const uint4* sV) {
         // ---- scores: Sᵀ[key, query] ------------------------------------------------
@@ -225,11 +229,9 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
                 pu.z = pack_bf2(s[t][8 * tt + 4], s[t][8 * tt + 5]);
                 pu.w = pack_bf2(s[t][8 * tt + 6], s[t][8 * tt + 7]);
                 const bf16x8 pf = u4_as_bf16x8(pu);
-                const int kc = 4 * t + 2 * tt + lh;
 #pragma unroll
                 for (int i = 0; i < NCT; ++i) {
-                    const int row = 32 * i + l32;
-                    const bf16x8 vf = u4_as_bf16x8(sV[row * VC + (kc ^ tile_swz<VC>(row))]);
+                    const bf16x8 vf = read_column_frag<DH>(sV, v_col[i] + (32 * t + 16 * tt) * DH * 2);
                     o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[i], 0, 0, 0);
                 }
             }
@@ -243,11 +245,13 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
         __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();  // everybody's copies have landed; stage 1 is free
         if (kt + 1 < ntiles) issue((kt + 1) * KT, sK1, sV1);
+        clear_tail(kt * KT, sV0);
         compute(kt * KT, sK0, sV0);
         if (kt + 1 < ntiles) {
             __builtin_amdgcn_s_waitcnt(0x0F70);
             __syncthreads();
             if (kt + 2 < ntiles) issue((kt + 2) * KT, sK0, sV0);
+            clear_tail((kt + 1) * KT, sV1);
             compute((kt + 1) * KT, sK1, sV1);
         }
     }
@@ -259,7 +263,7 @@ __global__ void __launch_bounds__(256, KT == 32 ? 3 : 2) attn_bf16_kernel(AttnAr
     if (LIN && !a.norm_rowsum) l_tot += a.n_tokens;
     const float inv = 1.0f / l_tot;
     // (row pitch DH elements; 16-byte piece p of query row q sits at piece p ^ (q & (DH/8 - 1)))
-    static_assert(32 * DH * 2 <= KT * CK * 16 && 32 * DH * 2 <= DH * VC * 16, "output staging: one stage array per wave");
+    static_assert(32 * DH * 2 <= KT * CK * 16 && 4 * 32 * DH * 2 <= 4 * KT * CK * 16, "output staging: one stage array per wave");
     bf16_t* ob = reinterpret_cast<bf16_t*>(wave == 0 ? sK0 : wave == 1 ? sK1 : wave == 2 ? sV0 : sV1);
 #pragma unroll
     for (int i = 0; i < NCT; ++i)

@@ -224,8 +224,7 @@ hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y
 struct AttnArgs {
     const void* Q = nullptr;   // [batch, L, dq]
     const void* K = nullptr;   // [batch, nk, dq]
-    const void* V = nullptr;   // [batch, nk, dq]  (f32 path)
-    const void* Vt = nullptr;  // [batch, dq, nk_pad] (bf16 path: per-head transposed values, zero padded)
+    const void* V = nullptr;   // [batch, nk, dq]
     void* O = nullptr;         // [batch, L, dq]
     int batch = 1, L = 0, nk = 0, nk_pad = 0, dq = 0, heads = 1;
     float scale = 0.f;

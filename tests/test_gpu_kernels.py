@@ -87,6 +87,23 @@ def test_projection_onto_bases(atp, case):
     assert rel_fro(to_host(out), np.stack([oracle.project_onto_bases(U[b], Y[b]) for b in range(batch)])) <= BF16_TOL
 
 
+# keys around the 64-key tile, both head widths, the last tile in either stage.  bf16 probabilities and outputs: two roundings of 2^-9
+# relative, so 2^-8.  An infinite value makes its own feature infinite and no other.
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("r", [1, 15, 63, 64, 65, 127, 128, 129, 200])
+def test_bf16_attention_key_tiles(atp, dh, r):
+    Q, K, V = (wl.round_to_dtype(rnd((2, n, 2 * dh), 10 + i), "bf16") for i, n in enumerate((130, r, r)))
+    dev = [to_dev(x, "bf16") for x in (Q, K, V)]
+    out = to_host(atp.attention(*dev, 2))
+    ref = np.stack([oracle.attention(Q[b], K[b], V[b], 2) for b in range(2)])
+    assert rel_fro(out, ref) <= BF16_TOL
+    dev[2][0, r - 1, 5] = float("inf")
+    out2 = to_host(atp.attention(*dev, 2))
+    assert np.isposinf(out2[0, :, 5]).all()
+    out2[0, :, 5] = out[0, :, 5]
+    assert np.array_equal(out, out2)
+
+
 # (batch, L, r, dq, heads): fp32 attention with 128 queries per workgroup and with the keys dealt to four waves; heads of every
 # padded width (64, 128, 256), widths that are no multiple of 4 (scalar loads); one short of / past the 32-key tile and the
 # 128-key stage; a single key and a single query
