@@ -784,10 +784,9 @@ atp_status atp_concat_factors(const void* U1, const void* C1, const void* U2, co
     uint8_t* Pb = reinterpret_cast<uint8_t*>(P);
     uint8_t* Cb = reinterpret_cast<uint8_t*>(C);
     ProfScope ps(st, ATP_K_STREAM, 0.0, 2.0 * (double)batch * (L + d) * m * es);
-    ATP_HIP(copy_block(st, U1, Pb, (int)L, (int)r1, r1, m, L * r1, L * m, (int)batch, es));
-    ATP_HIP(copy_block(st, U2, Pb + (size_t)r1 * es, (int)L, (int)r2, r2, m, L * r2, L * m, (int)batch, es));
-    ATP_HIP(copy_block(st, C1, Cb, (int)r1, (int)d, d, d, r1 * d, m * d, (int)batch, es));
-    ATP_HIP(copy_block(st, C2, Cb + (size_t)r1 * d * es, (int)r2, (int)d, d, d, r2 * d, m * d, (int)batch, es));
+    const ConcatBlock blocks[4] = {{U1, Pb, L, r1, m, L * r1, L * m}, {U2, Pb + (size_t)r1 * es, L, r2, m, L * r2, L * m},
+                                   {C1, Cb, r1, d, d, r1 * d, m * d}, {C2, Cb + (size_t)r1 * d * es, r2, d, d, r2 * d, m * d}};
+    ATP_HIP(concat_blocks(st, blocks, (int)batch, es));
     return ATP_OK;
 }
 
@@ -818,20 +817,17 @@ atp_status atp_norm_factored(const void* P, const void* C, const float* gain, fl
     float* PM = (float*)c.take((size_t)batch * L * m * 4);
     {
         ProfScope ps(st, ATP_K_STREAM, 0.0, 3.0 * (double)batch * m * d * es);
-        ATP_HIP(norm_coeff(st, C, gain, Cc, Cn, batch * m, (int)d, center ? 1 : 0, es));
+        ATP_HIP(norm_coeff(st, C, gain, center ? Cc : nullptr, Cn, batch * m, (int)d, es));
     }
     {   // M = Cc·Ccᵀ: the Gram matrix of the (centred) coefficient rows
         GemmArgs g;
-        g.A = Cc; g.B = Cc; g.lda = d; g.ldb = d; g.sA = m * d; g.sB = m * d;
+        g.A = g.B = center ? Cc : C; g.lda = d; g.ldb = d; g.sA = m * d; g.sB = m * d;
         g.M = (int)m; g.N = (int)m; g.K = (int)d; g.batch = (int)batch;
-        g.C32 = M32; g.ldc = m; g.sC = m * m;
+        if (mfma) g.C16 = M16; else g.C32 = M32;
+        g.ldc = m; g.sC = m * m;
         ATP_HIP(nt_product(st, mfma, g));
     }
-    const void* Mop = M32;
-    if (mfma) {
-        ATP_HIP(cast_f32_to_bf16(st, M32, M16, batch * m * m));
-        Mop = M16;
-    }
+    const void* Mop = mfma ? (const void*)M16 : M32;
     {   // PM = P·M (M is symmetric, so it is its own K-contiguous operand)
         GemmArgs g;
         g.A = P; g.B = Mop; g.lda = m; g.ldb = m; g.sA = L * m; g.sB = m * m;

@@ -163,17 +163,16 @@ hipError_t start_block_twin(hipStream_t st, const float* in, void* out, int rows
 hipError_t pad_rows(hipStream_t st, const void* in, void* out, int64_t rows, int cols, int ld_out, int elem_bytes);
 // columns from .. ld-1 of `rows` rows of three matrices set to zero (null or rows == 0: skipped)
 hipError_t zero_columns(hipStream_t st, void* const (&m)[3], const int64_t (&rows)[3], const int (&elem_bytes)[3], int from, int ld);
-hipError_t cast_f32_to_bf16(hipStream_t st, const float* in, bf16_t* out, int64_t n);
 // rotary position encoding of the rows of in [batch][L][dq] (heads of width dh, half-split pairs); in == out allowed
 hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L, int dq, int dh, float base, int pos0,
                      int elem_bytes);
 
-// rows×cols block of every batch item copied into another matrix (leading dimensions / batch strides in elements)
-hipError_t copy_block(hipStream_t st, const void* in, void* out, int rows, int cols, int64_t ld_in, int64_t ld_out,
-                      int64_t s_in, int64_t s_out, int batch, int elem_bytes);
-// row-wise normalisation of a factored matrix H = P·C: coefficient side (Cc = C - row mean if center; Cn = Cc·diag(gain))
+// a contiguous rows×cols block of every batch item, copied into another matrix (leading dimension and batch strides in elements)
+struct ConcatBlock { const void* in; void* out; int64_t rows, cols, ld_out, s_in, s_out; };
+hipError_t concat_blocks(hipStream_t st, const ConcatBlock (&b)[4], int batch, int elem_bytes);
+// row-wise normalisation of a factored matrix H = P·C: coefficient side (Cc = C - row mean, null: no centring, Cc = C; Cn = Cc·diag(gain))
 // and basis side (Pn[i] = P[i] / sqrt(p_i·M·p_iᵀ/d + eps), with PM = P·M, M = Cc·Ccᵀ, given in fp32)
-hipError_t norm_coeff(hipStream_t st, const void* C, const float* gain, void* Cc, void* Cn, int64_t rows, int d, int center,
+hipError_t norm_coeff(hipStream_t st, const void* C, const float* gain, void* Cc, void* Cn, int64_t rows, int d,
                       int elem_bytes);
 hipError_t norm_basis(hipStream_t st, const void* P, const float* PM, void* Pn, int64_t rows, int m, int d, float eps,
                       int elem_bytes);

@@ -3,6 +3,8 @@
 // casts, fills and the counter-based Gaussian generator of the start block.
 #include "common.h"
 
+#include <type_traits>
+
 namespace atp {
 namespace {
 
@@ -124,19 +126,6 @@ __global__ void __launch_bounds__(256) zero_columns_kernel(ZeroColumns a, int fr
     }
 }
 
-__global__ void cast_kernel(const float* __restrict__ in, bf16_t* __restrict__ out, int64_t n) {
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    if (i + 3 < n) {
-        const float4 v = *reinterpret_cast<const float4*>(in + i);
-        uint2 o;
-        o.x = pack_bf2(v.x, v.y);
-        o.y = pack_bf2(v.z, v.w);
-        *reinterpret_cast<uint2*>(out + i) = o;
-    } else {
-        for (int64_t j = i; j < n; ++j) out[j] = f2bf(in[j]);
-    }
-}
-
 // Rotary position encoding, half-split pairing: within a head of width dh, coordinate j < dh/2 of
 // row i is paired with j + dh/2 and the pair is rotated by (pos0 + i)·base^(-2j/dh).
 template <typename T>
@@ -160,65 +149,106 @@ __global__ void __launch_bounds__(256) rope_kernel(const T* __restrict__ in, T* 
 }
 
 
-// out[b][i][c_off + j] = in[b][i][j]: rows×cols block copied into a wider (or taller) matrix; 2- or 4-byte elements
+// Four blocks copied into wider (or taller) matrices in one launch, blockIdx.y = block, in pieces of sizeof(T) bytes.  2^tpr threads
+// share a row, so that short rows fill a workgroup.  HBM-bound: pairs of width 1024 joined at L = d = 4096 (67 MB) took 35 µs as four
+// launches that moved single elements.
+struct ConcatArgs { ConcatBlock b[4]; int tpr[4]; };
 template <typename T>
-__global__ void __launch_bounds__(256) copy_block_kernel(const T* __restrict__ in, T* __restrict__ out, int rows, int cols,
-                                                         int64_t ld_in, int64_t ld_out, int64_t s_in, int64_t s_out) {
-    const int b = blockIdx.z, i = blockIdx.y;
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (i >= rows || j >= cols) return;
-    out[(int64_t)b * s_out + (int64_t)i * ld_out + j] = in[(int64_t)b * s_in + (int64_t)i * ld_in + j];
+__global__ void __launch_bounds__(256) concat_kernel(ConcatArgs a) {
+    const ConcatBlock& k = a.b[blockIdx.y];
+    const T* src = reinterpret_cast<const T*>(k.in) + (int64_t)blockIdx.z * k.s_in;
+    T* dst = reinterpret_cast<T*>(k.out) + (int64_t)blockIdx.z * k.s_out;
+    const int tpr = a.tpr[blockIdx.y], sub = threadIdx.x >> tpr, lane = threadIdx.x & ((1 << tpr) - 1), rpb = 256 >> tpr;
+    for (int64_t i = (int64_t)blockIdx.x * rpb + sub; i < k.rows; i += (int64_t)gridDim.x * rpb)
+        for (int64_t j = lane; j < k.cols; j += 1 << tpr) dst[i * k.ld_out + j] = src[i * k.cols + j];
 }
 
-// Row-wise normalisation carried through a factored matrix H = P·C (one workgroup per row).
-// Coefficient side: Cc[j][:] = C[j][:] - mean_j (mean removed only when `center`), Cn = Cc · diag(gain).
-template <typename T>
+// N consecutive elements as floats, and back (N = 8: 16 bytes of bf16, 32 of fp32; rows start at multiples of 16 bytes then)
+template <int N, typename T>
+__device__ __forceinline__ void load_row(const T* p, float (&x)[N]) {
+    if constexpr (N == 1) {
+        if constexpr (sizeof(T) == 2) x[0] = bf2f(*p); else x[0] = *p;
+    } else if constexpr (sizeof(T) == 2) {
+        const uint4 u = *reinterpret_cast<const uint4*>(p);
+        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[2 * e] = __uint_as_float(w[e] << 16); x[2 * e + 1] = __uint_as_float(w[e] & 0xffff0000u); }
+    } else {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(p), b = *reinterpret_cast<const f32x4*>(p + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { x[e] = a[e]; x[4 + e] = b[e]; }
+    }
+}
+template <int N, typename T>
+__device__ __forceinline__ void store_row(T* p, const float (&x)[N]) {
+    if constexpr (N == 1) {
+        if constexpr (sizeof(T) == 2) *p = f2bf(x[0]); else *p = x[0];
+    } else if constexpr (sizeof(T) == 2) {
+        *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]), pack_bf2(x[4], x[5]), pack_bf2(x[6], x[7]));
+    } else {
+        *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
+        *reinterpret_cast<f32x4*>(p + 4) = f32x4{x[4], x[5], x[6], x[7]};
+    }
+}
+
+// Row-wise normalisation carried through a factored matrix H = P·C (one workgroup per row; HBM-bound, so 8 elements per access
+// where the row length is a multiple of 8).
+// Coefficient side: Cc[j][:] = C[j][:] - mean_j, Cn = Cc · diag(gain); without centring (Cc null) Cc is C itself.
+template <int N, typename T>
 __global__ void __launch_bounds__(256) norm_coeff_kernel(const T* __restrict__ C, const float* __restrict__ gain,
-                                                         T* __restrict__ Cc, T* __restrict__ Cn, int d, int center) {
+                                                         T* __restrict__ Cc, T* __restrict__ Cn, int d) {
     __shared__ float red[4];
     const int64_t row = blockIdx.x;
     const T* src = C + row * d;
-    float mean = 0.f;
-    if (center) {
+    float mean = 0.f, x[N], g[N];
+    if (Cc) {
         float s = 0.f;
-        for (int j = threadIdx.x; j < d; j += 256) {
-            if constexpr (sizeof(T) == 2) s += bf2f(src[j]); else s += src[j];
+        for (int j = threadIdx.x * N; j < d; j += 256 * N) {
+            load_row<N>(src + j, x);
+#pragma unroll
+            for (int e = 0; e < N; ++e) s += x[e];
         }
         for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
         __syncthreads();
         mean = (red[0] + red[1] + red[2] + red[3]) / (float)d;
     }
-    for (int j = threadIdx.x; j < d; j += 256) {
-        float x;
-        if constexpr (sizeof(T) == 2) x = bf2f(src[j]); else x = src[j];
-        x -= mean;
-        if constexpr (sizeof(T) == 2) { Cc[row * d + j] = f2bf(x); Cn[row * d + j] = f2bf(x * gain[j]); }
-        else { Cc[row * d + j] = x; Cn[row * d + j] = x * gain[j]; }
+    for (int j = threadIdx.x * N; j < d; j += 256 * N) {
+        load_row<N>(src + j, x);
+#pragma unroll
+        for (int e = 0; e < N; ++e) { g[e] = gain[j + e]; x[e] -= mean; }
+        if (Cc) store_row<N>(Cc + row * d + j, x);
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[e] *= g[e];
+        store_row<N>(Cn + row * d + j, x);
     }
 }
 
 // Basis side: var_i = (1/d)·p_i·M·p_iᵀ with T = P·M given; Pn[i][:] = P[i][:] / sqrt(var_i + eps).
-template <typename T>
+template <int N, typename T>
 __global__ void __launch_bounds__(256) norm_basis_kernel(const T* __restrict__ P, const float* __restrict__ PM,
                                                          T* __restrict__ Pn, int m, float inv_d, float eps) {
     __shared__ float red[4];
     const int64_t row = blockIdx.x;
     const T* p = P + row * m;
     const float* t = PM + row * m;
-    float s = 0.f;
-    for (int j = threadIdx.x; j < m; j += 256) {
-        float x;
-        if constexpr (sizeof(T) == 2) x = bf2f(p[j]); else x = p[j];
-        s += x * t[j];
+    float s = 0.f, x[N], y[N];
+    for (int j = threadIdx.x * N; j < m; j += 256 * N) {
+        load_row<N>(p + j, x);
+        load_row<N>(t + j, y);
+#pragma unroll
+        for (int e = 0; e < N; ++e) s += x[e] * y[e];
     }
     for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
     const float var = fmaxf((red[0] + red[1] + red[2] + red[3]) * inv_d, 0.f);
     const float sc = 1.0f / sqrtf(var + eps);
-    for (int j = threadIdx.x; j < m; j += 256) {
-        if constexpr (sizeof(T) == 2) Pn[row * m + j] = f2bf(bf2f(p[j]) * sc); else Pn[row * m + j] = p[j] * sc;
+    for (int j = threadIdx.x * N; j < m; j += 256 * N) {
+        load_row<N>(p + j, x);
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[e] *= sc;
+        store_row<N>(Pn + row * m + j, x);
     }
 }
 
@@ -258,30 +288,45 @@ hipError_t zero_columns(hipStream_t st, void* const (&m)[3], const int64_t (&row
     return hipGetLastError();
 }
 
-hipError_t copy_block(hipStream_t st, const void* in, void* out, int rows, int cols, int64_t ld_in, int64_t ld_out,
-                      int64_t s_in, int64_t s_out, int batch, int elem_bytes) {
-    if (rows <= 0 || cols <= 0 || batch <= 0) return hipSuccess;
-    dim3 grid((cols + 255) / 256, rows, batch);
-    if (grid.y > 65535 || grid.z > 65535) return hipErrorInvalidValue;   // the callers check their sizes against this
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL(copy_block_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, rows, cols,
-                           ld_in, ld_out, s_in, s_out);
-    else
-        hipLaunchKernelGGL(copy_block_kernel<uint32_t>, grid, dim3(256), 0, st, (const uint32_t*)in, (uint32_t*)out, rows, cols,
-                           ld_in, ld_out, s_in, s_out);
+namespace {
+template <typename T>
+hipError_t launch_concat(hipStream_t st, ConcatArgs a, int batch, int per) {   // per: elements in a T
+    int64_t blocks = 1;
+    for (int i = 0; i < 4; ++i) {
+        ConcatBlock& k = a.b[i];
+        k.cols /= per; k.ld_out /= per; k.s_in /= per; k.s_out /= per;
+        a.tpr[i] = 0;
+        while (a.tpr[i] < 8 && (1ll << a.tpr[i]) < k.cols) ++a.tpr[i];
+        const int64_t n = (k.rows + (256 >> a.tpr[i]) - 1) / (256 >> a.tpr[i]);
+        blocks = n > blocks ? n : blocks;
+    }
+    hipLaunchKernelGGL(concat_kernel<T>, dim3((unsigned)(blocks < 4096 ? blocks : 4096), 4, batch), dim3(256), 0, st, a);
     return hipGetLastError();
 }
+}  // namespace
 
-hipError_t norm_coeff(hipStream_t st, const void* C, const float* gain, void* Cc, void* Cn, int64_t rows, int d, int center,
-                      int elem_bytes) {
+hipError_t concat_blocks(hipStream_t st, const ConcatBlock (&b)[4], int batch, int elem_bytes) {
+    ConcatArgs a;
+    const int per = 16 / elem_bytes;
+    bool whole = true;   // every row of every block is made of aligned 16-byte pieces
+    for (int i = 0; i < 4; ++i) {
+        a.b[i] = b[i];
+        whole = whole && b[i].cols % per == 0 && b[i].ld_out % per == 0 && b[i].s_in % per == 0 && b[i].s_out % per == 0 &&
+                (((uintptr_t)b[i].in | (uintptr_t)b[i].out) & 15) == 0;
+    }
+    if (whole) return launch_concat<uint4>(st, a, batch, per);
+    return elem_bytes == 2 ? launch_concat<uint16_t>(st, a, batch, 1) : launch_concat<uint32_t>(st, a, batch, 1);
+}
+
+hipError_t norm_coeff(hipStream_t st, const void* C, const float* gain, void* Cc, void* Cn, int64_t rows, int d, int elem_bytes) {
     if (rows <= 0) return hipSuccess;
     if (rows > 0x7fffffff) return hipErrorInvalidValue;
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL(norm_coeff_kernel<bf16_t>, dim3((unsigned)rows), dim3(256), 0, st, (const bf16_t*)C, gain, (bf16_t*)Cc,
-                           (bf16_t*)Cn, d, center);
-    else
-        hipLaunchKernelGGL(norm_coeff_kernel<float>, dim3((unsigned)rows), dim3(256), 0, st, (const float*)C, gain, (float*)Cc,
-                           (float*)Cn, d, center);
+    const auto go = [&](auto kern, auto* t) {
+        using T = std::remove_reference_t<decltype(*t)>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(256), 0, st, (const T*)C, gain, (T*)Cc, (T*)Cn, d);
+    };
+    if (elem_bytes == 2) go(d % 8 ? norm_coeff_kernel<1, bf16_t> : norm_coeff_kernel<8, bf16_t>, (bf16_t*)nullptr);
+    else go(d % 8 ? norm_coeff_kernel<1, float> : norm_coeff_kernel<8, float>, (float*)nullptr);
     return hipGetLastError();
 }
 
@@ -289,12 +334,12 @@ hipError_t norm_basis(hipStream_t st, const void* P, const float* PM, void* Pn, 
                       int elem_bytes) {
     if (rows <= 0) return hipSuccess;
     if (rows > 0x7fffffff) return hipErrorInvalidValue;
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL(norm_basis_kernel<bf16_t>, dim3((unsigned)rows), dim3(256), 0, st, (const bf16_t*)P, PM, (bf16_t*)Pn, m,
-                           1.0f / (float)d, eps);
-    else
-        hipLaunchKernelGGL(norm_basis_kernel<float>, dim3((unsigned)rows), dim3(256), 0, st, (const float*)P, PM, (float*)Pn, m,
-                           1.0f / (float)d, eps);
+    const auto go = [&](auto kern, auto* t) {
+        using T = std::remove_reference_t<decltype(*t)>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3(256), 0, st, (const T*)P, PM, (T*)Pn, m, 1.0f / (float)d, eps);
+    };
+    if (elem_bytes == 2) go(m % 8 ? norm_basis_kernel<1, bf16_t> : norm_basis_kernel<8, bf16_t>, (bf16_t*)nullptr);
+    else go(m % 8 ? norm_basis_kernel<1, float> : norm_basis_kernel<8, float>, (float*)nullptr);
     return hipGetLastError();
 }
 
@@ -340,13 +385,6 @@ hipError_t fill_gaussian(hipStream_t st, float* out, int64_t n, uint64_t seed) {
 hipError_t fill_zero_i32(hipStream_t st, int32_t* p, int64_t n) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n);
-    return hipGetLastError();
-}
-
-hipError_t cast_f32_to_bf16(hipStream_t st, const float* in, bf16_t* out, int64_t n) {
-    if (n <= 0) return hipSuccess;
-    const int64_t nt = (n + 3) / 4;
-    hipLaunchKernelGGL(cast_kernel, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, st, in, out, n);
     return hipGetLastError();
 }
 

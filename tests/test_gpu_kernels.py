@@ -104,6 +104,24 @@ def test_bf16_attention_key_tiles(atp, dh, r):
     assert np.array_equal(out, out2)
 
 
+# (batch, L, d, r1, r2): rows of aligned 16-byte pieces and of single elements, pieces shared between few and many rows; copies are exact
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", [(1, 1, 8, 8, 8), (2, 65, 72, 16, 24), (2, 130, 2056, 40, 8), (1, 33, 70, 8, 12), (2, 40, 71, 5, 3), (1, 600, 64, 304, 280)])
+def test_concatenated_blocks_and_norm(atp, dtype, case):
+    batch, L, d, r1, r2 = case
+    U1, C1, U2, C2 = (to_dev(rnd((batch, *shape), 20 + i), dtype) for i, shape in enumerate(((L, r1), (r1, d), (L, r2), (r2, d))))
+    P, C = atp.concat_factors(U1, C1, U2, C2)
+    assert torch.equal(P, torch.cat([U1, U2], 2)) and torch.equal(C, torch.cat([C1, C2], 1))
+    gain = 1 + 0.1 * torch.randn(d, generator=torch.Generator().manual_seed(5))
+    for center in (False, True):
+        Pn, Cn = atp.norm_factored(P, C, gain.cuda(), 1e-6, center)
+        for b in range(batch):
+            Pr, Cr = oracle.norm_factored(to_host(P[b]), to_host(C[b]), gain.double().numpy(), 1e-6, center)
+            # bf16: M and each factor rounded once
+            assert rel_fro(to_host(Pn[b]), Pr) <= (1e-5 if dtype == "f32" else 2 * BF16_TOL)
+            assert rel_fro(to_host(Cn[b]), Cr) <= (1e-5 if dtype == "f32" else 2 * BF16_TOL)
+
+
 # (batch, L, r, dq, heads): fp32 attention with 128 queries per workgroup and with the keys dealt to four waves; heads of every
 # padded width (64, 128, 256), widths that are no multiple of 4 (scalar loads); one short of / past the 32-key tile and the
 # 128-key stage; a single key and a single query
