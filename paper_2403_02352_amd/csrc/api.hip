@@ -103,6 +103,10 @@ constexpr int NUM_CU = 256;  // compute units of an MI355X
 // product runs on the asynchronous bf16 kernel (K a multiple of 64, of 32 with lo planes, rows aligned to 16 bytes) whatever L, d and r
 // are; zero columns of Ω carry through as zero columns of every iterate.  Extents that this kernel takes as they are stay as they are
 // (r when it is a multiple of 32, L and d when multiples of 64).  The fp32 path pads to 4, for 16-byte loads.
+// On the bf16 path a matrix that a product contracts over its rows is read as it lies (operands stored by columns), so an iterate has
+// no transposed twin: the products and the applications of R^-1 wrote half of their bytes for twins.  There the row counts are padded
+// with zero rows.  The strided fp32 kernel prefers K-contiguous rows and keeps the twins.  Measured without twins against with:
+// L = 32768, d = 4096, r = 2048 12.0 against 12.9 ms, 4 × 4096 × 4096, r = 1024 8.17 against 8.55 ms, 2 × 1003 × 1536, r = 250 1.51 against 1.60.
 // Measured at 2 × 1003 × 1536, r = 250: whole block 4.32 ms with the products in the strided kernel, 1.71 ms padded.
 struct BasesDims {
     int64_t Lp, dp, rp;
@@ -114,16 +118,17 @@ BasesDims bases_dims(int64_t L, int64_t d, int64_t r, atp_dtype t) {
 }
 
 struct BasesWs {
-    void* XT;        // [batch, d, Lp]  type t
-    void* Xp;        // [batch, L, dp]  type t, only when dp != d
+    void* XT;        // [batch, d, Lp]  fp32 path: Xᵀ
+    void* Xp;        // [batch, Lp or L (fp32), dp]  type t, only when X itself is not of that shape
     float* Om;       // [d, r]   generated start block (only when Omega == NULL)
-    void* OmT;       // [rp, dp] type t
-    float* ZL[2];    // [batch, L, rp]
-    float* ZLT[2];   // [batch, rp, Lp]
-    float* ZD[2];    // [batch, d, rp]
-    float* ZDT[2];   // [batch, rp, dp]
-    void* TL;        // [batch, rp, Lp]  type t: transposed twin of the current U (finally of the returned U_r)
-    void* TD;        // [batch, rp, dp]  type t: transposed twin of the current V
+    void* OmT;       // start block in type t: [dp, rp], fp32 path [rp, dp]
+    float* ZL[2];    // [batch, Lp, rp]
+    float* ZLT[2];   // [batch, rp, Lp]  fp32 path
+    float* ZD[2];    // [batch, dp, rp]
+    float* ZDT[2];   // [batch, rp, dp]  fp32 path
+    void* TL;        // current U in type t: [batch, Lp, rp], fp32 path (and finally the returned U_r) transposed
+    void* TU;        // [batch, rp, Lp]  type t: transposed twin of the returned U_r
+    void* TD;        // current V in type t: [batch, dp, rp], fp32 path transposed
     float* Spart;    // [KSPLIT_MAX, batch, rp, rp] split-K partial Gram matrices
     float* S;        // [batch, rp, rp]
     float* Lf;       // [batch, rp, rp]
@@ -142,17 +147,19 @@ BasesWs carve_bases(void* ws, int64_t batch, int64_t L, int64_t d, int64_t r, at
     const size_t es = esize(t);
     w.dim = bases_dims(L, d, r, t);
     const int64_t Lp = w.dim.Lp, dp = w.dim.dp, rp = w.dim.rp;
-    w.XT = c.take((size_t)batch * d * Lp * es);
-    w.Xp = dp != d ? c.take((size_t)batch * L * dp * es) : nullptr;
+    const bool cols = t == ATP_BF16;
+    w.XT = cols ? nullptr : c.take((size_t)batch * d * Lp * es);
+    w.Xp = dp != d || (cols && Lp != L) ? c.take((size_t)batch * (cols ? Lp : L) * dp * es) : nullptr;
     w.Om = (float*)c.take((size_t)d * r * 4);
     w.OmT = c.take((size_t)dp * rp * es);
     for (int i = 0; i < 2; ++i) {
-        w.ZL[i] = (float*)c.take((size_t)batch * L * rp * 4);
-        w.ZLT[i] = (float*)c.take((size_t)batch * Lp * rp * 4);
-        w.ZD[i] = (float*)c.take((size_t)batch * d * rp * 4);
-        w.ZDT[i] = (float*)c.take((size_t)batch * dp * rp * 4);
+        w.ZL[i] = (float*)c.take((size_t)batch * Lp * rp * 4);
+        w.ZLT[i] = cols ? nullptr : (float*)c.take((size_t)batch * Lp * rp * 4);
+        w.ZD[i] = (float*)c.take((size_t)batch * dp * rp * 4);
+        w.ZDT[i] = cols ? nullptr : (float*)c.take((size_t)batch * dp * rp * 4);
     }
     w.TL = c.take((size_t)batch * rp * Lp * es);
+    w.TU = cols ? c.take((size_t)batch * rp * Lp * es) : w.TL;
     w.TD = c.take((size_t)batch * rp * dp * es);
     w.Spart = (float*)c.take((size_t)KSPLIT_MAX * batch * rp * rp * 4);
     w.S = (float*)c.take((size_t)batch * rp * rp * 4);
@@ -220,7 +227,7 @@ struct Work {
 inline void set_A(GemmArgs& g, bool mfma, const Work& w) { g.A = w.base; g.A_lo = mfma ? w.lo() : nullptr; }
 inline void set_B(GemmArgs& g, bool mfma, const Work& w) { g.B = w.base; g.B_lo = mfma ? w.lo() : nullptr; }
 inline void set_C(GemmArgs& g, bool mfma, const Work& c, const Work& ct) {
-    if (mfma) { g.C16 = c.hi(); g.C16lo = c.lo(); g.CT16 = ct.hi(); g.CT16lo = ct.lo(); }
+    if (mfma) { g.C16 = c.hi(); g.C16lo = c.lo(); }
     else { g.C32 = c.f32(); g.CT32 = ct.f32(); }
 }
 
@@ -229,12 +236,14 @@ struct QrOut {  // where the last pass writes
     bf16_t* C16 = nullptr;
     float* CT32 = nullptr;
     bf16_t* CT16 = nullptr;
+    bool padded = false;   // C16 is [n_pad, r], an operand of a product; else it is a result without padding
 };
 
 // Column block [off, off+width) of a product (bf16 path: all operands are bf16 planes).
 GemmArgs slice_n(GemmArgs g, int off, int width) {
-    g.B = reinterpret_cast<const bf16_t*>(g.B) + (int64_t)off * g.ldb;
-    if (g.B_lo) g.B_lo = reinterpret_cast<const bf16_t*>(g.B_lo) + (int64_t)off * g.ldb;
+    const int64_t step = g.b_cols ? 1 : g.ldb;
+    g.B = reinterpret_cast<const bf16_t*>(g.B) + off * step;
+    if (g.B_lo) g.B_lo = reinterpret_cast<const bf16_t*>(g.B_lo) + off * step;
     g.N = width;
     if (g.C32) g.C32 += off;
     if (g.C16) g.C16 += off;
@@ -300,8 +309,8 @@ hipError_t pipe_after(void* vctx, int j) {
     return err;
 }
 
-// Orthonormalise the columns of Z (n×r, fp32, with transposed twin ZT whose rows have length n_pad; r includes the padding
-// columns, r_true does not) by `passes` rounds of
+// Orthonormalise the columns of Z (n×r, and zero rows up to n_pad on the bf16 path; fp32 with transposed twin ZT whose rows have
+// length n_pad; r includes the padding columns, r_true does not) by `passes` rounds of
 // (Gram, Jacobi scaling + shift, Cholesky with inverse, apply).  Every round multiplies from the
 // right by an upper-triangular matrix with positive diagonal, so the result is the Q factor of
 // the positive-diagonal QR of Z.  Buffers ping-pong between slot `cur` and 1-cur; the last round
@@ -324,8 +333,10 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
         const bool last = (p == passes - 1);
         const bool certify = last && final_qr;
         GemmArgs g;
-        set_A(g, mfma, ZT[cur]); set_B(g, mfma, ZT[cur]);
-        g.lda = n_pad; g.ldb = n_pad; g.sA = (int64_t)r * n_pad; g.sB = (int64_t)r * n_pad;
+        const Work& gz = mfma ? Z[cur] : ZT[cur];
+        set_A(g, mfma, gz); set_B(g, mfma, gz);
+        g.a_cols = g.b_cols = mfma;
+        g.lda = g.ldb = mfma ? r : n_pad; g.sA = (int64_t)r * n_pad; g.sB = (int64_t)r * n_pad;
         g.M = r; g.N = r; g.K = n_pad; g.batch = batch;
         g.C32 = w.Spart; g.ldc = r; g.sC = (int64_t)r * r;
         g.symmetric = 1;
@@ -360,16 +371,17 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
         // the product Z·R^-1 below (set up here because the initialisation depends on its kernel)
         GemmArgs a;
         set_A(a, mfma, Z[cur]); set_B(a, mfma, linv);
-        a.lda = r; a.ldb = r; a.sA = (int64_t)n * r; a.sB = (int64_t)r * r;
+        const int64_t sZ = (int64_t)(mfma ? n_pad : n) * r;
+        a.lda = r; a.ldb = r; a.sA = sZ; a.sB = (int64_t)r * r;
         a.M = n; a.N = r; a.K = r; a.batch = batch;
-        a.ldc = r; a.sC = (int64_t)n * r; a.ldct = n_pad; a.sCT = (int64_t)r * n_pad;
+        a.ldc = r; a.sC = sZ; a.ldct = n_pad; a.sCT = (int64_t)r * n_pad;
         a.b_lower = 1;
         const bool apply_mfma = mfma && gemm_nt_mfma_ok(a);
         const int zero_all = !apply_mfma;
         if (last && out) {
             a.C32 = out->C32; a.C16 = out->C16;
             a.CT32 = out->CT32; a.CT16 = out->CT16;
-            if (out->C32 || out->C16) { a.N = r_true; a.ldc = r_true; a.sC = (int64_t)n * r_true; }   // a result: no padding columns
+            if ((out->C32 || out->C16) && !out->padded) { a.N = r_true; a.ldc = r_true; a.sC = (int64_t)n * r_true; }   // a result: no padding columns
         } else {
             set_C(a, mfma, Z[1 - cur], ZT[1 - cur]);
         }
@@ -499,49 +511,56 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
     const int64_t Lp = w.dim.Lp, dp = w.dim.dp, rp = w.dim.rp;
     const int iLp = (int)Lp, idp = (int)dp, irp = (int)rp, es = (int)esize(t);
 
-    // operand twins: Xᵀ and Ωᵀ (and X itself when its rows have to be filled up)
-    {
+    // X with its rows (and columns of rows) filled up where that is needed, and the fp32 path's Xᵀ
+    if (w.XT || w.Xp) {
         ProfScope ps(st, ATP_K_STREAM, 0.0, 2.0 * (double)batch * L * d * esize(t));
-        ATP_HIP(transpose_batched(st, X, w.XT, iL, id, Lp, L * d, Lp * d, ib, es, Lp != L));
-        if (w.Xp) ATP_HIP(pad_rows(st, X, w.Xp, batch * L, id, idp, es));
+        if (w.XT) ATP_HIP(transpose_batched(st, X, w.XT, iL, id, Lp, L * d, Lp * d, ib, es, Lp != L));
+        if (w.Xp) ATP_HIP(pad_matrix(st, X, w.Xp, iL, id, mfma ? Lp : L, idp, ib, es));
     }
     const void* Xk = w.Xp ? w.Xp : X;
+    // row counts of X and of the iterates in memory
+    const int64_t nL = mfma ? Lp : L, nD = mfma ? dp : d;
     const float* Om = Omega;
     if (!Om) {
         ATP_HIP(fill_gaussian(st, w.Om, d * r, seed));
         Om = w.Om;
     }
-    ATP_HIP(start_block_twin(st, Om, w.OmT, id, ir, idp, irp, es, inf, ib));
+    ATP_HIP(start_block(st, Om, w.OmT, id, ir, idp, irp, es, inf, ib));
 
     // Z = X·Ω
     int curL = 0, curD = 0;
     Work ZL[2], ZLT[2], ZD[2], ZDT[2];
     for (int i = 0; i < 2; ++i) {
-        ZL[i].base = w.ZL[i]; ZL[i].elems = batch * L * rp; ZLT[i].base = w.ZLT[i]; ZLT[i].elems = batch * Lp * rp;
-        ZD[i].base = w.ZD[i]; ZD[i].elems = batch * d * rp; ZDT[i].base = w.ZDT[i]; ZDT[i].elems = batch * dp * rp;
+        ZL[i].base = w.ZL[i]; ZL[i].elems = batch * nL * rp; ZLT[i].base = w.ZLT[i]; ZLT[i].elems = batch * Lp * rp;
+        ZD[i].base = w.ZD[i]; ZD[i].elems = batch * nD * rp; ZDT[i].base = w.ZDT[i]; ZDT[i].elems = batch * dp * rp;
     }
-    {   // the ends of twin rows, which no product writes (both planes of a bf16 twin are rows of one matrix)
-        const int64_t nz = batch * rp * (mfma ? 2 : 1);
-        ATP_HIP(zero_columns(st, {w.ZLT[0], w.ZLT[1], w.TL}, {nz, nz, batch * rp}, {es, es, es}, iL, iLp));
-        if (iters > 0) ATP_HIP(zero_columns(st, {w.ZDT[0], w.ZDT[1], w.TD}, {nz, nz, batch * rp}, {es, es, es}, id, idp));
+    // what no product writes: the padding rows of the iterates (both planes of a pair are items of one matrix) and the ends of twin rows
+    if (mfma) {
+        const int64_t fL = L * rp, eL = Lp * rp, fD = d * rp, eD = dp * rp, nd = iters > 0 ? batch : 0;
+        ATP_HIP(zero_tails(st, {{w.ZL[0], 2 * batch, fL, eL, 2}, {w.ZL[1], 2 * batch, fL, eL, 2}, {w.TL, batch, fL, eL, 2}, {w.TU, batch * rp, L, Lp, 2},
+                                {w.ZD[0], 2 * nd, fD, eD, 2}, {w.ZD[1], 2 * nd, fD, eD, 2}, {w.TD, nd, fD, eD, 2}, {nullptr, 0, 0, 0, 2}}));
+    } else {
+        const int64_t n = batch * rp, nd = iters > 0 ? n : 0;
+        ATP_HIP(zero_tails(st, {{w.ZLT[0], n, L, Lp, 4}, {w.ZLT[1], n, L, Lp, 4}, {w.TL, n, L, Lp, 4}, {nullptr, 0, 0, 0, 4},
+                                {w.ZDT[0], nd, d, dp, 4}, {w.ZDT[1], nd, d, dp, 4}, {w.TD, nd, d, dp, 4}, {nullptr, 0, 0, 0, 4}}));
     }
     {
         GemmArgs g;
-        g.A = Xk; g.B = w.OmT;
-        g.lda = dp; g.ldb = dp; g.sA = L * dp; g.sB = 0;
+        g.A = Xk; g.B = w.OmT; g.b_cols = mfma;
+        g.lda = dp; g.ldb = mfma ? rp : dp; g.sA = nL * dp; g.sB = 0;
         g.M = iL; g.N = irp; g.K = idp; g.batch = ib;
-        g.ldc = rp; g.sC = L * rp; g.ldct = Lp; g.sCT = Lp * rp;
+        g.ldc = rp; g.sC = nL * rp; g.ldct = Lp; g.sCT = Lp * rp;
         set_C(g, mfma, ZL[0], ZLT[0]);
         ATP_HIP(nt_product(st, mfma, g));
     }
-    // the last round of every orthonormalisation writes only what its consumer reads: the
-    // transposed twin in the storage type (B operand of the next product), and for the final one
-    // the outputs U_r / U_master
+    // the last round of every orthonormalisation writes only what its consumer reads: U or V in the storage type (fp32 path:
+    // its transposed twin), B operand of the next product, and for the final one the outputs U_r / U_master and the twin of
+    // U_r (which, unlike U_r itself, has rows of padded length)
     QrOut fin, midL, midD;
     if (t == ATP_BF16) {
-        fin.C16 = (bf16_t*)U_r; fin.C32 = U_master; fin.CT16 = (bf16_t*)w.TL;
-        midL.CT16 = (bf16_t*)w.TL;
-        midD.CT16 = (bf16_t*)w.TD;
+        fin.C16 = (bf16_t*)U_r; fin.C32 = U_master; fin.CT16 = (bf16_t*)w.TU;
+        midL.C16 = (bf16_t*)w.TL; midL.padded = true;
+        midD.C16 = (bf16_t*)w.TD; midD.padded = true;
     } else {
         fin.C32 = (float*)U_r; fin.CT32 = (float*)w.TL;
         midL.CT32 = (float*)w.TL;
@@ -550,23 +569,25 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
     // the three products that consume an orthonormalised iterate
     auto prod_w = [&]() {  // W = Xᵀ·U      (d×r)
         GemmArgs g;
-        g.A = w.XT; g.B = w.TL; g.lda = Lp; g.ldb = Lp; g.sA = d * Lp; g.sB = rp * Lp;
+        g.A = mfma ? Xk : w.XT; g.B = w.TL; g.a_cols = g.b_cols = mfma;
+        g.lda = mfma ? dp : Lp; g.ldb = mfma ? rp : Lp; g.sA = nD * Lp; g.sB = rp * Lp;
         g.M = id; g.N = irp; g.K = iLp; g.batch = ib;
-        g.ldc = rp; g.sC = d * rp; g.ldct = dp; g.sCT = rp * dp;
+        if (mfma) g.M = idp;   // whole 16-byte pieces of columns; those past d are zero and give zero rows
+        g.ldc = rp; g.sC = nD * rp; g.ldct = dp; g.sCT = rp * dp;
         set_C(g, mfma, ZD[0], ZDT[0]);
         return g;
     };
     auto prod_z = [&]() {  // Z = X·V       (L×r)
         GemmArgs h;
-        h.A = Xk; h.B = w.TD; h.lda = dp; h.ldb = dp; h.sA = L * dp; h.sB = rp * dp;
+        h.A = Xk; h.B = w.TD; h.b_cols = mfma; h.lda = dp; h.ldb = mfma ? rp : dp; h.sA = nL * dp; h.sB = rp * dp;
         h.M = iL; h.N = irp; h.K = idp; h.batch = ib;
-        h.ldc = rp; h.sC = L * rp; h.ldct = Lp; h.sCT = rp * Lp;
+        h.ldc = rp; h.sC = nL * rp; h.ldct = Lp; h.sCT = rp * Lp;
         set_C(h, mfma, ZL[0], ZLT[0]);
         return h;
     };
     auto prod_b = [&]() {  // B_r = U_rᵀ·X  (r×d) with the returned (rounded) U_r
         GemmArgs g;
-        g.A = w.TL; g.B = w.XT; g.lda = Lp; g.ldb = Lp; g.sA = rp * Lp; g.sB = d * Lp;
+        g.A = w.TU; g.B = mfma ? Xk : w.XT; g.b_cols = mfma; g.lda = Lp; g.ldb = mfma ? dp : Lp; g.sA = rp * Lp; g.sB = nD * Lp;
         g.M = ir; g.N = id; g.K = iLp; g.batch = ib;
         g.ldc = d; g.sC = r * d;
         if (t == ATP_BF16) g.C16 = (bf16_t*)B_r; else g.C32 = (float*)B_r;

@@ -118,8 +118,8 @@ struct GemmArgs {
 enum OperandType { OP_BF16 = 0, OP_F32 = 1 };
 
 // MFMA path (bf16 operands, optional lo planes).  Requirements: K % 64 == 0 (K % 32 == 0 with lo
-// planes), lda/ldb/sA/sB % 8 == 0, pointers 16-byte aligned; a_cols only with b_cols, both only for plain operands with
-// M % 8 == 0 (a_cols) and N % 8 == 0 (b_cols).
+// planes), lda/ldb/sA/sB % 8 == 0, pointers 16-byte aligned; a_cols only with b_cols (and with lo planes both or none),
+// with M % 8 == 0 (a_cols) and N, rounded up to a multiple of 8, within a row (b_cols); b_lower only for B[N,K].
 hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g);
 bool gemm_nt_mfma_ok(const GemmArgs& g);
 bool gemm_nt_mfma_big(const GemmArgs& g);  // true when the 256×256 tile configuration is chosen
@@ -156,13 +156,15 @@ hipError_t transpose_batched(hipStream_t st, const void* in, void* out, int rows
 // Omega generator: out[d*r] fp32 N(0,1), counter-based
 hipError_t fill_gaussian(hipStream_t st, float* out, int64_t n, uint64_t seed);
 hipError_t fill_zero_i32(hipStream_t st, int32_t* p, int64_t n);
-// out[cols_out][rows_out] (bf16 or fp32) = transpose of the fp32 matrix in[rows][cols], zeros outside it; also clears zero[0 .. n_zero)
-hipError_t start_block_twin(hipStream_t st, const float* in, void* out, int rows, int cols, int rows_out, int cols_out, int elem_bytes,
-                            int32_t* zero, int n_zero);
-// out[b][i][0 .. ld_out) = in[b][i][0 .. cols) followed by zeros
-hipError_t pad_rows(hipStream_t st, const void* in, void* out, int64_t rows, int cols, int ld_out, int elem_bytes);
-// columns from .. ld-1 of `rows` rows of three matrices set to zero (null or rows == 0: skipped)
-hipError_t zero_columns(hipStream_t st, void* const (&m)[3], const int64_t (&rows)[3], const int (&elem_bytes)[3], int from, int ld);
+// the fp32 matrix in[rows][cols] with zeros outside it, as bf16 out[rows_out][cols_out] (elem_bytes 2) or transposed as fp32
+// out[cols_out][rows_out] (elem_bytes 4); also clears zero[0 .. n_zero)
+hipError_t start_block(hipStream_t st, const float* in, void* out, int rows, int cols, int rows_out, int cols_out, int elem_bytes,
+                       int32_t* zero, int n_zero);
+// out[b][0 .. rows_out)[0 .. ld_out) = in[b][0 .. rows)[0 .. cols) with zeros outside it
+hipError_t pad_matrix(hipStream_t st, const void* in, void* out, int rows, int cols, int64_t rows_out, int ld_out, int batch, int elem_bytes);
+// elements from .. ld-1 of `rows` rows of 2-byte or 4-byte elements set to zero, for up to eight matrices (null: skipped)
+struct ZeroTail { void* m; int64_t rows, from, ld; int elem_bytes; };
+hipError_t zero_tails(hipStream_t st, const ZeroTail (&z)[8]);
 // rotary position encoding of the rows of in [batch][L][dq] (heads of width dh, half-split pairs); in == out allowed
 hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L, int dq, int dh, float base, int pos0,
                      int elem_bytes);

@@ -236,7 +236,7 @@ __device__ __forceinline__ int b_global_row(int b_row, int n0, int N, bool& ok) 
 
 
 // NP = 1: plain bf16 operands, BK = 64.  NP = 2: hi+lo planes, BK = 32, three products.
-// AC / BC: A is stored [K, M] / B is stored [K, N] (plain operands only).  A tile of it is staged as BK rows of columns, and its
+// AC / BC: A is stored [K, M] / B is stored [K, N] (with lo planes both or none).  A tile of it is staged as BK rows of columns, and its
 // fragments come from transposing LDS reads, which cost the same (within 5 % on products of 500×1536×1536 to 32768×4096×2048): a
 // pass that turned W, U or Y first, and its launch, are gone.  Gated feed-forward of 512 rows, k = 4096, f = 11008: the passes
 // moved 540 MB and took 156 of 360 µs.
@@ -253,7 +253,7 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     constexpr int PA = BM * CPR, PB = BN * CPR;            // plane sizes (uint4)
     constexpr int STAGE = NP * (PA + PB);
     static_assert((BM / RPI) % NW == 0 && (BN / RPI) % NW == 0, "tile/waves mismatch");
-    static_assert((!SWIGLU && !AC && !BC) || NP == 1, "swiglu epilogue and operands stored by columns only for plain operands");
+    static_assert(NP == 1 || (!SWIGLU && AC == BC), "forms of operands with lo planes");
 
     // two statically distinct stages: copies into one do not alias fragment reads from the other
     __shared__ __align__(16) uint4 stage0[STAGE];
@@ -381,13 +381,15 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
         for (int i = 0; i < TM; ++i) {
             if constexpr (AC) f.ah[i] = read_column_frag<BM>(st, a_col[i] + ks * 32 * BM);
             else f.ah[i] = as_bf16x8(st[rowA + i * 32 * CPR + kofs[ks]]);
-            if constexpr (NP == 2) f.al[i] = as_bf16x8(st[PA + rowA + i * 32 * CPR + kofs[ks]]);
+            if constexpr (NP == 2 && AC) f.al[i] = read_column_frag<BM>(st, a_col[i] + PA * 16 + ks * 32 * BM);
+            else if constexpr (NP == 2) f.al[i] = as_bf16x8(st[PA + rowA + i * 32 * CPR + kofs[ks]]);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             if constexpr (BC) f.bh[j] = read_column_frag<BN>(st, b_col[j] + ks * 32 * BN);
             else f.bh[j] = as_bf16x8(st[rowB + j * 32 * CPR + kofs[ks]]);
-            if constexpr (NP == 2) f.bl[j] = as_bf16x8(st[PB + rowB + j * 32 * CPR + kofs[ks]]);
+            if constexpr (NP == 2 && BC) f.bl[j] = read_column_frag<BN>(st, b_col[j] + PB * 16 + ks * 32 * BN);
+            else if constexpr (NP == 2) f.bl[j] = as_bf16x8(st[PB + rowB + j * 32 * CPR + kofs[ks]]);
         }
     };
     auto mfma_step = [&](const Frag& f) {
@@ -537,7 +539,8 @@ bool gemm_nt_mfma_ok(const GemmArgs& g) {
     if (g.symmetric && g.M != g.N) return false;
     if (g.CT32) return false;  // fp32 transposed output: only the SIMT kernel writes it
     if (g.a_cols && (!g.b_cols || g.swiglu || g.M % 8)) return false;
-    if (g.b_cols && (split || g.symmetric || g.b_lower || g.ksplit > 1 || g.N % 8)) return false;
+    if (g.b_cols && (g.b_lower || (split && !g.a_cols))) return false;
+    if (g.b_cols && g.N % 8 && (g.swiglu || (g.N + 7) / 8 * 8 > g.ldb)) return false;   // whole 16-byte pieces inside a row
     // copies address an operand as a base plus a 32-bit byte offset within the batch item (within 64 rows of one stored by columns)
     const int64_t reach_a = g.a_cols ? 64 * g.lda : (int64_t)g.M * g.lda;
     const int64_t reach_b = g.b_cols ? 64 * g.ldb : (int64_t)g.N * (g.swiglu ? 2 : 1) * g.ldb;
@@ -552,6 +555,7 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g) {
     const bool big = gemm_nt_mfma_big(g);
     if (g.A_lo) {
         // triangular apply: 256×128 tiles give two rounds of workgroups whose K extents pair up
+        if (g.a_cols) return big ? launch_async<256, 256, 128, 64, 2, false, true, true>(st, g) : launch_async<128, 128, 64, 64, 2, false, true, true>(st, g);
         if (big && g.b_lower && !g.symmetric && g.ksplit <= 1) return launch_async<256, 128, 64, 64, 2, false>(st, g);
         if (big) return launch_async<256, 256, 128, 64, 2, false>(st, g);
         return launch_async<128, 128, 64, 64, 2, false>(st, g);

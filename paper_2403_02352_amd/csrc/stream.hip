@@ -89,11 +89,19 @@ __global__ void zero_i32_kernel(int32_t* p, int64_t n) {
     if (i < n) p[i] = 0;
 }
 
-// Twin of the start block: transposed, padded with zeros and rounded to the storage type in one pass (and `zero` cleared), where
-// a transpose, a cast and a fill were three launches of about 5 µs each.
-template <typename T>
-__global__ void __launch_bounds__(256) start_block_kernel(const float* __restrict__ in, T* __restrict__ out, int rows, int cols,
-                                                          int rows_out, int cols_out, int32_t* __restrict__ zero, int n_zero) {
+// Start block in the form its product reads it, padded with zeros: rounded to bf16 as it lies, or turned (fp32 path), and `zero`
+// cleared in the same pass.
+__global__ void __launch_bounds__(256) start_block_bf16_kernel(const float* __restrict__ in, bf16_t* __restrict__ out, int rows, int cols,
+                                                               int cols_out, int64_t n_out, int32_t* __restrict__ zero, int n_zero) {
+    const int64_t first = (int64_t)blockIdx.x * 256 + threadIdx.x, step = (int64_t)gridDim.x * 256;
+    for (int64_t e = first; e < n_zero; e += step) zero[e] = 0;
+    for (int64_t e = first; e < n_out; e += step) {
+        const int64_t r = e / cols_out, c = e % cols_out;
+        out[e] = (r < rows && c < cols) ? f2bf(in[r * cols + c]) : (bf16_t)0;
+    }
+}
+__global__ void __launch_bounds__(256) start_block_f32_kernel(const float* __restrict__ in, float* __restrict__ out, int rows, int cols,
+                                                              int rows_out, int cols_out, int32_t* __restrict__ zero, int n_zero) {
     __shared__ float tile[TT][TT + 1];
     const int r0 = blockIdx.y * TT, c0 = blockIdx.x * TT, tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     if (blockIdx.y == 0)
@@ -102,27 +110,27 @@ __global__ void __launch_bounds__(256) start_block_kernel(const float* __restric
     __syncthreads();
     for (int i = ty; i < TT; i += 4) {
         const int c = c0 + i, r = r0 + tx;
-        if (c < cols_out && r < rows_out) {
-            if constexpr (sizeof(T) == 2) out[(int64_t)c * rows_out + r] = f2bf(tile[tx][i]);
-            else out[(int64_t)c * rows_out + r] = tile[tx][i];
-        }
+        if (c < cols_out && r < rows_out) out[(int64_t)c * rows_out + r] = tile[tx][i];
     }
 }
 
 template <typename T>
-__global__ void __launch_bounds__(256) pad_rows_kernel(const T* __restrict__ in, T* __restrict__ out, int cols, int ld_out) {
-    const int64_t i = blockIdx.x;
-    for (int j = threadIdx.x; j < ld_out; j += 256) out[i * ld_out + j] = j < cols ? in[i * cols + j] : (T)0;
+__global__ void __launch_bounds__(256) pad_matrix_kernel(const T* __restrict__ in, T* __restrict__ out, int rows, int cols, int64_t rows_out,
+                                                         int ld_out) {
+    const int64_t b = blockIdx.x / rows_out, i = blockIdx.x % rows_out;
+    const T* src = in + (b * rows + i) * cols;
+    T* dst = out + (int64_t)blockIdx.x * ld_out;
+    for (int j = threadIdx.x; j < ld_out; j += 256) dst[j] = (i < rows && j < cols) ? src[j] : (T)0;
 }
 
-struct ZeroColumns { void* m[3]; int64_t rows[3]; int elem_bytes[3]; };
-__global__ void __launch_bounds__(256) zero_columns_kernel(ZeroColumns a, int from, int ld) {
-    const int w = blockIdx.y, nc = ld - from;   // at most 63 columns: 4 rows per workgroup pass
-    for (int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); i < a.rows[w]; i += (int64_t)gridDim.x * 4) {
-        const int c = threadIdx.x & 63;
-        if (c >= nc) continue;
-        if (a.elem_bytes[w] == 2) reinterpret_cast<uint16_t*>(a.m[w])[i * ld + from + c] = 0;
-        else reinterpret_cast<uint32_t*>(a.m[w])[i * ld + from + c] = 0u;
+struct ZeroTails { ZeroTail t[8]; };
+__global__ void __launch_bounds__(256) zero_tails_kernel(ZeroTails a) {
+    const ZeroTail& z = a.t[blockIdx.y];
+    const int64_t nc = z.ld - z.from;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < z.rows * nc; i += (int64_t)gridDim.x * 256) {
+        const int64_t e = i / nc * z.ld + z.from + i % nc;
+        if (z.elem_bytes == 2) reinterpret_cast<uint16_t*>(z.m)[e] = 0;
+        else reinterpret_cast<uint32_t*>(z.m)[e] = 0u;
     }
 }
 
@@ -265,37 +273,42 @@ __global__ void __launch_bounds__(256) norm_basis_kernel(const T* __restrict__ P
 
 }  // namespace
 
-hipError_t start_block_twin(hipStream_t st, const float* in, void* out, int rows, int cols, int rows_out, int cols_out, int elem_bytes,
-                            int32_t* zero, int n_zero) {
+hipError_t start_block(hipStream_t st, const float* in, void* out, int rows, int cols, int rows_out, int cols_out, int elem_bytes,
+                       int32_t* zero, int n_zero) {
+    if (elem_bytes == 2) {
+        const int64_t n = (int64_t)rows_out * cols_out, blocks = (n + 1023) / 1024;
+        hipLaunchKernelGGL(start_block_bf16_kernel, dim3((unsigned)(blocks < 4096 ? blocks : 4096)), dim3(256), 0, st, in, (bf16_t*)out, rows, cols,
+                           cols_out, n, zero, n_zero);
+        return hipGetLastError();
+    }
     const dim3 grid((cols_out + TT - 1) / TT, (rows_out + TT - 1) / TT);
     if (grid.y > 65535) return hipErrorInvalidValue;
-    if (elem_bytes == 2)
-        hipLaunchKernelGGL(start_block_kernel<bf16_t>, grid, dim3(256), 0, st, in, (bf16_t*)out, rows, cols, rows_out, cols_out, zero, n_zero);
-    else
-        hipLaunchKernelGGL(start_block_kernel<float>, grid, dim3(256), 0, st, in, (float*)out, rows, cols, rows_out, cols_out, zero, n_zero);
+    hipLaunchKernelGGL(start_block_f32_kernel, grid, dim3(256), 0, st, in, (float*)out, rows, cols, rows_out, cols_out, zero, n_zero);
     return hipGetLastError();
 }
 
-hipError_t pad_rows(hipStream_t st, const void* in, void* out, int64_t rows, int cols, int ld_out, int elem_bytes) {
-    if (rows > 0x7fffffff) return hipErrorInvalidValue;
+hipError_t pad_matrix(hipStream_t st, const void* in, void* out, int rows, int cols, int64_t rows_out, int ld_out, int batch, int elem_bytes) {
+    if (batch * rows_out > 0x7fffffff) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(batch * rows_out));
     if (elem_bytes == 2)
-        hipLaunchKernelGGL(pad_rows_kernel<uint16_t>, dim3((unsigned)rows), dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, cols, ld_out);
+        hipLaunchKernelGGL(pad_matrix_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, rows, cols, rows_out, ld_out);
     else
-        hipLaunchKernelGGL(pad_rows_kernel<uint32_t>, dim3((unsigned)rows), dim3(256), 0, st, (const uint32_t*)in, (uint32_t*)out, cols, ld_out);
+        hipLaunchKernelGGL(pad_matrix_kernel<uint32_t>, grid, dim3(256), 0, st, (const uint32_t*)in, (uint32_t*)out, rows, cols, rows_out, ld_out);
     return hipGetLastError();
 }
 
-hipError_t zero_columns(hipStream_t st, void* const (&m)[3], const int64_t (&rows)[3], const int (&elem_bytes)[3], int from, int ld) {
-    if (from >= ld) return hipSuccess;
-    if (ld - from > 64) return hipErrorInvalidValue;
-    ZeroColumns a;
+hipError_t zero_tails(hipStream_t st, const ZeroTail (&z)[8]) {
+    ZeroTails a;
     int64_t most = 0;
-    for (int i = 0; i < 3; ++i) {
-        a.m[i] = m[i]; a.rows[i] = m[i] ? rows[i] : 0; a.elem_bytes[i] = elem_bytes[i];
-        most = a.rows[i] > most ? a.rows[i] : most;
-    }
-    const int64_t blocks = (most + 3) / 4;
-    hipLaunchKernelGGL(zero_columns_kernel, dim3((unsigned)(blocks < 1024 ? (blocks < 1 ? 1 : blocks) : 1024), 3), dim3(256), 0, st, a, from, ld);
+    int n = 0;
+    for (const ZeroTail& t : z)
+        if (t.m && t.rows > 0 && t.from < t.ld) {
+            a.t[n++] = t;
+            most = t.rows * (t.ld - t.from) > most ? t.rows * (t.ld - t.from) : most;
+        }
+    if (n == 0) return hipSuccess;
+    const int64_t blocks = (most + 255) / 256;
+    hipLaunchKernelGGL(zero_tails_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024), n), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
