@@ -924,6 +924,24 @@ atp_status atp_lowrank_linear(const void* B, const void* W, void* out, int64_t b
         f.M = (int)(batch * m); f.batch = 1; f.sA = 0; f.sC = 0;
         if (gemm_nt_mfma_ok(f)) g = f;
     }
+    // A long contraction with few tiles leaves compute units idle: split it along k, the fp32 partial products in the workspace (which
+    // W in [k, n] order comes with and no longer needs).  Up to 128 tiles of 128×128 there are two or more slices for every
+    // compute unit; a slice has to be worth the sum of the parts, 32 k-tiles of 64 (about 20 µs against 5).
+    // 512 × 4096 × 11008 (two slices): gate, up and down products together 266 -> 218 µs.
+    const int64_t tiles = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch, elems = (int64_t)g.batch * g.M * g.N;
+    if (g.b_cols && !swiglu && gemm_nt_mfma_ok(g) && tiles <= 128 && nout % 8 == 0) {
+        const int64_t fit = (int64_t)(need / 4) / elems;
+        const int parts = (int)std::min(std::min<int64_t>(256 / tiles, fit), std::min<int64_t>(g.K / 2048, KSPLIT_MAX));
+        if (parts >= 2) {
+            GemmArgs h = g;
+            h.C16 = nullptr; h.C32 = (float*)workspace;
+            h.ksplit = parts; h.sKsplit = elems;
+            ATP_HIP(nt_product(st, true, h));
+            ProfScope ps(st, ATP_K_STREAM, 0.0, (4.0 * parts + 2.0) * (double)elems);
+            ATP_HIP(sum_parts(st, (const float*)workspace, parts, (bf16_t*)out, elems));
+            return ATP_OK;
+        }
+    }
     ATP_HIP(nt_product(st, true, g));
     return ATP_OK;
 }

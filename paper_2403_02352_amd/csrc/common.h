@@ -165,6 +165,8 @@ hipError_t pad_matrix(hipStream_t st, const void* in, void* out, int rows, int c
 // elements from .. ld-1 of `rows` rows of 2-byte or 4-byte elements set to zero, for up to eight matrices (null: skipped)
 struct ZeroTail { void* m; int64_t rows, from, ld; int elem_bytes; };
 hipError_t zero_tails(hipStream_t st, const ZeroTail (&z)[8]);
+// out = sum of `parts` fp32 arrays of n elements (n a multiple of 8, 16-byte aligned), rounded to bf16
+hipError_t sum_parts(hipStream_t st, const float* in, int parts, bf16_t* out, int64_t n);
 // rotary position encoding of the rows of in [batch][L][dq] (heads of width dh, half-split pairs); in == out allowed
 hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L, int dq, int dh, float base, int pos0,
                      int elem_bytes);

@@ -210,6 +210,20 @@ __global__ void __launch_bounds__(256) rope_kernel(const T* in, T* out, int L, i
     }
 }
 
+// sum of the partial products of a product split along k
+__global__ void __launch_bounds__(256) sum_parts_kernel(const float* __restrict__ in, int parts, bf16_t* __restrict__ out, int64_t n) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8;
+    if (i >= n) return;
+    float s[8], x[8];
+    load_row<8>(in + i, s);
+    for (int p = 1; p < parts; ++p) {
+        load_row<8>(in + p * n + i, x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += x[e];
+    }
+    store_row<8>(out + i, s);
+}
+
 // Row-wise normalisation carried through a factored matrix H = P·C (one workgroup per row; HBM-bound, so 8 elements per access
 // where the row length is a multiple of 8).
 // Coefficient side: Cc[j][:] = C[j][:] - mean_j, Cn = Cc · diag(gain); without centring (Cc null) Cc is C itself.
@@ -364,6 +378,13 @@ hipError_t norm_basis(hipStream_t st, const void* P, const float* PM, void* Pn, 
     };
     if (elem_bytes == 2) go(m % 8 ? norm_basis_kernel<1, bf16_t> : norm_basis_kernel<8, bf16_t>, (bf16_t*)nullptr);
     else go(m % 8 ? norm_basis_kernel<1, float> : norm_basis_kernel<8, float>, (float*)nullptr);
+    return hipGetLastError();
+}
+
+hipError_t sum_parts(hipStream_t st, const float* in, int parts, bf16_t* out, int64_t n) {
+    const int64_t blocks = (n / 8 + 255) / 256;
+    if (n % 8 || blocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)blocks), dim3(256), 0, st, in, parts, out, n);
     return hipGetLastError();
 }
 

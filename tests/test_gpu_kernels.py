@@ -51,9 +51,9 @@ def test_strided_products(atp, dtype, layout, epilogue, case):
 
 
 # (batch, m, k, n): one shape per tile of the asynchronous kernel (128×64, 128×128, 256×256), one past and one short of the tiles,
-# columns a multiple of 8 and not, one k-tile, an odd and an even number of them
+# columns a multiple of 8 and not, one k-tile, an odd and an even number of them; contractions split along k
 ASYNC = [(1, 1, 64, 8), (1, 129, 128, 63), (3, 127, 192, 72), (1, 1100, 256, 1032), (2, 1025, 64, 1031), (1, 4097, 192, 3080),
-         (1, 4100, 128, 3101)]
+         (1, 4100, 128, 3101), (1, 40, 4160, 136), (2, 130, 6272, 264)]
 
 
 @pytest.mark.parametrize("layout", ["kn", "nk"])
