@@ -344,6 +344,21 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
     bf16_t* CT16 = p.CT16 ? p.CT16 + (int64_t)bz * p.sCT : nullptr;
     bf16_t* C16lo = p.C16lo ? p.C16lo + (int64_t)bz * p.sC : nullptr;
     bf16_t* CT16lo = p.CT16lo ? p.CT16lo + (int64_t)bz * p.sCT : nullptr;
+    // four consecutive rows of an accumulator are one 16-byte piece of a row of Cᵀ; single elements would touch a line each
+    const bool wideT = !SWIGLU && p.M % 4 == 0 && p.ldct % 4 == 0 && p.sCT % 4 == 0 && ((uintptr_t)p.CT32 & 15) == 0;
+    if (CT32 && wideT) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const int row = m0 + 32 * (wm * TM + i) + 8 * g + 4 * lh, col = n0 + 32 * (wn * TN + j) + l32;
+                    const f32x16& c = acc[0][i][j];
+                    if (row < p.M && col < p.N)
+                        *reinterpret_cast<f32x4*>(CT32 + (int64_t)col * p.ldct + row) = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+                }
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -359,7 +374,7 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
                     const bf16_t l = f2bf(o - bf2f(h));
                     if (C16) C16[(int64_t)row * p.ldc + col] = h;
                     if (C16lo) C16lo[(int64_t)row * p.ldc + col] = l;
-                    if (CT32) CT32[(int64_t)col * p.ldct + row] = o;
+                    if (CT32 && !wideT) CT32[(int64_t)col * p.ldct + row] = o;
                     if (CT16) CT16[(int64_t)col * p.ldct + row] = h;
                     if (CT16lo) CT16lo[(int64_t)col * p.ldct + row] = l;
                 }
