@@ -388,7 +388,7 @@ typedef enum {
     ATP_K_ATTENTION = 5,
     ATP_K_CHOLESKY = 6,         /* scaling + all block columns of one factorisation */
     ATP_K_STREAM = 7,           /* transposes, casts, fills, column sums, Alg.1     */
-    ATP_K_GEMM_SIMT = 8,        /* fp32-FMA GEMM (fp32 path, odd shapes)            */
+    ATP_K_GEMM_SIMT = 8,        /* strided GEMM (fp32 path, odd shapes)             */
     ATP_K_COUNT = 9
 } atp_kernel_class;
 

@@ -180,7 +180,7 @@ BasesWs carve_bases(void* ws, int64_t batch, int64_t L, int64_t d, int64_t r, at
     } while (0)
 
 // C = A · Bᵀ on the backend the storage type calls for: bf16 path -> MFMA kernel (operands bf16,
-// optionally hi+lo planes), fp32 path or shapes the MFMA kernel does not cover -> fp32 FMA kernel.
+// optionally hi+lo planes), fp32 path or shapes the asynchronous kernel does not cover -> strided kernel.
 hipError_t nt_product(hipStream_t st, bool mfma, const GemmArgs& g) {
     const bool split = g.A_lo != nullptr;
     const bool gram = g.symmetric != 0;   // the Gram matrix of the orthonormalisation, from one or both planes

@@ -124,7 +124,7 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g);
 bool gemm_nt_mfma_ok(const GemmArgs& g);
 bool gemm_nt_mfma_big(const GemmArgs& g);  // true when the 256×256 tile configuration is chosen
 
-// Generic SIMT fp32-FMA path with element strides (any layout, any size).  ta/tb give the
+// Strided path (any layout, any size).  ta/tb give the
 // element type of A/B; bf16 operands may carry a lo plane (same strides) that is added on load.
 struct SimtArgs {
     const void* A = nullptr;

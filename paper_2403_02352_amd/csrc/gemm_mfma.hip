@@ -1,4 +1,4 @@
-// bf16 MFMA GEMM for gfx950:  C = A · Bᵀ, both operands K-contiguous.
+// bf16 MFMA GEMM for gfx950:  C = A · Bᵀ, operands K-contiguous or stored by columns ([K, M], [K, N]).
 //
 // One kernel template carries every dense contraction of the ATP path that is not the fused
 // attention: the power-iteration products X·V and Xᵀ·U, the coefficient product B_r = U_rᵀ·X
@@ -16,6 +16,7 @@
 // Bank conflicts of the fragment reads (32 lanes = 32 consecutive rows) are avoided on the GLOBAL
 // side: position s of row r holds chunk s ^ swz(r).  Rows of one lane's fragments differ by
 // multiples of 32, so swz is a per-lane constant and each k-step needs one precomputed offset.
+// An operand stored by columns is staged as rows of BM (BN) columns and read by transposing LDS reads.
 //
 // Workgroup ids are remapped so that consecutive tiles share an XCD (its L2) and walk the output
 // in groups of 8 tile rows.
