@@ -9,9 +9,15 @@
 // transposed operand needs no pass of its own); LDS always holds rows of k, padded by 16 bytes, so a fragment read is
 // one conflict-free 16-byte access.
 //
+// Order of the sums.  The fp32 matrix instructions add their products one by one, k ascending, each with a single rounding (compared bit
+// by bit with a chain of fmaf, denormal results included).  On the fp32 path every output is therefore one chain over k = 0 .. K-1,
+// whatever the tile: the same bits as scalar fused multiply-adds in that order give.  The trailing columns of U_r
+// magnify the last bits of these products a few hundred times where the spectrum of X falls below its noise, up to two thousand: an
+// order that changes with the tile shows there as 1e-4.
+//
 // Tile choice.  The fp32 matrix cores do 256 flop per clock and compute unit, so what counts is that the 256 compute
-// units have work: 128×128 tiles when at least 192 of them exist, else 64×64, else 32×32 with four waves that share
-// the tile and split k (their sums meet in LDS at the end).
+// units have work: 128×128 tiles when at least 192 of them exist, else 64×64, else 32×32.  The four waves of a 32×32 tile take a
+// 16×16 quarter each (fp32), or share the tile and split k, their sums meeting in LDS at the end (bf16).
 // Measured on one MI355X against a scalar-FMA kernel with 64×64 tiles: four products (512×768)·(768×128) 151 -> 14 µs, their
 // Gram matrices (128×128, k = 512) 103 -> 10 µs, the block at that shape 5.08 -> 1.47 ms.
 #include "common.h"
@@ -45,7 +51,8 @@ template <> __device__ __forceinline__ float widen<float>(float x) { return x; }
 template <> __device__ __forceinline__ float widen<bf16_t>(bf16_t x) { return bf2f(x); }
 
 // ---- fp32 tiles: ROWS × BK floats in LDS, pitch BK + 4; a piece is four elements along the contiguous direction --
-template <typename T, int ROWS, int BK, int NT>
+// PERM: each group of eight k lies in LDS as 0 2 4 6 1 3 5 7, so that the four k of a lane half, every second one, are one 16-byte read
+template <typename T, int ROWS, int BK, int NT, bool PERM>
 struct LoadF32 {
     static constexpr int P = BK + 4, N = ROWS * BK / 4 / NT, WORDS = ROWS * P;
     static_assert(ROWS * BK % (4 * NT) == 0, "tile / threads mismatch");
@@ -107,7 +114,12 @@ struct LoadF32 {
             if (mode == 1) {
                 const int k = c / (ROWS / 4), rq = c % (ROWS / 4);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) lds[(4 * rq + e) * P + k] = v[i][e];
+                for (int e = 0; e < 4; ++e) lds[(4 * rq + e) * P + (PERM ? (k & ~7) + 4 * (k & 1) + ((k & 7) >> 1) : k)] = v[i][e];
+            } else if constexpr (PERM) {
+                const int q = c % (BK / 4);
+                float* d = lds + (c / (BK / 4)) * P + 8 * (q >> 1) + 2 * (q & 1);
+                *reinterpret_cast<f32x2*>(d) = f32x2{v[i][0], v[i][2]};
+                *reinterpret_cast<f32x2*>(d + 4) = f32x2{v[i][1], v[i][3]};
             } else {
                 *reinterpret_cast<f32x4*>(lds + (c / (BK / 4)) * P + 4 * (c % (BK / 4))) = v[i];
             }
@@ -199,14 +211,18 @@ struct LoadBF16 {
     }
 };
 
-// BM×BN block tile, waves of (32·TM)×(32·TN); KW waves share a wave tile and take every KW-th k-step.
+// BM×BN block tile, waves of (UT·TM)×(UT·TN), UT = 32 or 16 the matrix instruction's tile; KW waves share a wave tile and take every
+// KW-th k-step (bf16 only: on the fp32 path the order of a sum is fixed).
 // BF: operands stay bf16 (v_mfma_f32_32x32x16_bf16: exact products, fp32 accumulation), else everything is fp32.
-template <typename TA, typename TB, bool BF, int BM, int BN, int TM, int TN, int KW, int BK, bool SWIGLU>
-__global__ void __launch_bounds__((BM / (32 * TM)) * (BN / (32 * TN)) * KW * 64)
+template <typename TA, typename TB, bool BF, int BM, int BN, int UT, int TM, int TN, int KW, int BK, bool SWIGLU>
+__global__ void __launch_bounds__((BM / (UT * TM)) * (BN / (UT * TN)) * KW * 64)
 gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) {
-    constexpr int NWN = BN / (32 * TN), NWT = (BM / (32 * TM)) * NWN, NT = NWT * KW * 64;
-    using LA = std::conditional_t<BF, LoadBF16<BM, BK, NT>, LoadF32<TA, BM, BK, NT>>;
-    using LB = std::conditional_t<BF, LoadBF16<BN, BK, NT>, LoadF32<TB, BN, BK, NT>>;
+    static_assert((BF && UT == 32) || (!BF && KW == 1), "one chain over k on the fp32 path");
+    constexpr int NWN = BN / (UT * TN), NWT = (BM / (UT * TM)) * NWN, NT = NWT * KW * 64;
+    using LA = std::conditional_t<BF, LoadBF16<BM, BK, NT>, LoadF32<TA, BM, BK, NT, UT == 32>>;
+    using LB = std::conditional_t<BF, LoadBF16<BN, BK, NT>, LoadF32<TB, BN, BK, NT, UT == 32>>;
+    using Acc = std::conditional_t<UT == 32, f32x16, f32x4>;
+    constexpr int NV = UT == 32 ? 16 : 4;   // accumulator registers
     constexpr int NB2 = SWIGLU ? 2 : 1;
     constexpr int STAGE = LA::WORDS + NB2 * LB::WORDS;
     static_assert(KW == 1 || (KW - 1) * NWT * TM * TN * NB2 * 1024 <= 2 * STAGE, "the partial sums meet in the stages");
@@ -218,7 +234,7 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
     const int bz = id / (tilesM * tilesN), m0 = id / tilesN % tilesM * BM, n0 = id % tilesN * BN;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int kw = wave / NWT, wt = wave % NWT, wm = wt / NWN, wn = wt % NWN;
-    const int l32 = lane & 31, lh = lane >> 5;
+    const int l32 = lane & (UT - 1), lh = lane / UT;   // column of the accumulators, and which of their rows
     oa.p = reinterpret_cast<const TA*>(oa.p) + (int64_t)bz * p.sA;
     if (oa.lo) oa.lo = reinterpret_cast<const TA*>(oa.lo) + (int64_t)bz * p.sA;
     ob.p = reinterpret_cast<const TB*>(ob.p) + (int64_t)bz * p.sB;
@@ -226,7 +242,7 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
     Operand ob2 = ob;   // SWIGLU: the up rows, N rows further on
     if constexpr (SWIGLU) ob2.p = reinterpret_cast<const TB*>(ob.p) + (int64_t)p.N * ob.rs;
 
-    f32x16 acc[NB2][TM][TN];
+    Acc acc[NB2][TM][TN];
 #pragma unroll
     for (int h = 0; h < NB2; ++h)
 #pragma unroll
@@ -234,7 +250,7 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[h][i][j][v] = 0.f;
+                for (int v = 0; v < NV; ++v) acc[h][i][j][v] = 0.f;
 
     struct Regs { LA a; LB b, b2; };
     auto load = [&](Regs& r, int kt) {
@@ -269,11 +285,26 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
                         for (int i = 0; i < TM; ++i) acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b, acc[h][i][j], 0, 0, 0);
                     }
             }
+        } else if constexpr (UT == 16) {
+#pragma unroll 8
+            for (int k = 0; k < BK; k += 4) {   // lanes of quarter lh take k + lh; rows of 132 floats: the 64 lanes meet 64 banks
+                float a[TM];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) a[i] = sa[(16 * (wm * TM + i) + l32) * LA::P + k + lh];
+#pragma unroll
+                for (int h = 0; h < NB2; ++h)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const float b = sb[h * LB::WORDS + (16 * (wn * TN + j) + l32) * LB::P + k + lh];
+#pragma unroll
+                        for (int i = 0; i < TM; ++i) acc[h][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b, acc[h][i][j], 0, 0, 0);
+                    }
+            }
         } else {
 #pragma unroll
-            for (int s = 0; s < BK / 8 / KW; ++s) {
-                // lanes of half lh take k = +4·lh .. +3: one 16-byte read per operand feeds four MFMAs
-                const int k = 8 * (s * KW + kw) + 4 * lh;
+            for (int s = 0; s < BK / 8; ++s) {
+                // lanes of half lh take k = lh, 2 + lh, 4 + lh, 6 + lh: one 16-byte read per operand feeds four MFMAs
+                const int k = 8 * s + 4 * lh;
                 f32x4 a[TM];
 #pragma unroll
                 for (int i = 0; i < TM; ++i) a[i] = *reinterpret_cast<const f32x4*>(sa + (32 * (wm * TM + i) + l32) * LA::P + k);
@@ -352,9 +383,9 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int row = m0 + 32 * (wm * TM + i) + 8 * g + 4 * lh, col = n0 + 32 * (wn * TN + j) + l32;
-                    const f32x16& c = acc[0][i][j];
+                for (int g = 0; g < NV / 4; ++g) {
+                    const int row = m0 + UT * (wm * TM + i) + 8 * g + 4 * lh, col = n0 + UT * (wn * TN + j) + l32;
+                    const Acc& c = acc[0][i][j];
                     if (row < p.M && col < p.N)
                         *reinterpret_cast<f32x4*>(CT32 + (int64_t)col * p.ldct + row) = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
                 }
@@ -364,8 +395,8 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = m0 + 32 * (wm * TM + i) + 8 * (v >> 2) + 4 * lh + (v & 3), col = n0 + 32 * (wn * TN + j) + l32;
+            for (int v = 0; v < NV; ++v) {
+                const int row = m0 + UT * (wm * TM + i) + 8 * (v >> 2) + 4 * lh + (v & 3), col = n0 + UT * (wn * TN + j) + l32;
                 if (row < p.M && col < p.N) {
                     float o = acc[0][i][j][v];
                     if constexpr (SWIGLU) o = silu_f(o) * acc[NB2 - 1][i][j][v];
@@ -396,13 +427,13 @@ Operand operand(const void* ptr, const void* lo, int64_t rs, int64_t cs, int64_t
     return o;
 }
 
-template <typename TA, typename TB, bool BF, int BM, int BN, int TM, int TN, int KW, int BK, bool SWIGLU>
+template <typename TA, typename TB, bool BF, int BM, int BN, int UT, int TM, int TN, int KW, int BK, bool SWIGLU>
 hipError_t launch_tile(hipStream_t st, const SimtArgs& g, const Operand& oa, const Operand& ob) {
     const int tm = (g.M + BM - 1) / BM, tn = (g.N + BN - 1) / BN;
     const int64_t tiles = (int64_t)tm * tn * g.batch;
     if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-    constexpr int NT = (BM / (32 * TM)) * (BN / (32 * TN)) * KW * 64;
-    hipLaunchKernelGGL((gemm_strided_kernel<TA, TB, BF, BM, BN, TM, TN, KW, BK, SWIGLU>), dim3((unsigned)tiles), dim3(NT), 0, st, g, oa, ob, tm, tn);
+    constexpr int NT = (BM / (UT * TM)) * (BN / (UT * TN)) * KW * 64;
+    hipLaunchKernelGGL((gemm_strided_kernel<TA, TB, BF, BM, BN, UT, TM, TN, KW, BK, SWIGLU>), dim3((unsigned)tiles), dim3(NT), 0, st, g, oa, ob, tm, tn);
     return hipGetLastError();
 }
 
@@ -413,9 +444,9 @@ hipError_t launch_strided(hipStream_t st, const SimtArgs& g) {
     const Operand ob = operand(g.B, g.B_lo, g.b_rs, g.b_cs, g.sB, g.N, g.K, sizeof(TB), piece);
     const auto tiles = [&](int t) { return (int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t) * g.batch; };
     constexpr int BK = BF ? 64 : 32;
-    if (tiles(128) >= 192) return launch_tile<TA, TB, BF, 128, SWIGLU ? 64 : 128, 2, SWIGLU ? 1 : 2, 1, BK, SWIGLU>(st, g, oa, ob);
-    if (tiles(64) >= 192) return launch_tile<TA, TB, BF, 64, 64, 1, 1, 1, BK, SWIGLU>(st, g, oa, ob);
-    return launch_tile<TA, TB, BF, 32, 32, 1, 1, 4, 128, SWIGLU>(st, g, oa, ob);
+    if (tiles(128) >= 192) return launch_tile<TA, TB, BF, 128, SWIGLU ? 64 : 128, 32, 2, SWIGLU ? 1 : 2, 1, BK, SWIGLU>(st, g, oa, ob);
+    if (tiles(64) >= 192) return launch_tile<TA, TB, BF, 64, 64, 32, 1, 1, 1, BK, SWIGLU>(st, g, oa, ob);
+    return launch_tile<TA, TB, BF, 32, 32, BF ? 32 : 16, 1, 1, BF ? 4 : 1, 128, SWIGLU>(st, g, oa, ob);
 }
 
 }  // namespace

@@ -50,6 +50,33 @@ def test_strided_products(atp, dtype, layout, epilogue, case):
     assert rel_fro(to_host(out), ref) <= (F32_TOL if dtype == "f32" else BF16_TOL)
 
 
+def _fmaf():
+    import ctypes
+    f = ctypes.CDLL("libm.so.6").fmaf
+    f.restype, f.argtypes = ctypes.c_float, [ctypes.c_float] * 3
+    return f
+
+
+# (batch, m, k, n): the three tiles of the strided kernel (the first wherever fewer than 192 tiles of 64×64 exist), k around its k-tiles
+CHAINS = [(1, 33, 70, 35), (2, 64, 259, 40), (50, 70, 65, 66), (200, 20, 33, 30), (1, 1800, 36, 1796)]
+
+
+@pytest.mark.parametrize("layout", ["kn", "nk"])
+@pytest.mark.parametrize("case", CHAINS)
+def test_fp32_products_are_one_chain_over_k(atp, layout, case):
+    """Every output of the fp32 path is fmaf over k = 0 .. K-1, bit for bit, whichever tile is taken (60 entries of each case)."""
+    batch, m, k, n = case
+    A, W = (rnd(shape, s).astype(np.float32) for s, shape in ((1, (batch, m, k)), (2, (batch, k, n))))
+    Wd = W if layout == "kn" else np.ascontiguousarray(W.transpose(0, 2, 1))
+    out = atp.lowrank_linear(to_dev(A, "f32"), to_dev(Wd, "f32"), atp.ATP_W_KN if layout == "kn" else atp.ATP_W_NK).cpu().numpy()
+    fma, rng = _fmaf(), np.random.default_rng(3)
+    for b, i, j in zip(rng.integers(batch, size=60), rng.integers(m, size=60), rng.integers(n, size=60)):
+        acc = 0.0
+        for t in range(k):
+            acc = fma(float(A[b, i, t]), float(W[b, t, j]), acc)
+        assert np.float32(acc) == out[b, i, j]
+
+
 # (batch, m, k, n): one shape per tile of the asynchronous kernel (128×64, 128×128, 256×256), one past and one short of the tiles,
 # columns a multiple of 8 and not, one k-tile, an odd and an even number of them; contractions split along k
 ASYNC = [(1, 1, 64, 8), (1, 129, 128, 63), (3, 127, 192, 72), (1, 1100, 256, 1032), (2, 1025, 64, 1031), (1, 4097, 192, 3080),
