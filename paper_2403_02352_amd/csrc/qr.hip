@@ -103,8 +103,9 @@ __global__ void __launch_bounds__(256) prepare_kernel(const float* __restrict__ 
             f32x4 v;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                v[e] = s[q][e] * sc[0][li] * sc[1][(tid & 15) * 4 + e];
-                if (i == j + e) v[e] = (i < r_true ? v[e] : 1.f) + shift;
+                const float t = s[q][e] * sc[0][li], dj = sc[1][(tid & 15) * 4 + e];
+                v[e] = t * dj;
+                if (i == j + e) v[e] = i < r_true ? fmaf(t, dj, shift) : 1.f + shift;   // the diagonal rounds once
             }
             *reinterpret_cast<f32x4*>(S + base + (int64_t)i * r + j) = v;
         }
