@@ -80,7 +80,7 @@ __device__ __forceinline__ bf16x8 read_column_frag(const uint4* base, int ofs) {
 // MFMA path: operands are bf16.  A value that needs more than bf16 precision is held as a
 // hi + lo pair of bf16 planes (hi = bf16(x), lo = bf16(x - hi), ≈16 mantissa bits); when both
 // operands carry a lo plane the product is formed from three MFMA products (hi·hi, hi·lo,
-// lo·hi, ≈2^-17 relative error).
+// lo·hi, ≈2^-17 relative error), with lo_lo from four (all of the held values).
 // Any subset of the outputs may be requested (null = skip):
 //   C32 / C16 (+C16lo) : C[M,N] row-major (ldc);  CT32 / CT16 (+CT16lo) : Cᵀ[N,M] (ldct).
 // SWIGLU epilogue: B has 2·Nh rows (gate rows then up rows); the output has Nh
@@ -94,6 +94,7 @@ struct GemmArgs {
     int64_t lda = 0, ldb = 0, sA = 0, sB = 0;  // leading dims, batch strides (elements)
     int M = 0, N = 0, K = 0, batch = 1;
     int a_cols = 0, b_cols = 0;
+    int lo_lo = 0;
     float* C32 = nullptr;
     bf16_t* C16 = nullptr;
     bf16_t* C16lo = nullptr;

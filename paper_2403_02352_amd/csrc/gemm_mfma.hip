@@ -236,12 +236,12 @@ __device__ __forceinline__ int b_global_row(int b_row, int n0, int N, bool& ok) 
 }
 
 
-// NP = 1: plain bf16 operands, BK = 64.  NP = 2: hi+lo planes, BK = 32, three products.
+// NP = 1: plain bf16 operands, BK = 64.  NP = 2: hi+lo planes, BK = 32, three products (LL: four).
 // AC / BC: A is stored [K, M] / B is stored [K, N] (with lo planes both or none).  A tile of it is staged as BK rows of columns, and its
 // fragments come from transposing LDS reads, which cost the same (within 5 % on products of 500×1536×1536 to 32768×4096×2048): a
 // pass that turned W, U or Y first, and its launch, are gone.  Gated feed-forward of 512 rows, k = 4096, f = 11008: the passes
 // moved 540 MB and took 156 of 360 µs.
-template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC, bool BC>
+template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC, bool BC, bool LL>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     constexpr int BK = 64 / NP;
@@ -255,6 +255,7 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     constexpr int STAGE = NP * (PA + PB);
     static_assert((BM / RPI) % NW == 0 && (BN / RPI) % NW == 0, "tile/waves mismatch");
     static_assert(NP == 1 || (!SWIGLU && AC == BC), "forms of operands with lo planes");
+    static_assert(NP == 2 || !LL, "no lo planes");
 
     // two statically distinct stages: copies into one do not alias fragment reads from the other
     __shared__ __align__(16) uint4 stage0[STAGE];
@@ -398,6 +399,7 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
+                if constexpr (LL) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.al[i], f.bl[j], acc[i][j], 0, 0, 0);
                 if constexpr (NP == 2) {
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.al[i], f.bh[j], acc[i][j], 0, 0, 0);
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.ah[i], f.bl[j], acc[i][j], 0, 0, 0);
@@ -486,10 +488,10 @@ gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {
     }
 }
 
-template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC = false, bool BC = false>
+template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC = false, bool BC = false, bool LL = false>
 hipError_t launch_async(hipStream_t st, const GemmArgs& g) {
     constexpr int NT = (BM / WM) * (BN / WN) * 64;
-    auto kern = gemm_bf16_async_kernel<BM, BN, WM, WN, NP, SWIGLU, AC, BC>;
+    auto kern = gemm_bf16_async_kernel<BM, BN, WM, WN, NP, SWIGLU, AC, BC, LL>;
     const int tilesM = (g.M + BM - 1) / BM;
     const int tilesN = (g.N + (SWIGLU ? BN / 2 : BN) - 1) / (SWIGLU ? BN / 2 : BN);
     dim3 grid(tilesM * tilesN * g.batch, 1, g.ksplit > 1 ? g.ksplit : 1);
@@ -554,6 +556,10 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g) {
     if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;
     if (!gemm_nt_mfma_ok(g)) return hipErrorInvalidValue;
     const bool big = gemm_nt_mfma_big(g);
+    if (g.A_lo && g.lo_lo) {
+        if (g.a_cols) return big ? launch_async<256, 256, 128, 64, 2, false, true, true, true>(st, g) : launch_async<128, 128, 64, 64, 2, false, true, true, true>(st, g);
+        return big ? launch_async<256, 128, 64, 64, 2, false, false, false, true>(st, g) : launch_async<128, 128, 64, 64, 2, false, false, false, true>(st, g);
+    }
     if (g.A_lo) {
         // triangular apply: 256×128 tiles give two rounds of workgroups whose K extents pair up
         if (g.a_cols) return big ? launch_async<256, 256, 128, 64, 2, false, true, true>(st, g) : launch_async<128, 128, 64, 64, 2, false, true, true>(st, g);
