@@ -392,9 +392,11 @@ __global__ void __launch_bounds__(256, 1) attn_f32_kernel(AttnArgs a, int dh, in
                     for (int v = 0; v < 16; ++v) o[i][v] *= alpha;
                 m_run = m_new;
             }
+            // no finite score so far (this wave's keys may all be at -inf while another's are not): weights of zero, not -inf - -inf
+            const float m_ref = m_run == -INFINITY ? 0.f : m_run;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                s[v] = expf(s[v] - m_run);
+                s[v] = expf(s[v] - m_ref);
                 l_run += s[v];
             }
         }

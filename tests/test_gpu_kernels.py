@@ -192,6 +192,21 @@ def test_attention_f32(atp, case, variant):
     assert err <= F32_TOL
 
 
+# (batch, L, heads): keys dealt to four waves; 128 queries per workgroup
+@pytest.mark.parametrize("case", [(1, 40, 1), (4, 1000, 4)])
+@pytest.mark.parametrize("dead", [(32, 64), (0, 32), (0, 128), (96, 300)])
+def test_attention_f32_keys_at_minus_infinity(atp, case, dead):
+    """Keys whose score is -inf weigh nothing, whichever wave or tile they fill."""
+    batch, L, heads = case
+    Q, K, V = (rnd((batch, n, 64 * heads), 50 + i).astype(np.float32) for i, n in enumerate((L, 300, 300)))
+    Q = np.abs(Q) + np.float32(0.1)
+    K[:, dead[0]:dead[1]] = -np.inf
+    out = to_host(atp.attention(*(to_dev(x, "f32") for x in (Q, K, V)), heads))
+    live = np.r_[0:dead[0], dead[1]:300]
+    ref = np.stack([oracle.attention(Q[b], K[b][live], V[b][live], heads) for b in range(batch)])
+    assert rel_fro(out, ref) <= F32_TOL
+
+
 # r: one index, an odd one, one short of / at / past one block pair (64), block counts with padding blocks, several pairs
 @pytest.mark.parametrize("r", [1, 2, 33, 63, 64, 65, 96, 97, 128, 129, 200])
 def test_rayleigh_ritz_block_edges(atp, r):
