@@ -32,17 +32,18 @@ __device__ __forceinline__ void block_pair(int i, int k, int nb, int& first, int
 __device__ __forceinline__ int pair_index(int l, int first, int second) { return (l < JB ? first : second - 1) * JB + l; }
 
 // rotation that annihilates the entry pq of [[pp, pq], [pq, qq]]: J = [[c, s], [-s, c]] as s and u = s/(1 + c); identity when the
-// entry is zero (as it is for padding indices, whose rows and columns are zero) or has no reciprocal.
+// entry is zero (as it is for padding indices, whose rows and columns are zero).  The entry is divided by through its mantissa and
+// exponent, so every size that fp32 holds is rotated, denormal ones included: a plain hardware reciprocal ends below 2^-126 and above 2^126.
 // Hardware reciprocals and roots (1 unit in the last place): an angle that is off by 1e-7 leaves 1e-7 of the entry, and what keeps the
 // rotation orthogonal is u against s, where the same error counts s²/2 at most.  Every wave derives all 32 rotations of a step, so
 // these instructions count: 37.6 -> 32.7 µs per launch of jacobi_pair_kernel (34 steps on average) against correctly rounded divisions.
 __device__ __forceinline__ void jacobi_su(float app, float aqq, float apq, float& s, float& u) {
-    const float tau = 0.5f * (aqq - app) * __builtin_amdgcn_rcpf(apq);
+    const float tau = __builtin_ldexpf(0.5f * (aqq - app), -__builtin_amdgcn_frexp_expf(apq)) * __builtin_amdgcn_rcpf(__builtin_amdgcn_frexp_mantf(apq));
     const float t = __builtin_copysignf(__builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.f))), tau);
     const float c = __builtin_amdgcn_rsqf(fmaf(t, t, 1.f));
     s = t * c;
     u = s * __builtin_amdgcn_rcpf(1.f + c);
-    if (fabsf(apq) < 1e-37f) { s = 0.f; u = 0.f; }
+    if (apq == 0.f) { s = 0.f; u = 0.f; }
 }
 // (x, y) <- (c·x - s·y, s·x + c·y) with c = 1 - s·u never rounded to fp32: near convergence a rounded c is too large by up to
 // half a unit on average, which scaled the whole spectrum up by 6e-5 in ten sweeps at r = 512 (3e-6 this way)

@@ -331,3 +331,26 @@ def test_ragged_bases_are_orthonormal_to_fp32(atp, case, mode):
     dev = U.T @ U - np.eye(r)
     print(case, mode, abs(np.diag(dev).mean()), np.abs(dev).max(), flush=True)
     assert abs(np.diag(dev).mean()) <= 5e-7
+
+
+# eigenvalues of T at both ends of the fp32 range: 5e-35 (the entries that are still to be annihilated reach down to the smallest numbers
+# that fp32 holds) and 2e37
+@pytest.mark.parametrize("exponent", [-57, 62])
+@pytest.mark.parametrize("r", [40, 130])
+def test_rayleigh_ritz_at_the_ends_of_the_range(atp, r, exponent):
+    """B scaled by a power of two: the same singular values and vectors, to the tolerance of the unscaled ones."""
+    L, d = 210, 230
+    rng = np.random.default_rng(177 + r)
+    M = np.linalg.qr(rng.standard_normal((r, r)))[0]
+    U = (np.linalg.qr(rng.standard_normal((L, r)) + 0.2)[0] @ M).astype(np.float32)
+    B = (M.T @ (np.linspace(1.0, 0.5, r)[:, None] * np.linalg.qr(rng.standard_normal((d, r)))[0].T)).astype(np.float32)
+    scale = 2.0 ** exponent
+    Uo, Bo, sig, diag = atp.rayleigh_ritz(to_dev(U[None], "f32"), to_dev((B * scale)[None], "f32"), 10)
+    sr = np.linalg.svd(B.astype(np.float64))[1]
+    print(r, exponent, np.abs(sig[0].cpu().numpy() / scale - sr).max(), float(diag[0, 1]), flush=True)
+    assert np.abs(sig[0].cpu().numpy() / scale - sr).max() <= 5e-6
+    assert float(diag[0, 1]) <= 1e-5
+    Uo, Bo = to_host(Uo[0]), to_host(Bo[0]) / scale
+    assert rel_fro(Uo @ Bo, U.astype(np.float64) @ B) <= 2e-5
+    G = Bo @ Bo.T
+    assert np.linalg.norm(G - np.diag(np.diag(G))) <= 2e-5 * np.linalg.norm(G)
