@@ -8,7 +8,8 @@
 // takes the 64×64 diagonal sub-matrix of every block pair into LDS and annihilates each of its cross entries once, 32
 // steps of 32 disjoint rotations, keeping their product W; jacobi_apply_kernel carries the W of all pairs to T (W_P·T_PQ·W_Qᵀ) and
 // to the eigenvector rows (W_P·R_P) with fp32 MFMA.  The first round of a sweep also annihilates the entries inside the blocks, so a
-// sweep still visits every index pair exactly once.  r <= 64 is one pair and one launch.
+// sweep still visits every index pair exactly once.  r <= 64 is one launch, whose sweeps are r-1 steps of a round-robin over the indices
+// themselves: with the 63 steps of two blocks of 32, ten sweeps took 440 µs whatever r was, at r = 1 six times what a launch per step took.
 //
 // What bounds it: the chain of r-1 dependent steps per sweep, each at best an LDS round trip plus the rotation formula (about 0.5 µs).
 // A launch per step instead, with every step a pass over T and R, cost 7.4 µs per step: at r = 512, ten sweeps, 37.8 ms for the whole
@@ -52,12 +53,23 @@ __device__ __forceinline__ void rotate(float s, float u, float x, float y, float
     yr = fmaf(s, fmaf(-u, y, x), y);
 }
 
-// indices (p < q) of rotation i (0 .. 31) in step k: the 32 cross pairs of two blocks (32 steps), or 16 pairs inside each
-// block (31 steps of a round-robin over 32)
-template <bool CROSS>
-__device__ __forceinline__ void step_pair(int i, int k, int& p, int& q) {
-    if constexpr (CROSS) { p = i; q = JB + ((i + k) & (JB - 1)); }
-    else {
+// indices (p < q) of rotation i (0 .. 31) in step k: the 32 cross pairs of two blocks (32 steps), 16 pairs inside each
+// block (31 steps of a round-robin over 32), or m/2 pairs of the first m indices (m even, m-1 steps) and the padding in neighbours
+enum StepKind { STEP_CROSS, STEP_WITHIN, STEP_ROBIN };
+template <StepKind KIND>
+__device__ __forceinline__ void step_pair(int i, int k, int m, int& p, int& q) {
+    if constexpr (KIND == STEP_CROSS) { p = i; q = JB + ((i + k) & (JB - 1)); }
+    else if constexpr (KIND == STEP_ROBIN) {
+        int a = 2 * i, b = 2 * i + 1;
+        if (2 * i < m) {
+            a = m - 1; b = k;
+            if (i) {
+                a = k + i; if (a >= m - 1) a -= m - 1;
+                b = k - i; if (b < 0) b += m - 1;
+            }
+        }
+        p = min(a, b); q = max(a, b);
+    } else {
         int e = i & 15, a = JB - 1, b = k;
         if (e) {
             a = k + e; if (a >= JB - 1) a -= JB - 1;
@@ -69,18 +81,18 @@ __device__ __forceinline__ void step_pair(int i, int k, int& p, int& q) {
 
 // One step: A0 -> A1 = J·A0·Jᵀ (every thread two 2×2 blocks of the 32×32 grid of rotation pairs), W <- J·W in place.
 // Lane l of every wave derives rotation l % 32, so the step needs a single barrier.
-template <bool CROSS>
-__device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W, int k, int wave, int lane) {
+template <StepKind KIND>
+__device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W, int k, int m, int wave, int lane) {
     const int j = lane & 31;
     int pj, qj;
-    step_pair<CROSS>(j, k, pj, qj);
+    step_pair<KIND>(j, k, m, pj, qj);
     float sj, uj;
     jacobi_su(A0[pj * JP + pj], A0[qj * JP + qj], A0[pj * JP + qj], sj, uj);
     const auto lane_of = [](float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
 #pragma unroll
     for (int h = 0; h < 32; h += 16) {
         int pi, qi;
-        step_pair<CROSS>(2 * wave + (lane >> 5) + h, k, pi, qi);
+        step_pair<KIND>(2 * wave + (lane >> 5) + h, k, m, pi, qi);
         const float b00 = A0[pi * JP + pj], b01 = A0[pi * JP + qj], b10 = A0[qi * JP + pj], b11 = A0[qi * JP + qj];
         const float w00 = W[pi * JP + j], w01 = W[pi * JP + j + 32], w10 = W[qi * JP + j], w11 = W[qi * JP + j + 32];
         const float s0 = lane_of(sj, 2 * wave + h), s1 = lane_of(sj, 2 * wave + h + 1);
@@ -106,7 +118,8 @@ __device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W
 }
 
 // One workgroup per (block pair of round k, item): the rotations of the pair's 64×64 sub-matrix of T.  Their product goes to
-// Wout[item][pair][64][64].  With a single pair (nb == 2) all `sweeps` sweeps run here; T and the product (then all of R) are the results.
+// Wout[item][pair][64][64].  With a single pair (nb == 2) all `sweeps` sweeps run here, over the r indices; T and the product (then all of
+// R) are the results.
 __global__ void __launch_bounds__(512) jacobi_pair_kernel(float* __restrict__ T, float* __restrict__ Wout, int64_t w_stride, int w_rows,
                                                            int r, int nb, int k, int sweeps) {
     __shared__ float A[2][JW * JP];
@@ -122,10 +135,14 @@ __global__ void __launch_bounds__(512) jacobi_pair_kernel(float* __restrict__ T,
     }
     __syncthreads();
     int buf = 0;
-    for (int sw = 0; sw < sweeps; ++sw) {
+    if (nb == 2) {
+        const int m = r + (r & 1);
+        for (int sw = 0; sw < sweeps; ++sw)
+            for (int t = 0; t < m - 1; ++t, buf ^= 1) jacobi_step<STEP_ROBIN>(A[buf], A[buf ^ 1], W, t, m, wave, lane);
+    } else {
         if (k == 0)
-            for (int t = 0; t < JB - 1; ++t, buf ^= 1) jacobi_step<false>(A[buf], A[buf ^ 1], W, t, wave, lane);
-        for (int t = 0; t < JB; ++t, buf ^= 1) jacobi_step<true>(A[buf], A[buf ^ 1], W, t, wave, lane);
+            for (int t = 0; t < JB - 1; ++t, buf ^= 1) jacobi_step<STEP_WITHIN>(A[buf], A[buf ^ 1], W, t, 0, wave, lane);
+        for (int t = 0; t < JB; ++t, buf ^= 1) jacobi_step<STEP_CROSS>(A[buf], A[buf ^ 1], W, t, 0, wave, lane);
     }
     float* Wb = Wout + (int64_t)blockIdx.y * w_stride + (int64_t)blockIdx.x * JW * JW;
     for (int e = tid; e < JW * JW; e += 512) {
