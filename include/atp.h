@@ -197,8 +197,8 @@ atp_status atp_alternating_bases(const void* X, int64_t batch, int64_t L, int64_
  * atp_rayleigh_ritz — turns any orthonormal basis pair (U_r, B_r = U_rᵀX) of a subspace into the
  * singular basis of the rank-r approximation U_r·B_r, the X' = [σ_1 v_1 … σ_r v_r] of Eq.9, and
  * returns the diagnostics the paper derives from the singular values.
- *   T = B_r·B_rᵀ = R·Λ·Rᵀ (cyclic two-sided Jacobi, fp32, `sweeps` sweeps of r-1 rounds; 10 are
- *   enough for r ≤ 2048); columns of R ordered by descending eigenvalue;
+ *   T = B_r·B_rᵀ = R·Λ·Rᵀ (two-sided Jacobi, fp32, `sweeps` sweeps over all pairs of
+ *   indices; 10 are enough for r ≤ 2048); columns of R ordered by descending eigenvalue;
  *   U_out = U_r·R,  B_out = Rᵀ·B_r  (so U_out·B_out = U_r·B_r, rows of B_out mutually orthogonal);
  *   sigma_i = sqrt(λ_i) = ‖B_out[i, :]‖;
  *   sign: 1ᵀ·u_i ≥ 0 (the 1·U term of Eq.8); when |1ᵀ·u_i| is below the rounding level of the

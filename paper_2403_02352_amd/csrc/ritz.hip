@@ -7,13 +7,17 @@
 // Jacobi in blocks of 32 indices.  A round pairs the blocks (round-robin) and runs two launches: jacobi_pair_kernel
 // takes the 64×64 diagonal sub-matrix of every block pair into LDS and annihilates each of its cross entries once, 32
 // steps of 32 disjoint rotations, keeping their product W; jacobi_apply_kernel carries the W of all pairs to T (W_P·T_PQ·W_Qᵀ) and
-// to the eigenvector rows (W_P·R_P) with fp32 MFMA.  The first round of a sweep also annihilates the entries inside the blocks, so a
-// sweep still visits every index pair exactly once.  r <= 64 is one launch, whose sweeps are r-1 steps of a round-robin over the indices
+// to the eigenvector rows (W_P·R_P) with fp32 MFMA.  Every
+// second round (for r <= 128 each of the three) also annihilates the entries inside the blocks, and a rotation leaves the larger of its
+// two diagonal entries at the smaller index.  Without either, each entry once a sweep, a sweep got less far than one that goes index by
+// index: after ten, spectra 0.9^i and groups of eight at r = 300 were left with off-diagonal entries of 4e-6 to 1e-5 of the largest
+// eigenvalue (index by index 7e-8 to 4e-7, now 1e-8 or less).  It costs a quarter: r = 512, ten sweeps, 6.44 -> 8.33 ms.
+// r <= 64 is one launch, whose sweeps are r-1 steps of a round-robin over the indices
 // themselves: with the 63 steps of two blocks of 32, ten sweeps took 440 µs whatever r was, at r = 1 six times what a launch per step took.
 //
 // What bounds it: the chain of r-1 dependent steps per sweep, each at best an LDS round trip plus the rotation formula (about 0.5 µs).
 // A launch per step instead, with every step a pass over T and R, cost 7.4 µs per step: at r = 512, ten sweeps, 37.8 ms for the whole
-// call against 6.5 ms.
+// call against 8.3 ms.
 #include "common.h"
 
 namespace atp {
@@ -79,7 +83,9 @@ __device__ __forceinline__ void step_pair(int i, int k, int m, int& p, int& q) {
     }
 }
 
-// One step: A0 -> A1 = J·A0·Jᵀ (every thread two 2×2 blocks of the 32×32 grid of rotation pairs), W <- J·W in place.
+// One step: A0 -> A1 = J·A0·Jᵀ (every thread two 2×2 blocks of the 32×32 grid of rotation pairs), W <- J·W in place.  Between blocks, J with
+// its rows exchanged where that puts the larger diagonal entry first: what is written changes places, no arithmetic.  (A round-robin
+// over the indices themselves converges worse with exchanges.)
 // Lane l of every wave derives rotation l % 32, so the step needs a single barrier.
 template <StepKind KIND>
 __device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W, int k, int m, int wave, int lane) {
@@ -87,7 +93,12 @@ __device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W
     int pj, qj;
     step_pair<KIND>(j, k, m, pj, qj);
     float sj, uj;
-    jacobi_su(A0[pj * JP + pj], A0[qj * JP + qj], A0[pj * JP + qj], sj, uj);
+    const float app = A0[pj * JP + pj], aqq = A0[qj * JP + qj], apq = A0[pj * JP + qj];
+    jacobi_su(app, aqq, apq, sj, uj);
+    // (padding, whose entries are zero, stays last)
+    const uint64_t swaps = KIND == STEP_ROBIN ? 0 : __builtin_amdgcn_ballot_w64(apq != 0.f && aqq > app);
+    const bool swap_j = (swaps >> j) & 1;
+    const int tpj = swap_j ? qj : pj, tqj = swap_j ? pj : qj;
     const auto lane_of = [](float x, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
 #pragma unroll
     for (int h = 0; h < 32; h += 16) {
@@ -98,21 +109,23 @@ __device__ __forceinline__ void jacobi_step(const float* A0, float* A1, float* W
         const float s0 = lane_of(sj, 2 * wave + h), s1 = lane_of(sj, 2 * wave + h + 1);
         const float u0 = lane_of(uj, 2 * wave + h), u1 = lane_of(uj, 2 * wave + h + 1);
         const float si = lane < 32 ? s0 : s1, ui = lane < 32 ? u0 : u1;
+        const bool swap_i = (swaps >> (2 * wave + (lane >> 5) + h)) & 1;
+        const int tpi = swap_i ? qi : pi, tqi = swap_i ? pi : qi;
         float r00, r01, r10, r11, x, y;
         rotate(si, ui, b00, b10, r00, r10);
         rotate(si, ui, b01, b11, r01, r11);
         rotate(sj, uj, r00, r01, x, y);
-        A1[pi * JP + pj] = x;
-        A1[pi * JP + qj] = y;
+        A1[tpi * JP + tpj] = x;
+        A1[tpi * JP + tqj] = y;
         rotate(sj, uj, r10, r11, x, y);
-        A1[qi * JP + pj] = x;
-        A1[qi * JP + qj] = y;
+        A1[tqi * JP + tpj] = x;
+        A1[tqi * JP + tqj] = y;
         rotate(si, ui, w00, w10, x, y);
-        W[pi * JP + j] = x;
-        W[qi * JP + j] = y;
+        W[tpi * JP + j] = x;
+        W[tqi * JP + j] = y;
         rotate(si, ui, w01, w11, x, y);
-        W[pi * JP + j + 32] = x;
-        W[qi * JP + j + 32] = y;
+        W[tpi * JP + j + 32] = x;
+        W[tqi * JP + j + 32] = y;
     }
     __syncthreads();
 }
@@ -140,7 +153,7 @@ __global__ void __launch_bounds__(512) jacobi_pair_kernel(float* __restrict__ T,
         for (int sw = 0; sw < sweeps; ++sw)
             for (int t = 0; t < m - 1; ++t, buf ^= 1) jacobi_step<STEP_ROBIN>(A[buf], A[buf ^ 1], W, t, m, wave, lane);
     } else {
-        if (k == 0)
+        if (k % 2 == 0 || nb == 4)
             for (int t = 0; t < JB - 1; ++t, buf ^= 1) jacobi_step<STEP_WITHIN>(A[buf], A[buf ^ 1], W, t, 0, wave, lane);
         for (int t = 0; t < JB; ++t, buf ^= 1) jacobi_step<STEP_CROSS>(A[buf], A[buf ^ 1], W, t, 0, wave, lane);
     }

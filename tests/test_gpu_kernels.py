@@ -389,3 +389,22 @@ def test_rayleigh_ritz_small_r_sweeps_are_row_cyclic(atp, r):
     ref = _row_cyclic_off_diagonal(B.astype(np.float64) @ B.astype(np.float64).T, sweeps)
     print(r, off, ref, flush=True)
     assert abs(off - ref) <= 1e-2 * ref
+
+
+# three pairs of blocks, five, eight
+@pytest.mark.parametrize("spectrum", ["steep", "clustered"])
+@pytest.mark.parametrize("r", [130, 300, 500])
+def test_rayleigh_ritz_converges_in_ten_sweeps(atp, r, spectrum):
+    """Spectra whose eigenvalues of T fall below the rounding of the first (0.9^i) or stand in groups of eight.  What is left off the diagonal
+    after ten sweeps is rounding: 64 products of 2^-24 in each pass over a tile, a few passes since the last large rotation."""
+    rng = np.random.default_rng(377 + r)
+    i = np.arange(r)
+    s = 0.9 ** i if spectrum == "steep" else 1.0 - 0.1 * (i // 8) / (r // 8)
+    M = np.linalg.qr(rng.standard_normal((r, r)))[0]
+    U = (np.linalg.qr(rng.standard_normal((520, r)) + 0.2)[0] @ M).astype(np.float32)
+    B = (M.T @ (s[:, None] * np.linalg.qr(rng.standard_normal((530, r)))[0].T)).astype(np.float32)
+    Uo, Bo, sig, diag = atp.rayleigh_ritz(to_dev(U[None], "f32"), to_dev(B[None], "f32"), 10)
+    print(r, spectrum, float(diag[0, 1]), flush=True)
+    assert float(diag[0, 1]) <= 8 * 2.0 ** -24
+    G = to_host(Bo[0]) @ to_host(Bo[0]).T
+    assert np.linalg.norm(G - np.diag(np.diag(G))) <= 5e-6 * np.linalg.norm(G)
