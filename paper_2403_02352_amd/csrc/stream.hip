@@ -3,6 +3,7 @@
 // casts, fills and the counter-based Gaussian generator of the start block.
 #include "common.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace atp {
@@ -148,11 +149,21 @@ __global__ void __launch_bounds__(256) concat_kernel(ConcatArgs a) {
         for (int64_t j = lane; j < k.cols; j += 1 << tpr) dst[i * k.ld_out + j] = src[i * k.cols + j];
 }
 
-// N consecutive elements as floats, and back (N = 8: 16 bytes of bf16, 32 of fp32; rows start at multiples of 16 bytes then)
+// N consecutive elements as floats, and back (N = 8: 16 bytes of bf16, 32 of fp32; N = 4: 8 and 16; rows start at multiples of that)
 template <int N, typename T>
 __device__ __forceinline__ void load_row(const T* p, float (&x)[N]) {
     if constexpr (N == 1) {
         if constexpr (sizeof(T) == 2) x[0] = bf2f(*p); else x[0] = *p;
+    } else if constexpr (N == 4) {
+        if constexpr (sizeof(T) == 2) {
+            const uint2 u = *reinterpret_cast<const uint2*>(p);
+            x[0] = __uint_as_float(u.x << 16); x[1] = __uint_as_float(u.x & 0xffff0000u);
+            x[2] = __uint_as_float(u.y << 16); x[3] = __uint_as_float(u.y & 0xffff0000u);
+        } else {
+            const f32x4 a = *reinterpret_cast<const f32x4*>(p);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = a[e];
+        }
     } else if constexpr (sizeof(T) == 2) {
         const uint4 u = *reinterpret_cast<const uint4*>(p);
         const uint32_t w[4] = {u.x, u.y, u.z, u.w};
@@ -168,6 +179,9 @@ template <int N, typename T>
 __device__ __forceinline__ void store_row(T* p, const float (&x)[N]) {
     if constexpr (N == 1) {
         if constexpr (sizeof(T) == 2) *p = f2bf(x[0]); else *p = x[0];
+    } else if constexpr (N == 4) {
+        if constexpr (sizeof(T) == 2) *reinterpret_cast<uint2*>(p) = make_uint2(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]));
+        else *reinterpret_cast<f32x4*>(p) = f32x4{x[0], x[1], x[2], x[3]};
     } else if constexpr (sizeof(T) == 2) {
         *reinterpret_cast<uint4*>(p) = make_uint4(pack_bf2(x[0], x[1]), pack_bf2(x[2], x[3]), pack_bf2(x[4], x[5]), pack_bf2(x[6], x[7]));
     } else {
@@ -177,24 +191,27 @@ __device__ __forceinline__ void store_row(T* p, const float (&x)[N]) {
 }
 
 // Rotary position encoding, half-split pairing: within a head of width 2·half, coordinate j < half of row i is paired with
-// j + half and the pair is rotated by (pos0 + i)·base^(-2j/dh).  A workgroup takes `rows` rows and up to ROPE_J values of j: it
-// forms their sines and cosines once, in LDS, for all heads (formed per pair they took longer than the memory traffic), then
-// moves N elements per access.  2 × 2048 × 4096 bf16 (67 MB), 32 heads: the call took 12 µs less.  in == out allowed.
+// j + half and the pair is rotated by (pos0 + i)·base^(-2j/dh).  A workgroup takes `rows` rows, up to ROPE_J values of j and one of
+// `groups` groups of heads: it forms their sines and cosines once, in LDS, for all of its heads (formed per pair they took longer than
+// the memory traffic), then moves N elements per access.  2 × 2048 × 4096 bf16 (67 MB), 32 heads: the call took 12 µs less.
+// in == out allowed.
 constexpr int ROPE_J = 256;
 template <int N, typename T>
-__global__ void __launch_bounds__(256) rope_kernel(const T* in, T* out, int L, int dq, int half, int rows, float log2_base, int pos0) {
+__global__ void __launch_bounds__(256) rope_kernel(const T* in, T* out, int L, int dq, int half, int rows, int groups, float log2_base, int pos0) {
     __shared__ float sn[ROPE_J], cs[ROPE_J];   // rows·J values, J·rows <= ROPE_J
-    const int nj = (half + ROPE_J - 1) / ROPE_J;
-    const int row0 = (int)(blockIdx.x / nj) * rows, j0 = (int)(blockIdx.x % nj) * ROPE_J;
+    const int nj = (half + ROPE_J - 1) / ROPE_J, bx = (int)(blockIdx.x / groups), group = (int)(blockIdx.x % groups);
+    const int row0 = bx / nj * rows, j0 = bx % nj * ROPE_J;
     const int J = min(half - j0, ROPE_J), dh = 2 * half, n_rows = min(rows, L - row0);
     for (int e = threadIdx.x; e < n_rows * J; e += 256) {
         const float freq = exp2f(-2.0f * (float)(j0 + e % J) / (float)dh * log2_base);
         sincosf((float)(pos0 + row0 + e / J) * freq, &sn[e], &cs[e]);
     }
     __syncthreads();
-    const int per = J / N, heads = dq / dh;
-    for (int64_t e = threadIdx.x; e < (int64_t)n_rows * heads * per; e += 256) {
-        const int jc = (int)(e % per) * N, rest = (int)(e / per), h = rest % heads, r = rest / heads;
+    const unsigned per = J / N;
+    const int all = dq / dh, h0 = (int)((int64_t)group * all / groups), heads = (int)((int64_t)(group + 1) * all / groups) - h0;
+    const unsigned n = (unsigned)n_rows * heads * per;   // (the host keeps it below 2^31)
+    for (unsigned e = threadIdx.x; e < n; e += 256) {
+        const int rest = (int)(e / per), jc = (int)(e - (unsigned)rest * per) * N, r = rest / heads, h = h0 + rest - r * heads;
         const int64_t o = ((int64_t)blockIdx.y * L + row0 + r) * dq + (int64_t)h * dh + j0 + jc;
         float x[N], y[N];
         load_row<N>(in + o, x);
@@ -390,19 +407,25 @@ hipError_t sum_parts(hipStream_t st, const float* in, int parts, bf16_t* out, in
 
 hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L, int dq, int dh, float base, int pos0,
                      int elem_bytes) {
-    const int half = dh / 2, J = half < ROPE_J ? half : ROPE_J;
-    // several rows to a workgroup once one row each would give more than two workgroups per compute unit
-    const int rows = (int64_t)L * batch >= 2048 ? ROPE_J / J : 1;
-    const int64_t nx = (int64_t)((L + rows - 1) / rows) * ((half + ROPE_J - 1) / ROPE_J);
+    const int half = dh / 2, J = half < ROPE_J ? half : ROPE_J, heads = dq / dh;
+    // Two workgroups per compute unit (512) as far as the sizes go: more rows to a workgroup only while that many remain, and where rows
+    // are too few for them the heads are dealt out as well.  With as many rows as ROPE_J sines
+    // allow, 4 × 4096 rows of 128 heads of 8 in bf16 took 60 µs against 15 (single elements in both halves then, four at a time now),
+    // 2048 of them 42 against 9.
+    const int64_t target = 512, row_share = (int64_t)L * batch / target;
+    const int rows = (int)std::max<int64_t>(1, std::min<int64_t>(row_share, ROPE_J / J));
+    const int64_t nb = (int64_t)((L + rows - 1) / rows) * ((half + ROPE_J - 1) / ROPE_J);
+    const int groups = (int)std::max<int64_t>(1 + ((int64_t)rows * J * heads >> 30), std::min<int64_t>(target / (nb * batch), heads));
+    const int64_t nx = nb * groups;
     if (nx > 0x7fffffff || batch > 65535) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nx, batch);
     const float lb = log2f(base);
     const auto go = [&](auto kern, auto* t) {
         using T = std::remove_reference_t<decltype(*t)>;
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, (const T*)in, (T*)out, L, dq, half, rows, lb, pos0);
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, (const T*)in, (T*)out, L, dq, half, rows, groups, lb, pos0);
     };
-    if (elem_bytes == 2) go(half % 8 ? rope_kernel<1, bf16_t> : rope_kernel<8, bf16_t>, (bf16_t*)nullptr);
-    else go(half % 8 ? rope_kernel<1, float> : rope_kernel<8, float>, (float*)nullptr);
+    if (elem_bytes == 2) go(half % 4 ? rope_kernel<1, bf16_t> : half % 8 ? rope_kernel<4, bf16_t> : rope_kernel<8, bf16_t>, (bf16_t*)nullptr);
+    else go(half % 4 ? rope_kernel<1, float> : half % 8 ? rope_kernel<4, float> : rope_kernel<8, float>, (float*)nullptr);
     return hipGetLastError();
 }
 

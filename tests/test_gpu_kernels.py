@@ -149,10 +149,11 @@ def test_concatenated_blocks_and_norm(atp, dtype, case):
             assert rel_fro(to_host(Cn[b]), Cr) <= (1e-5 if dtype == "f32" else 2 * BF16_TOL)
 
 
-# (batch, L, heads, dh): several rows to a workgroup and one, a last workgroup with fewer, head halves of 1, 3, 8, 32, 256 and more
-# than the 256 of a workgroup.  fp32: angles up to 4096 rad carry 2^-24 of themselves, 2.5e-4 at most
+# (batch, L, heads, dh): several rows to a workgroup and one, a last workgroup with fewer, heads in one group, in groups of one and in uneven
+# groups, head halves of 1, 3, 8, 32, 256 and more than the 256 of a workgroup.  fp32: angles up to 4096 rad carry 2^-24 of themselves, 2.5e-4 at most
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("case", [(1, 1, 1, 2), (2, 5, 3, 6), (1, 4093, 2, 16), (3, 700, 3, 64), (1, 2050, 1, 512), (2, 9, 1, 1040)])
+@pytest.mark.parametrize("case", [(1, 1, 1, 2), (2, 5, 3, 6), (1, 4093, 2, 16), (3, 700, 3, 64), (1, 2050, 1, 512), (2, 9, 1, 1040),
+                                  (1, 1, 700, 8), (1, 60, 13, 128), (2, 130, 7, 6), (1, 1025, 5, 4)])
 def test_rope_rows(atp, dtype, case):
     batch, L, heads, dh = case
     Y = wl.round_to_dtype(rnd((batch, L, heads * dh), 30), dtype)
