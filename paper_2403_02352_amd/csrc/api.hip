@@ -188,8 +188,7 @@ hipError_t nt_product(hipStream_t st, bool mfma, const GemmArgs& g) {
     double flops = 2.0 * work * (g.swiglu ? 2.0 : 1.0);
     if (g.symmetric || g.b_lower) flops *= 0.5;  // algorithmic count: symmetric / triangular operand
     const double eb = mfma ? (split ? 4 : 2) : 4;
-    const double out_b = (g.C32 ? 4 : 0) + (g.C16 ? 2 : 0) + (g.C16lo ? 2 : 0) + (g.CT32 ? 4 : 0) + (g.CT16 ? 2 : 0) +
-                         (g.CT16lo ? 2 : 0);
+    const double out_b = (g.C32 ? 4 : 0) + (g.C16 ? 2 : 0) + (g.C16lo ? 2 : 0) + (g.CT32 ? 4 : 0) + (g.CT16 ? 2 : 0);
     const double bytes = (double)g.batch * g.M * g.K * eb +
                          (double)(g.sB ? g.batch : 1) * g.N * (g.swiglu ? 2 : 1) * g.K * eb +
                          (double)g.batch * g.M * g.N * out_b * (g.ksplit > 1 ? g.ksplit : 1);
@@ -209,7 +208,7 @@ hipError_t nt_product(hipStream_t st, bool mfma, const GemmArgs& g) {
     s.sA = g.sA; s.sB = g.sB;
     s.M = g.M; s.N = g.N; s.K = g.K; s.batch = g.batch;
     s.C32 = g.C32; s.C16 = g.C16; s.C16lo = g.C16lo; s.ldc = g.ldc; s.sC = g.sC;
-    s.CT32 = g.CT32; s.CT16 = g.CT16; s.CT16lo = g.CT16lo; s.ldct = g.ldct; s.sCT = g.sCT;
+    s.CT32 = g.CT32; s.CT16 = g.CT16; s.ldct = g.ldct; s.sCT = g.sCT;
     s.swiglu = g.swiglu;
     const OperandType t = mfma ? OP_BF16 : OP_F32;
     return gemm_simt(st, t, t, s);
@@ -250,7 +249,6 @@ GemmArgs slice_n(GemmArgs g, int off, int width) {
     if (g.C16lo) g.C16lo += off;
     if (g.CT32) g.CT32 += (int64_t)off * g.ldct;
     if (g.CT16) g.CT16 += (int64_t)off * g.ldct;
-    if (g.CT16lo) g.CT16lo += (int64_t)off * g.ldct;
     return g;
 }
 // Row block [off, off+width) of a product.
@@ -263,13 +261,12 @@ GemmArgs slice_m(GemmArgs g, int off, int width) {
     if (g.C16lo) g.C16lo += (int64_t)off * g.ldc;
     if (g.CT32) g.CT32 += off;
     if (g.CT16) g.CT16 += off;
-    if (g.CT16lo) g.CT16lo += off;
     return g;
 }
 
 // The product that consumes the orthonormalised matrix Q right after a round: Q's column block k
-// is the block k of its N dimension (FOLLOW_N: B operand = Qᵀ twin) or of its M dimension
-// (FOLLOW_M: A operand = Qᵀ twin).
+// is the block k of its N dimension (FOLLOW_N: Q is the B operand, stored by columns) or of its M dimension
+// (FOLLOW_M: the A operand is the transposed twin of Q).
 enum FollowSlice { FOLLOW_NONE = 0, FOLLOW_N = 1, FOLLOW_M = 2 };
 struct Follow {
     GemmArgs g;
@@ -519,7 +516,7 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
     // X with its rows (and columns of rows) filled up where that is needed, and the fp32 path's Xᵀ
     if (w.XT || w.Xp) {
         ProfScope ps(st, ATP_K_STREAM, 0.0, 2.0 * (double)batch * L * d * esize(t));
-        if (w.XT) ATP_HIP(transpose_batched(st, X, w.XT, iL, id, Lp, L * d, Lp * d, ib, es, Lp != L));
+        if (w.XT) ATP_HIP(transpose_batched(st, X, w.XT, iL, id, Lp, L * d, Lp * d, ib, es));
         if (w.Xp) ATP_HIP(pad_matrix(st, X, w.Xp, iL, id, mfma ? Lp : L, idp, ib, es));
     }
     const void* Xk = w.Xp ? w.Xp : X;
@@ -546,7 +543,7 @@ atp_status atp_principal_bases(const void* X, int64_t batch, int64_t L, int64_t 
                                 {w.ZD[0], 2 * nd, fD, eD, 2}, {w.ZD[1], 2 * nd, fD, eD, 2}, {w.TD, nd, fD, eD, 2}, {nullptr, 0, 0, 0, 2}}));
     } else {
         const int64_t n = batch * rp, nd = iters > 0 ? n : 0;
-        ATP_HIP(zero_tails(st, {{w.ZLT[0], n, L, Lp, 4}, {w.ZLT[1], n, L, Lp, 4}, {w.TL, n, L, Lp, 4}, {nullptr, 0, 0, 0, 4},
+        ATP_HIP(zero_tails(st, {{w.ZLT[0], n, L, Lp, 4}, {w.ZLT[1], n, L, Lp, 4}, {w.TL, n, L, Lp, 4}, {w.XT, batch * d, L, Lp, 4},
                                 {w.ZDT[0], nd, d, dp, 4}, {w.ZDT[1], nd, d, dp, 4}, {w.TD, nd, d, dp, 4}, {nullptr, 0, 0, 0, 4}}));
     }
     {
@@ -789,8 +786,8 @@ atp_status atp_project_onto_bases(const void* U_r, const void* Y, void* out, int
         void* UT = c.take((size_t)batch * r * L * 2);
         void* YT = c.take((size_t)batch * dq * L * 2);
         ProfScope ps(st, ATP_K_STREAM, 0.0, 4.0 * (double)batch * L * (r + dq));
-        ATP_HIP(transpose_batched(st, U_r, UT, (int)L, (int)r, L, L * r, r * L, (int)batch, 2, 0));
-        ATP_HIP(transpose_batched(st, Y, YT, (int)L, (int)dq, L, L * dq, dq * L, (int)batch, 2, 0));
+        ATP_HIP(transpose_batched(st, U_r, UT, (int)L, (int)r, L, L * r, r * L, (int)batch, 2));
+        ATP_HIP(transpose_batched(st, Y, YT, (int)L, (int)dq, L, L * dq, dq * L, (int)batch, 2));
         g.A = UT; g.B = YT; g.lda = L; g.ldb = L; g.a_cols = 0; g.b_cols = 0;
     }
     ATP_HIP(nt_product(st, true, g));
@@ -917,7 +914,7 @@ atp_status atp_lowrank_linear(const void* B, const void* W, void* out, int64_t b
         if (!gemm_nt_mfma_ok(g) && (nout % 8 || w_stride % 8)) {
             const int nb = w_stride ? (int)batch : 1;
             ProfScope ps(st, ATP_K_STREAM, 0.0, 4.0 * (double)nb * k * n);
-            ATP_HIP(transpose_batched(st, W, workspace, (int)k, (int)n, k, w_stride, k * n, nb, 2, 0));
+            ATP_HIP(transpose_batched(st, W, workspace, (int)k, (int)n, k, w_stride, k * n, nb, 2));
             g.B = workspace; g.b_cols = 0; g.ldb = k;
             g.sB = w_stride ? k * n : 0;
         }

@@ -82,7 +82,7 @@ __device__ __forceinline__ bf16x8 read_column_frag(const uint4* base, int ofs) {
 // operands carry a lo plane the product is formed from three MFMA products (hi·hi, hi·lo,
 // lo·hi, ≈2^-17 relative error), with lo_lo from four (all of the held values).
 // Any subset of the outputs may be requested (null = skip):
-//   C32 / C16 (+C16lo) : C[M,N] row-major (ldc);  CT32 / CT16 (+CT16lo) : Cᵀ[N,M] (ldct).
+//   C32 / C16 (+C16lo) : C[M,N] row-major (ldc);  CT32 / CT16 : Cᵀ[N,M] (ldct).
 // SWIGLU epilogue: B has 2·Nh rows (gate rows then up rows); the output has Nh
 // columns: SiLU(A·gateᵀ) ⊙ (A·upᵀ).  N below is Nh in that case.
 // ---------------------------------------------------------------------------
@@ -101,7 +101,6 @@ struct GemmArgs {
     int64_t ldc = 0, sC = 0;
     float* CT32 = nullptr;
     bf16_t* CT16 = nullptr;
-    bf16_t* CT16lo = nullptr;
     int64_t ldct = 0, sCT = 0;
     int swiglu = 0;
     // K range limit per output tile for triangular B (B[n][k] = 0 for k > n): 1 = on.  When B is a
@@ -125,7 +124,7 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g);
 bool gemm_nt_mfma_ok(const GemmArgs& g);
 bool gemm_nt_mfma_big(const GemmArgs& g);  // true when the 256×256 tile configuration is chosen
 
-// Strided path (any layout, any size).  ta/tb give the
+// Strided path (any layout, any size; the "simt" of the names is its first, scalar form: it runs on the matrix cores).  ta/tb give the
 // element type of A/B; bf16 operands may carry a lo plane (same strides) that is added on load.
 struct SimtArgs {
     const void* A = nullptr;
@@ -141,7 +140,6 @@ struct SimtArgs {
     int64_t ldc = 0, sC = 0;
     float* CT32 = nullptr;
     bf16_t* CT16 = nullptr;
-    bf16_t* CT16lo = nullptr;
     int64_t ldct = 0, sCT = 0;
     int swiglu = 0;
 };
@@ -152,8 +150,7 @@ hipError_t gemm_simt(hipStream_t st, OperandType ta, OperandType tb, const SimtA
 // ---------------------------------------------------------------------------
 // out[b][c][r] = in[b][r][c]   (rows×cols -> cols×rows), elem_bytes 2 or 4; out row length ld_out
 hipError_t transpose_batched(hipStream_t st, const void* in, void* out, int rows, int cols,
-                             int64_t ld_out, int64_t s_in, int64_t s_out, int batch, int elem_bytes,
-                             int zero_pad_cols);
+                             int64_t ld_out, int64_t s_in, int64_t s_out, int batch, int elem_bytes);
 // Omega generator: out[d*r] fp32 N(0,1), counter-based
 hipError_t fill_gaussian(hipStream_t st, float* out, int64_t n, uint64_t seed);
 hipError_t fill_zero_i32(hipStream_t st, int32_t* p, int64_t n);

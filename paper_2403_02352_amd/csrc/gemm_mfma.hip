@@ -48,7 +48,7 @@ constexpr int WBUF = 64 * WPITCH;     // elements per wave
 
 struct EpiPtrs {
     float* C32;
-    bf16_t *C16, *C16lo, *CT16, *CT16lo;
+    bf16_t *C16, *C16lo, *CT16;
     bool vecC, vecT;  // 16-byte stores allowed (leading dimensions and, for C, N multiples of 8, aligned bases)
 };
 
@@ -100,10 +100,7 @@ __device__ __forceinline__ void store_piece(const GemmArgs& p, const EpiPtrs& e,
             }
         }
     }
-#pragma unroll
-    for (int pl = 0; pl < 2; ++pl) {
-        bf16_t* dst = pl ? e.CT16lo : e.CT16;
-        if (!dst) continue;
+    if (bf16_t* dst = e.CT16) {
 #pragma unroll
         for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
@@ -112,11 +109,7 @@ __device__ __forceinline__ void store_piece(const GemmArgs& p, const EpiPtrs& e,
                 for (int vq = 0; vq < 4; ++vq) {
                     bf16_t h[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float a = acc[2 * IH + i2][2 * JH + j][4 * vq + q];
-                        h[q] = f2bf(a);
-                        if (pl) h[q] = f2bf(a - bf2f(h[q]));
-                    }
+                    for (int q = 0; q < 4; ++q) h[q] = f2bf(acc[2 * IH + i2][2 * JH + j][4 * vq + q]);
                     uint2 w;
                     w.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
                     w.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
@@ -158,11 +151,9 @@ __device__ __forceinline__ void store_outputs(const GemmArgs& p, const f32x16 (&
     e.C16 = p.C16 ? p.C16 + (int64_t)bz * p.sC : nullptr;
     e.C16lo = p.C16lo ? p.C16lo + (int64_t)bz * p.sC : nullptr;
     e.CT16 = p.CT16 ? p.CT16 + (int64_t)bz * p.sCT : nullptr;
-    e.CT16lo = p.CT16lo ? p.CT16lo + (int64_t)bz * p.sCT : nullptr;
     e.vecC = (p.N % 8 == 0) && (p.ldc % 8 == 0) && (p.sC % 8 == 0) &&
              ((((uintptr_t)p.C16) | ((uintptr_t)p.C16lo)) & 15) == 0;
-    e.vecT = (p.ldct % 8 == 0) && (p.sCT % 8 == 0) &&
-             ((((uintptr_t)p.CT16) | ((uintptr_t)p.CT16lo)) & 15) == 0;
+    e.vecT = (p.ldct % 8 == 0) && (p.sCT % 8 == 0) && ((uintptr_t)p.CT16 & 15) == 0;
     store_pieces<TM, TN>(std::make_integer_sequence<int, (TM / 2) * (TN / 2)>{}, p, e, acc, wbuf, row0, col0, lane);
 }
 
@@ -535,12 +526,13 @@ bool gemm_nt_mfma_big(const GemmArgs& g) {
 bool gemm_nt_mfma_ok(const GemmArgs& g) {
     const bool split = g.A_lo != nullptr || g.B_lo != nullptr;
     if (split && (!g.A_lo || !g.B_lo || g.swiglu)) return false;
+    if (split && !g.a_cols && (!g.b_lower || g.symmetric || g.ksplit > 1)) return false;   // with lo planes: Gram matrix by columns, or triangular apply
     const int bk = split ? 32 : 64;
     if (g.K < bk || g.K % bk || g.lda % 8 || g.ldb % 8 || g.sA % 8 || g.sB % 8) return false;
     if (((uintptr_t)g.A & 15) || ((uintptr_t)g.B & 15) || ((uintptr_t)g.A_lo & 15) || ((uintptr_t)g.B_lo & 15))
         return false;
     if (g.symmetric && g.M != g.N) return false;
-    if (g.CT32) return false;  // fp32 transposed output: only the SIMT kernel writes it
+    if (g.CT32) return false;  // fp32 transposed output: only the strided kernel writes it
     if (g.a_cols && (!g.b_cols || g.swiglu || g.M % 8)) return false;
     if (g.b_cols && (g.b_lower || (split && !g.a_cols))) return false;
     if (g.b_cols && g.N % 8 && (g.swiglu || (g.N + 7) / 8 * 8 > g.ldb)) return false;   // whole 16-byte pieces inside a row
@@ -563,9 +555,7 @@ hipError_t gemm_nt_mfma(hipStream_t st, const GemmArgs& g) {
     if (g.A_lo) {
         // triangular apply: 256×128 tiles give two rounds of workgroups whose K extents pair up
         if (g.a_cols) return big ? launch_async<256, 256, 128, 64, 2, false, true, true>(st, g) : launch_async<128, 128, 64, 64, 2, false, true, true>(st, g);
-        if (big && g.b_lower && !g.symmetric && g.ksplit <= 1) return launch_async<256, 128, 64, 64, 2, false>(st, g);
-        if (big) return launch_async<256, 256, 128, 64, 2, false>(st, g);
-        return launch_async<128, 128, 64, 64, 2, false>(st, g);
+        return big ? launch_async<256, 128, 64, 64, 2, false>(st, g) : launch_async<128, 128, 64, 64, 2, false>(st, g);
     }
     const bool small = !g.symmetric && g.ksplit <= 1 && plain_tile(g) == TILE_128x64;
     if (g.swiglu) {

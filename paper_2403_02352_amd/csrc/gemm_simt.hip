@@ -374,7 +374,6 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
     float* CT32 = p.CT32 ? p.CT32 + (int64_t)bz * p.sCT : nullptr;
     bf16_t* CT16 = p.CT16 ? p.CT16 + (int64_t)bz * p.sCT : nullptr;
     bf16_t* C16lo = p.C16lo ? p.C16lo + (int64_t)bz * p.sC : nullptr;
-    bf16_t* CT16lo = p.CT16lo ? p.CT16lo + (int64_t)bz * p.sCT : nullptr;
     // four consecutive rows of an accumulator are one 16-byte piece of a row of Cᵀ; single elements would touch a line each
     const bool wideT = !SWIGLU && p.M % 4 == 0 && p.ldct % 4 == 0 && p.sCT % 4 == 0 && ((uintptr_t)p.CT32 & 15) == 0;
     if (CT32 && wideT) {
@@ -407,7 +406,6 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
                     if (C16lo) C16lo[(int64_t)row * p.ldc + col] = l;
                     if (CT32 && !wideT) CT32[(int64_t)col * p.ldct + row] = o;
                     if (CT16) CT16[(int64_t)col * p.ldct + row] = h;
-                    if (CT16lo) CT16lo[(int64_t)col * p.ldct + row] = l;
                 }
             }
 }

@@ -1,6 +1,5 @@
-// HBM-bound streaming passes: batched transposes (operand twins for the
-// K-contiguous GEMM kernel, per-head value re-layout for the attention kernel),
-// casts, fills and the counter-based Gaussian generator of the start block.
+// HBM-bound streaming passes: batched transposes (the fp32 path's Xᵀ, bf16 operands whose rows start at no multiple of 16 bytes),
+// padding, fills, the start block and its counter-based Gaussian generator, concatenation and Norm of factored pairs, rotary encoding.
 #include "common.h"
 
 #include <algorithm>
@@ -11,12 +10,10 @@ namespace {
 
 constexpr int TT = 64;  // transpose tile
 
-// out[b][c][r] = in[b][r][c]; out rows have length ld_out (>= rows); when zero_pad is set the
-// columns rows..ld_out-1 of out are written with zeros.
+// out[b][c][r] = in[b][r][c]; out rows have length ld_out (>= rows), what lies past `rows` keeps its value.
 template <typename T>
 __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ in, T* __restrict__ out, int rows,
-                                                        int cols, int64_t ld_out, int64_t s_in, int64_t s_out,
-                                                        int zero_pad) {
+                                                        int cols, int64_t ld_out, int64_t s_in, int64_t s_out) {
     __shared__ T tile[TT][TT + 2];
     const int b = blockIdx.z;
     const T* src = in + (int64_t)b * s_in;
@@ -28,10 +25,9 @@ __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ in
         tile[i][tx] = (r < rows && c < cols) ? src[(int64_t)r * cols + c] : (T)0;
     }
     __syncthreads();
-    const int out_cols = zero_pad ? (int)ld_out : rows;
     for (int i = ty; i < TT; i += 4) {
         const int c = c0 + i, r = r0 + tx;
-        if (c < cols && r < out_cols) dst[(int64_t)c * ld_out + r] = tile[tx][i];
+        if (c < cols && r < rows) dst[(int64_t)c * ld_out + r] = tile[tx][i];
     }
 }
 
@@ -39,7 +35,7 @@ __global__ void __launch_bounds__(256) transpose_kernel(const T* __restrict__ in
 // 16-byte pieces (8 elements) on both sides, the 64×64 tile turns in LDS.
 __global__ void __launch_bounds__(256) transpose_u16x8_kernel(const uint16_t* __restrict__ in, uint16_t* __restrict__ out,
                                                               int rows, int cols, int64_t ld_out, int64_t s_in,
-                                                              int64_t s_out, int zero_pad) {
+                                                              int64_t s_out) {
     __shared__ __align__(16) uint16_t tile[TT][TT + 2];
     const int b = blockIdx.z;
     const uint16_t* src = in + (int64_t)b * s_in;
@@ -54,11 +50,10 @@ __global__ void __launch_bounds__(256) transpose_u16x8_kernel(const uint16_t* __
         d[0] = x.x; d[1] = x.y; d[2] = x.z; d[3] = x.w;
     }
     __syncthreads();
-    const int out_cols = zero_pad ? (int)ld_out : rows;
     for (int v = threadIdx.x; v < TT * 8; v += 256) {
         const int i = v >> 3, q = v & 7;
         const int c = c0 + i, r = r0 + 8 * q;
-        if (c < cols && r < out_cols) {
+        if (c < cols && r < rows) {
             uint4 x;
             x.x = (uint32_t)tile[8 * q + 0][i] | ((uint32_t)tile[8 * q + 1][i] << 16);
             x.y = (uint32_t)tile[8 * q + 2][i] | ((uint32_t)tile[8 * q + 3][i] << 16);
@@ -430,22 +425,21 @@ hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L
 }
 
 hipError_t transpose_batched(hipStream_t st, const void* in, void* out, int rows, int cols, int64_t ld_out,
-                             int64_t s_in, int64_t s_out, int batch, int elem_bytes, int zero_pad) {
+                             int64_t s_in, int64_t s_out, int batch, int elem_bytes) {
     if (rows <= 0 || cols <= 0 || batch <= 0) return hipSuccess;
-    const int span = zero_pad ? (int)ld_out : rows;
-    dim3 grid((cols + TT - 1) / TT, (span + TT - 1) / TT, batch);
+    dim3 grid((cols + TT - 1) / TT, (rows + TT - 1) / TT, batch);
     if (grid.y > 65535 || grid.z > 65535) return hipErrorInvalidValue;
     const bool vec8 = elem_bytes == 2 && rows % 8 == 0 && cols % 8 == 0 && ld_out % 8 == 0 && s_in % 8 == 0 &&
                       s_out % 8 == 0 && ((((uintptr_t)in) | ((uintptr_t)out)) & 15) == 0;
     if (vec8)
         hipLaunchKernelGGL(transpose_u16x8_kernel, grid, dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out, rows, cols,
-                           ld_out, s_in, s_out, zero_pad);
+                           ld_out, s_in, s_out);
     else if (elem_bytes == 2)
         hipLaunchKernelGGL(transpose_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)in, (uint16_t*)out,
-                           rows, cols, ld_out, s_in, s_out, zero_pad);
+                           rows, cols, ld_out, s_in, s_out);
     else
         hipLaunchKernelGGL(transpose_kernel<uint32_t>, grid, dim3(256), 0, st, (const uint32_t*)in, (uint32_t*)out,
-                           rows, cols, ld_out, s_in, s_out, zero_pad);
+                           rows, cols, ld_out, s_in, s_out);
     return hipGetLastError();
 }
 
