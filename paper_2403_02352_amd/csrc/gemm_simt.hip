@@ -18,8 +18,8 @@
 // Tile choice.  The fp32 matrix cores do 256 flop per clock and compute unit, so what counts is that the 256 compute
 // units have work: 128×128 tiles when at least 192 of them exist, else 64×64, else 32×32.  The four waves of a 32×32 tile take a
 // 16×16 quarter each (fp32), or share the tile and split k, their sums meeting in LDS at the end (bf16).
-// Measured on one MI355X against a scalar-FMA kernel with 64×64 tiles: four products (512×768)·(768×128) 151 -> 14 µs, their
-// Gram matrices (128×128, k = 512) 103 -> 10 µs, the block at that shape 5.08 -> 1.47 ms.
+// Measured on one MI355X against a scalar-FMA kernel with 64×64 tiles: four products (512×768)·(768×128) 151 -> 12 µs, the block at
+// that shape 5.07 -> 0.89 ms, 2096×968 with k = 8 (tiles that are all epilogue) 15.1 -> 14 µs.
 #include "common.h"
 
 #include <type_traits>
@@ -50,60 +50,74 @@ template <typename T> __device__ __forceinline__ float widen(T x);
 template <> __device__ __forceinline__ float widen<float>(float x) { return x; }
 template <> __device__ __forceinline__ float widen<bf16_t>(bf16_t x) { return bf2f(x); }
 
-// ---- fp32 tiles: ROWS × BK floats in LDS, pitch BK + 4; a piece is four elements along the contiguous direction --
+typedef f32x4 f32x4_4 __attribute__((aligned(4)));   // four floats at a multiple of four bytes: all that a 16-byte load needs
+
+// Pieces of a tile run along the contiguous direction of the operand (along k where there is none).  A thread's pieces lie at even
+// distances, so it keeps the address and the coordinates of its first one in tile 0; everything else is the same for all threads.
+// Registers: with addresses per piece and form of the operand, hoisted out of the k loop, and element loads under conditions of their
+// own, the kernels took 260 to 446, one workgroup on a compute unit that has LDS for two to four.  Now 115 to 255: four products
+// (512×768)·(768×768) 63 -> 41 µs, 2096×968 with k = 8 22.6 -> 14.
+template <typename T>
+struct First {
+    const T *p, *lo;
+    int row, k;
+};
+template <typename T>
+__device__ __forceinline__ First<T> first_piece(const Operand& o, int row, int k) {
+    const int64_t off = (int64_t)row * o.rs + (int64_t)k * o.cs;
+    const T* lo = reinterpret_cast<const T*>(o.lo);
+    return {reinterpret_cast<const T*>(o.p) + off, lo ? lo + off : nullptr, row, k};
+}
+
+// ---- fp32 tiles: ROWS × BK floats in LDS, pitch BK + 4; a piece is four elements --
 // PERM: each group of eight k lies in LDS as 0 2 4 6 1 3 5 7, so that the four k of a lane half, every second one, are one 16-byte read
 template <typename T, int ROWS, int BK, int NT, bool PERM>
 struct LoadF32 {
     static constexpr int P = BK + 4, N = ROWS * BK / 4 / NT, WORDS = ROWS * P;
-    static_assert(ROWS * BK % (4 * NT) == 0, "tile / threads mismatch");
+    static constexpr int CK = BK / 4, CR = ROWS / 4;   // pieces of a row of k, of a column of rows
+    static_assert(ROWS * BK % (4 * NT) == 0 && NT % CK == 0 && NT % CR == 0, "tile / threads mismatch");
     f32x4 v[N];
+    static __device__ __forceinline__ First<T> first(const Operand& o, int row0, int tid) {
+        return o.mode == 1 ? first_piece<T>(o, row0 + 4 * (tid % CR), tid / CR) : first_piece<T>(o, row0 + tid / CK, 4 * (tid % CK));
+    }
     static __device__ __forceinline__ f32x4 piece(const T* q) {
-        if constexpr (sizeof(T) == 4) return *reinterpret_cast<const f32x4*>(q);
+        if constexpr (sizeof(T) == 4) return *reinterpret_cast<const f32x4_4*>(q);
         else {
             const uint2 u = *reinterpret_cast<const uint2*>(q);
             return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
                          __uint_as_float(u.y & 0xffff0000u)};
         }
     }
-    __device__ __forceinline__ void load(const Operand& o, int row0, int k0, int tid) {
-        const T* hi = reinterpret_cast<const T*>(o.p);
-        const T* lo = reinterpret_cast<const T*>(o.lo);
-        // whole pieces: one past the end of K reads the last valid piece and becomes zero, rows past the end read a
-        // valid row and are never stored
-        if (o.mode == 0 && o.vec >= 4) {
+    __device__ __forceinline__ void load(const Operand& o, const First<T>& f, int row0, int kt) {
+        const bool by_row = o.mode == 1, wide = sizeof(T) == 4 ? o.mode != 2 : o.vec >= 4;
+        const int64_t tile = (int64_t)kt * BK * o.cs, step = by_row ? (NT / CR) * o.cs : (NT / CK) * o.rs, along = by_row ? o.rs : o.cs;
+        const int room = by_row ? o.rows - f.row : o.K - kt * BK - f.k;   // elements from here to the end along the piece
+        if (wide && row0 + ROWS <= o.rows && (kt + 1) * BK <= o.K) {   // a tile inside the matrix
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int c = i * NT + tid, row = c / (BK / 4), k = k0 + 4 * (c % (BK / 4));
-                const int64_t off = (int64_t)min(row0 + row, o.rows - 1) * o.rs + min(k, o.K - 4);
-                v[i] = piece(hi + off);
-                if (lo) v[i] += piece(lo + off);
-                if (k >= o.K) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        } else if (o.mode == 1 && o.vec >= 4) {
+            for (int i = 0; i < N; ++i) v[i] = piece(f.p + (tile + i * step));
+            if (f.lo)
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int c = i * NT + tid, k = k0 + c / (ROWS / 4), rq = c % (ROWS / 4);
-                const int64_t off = (int64_t)min(k, o.K - 1) * o.cs + min(row0 + 4 * rq, o.rows - 4);
-                v[i] = piece(hi + off);
-                if (lo) v[i] += piece(lo + off);
-                if (k >= o.K) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        } else {
+                for (int i = 0; i < N; ++i) v[i] += piece(f.lo + (tile + i * step));
+            return;
+        }
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int c = i * NT + tid;
+        for (int i = 0; i < N; ++i) {
+            v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (room <= 0 || (by_row ? f.k + kt * BK + i * (NT / CR) >= o.K : f.row + i * (NT / CK) >= o.rows)) continue;
+            const T* q = f.p + (tile + i * step);
+            const T* l = f.lo + (tile + i * step);
+            if (wide && room >= 4) {
+                v[i] = piece(q);
+                if (f.lo) v[i] += piece(l);
+            } else {   // element by element, those past the end from the last one's place and then zero
+                f32x4 x;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int row = row0 + (o.mode == 1 ? 4 * (c % (ROWS / 4)) + e : c / (BK / 4));
-                    const int k = k0 + (o.mode == 1 ? c / (ROWS / 4) : 4 * (c % (BK / 4)) + e);
-                    float x = 0.f;
-                    if (row < o.rows && k < o.K) {
-                        const int64_t off = (int64_t)row * o.rs + (int64_t)k * o.cs;
-                        x = widen<T>(hi[off]);
-                        if (lo) x += widen<T>(lo[off]);
-                    }
-                    v[i][e] = x;
-                }
+                for (int e = 0; e < 4; ++e) x[e] = widen<T>(q[min(e, room - 1) * along]);
+                if (f.lo)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] += widen<T>(l[min(e, room - 1) * along]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = e < room ? x[e] : 0.f;
             }
         }
     }
@@ -131,57 +145,42 @@ struct LoadF32 {
 template <int ROWS, int BK, int NT>
 struct LoadBF16 {
     static constexpr int P = BK + 8, N = ROWS * BK / 8 / NT, WORDS = ROWS * P / 2;
-    static_assert(ROWS * BK % (16 * NT) == 0, "tile / threads mismatch");
+    static constexpr int CK = BK / 8, CR = ROWS / 8;
+    static_assert(ROWS * BK % (16 * NT) == 0 && NT % CK == 0 && NT % CR == 0, "tile / threads mismatch");
     uint4 v[N];
-    __device__ __forceinline__ void load(const Operand& o, int row0, int k0, int tid) {
-        const bf16_t* hi = reinterpret_cast<const bf16_t*>(o.p);
-        const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
-        if (o.mode == 0 && o.vec >= 8) {
+    static __device__ __forceinline__ First<bf16_t> first(const Operand& o, int row0, int tid) {
+        return o.mode == 1 ? first_piece<bf16_t>(o, row0 + 8 * (tid % CR), 2 * (tid / CR)) : first_piece<bf16_t>(o, row0 + tid / CK, 8 * (tid % CK));
+    }
+    __device__ __forceinline__ void load(const Operand& o, const First<bf16_t>& f, int row0, int kt) {
+        const bool by_row = o.mode == 1;
+        const int64_t tile = (int64_t)kt * BK * o.cs, step = by_row ? 2 * (NT / CR) * o.cs : (NT / CK) * o.rs, along = by_row ? o.rs : o.cs;
+        const int room = by_row ? o.rows - f.row : o.K - kt * BK - f.k;
+        // pieces 2j and 2j + 1 of a by_row operand are two consecutive k
+        const auto at = [&](int i) { return f.p + (tile + (by_row ? (i / 2) * step + (i & 1) * o.cs : i * step)); };
+        if (o.vec >= 8 && row0 + ROWS <= o.rows && (kt + 1) * BK <= o.K) {   // a tile inside the matrix
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int c = i * NT + tid, row = c / (BK / 8), k = k0 + 8 * (c % (BK / 8));
-                v[i] = *reinterpret_cast<const uint4*>(hi + (int64_t)min(row0 + row, o.rows - 1) * o.rs + min(k, o.K - 8));
-                if (k >= o.K) v[i] = zero;
-            }
-        } else if (o.mode == 1 && o.vec >= 8) {
+            for (int i = 0; i < N; ++i) v[i] = *reinterpret_cast<const uint4*>(at(i));
+            return;
+        }
 #pragma unroll
-            for (int i = 0; i < N / 2; ++i) {
-                const int c = i * NT + tid, k = k0 + 2 * (c / (ROWS / 8)), rq = c % (ROWS / 8);
-                const bf16_t* q = hi + min(row0 + 8 * rq, o.rows - 8);
-                v[2 * i] = *reinterpret_cast<const uint4*>(q + (int64_t)min(k, o.K - 1) * o.cs);
-                v[2 * i + 1] = *reinterpret_cast<const uint4*>(q + (int64_t)min(k + 1, o.K - 1) * o.cs);
-                if (k >= o.K) v[2 * i] = zero;
-                if (k + 1 >= o.K) v[2 * i + 1] = zero;
-            }
-        } else if (o.mode == 0 && o.vec >= 2) {   // 4-byte loads; K is even, so a pair is inside or outside as a whole
-#pragma unroll
-            for (int i = 0; i < N; ++i) {
-                const int c = i * NT + tid, row = c / (BK / 8), k = k0 + 8 * (c % (BK / 8));
-                const bf16_t* q = hi + (int64_t)min(row0 + row, o.rows - 1) * o.rs;
+        for (int i = 0; i < N; ++i) {
+            v[i] = make_uint4(0u, 0u, 0u, 0u);
+            if (room <= 0 || (by_row ? f.k + kt * BK + 2 * (i / 2) * (NT / CR) + (i & 1) >= o.K : f.row + i * (NT / CK) >= o.rows)) continue;
+            const bf16_t* q = at(i);
+            if (o.vec >= 8) v[i] = *reinterpret_cast<const uint4*>(q);
+            else {   // two or one at a time, those past the end from the last one's place and then zero
                 uint32_t w[4];
+                if (o.vec >= 2) {   // 4-byte loads; K is even, so a pair is inside or outside as a whole
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (k + 2 * e < o.K) ? *reinterpret_cast<const uint32_t*>(q + k + 2 * e) : 0u;
-                v[i] = make_uint4(w[0], w[1], w[2], w[3]);
-            }
-        } else {
+                    for (int e = 0; e < 4; ++e) w[e] = *reinterpret_cast<const uint32_t*>(q + min(2 * e, room - 2));
 #pragma unroll
-            for (int i = 0; i < N; ++i) {
-                uint32_t w[4];
+                    for (int e = 0; e < 4; ++e) w[e] = 2 * e < room ? w[e] : 0u;
+                } else {
+                    uint32_t x[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    int row, k;
-                    if (o.mode == 1) {
-                        const int c = (i / 2) * NT + tid;
-                        row = row0 + 8 * (c % (ROWS / 8)) + e;
-                        k = k0 + 2 * (c / (ROWS / 8)) + (i & 1);
-                    } else {
-                        const int c = i * NT + tid;
-                        row = row0 + c / (BK / 8);
-                        k = k0 + 8 * (c % (BK / 8)) + e;
-                    }
-                    uint32_t x = 0u;
-                    if (row < o.rows && k < o.K) x = hi[(int64_t)row * o.rs + (int64_t)k * o.cs];
-                    if (e & 1) w[e / 2] |= x << 16; else w[e / 2] = x;
+                    for (int e = 0; e < 8; ++e) x[e] = q[min(e, room - 1) * along];
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) w[e / 2] = (e < room ? x[e] : 0u) | (e + 1 < room ? x[e + 1] << 16 : 0u);
                 }
                 v[i] = make_uint4(w[0], w[1], w[2], w[3]);
             }
@@ -215,7 +214,7 @@ struct LoadBF16 {
 // KW-th k-step (bf16 only: on the fp32 path the order of a sum is fixed).
 // BF: operands stay bf16 (v_mfma_f32_32x32x16_bf16: exact products, fp32 accumulation), else everything is fp32.
 template <typename TA, typename TB, bool BF, int BM, int BN, int UT, int TM, int TN, int KW, int BK, bool SWIGLU>
-__global__ void __launch_bounds__((BM / (UT * TM)) * (BN / (UT * TN)) * KW * 64)
+__global__ void __launch_bounds__((BM / (UT * TM)) * (BN / (UT * TN)) * KW * 64, 2)
 gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) {
     static_assert((BF && UT == 32) || (!BF && KW == 1), "one chain over k on the fp32 path");
     constexpr int NWN = BN / (UT * TN), NWT = (BM / (UT * TM)) * NWN, NT = NWT * KW * 64;
@@ -253,10 +252,13 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
                 for (int v = 0; v < NV; ++v) acc[h][i][j][v] = 0.f;
 
     struct Regs { LA a; LB b, b2; };
+    const auto fa = LA::first(oa, m0, tid);
+    const auto fb = LB::first(ob, n0, tid);
+    const auto fb2 = LB::first(ob2, n0, tid);
     auto load = [&](Regs& r, int kt) {
-        r.a.load(oa, m0, kt * BK, tid);
-        r.b.load(ob, n0, kt * BK, tid);
-        if constexpr (SWIGLU) r.b2.load(ob2, n0, kt * BK, tid);
+        r.a.load(oa, fa, m0, kt);
+        r.b.load(ob, fb, n0, kt);
+        if constexpr (SWIGLU) r.b2.load(ob2, fb2, n0, kt);
     };
     auto store = [&](const Regs& r, int buf) {
         r.a.store(lds + buf * STAGE, oa.mode, tid);
@@ -369,45 +371,52 @@ gemm_strided_kernel(SimtArgs p, Operand oa, Operand ob, int tilesM, int tilesN) 
         }
     }
 
-    float* C32 = p.C32 ? p.C32 + (int64_t)bz * p.sC : nullptr;
-    bf16_t* C16 = p.C16 ? p.C16 + (int64_t)bz * p.sC : nullptr;
-    float* CT32 = p.CT32 ? p.CT32 + (int64_t)bz * p.sCT : nullptr;
-    bf16_t* CT16 = p.CT16 ? p.CT16 + (int64_t)bz * p.sCT : nullptr;
-    bf16_t* C16lo = p.C16lo ? p.C16lo + (int64_t)bz * p.sC : nullptr;
-    // four consecutive rows of an accumulator are one 16-byte piece of a row of Cᵀ; single elements would touch a line each
-    const bool wideT = !SWIGLU && p.M % 4 == 0 && p.ldct % 4 == 0 && p.sCT % 4 == 0 && ((uintptr_t)p.CT32 & 15) == 0;
-    if (CT32 && wideT) {
+    if constexpr (SWIGLU) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int g = 0; g < NV / 4; ++g) {
-                    const int row = m0 + UT * (wm * TM + i) + 8 * g + 4 * lh, col = n0 + UT * (wn * TN + j) + l32;
-                    const Acc& c = acc[0][i][j];
-                    if (row < p.M && col < p.N)
-                        *reinterpret_cast<f32x4*>(CT32 + (int64_t)col * p.ldct + row) = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
-                }
+                for (int v = 0; v < NV; ++v) acc[0][i][j][v] = silu_f(acc[0][i][j][v]) * acc[NB2 - 1][i][j][v];
     }
+    // one output after the other, each with a pointer of its own that walks down the rows
+    const auto each = [&](int64_t row_step, int64_t col_step, auto put) {   // put(offset in the output, value)
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+            for (int j = 0; j < TN; ++j) {
+                const int row0 = m0 + UT * (wm * TM + i) + 4 * lh, col = n0 + UT * (wn * TN + j) + l32;
+                if (col >= p.N) continue;
+                int64_t at = (int64_t)row0 * row_step + (int64_t)col * col_step;
 #pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const int row = m0 + UT * (wm * TM + i) + 8 * (v >> 2) + 4 * lh + (v & 3), col = n0 + UT * (wn * TN + j) + l32;
-                if (row < p.M && col < p.N) {
-                    float o = acc[0][i][j][v];
-                    if constexpr (SWIGLU) o = silu_f(o) * acc[NB2 - 1][i][j][v];
-                    if (C32) C32[(int64_t)row * p.ldc + col] = o;
-                    const bf16_t h = f2bf(o);
-                    const bf16_t l = f2bf(o - bf2f(h));
-                    if (C16) C16[(int64_t)row * p.ldc + col] = h;
-                    if (C16lo) C16lo[(int64_t)row * p.ldc + col] = l;
-                    if (CT32 && !wideT) CT32[(int64_t)col * p.ldct + row] = o;
-                    if (CT16) CT16[(int64_t)col * p.ldct + row] = h;
-                }
+                for (int g = 0; g < NV / 4; ++g, at += 4 * row_step)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e, at += row_step)
+                        if (row0 + 8 * g + e < p.M) put(at, acc[0][i][j][4 * g + e]);
             }
+    };
+    if (p.C32) each(p.ldc, 1, [&, d = p.C32 + (int64_t)bz * p.sC](int64_t at, float x) { d[at] = x; });
+    if (p.C16) each(p.ldc, 1, [&, d = p.C16 + (int64_t)bz * p.sC](int64_t at, float x) { d[at] = f2bf(x); });
+    if (p.C16lo) each(p.ldc, 1, [&, d = p.C16lo + (int64_t)bz * p.sC](int64_t at, float x) { d[at] = f2bf(x - bf2f(f2bf(x))); });
+    if (p.CT16) each(1, p.ldct, [&, d = p.CT16 + (int64_t)bz * p.sCT](int64_t at, float x) { d[at] = f2bf(x); });
+    if (p.CT32) {
+        float* d = p.CT32 + (int64_t)bz * p.sCT;
+        // four consecutive rows of an accumulator are one 16-byte piece of a row of Cᵀ; single elements would touch a line each
+        if (p.M % 4 == 0 && p.ldct % 4 == 0 && p.sCT % 4 == 0 && ((uintptr_t)p.CT32 & 15) == 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int row0 = m0 + UT * (wm * TM + i) + 4 * lh, col = n0 + UT * (wn * TN + j) + l32;
+                    if (col >= p.N) continue;
+                    float* q = d + (int64_t)col * p.ldct + row0;
+                    const Acc& c = acc[0][i][j];
+#pragma unroll
+                    for (int g = 0; g < NV / 4; ++g)
+                        if (row0 + 8 * g < p.M) *reinterpret_cast<f32x4*>(q + 8 * g) = f32x4{c[4 * g], c[4 * g + 1], c[4 * g + 2], c[4 * g + 3]};
+                }
+        } else each(1, p.ldct, [&](int64_t at, float x) { d[at] = x; });
+    }
 }
 
 // how the loads of an operand may be widened: `piece` elements at once need 16-byte (8-byte when bf16 is widened to

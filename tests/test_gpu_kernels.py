@@ -58,7 +58,8 @@ def _fmaf():
 
 
 # (batch, m, k, n): the three tiles of the strided kernel (the first wherever fewer than 192 tiles of 64×64 exist), k around its k-tiles
-CHAINS = [(1, 33, 70, 35), (2, 64, 259, 40), (50, 70, 65, 66), (200, 20, 33, 30), (1, 1800, 36, 1796)]
+# (some tiles whole, rows of a multiple of 16 bytes and not)
+CHAINS = [(1, 33, 70, 35), (2, 64, 259, 40), (50, 70, 65, 66), (200, 20, 33, 30), (1, 1800, 36, 1796), (1, 1801, 37, 1795)]
 
 
 @pytest.mark.parametrize("layout", ["kn", "nk"])
