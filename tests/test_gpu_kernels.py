@@ -168,7 +168,10 @@ def test_rope_rows(atp, dtype, case):
 # 128-key stage; a single key and a single query
 F32_ATTENTION = [(1, 1, 1, 5, 1), (1, 33, 31, 64, 1), (2, 129, 33, 130, 2), (1, 127, 127, 128, 1), (1, 65, 129, 256, 2),
                  (1, 40, 300, 96, 1), (1, 130, 65, 200, 1), (1, 100, 257, 512, 2), (4, 500, 97, 640, 10), (3, 260, 129, 1408, 22),
-                 (2, 512, 96, 8192, 64)]
+                 (2, 512, 96, 8192, 64),
+                 # few keys of wide heads, a wave per query: one and the most it takes, one more, one query too many, a ragged width
+                 (1, 1, 1, 128, 1), (2, 33, 8, 256, 2), (1, 33, 9, 130, 1), (1, 50, 16, 410, 2), (1, 50, 17, 410, 2), (2, 65, 2, 768, 3), (1, 8192, 3, 200, 1),
+                 (1, 8193, 3, 200, 1)]
 
 
 @pytest.mark.parametrize("variant", ["softmax", "taylor", "rowsum"])
@@ -207,6 +210,16 @@ def test_attention_f32_keys_at_minus_infinity(atp, case, dead):
     live = np.r_[0:dead[0], dead[1]:300]
     ref = np.stack([oracle.attention(Q[b], K[b][live], V[b][live], heads) for b in range(batch)])
     assert rel_fro(out, ref) <= F32_TOL
+
+
+@pytest.mark.parametrize("dead", [0, 2, 4])
+def test_attention_f32_few_keys_at_minus_infinity(atp, dead):
+    Q, K, V = (rnd((1, n, 200), 60 + i).astype(np.float32) for i, n in enumerate((30, 5, 5)))
+    Q = np.abs(Q) + np.float32(0.1)
+    K[:, dead] = -np.inf
+    live = [j for j in range(5) if j != dead]
+    out = to_host(atp.attention(*(to_dev(x, "f32") for x in (Q, K, V)), 1))
+    assert rel_fro(out[0], oracle.attention(Q[0], K[0][live], V[0][live], 1)) <= F32_TOL
 
 
 # r: one index, an odd one, one short of / at / past one block pair (64), block counts with padding blocks, several pairs
