@@ -592,10 +592,15 @@ hipError_t attention_bf16(hipStream_t st, const AttnArgs& a) {
 hipError_t attention_f32(hipStream_t st, const AttnArgs& a) {
     const int dh = a.dq / a.heads;
     if (dh > 256 || a.heads > 65535 || a.batch > 65535) return hipErrorInvalidValue;
-    // few enough queries that their waves run at once (32 on each of 256 compute units), and few keys: see the kernel.  Measured against
-    // the tiles at 256 queries, head width 256, 3 heads: 1 key 11.7 µs against 24.3, 16 keys 21.4 against 24.7; 640 queries of width 128,
-    // 7 heads: 4 keys 11.2 against 12.9, 8 keys 11.8 against 13.0; 4 × 4096 queries of width 64, 8 heads, 1 key: 36 µs against 25.
-    if (dh > 64 && a.nk <= (dh > 128 ? 16 : 8) && (int64_t)a.L * a.heads * a.batch <= 8192) {
+    // A wave per query for a few keys (see the kernel), as far as it is ahead of the tiles.  Measured in µs, wave / tiles:
+    // width 256, 8192 queries: 1 key 11.6 / 25.8, 16 keys 25.5 / 25.9; 16384: 8 keys 26.6 / 27.3; 131072: 2 keys 112 / 150, 4 keys 182 / 137;
+    // width 128, 8192 queries: 8 keys 12.8 / 13.2, 12 keys 16 / 13.4; 16384: 2 keys 12.1 / 14.1, 4 keys 14.0 / 13.8; 131072: 1 key 48 / 53, 2 keys 67 / 54;
+    // width 64, 131072 queries: 1 key 34.5 / 25.3; width 30 (rows at no multiple of 16 bytes), 65536: 1 key 16.9 / 19.4, 2 keys 22 / 19.
+    const int64_t queries = (int64_t)a.L * a.heads * a.batch;
+    const bool few = dh > 128 ? a.nk <= 2 || (a.nk <= 16 && queries <= 16384 && queries * a.nk <= 131072)
+                   : dh > 64  ? a.nk == 1 || (a.nk <= 2 && queries <= 16384) || (a.nk <= 8 && queries <= 8192)
+                              : a.nk == 1 && dh % 4 != 0;
+    if (few) {
         const dim3 grid((a.L + 3) / 4, a.heads, a.batch);
         if (a.linearised) hipLaunchKernelGGL(attn_f32_few_keys_kernel<true>, grid, dim3(256), 0, st, a, dh);
         else hipLaunchKernelGGL(attn_f32_few_keys_kernel<false>, grid, dim3(256), 0, st, a, dh);

@@ -169,9 +169,9 @@ def test_rope_rows(atp, dtype, case):
 F32_ATTENTION = [(1, 1, 1, 5, 1), (1, 33, 31, 64, 1), (2, 129, 33, 130, 2), (1, 127, 127, 128, 1), (1, 65, 129, 256, 2),
                  (1, 40, 300, 96, 1), (1, 130, 65, 200, 1), (1, 100, 257, 512, 2), (4, 500, 97, 640, 10), (3, 260, 129, 1408, 22),
                  (2, 512, 96, 8192, 64),
-                 # few keys of wide heads, a wave per query: one and the most it takes, one more, one query too many, a ragged width
-                 (1, 1, 1, 128, 1), (2, 33, 8, 256, 2), (1, 33, 9, 130, 1), (1, 50, 16, 410, 2), (1, 50, 17, 410, 2), (2, 65, 2, 768, 3), (1, 8192, 3, 200, 1),
-                 (1, 8193, 3, 200, 1)]
+                 # few keys, a wave per query: one and the most it takes, one more, one query too many, ragged widths
+                 (1, 1, 1, 128, 1), (2, 33, 8, 256, 2), (1, 33, 9, 130, 1), (1, 50, 16, 410, 2), (1, 50, 17, 410, 2), (2, 65, 2, 768, 3), (1, 16384, 3, 200, 1),
+                 (1, 16385, 3, 200, 1), (1, 70, 1, 66, 2), (1, 70, 2, 66, 2)]
 
 
 @pytest.mark.parametrize("variant", ["softmax", "taylor", "rowsum"])
