@@ -192,11 +192,12 @@ __device__ __forceinline__ void store_row(T* p, const float (&x)[N]) {
 // in == out allowed.
 constexpr int ROPE_J = 256;
 template <int N, typename T>
-__global__ void __launch_bounds__(256) rope_kernel(const T* in, T* out, int L, int dq, int half, int rows, int groups, float log2_base, int pos0) {
+__global__ void __launch_bounds__(256) rope_kernel(const T* in, T* out, int L, int dq, int half, int j_step, int rows, int groups, float log2_base,
+                                                   int pos0) {
     __shared__ float sn[ROPE_J], cs[ROPE_J];   // rows·J values, J·rows <= ROPE_J
-    const int nj = (half + ROPE_J - 1) / ROPE_J, bx = (int)(blockIdx.x / groups), group = (int)(blockIdx.x % groups);
-    const int row0 = bx / nj * rows, j0 = bx % nj * ROPE_J;
-    const int J = min(half - j0, ROPE_J), dh = 2 * half, n_rows = min(rows, L - row0);
+    const int nj = (half + j_step - 1) / j_step, bx = (int)(blockIdx.x / groups), group = (int)(blockIdx.x % groups);
+    const int row0 = bx / nj * rows, j0 = bx % nj * j_step;
+    const int J = min(half - j0, j_step), dh = 2 * half, n_rows = min(rows, L - row0);
     for (int e = threadIdx.x; e < n_rows * J; e += 256) {
         const float freq = exp2f(-2.0f * (float)(j0 + e % J) / (float)dh * log2_base);
         sincosf((float)(pos0 + row0 + e / J) * freq, &sn[e], &cs[e]);
@@ -402,14 +403,15 @@ hipError_t sum_parts(hipStream_t st, const float* in, int parts, bf16_t* out, in
 
 hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L, int dq, int dh, float base, int pos0,
                      int elem_bytes) {
-    const int half = dh / 2, J = half < ROPE_J ? half : ROPE_J, heads = dq / dh;
+    const int half = dh / 2, nj = (half + ROPE_J - 1) / ROPE_J, heads = dq / dh;
+    const int J = nj == 1 ? half : ((half + nj - 1) / nj + 7) & ~7;   // even shares of wide heads, whole accesses
     // Two workgroups per compute unit (512) as far as the sizes go: more rows to a workgroup only while that many remain, and where rows
     // are too few for them the heads are dealt out as well.  With as many rows as ROPE_J sines
     // allow, 4 × 4096 rows of 128 heads of 8 in bf16 took 60 µs against 15 (single elements in both halves then, four at a time now),
     // 2048 of them 42 against 9.
     const int64_t target = 512, row_share = (int64_t)L * batch / target;
     const int rows = (int)std::max<int64_t>(1, std::min<int64_t>(row_share, ROPE_J / J));
-    const int64_t nb = (int64_t)((L + rows - 1) / rows) * ((half + ROPE_J - 1) / ROPE_J);
+    const int64_t nb = (int64_t)((L + rows - 1) / rows) * ((half + J - 1) / J);
     const int groups = (int)std::max<int64_t>(1 + ((int64_t)rows * J * heads >> 30), std::min<int64_t>(target / (nb * batch), heads));
     const int64_t nx = nb * groups;
     if (nx > 0x7fffffff || batch > 65535) return hipErrorInvalidValue;
@@ -417,7 +419,7 @@ hipError_t rope_rows(hipStream_t st, const void* in, void* out, int batch, int L
     const float lb = log2f(base);
     const auto go = [&](auto kern, auto* t) {
         using T = std::remove_reference_t<decltype(*t)>;
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, (const T*)in, (T*)out, L, dq, half, rows, groups, lb, pos0);
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, (const T*)in, (T*)out, L, dq, half, J, rows, groups, lb, pos0);
     };
     if (elem_bytes == 2) go(half % 4 ? rope_kernel<1, bf16_t> : half % 8 ? rope_kernel<4, bf16_t> : rope_kernel<8, bf16_t>, (bf16_t*)nullptr);
     else go(half % 4 ? rope_kernel<1, float> : half % 8 ? rope_kernel<4, float> : rope_kernel<8, float>, (float*)nullptr);
