@@ -815,8 +815,8 @@ atp_status atp_concat_factors(const void* U1, const void* C1, const void* U2, co
 
 size_t atp_norm_factored_workspace(int64_t batch, int64_t L, int64_t d, int64_t m, atp_dtype t) {
     if (batch < 1 || L < 1 || d < 1 || m < 1 || bad_dtype(t)) return 0;
-    return align_up((size_t)batch * m * d * esize(t)) + align_up((size_t)batch * m * m * 4) + align_up((size_t)batch * m * m * 2) +
-           align_up((size_t)batch * L * m * 4);
+    // centred coefficients (the query does not know `center`), M in the storage type, P·M in fp32
+    return align_up((size_t)batch * m * d * esize(t)) + align_up((size_t)batch * m * m * esize(t)) + align_up((size_t)batch * L * m * 4);
 }
 
 atp_status atp_norm_factored(const void* P, const void* C, const float* gain, float eps, int center, void* Pn, void* Cn,
@@ -835,8 +835,7 @@ atp_status atp_norm_factored(const void* P, const void* C, const float* gain, fl
     const int es = (int)esize(t);
     Carver c(workspace);
     void* Cc = c.take((size_t)batch * m * d * es);
-    float* M32 = (float*)c.take((size_t)batch * m * m * 4);
-    bf16_t* M16 = (bf16_t*)c.take((size_t)batch * m * m * 2);
+    void* M = c.take((size_t)batch * m * m * es);
     float* PM = (float*)c.take((size_t)batch * L * m * 4);
     {
         ProfScope ps(st, ATP_K_STREAM, 0.0, 3.0 * (double)batch * m * d * es);
@@ -846,14 +845,13 @@ atp_status atp_norm_factored(const void* P, const void* C, const float* gain, fl
         GemmArgs g;
         g.A = g.B = center ? Cc : C; g.lda = d; g.ldb = d; g.sA = m * d; g.sB = m * d;
         g.M = (int)m; g.N = (int)m; g.K = (int)d; g.batch = (int)batch;
-        if (mfma) g.C16 = M16; else g.C32 = M32;
+        if (mfma) g.C16 = (bf16_t*)M; else g.C32 = (float*)M;
         g.ldc = m; g.sC = m * m;
         ATP_HIP(nt_product(st, mfma, g));
     }
-    const void* Mop = mfma ? (const void*)M16 : M32;
     {   // PM = P·M (M is symmetric, so it is its own K-contiguous operand)
         GemmArgs g;
-        g.A = P; g.B = Mop; g.lda = m; g.ldb = m; g.sA = L * m; g.sB = m * m;
+        g.A = P; g.B = M; g.lda = m; g.ldb = m; g.sA = L * m; g.sB = m * m;
         g.M = (int)L; g.N = (int)m; g.K = (int)m; g.batch = (int)batch;
         g.C32 = PM; g.ldc = m; g.sC = L * m;
         ATP_HIP(nt_product(st, mfma, g));

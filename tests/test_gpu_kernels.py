@@ -79,9 +79,10 @@ def test_fp32_products_are_one_chain_over_k(atp, layout, case):
 
 
 # (batch, m, k, n): one shape per tile of the asynchronous kernel (128×64, 128×128, 256×256), one past and one short of the tiles,
-# columns a multiple of 8 and not, one k-tile, an odd and an even number of them; contractions split along k
+# columns a multiple of 8 and not, one k-tile, an odd and an even number of them; the middle tile with W as it lies; contractions split
+# along k
 ASYNC = [(1, 1, 64, 8), (1, 129, 128, 63), (3, 127, 192, 72), (1, 1100, 256, 1032), (2, 1025, 64, 1031), (1, 4097, 192, 3080),
-         (1, 4100, 128, 3101), (1, 40, 4160, 136), (2, 130, 6272, 264)]
+         (1, 4100, 128, 3101), (2, 1025, 64, 1032), (1, 40, 4160, 136), (2, 130, 6272, 264)]
 
 
 @pytest.mark.parametrize("layout", ["kn", "nk"])
@@ -101,9 +102,9 @@ def test_async_products(atp, layout, epilogue, case):
     assert rel_fro(to_host(out), ref) <= BF16_TOL
 
 
-# (batch, L, r, dq): both operands stored by columns in the asynchronous kernel (L a multiple of 64; its three tiles), in the strided
-# one, and turned first (columns no multiple of 8)
-PROJECTED = [(1, 64, 8, 64), (2, 192, 72, 264), (1, 128, 1032, 1096), (1, 64, 3080, 4104), (2, 100, 40, 136), (1, 256, 33, 130), (1, 77, 9, 70)]
+# (batch, L, r, dq): both operands stored by columns in the asynchronous kernel (L a multiple of 64; 128×64 tiles three times, 128×128,
+# 256×256), in the strided one, and turned first (columns no multiple of 8)
+PROJECTED = [(1, 64, 8, 64), (2, 192, 72, 264), (1, 128, 1032, 1096), (1, 64, 1544, 1800), (1, 64, 3080, 4104), (2, 100, 40, 136), (1, 256, 33, 130), (1, 77, 9, 70)]
 
 
 @pytest.mark.parametrize("case", PROJECTED)
@@ -423,3 +424,50 @@ def test_rayleigh_ritz_converges_in_ten_sweeps(atp, r, spectrum):
     assert float(diag[0, 1]) <= 8 * 2.0 ** -24
     G = to_host(Bo[0]) @ to_host(Bo[0]).T
     assert np.linalg.norm(G - np.diag(np.diag(G))) <= 5e-6 * np.linalg.norm(G)
+
+
+@pytest.mark.parametrize("level", [1, 2])
+@pytest.mark.parametrize("case", RAGGED_ORTH)
+def test_ragged_bases_with_single_conditioning_products(atp, case, level):
+    """The passes before the last from the hi planes alone: the last one still certifies U, and the basis captures X as the oracle's does."""
+    L, d, r, iters = case
+    X = wl.round_to_dtype(wl.make_X(L, d, np.sqrt(L * d / min(L, d)) * np.linspace(1.0, 0.5, min(L, d)), 0.0, 7), "bf16")
+    Om = wl.make_omega(d, r, 3)
+    atp.set_conditioning_gram(level)
+    try:
+        U, B, info, Um = atp.principal_bases(to_dev(X[None], "bf16"), r, iters, to_dev(Om, "f32"), want_master=True)
+        torch.cuda.synchronize()
+    finally:
+        atp.set_conditioning_gram(0)
+    assert (info == 0).all()
+    Ub, Bb, M = to_host(U[0]), to_host(B[0]), to_host(Um[0])
+    Uo, Bo = oracle.principal_bases(X, Om, iters)
+    assert abs(np.diag(M.T @ M - np.eye(r)).mean()) <= 5e-7 and np.abs(M.T @ M - np.eye(r)).max() <= 1e-4
+    assert rel_fro(Bb, Ub.T @ X) <= 2.0 ** -8
+    assert abs(np.linalg.norm(X - Ub @ Bb) - np.linalg.norm(X - Uo @ Bo)) / np.linalg.norm(X) <= 1e-2
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("call", ["bases", "norm", "linear", "ritz"])
+def test_calls_stay_within_the_queried_workspace(atp, dtype, call):
+    """Ragged extents, a workspace of exactly the queried size, and what lies behind it."""
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    code = atp.binding._dt(torch.empty(0, dtype=t))
+    X, P = to_dev(rnd((2, 131, 70), 1), dtype), to_dev(rnd((2, 131, 33), 2), dtype)
+    C = to_dev(rnd((2, 33, 70), 3), dtype)
+    W = to_dev(rnd((2, 70, 40), 4), dtype)
+    long_B, long_W = to_dev(rnd((1, 40, 4160), 5), dtype), to_dev(rnd((4160, 136), 6, 1 / 64), dtype)
+    lib = atp.binding.lib
+    runs = {"bases": [(atp.binding.principal_bases_workspace(2, 131, 70, 33, 1, t), lambda ws: atp.principal_bases(X, 33, 1, seed=1, workspace=ws)[:2])],
+            "norm": [(lib.atp_norm_factored_workspace(2, 131, 70, 33, code), lambda ws, c=c: atp.norm_factored(P, C, torch.ones(70, device="cuda"), 1e-6, c, workspace=ws))
+                     for c in (False, True)],
+            "linear": [(atp.lowrank_linear_workspace(2, 131, 70, 40, 2800, atp.ATP_W_KN, t), lambda ws: [atp.lowrank_linear(X, W, atp.ATP_W_KN, workspace=ws)]),
+                       (atp.lowrank_linear_workspace(1, 40, 4160, 136, 0, atp.ATP_W_KN, t), lambda ws: [atp.lowrank_linear(long_B, long_W, atp.ATP_W_KN, workspace=ws)])],
+            "ritz": [(atp.rayleigh_ritz_workspace(2, 131, 70, 33, t), lambda ws: atp.rayleigh_ritz(P, C, 2, workspace=ws)[:3])]}
+    for need, run in runs[call]:
+        buf = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        ref = run(None)
+        out = run(buf[:need] if need else None)
+        torch.cuda.synchronize()
+        assert (buf[need:] == 0xA5).all()
+        assert all(torch.equal(a, b) for a, b in zip(out, ref))
