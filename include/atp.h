@@ -20,7 +20,8 @@
  *    and are not thread-safe: call them from one thread, between calls.
  *  - `t` is the storage type of all matrix arguments of that call (ATP_F32 or
  *    ATP_BF16); accumulation is always fp32.  Inputs are never modified,
- *    outputs are fully overwritten.
+ *    outputs are fully overwritten: an output must not overlap an input or
+ *    the workspace, except where a call says so (atp_rope).
  *  - All work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL =
  *    the null stream) and the call returns without synchronising.
  *  - The return value reports host-side argument checks and launch errors
@@ -236,8 +237,8 @@ atp_status atp_rayleigh_ritz(const void* U_r, const void* B_r, int64_t batch, in
  *                 [batch, m, n/2] for ATP_EPI_SWIGLU (gate columns first, then
  *                 up columns, in W: the gated feed-forward applied to the bases)
  *  workspace      device; needed only for (ATP_BF16, ATP_W_KN): the call
- *                 may transpose W there first.  May be NULL when the query
- *                 returns 0.
+ *                 may transpose W there first, or keep fp32 partial sums
+ *                 there.  May be NULL when the query returns 0.
  *
  * Errors: ATP_ERR_INVALID_ARG (null pointer, size < 1, n odd with SWIGLU, bad
  * enum, misaligned pointer), ATP_ERR_WORKSPACE, ATP_ERR_DEVICE.

@@ -925,8 +925,9 @@ atp_status atp_lowrank_linear(const void* B, const void* W, void* out, int64_t b
         if (gemm_nt_mfma_ok(f)) g = f;
     }
     // A long contraction with few tiles leaves compute units idle: split it along k, the fp32 partial products in the workspace (which
-    // W in [k, n] order comes with and no longer needs).  Up to 128 tiles of 128×128 there are two or more slices for every
-    // compute unit; a slice has to be worth the sum of the parts, 32 k-tiles of 64 (about 20 µs against 5).
+    // W in [k, n] order comes with and no longer needs; weights in [n, k] order come without one and stay unsplit).  Up to 128 tiles of 128×128
+    // a tile can be cut into two or more slices, about one workgroup for every compute unit; a slice has to be worth the sum of the
+    // parts, 32 k-tiles of 64 (about 20 µs against 5).
     // 512 × 4096 × 11008 (two slices): gate, up and down products together 266 -> 218 µs.
     const int64_t tiles = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128) * g.batch, elems = (int64_t)g.batch * g.M * g.N;
     if (g.b_cols && !swiglu && gemm_nt_mfma_ok(g) && tiles <= 128 && nout % 8 == 0) {
