@@ -22,7 +22,6 @@
 // in groups of 8 tile rows.
 #include "common.h"
 
-#include <algorithm>
 #include <utility>
 
 namespace atp {
@@ -496,21 +495,20 @@ hipError_t launch_async(hipStream_t st, const GemmArgs& g) {
 namespace {
 
 // Tile of a plain product.  A CU holds one workgroup of 256×256, two of 128×128 or three of 128×64, so the chip holds 256, 512
-// or 768.  Cost of a round of workgroups per 64-deep k-tile, measured in µs on products from 500×1536×1536 to 4096×2048×32768
-// (epilogues included): 256×256 1.65 whether or not the round is full, 128×128 1.0 for two on a CU and 0.61 for one alone; rounds of
-// 128×128 overlap, so their number is no whole number, with 0.2 for the uneven end.
-// 256×256 is ahead from about 190 of its tiles: 4096×4096×4096 (256 tiles) 109 µs against 133 with 128×128; behind below:
-// 4096×2048×32768 (128 tiles) 752 against 511, 512×4096×11008 (32) 200 against 105.  128×64 is ahead while 128×128 leaves every
-// second CU idle (96 against 105 µs there, 500×1536×1536 12.8 against 14.4) and behind once it does not (2048×2048×4096,
-// 256 tiles of 128×128: 50 against 44).
+// or 768.  256×256 costs the same for a round of workgroups whether or not the round is full, so it wants the last round more than
+// half full; from the fourth round on the last one does not matter.  Measured on 320 products (256 to 6144 rows, 1024 to 11008
+// columns, k = 1024 and 4096, plain and gated, both forms of W), time with 128×128 over time with 256×256 at k = 4096:
+//   first round   32 tiles of 256×256 0.50, 64 0.54, 96 0.65, 128 0.75, 129 1.31 to 1.42 (516 of 128×128: a second round of four), 160 to 192 1.02 to 1.10, 256 1.14
+//   second        258 0.84, 320 0.85, 344 0.90 to 0.95, 384 0.91 to 0.96, 512 1.11 to 1.14
+//   third         516 0.90 to 0.94, 640 0.99 to 1.01, 688 1.08 to 1.12, 768 1.14       later   860 1.05, 1032 1.03, 1376 to 2064 1.10 to 1.14
+// 128×64 is ahead while 128×128 leaves every second CU idle (96 against 105 µs at 512×4096×11008, 500×1536×1536 12.8 against 14.4) and
+// behind once it does not (2048×2048×4096, 256 tiles of 128×128: 50 against 44).
 enum Tile { TILE_256, TILE_128, TILE_128x64 };
 Tile plain_tile(const GemmArgs& g) {
     const auto tiles = [&](int bm, int bn) { return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * g.batch; };
     const int half = g.swiglu ? 2 : 1;   // a tile has half the output columns with the gated epilogue
-    const int64_t t256 = tiles(256, 256 / half), t128 = tiles(128, 128 / half);
-    const double c256 = 1.65 * (double)((t256 + 255) / 256);
-    const double c128 = t128 <= 256 ? 0.61 : std::max(1.0, (double)t128 / 512 + 0.2);
-    if (c256 < c128) return TILE_256;
+    const int64_t t256 = tiles(256, 256 / half), t128 = tiles(128, 128 / half), before_last = (t256 - 1) / 256;   // full rounds before the last
+    if (t256 - 256 * before_last > 128 || before_last >= 3) return TILE_256;
     return t128 <= 128 && !g.swiglu ? TILE_128x64 : TILE_128;
 }
 
