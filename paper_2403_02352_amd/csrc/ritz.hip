@@ -11,11 +11,11 @@
 // second round (for r <= 128 each of the three) also annihilates the entries inside the blocks, and a rotation leaves the larger of its
 // two diagonal entries at the smaller index.  Without either, each entry once a sweep, a sweep got less far than one that goes index by
 // index: after ten, spectra 0.9^i and groups of eight at r = 300 were left with off-diagonal entries of 4e-6 to 1e-5 of the largest
-// eigenvalue (index by index 7e-8 to 4e-7, now 1e-8 or less).  It costs a quarter: r = 512, ten sweeps, 6.44 -> 8.33 ms.
-// r <= 64 is one launch, whose sweeps are r-1 steps of a round-robin over the indices
-// themselves: with the 63 steps of two blocks of 32, ten sweeps took 440 µs whatever r was, at r = 1 six times what a launch per step took.
+// eigenvalue (index by index 7e-8 to 4e-7, now 1e-7 or less).  It costs a quarter: r = 512, ten sweeps, 6.44 -> 8.33 ms.
+// r <= 64 is one launch, whose sweeps are r-1 steps of a round-robin over the indices themselves: with the 63 steps of two blocks of 32, ten sweeps took 440 µs whatever r was, at r = 1 six times what a launch per step took.
 //
-// What bounds it: the chain of r-1 dependent steps per sweep, each at best an LDS round trip plus the rotation formula (about 0.5 µs).
+// What bounds it: the chain of dependent steps (48 in a round on average), each at best an LDS round trip plus the rotation formula
+// (about 0.5 µs).
 // A launch per step instead, with every step a pass over T and R, cost 7.4 µs per step: at r = 512, ten sweeps, 37.8 ms for the whole
 // call against 8.3 ms.
 #include "common.h"
@@ -41,7 +41,7 @@ __device__ __forceinline__ int pair_index(int l, int first, int second) { return
 // exponent, so every size that fp32 holds is rotated, denormal ones included: a plain hardware reciprocal ends below 2^-126 and above 2^126.
 // Hardware reciprocals and roots (1 unit in the last place): an angle that is off by 1e-7 leaves 1e-7 of the entry, and what keeps the
 // rotation orthogonal is u against s, where the same error counts s²/2 at most.  Every wave derives all 32 rotations of a step, so
-// these instructions count: 37.6 -> 32.7 µs per launch of jacobi_pair_kernel (34 steps on average) against correctly rounded divisions.
+// these instructions count: a launch of 34 steps took 32.7 µs against 37.6 with correctly rounded divisions.
 __device__ __forceinline__ void jacobi_su(float app, float aqq, float apq, float& s, float& u) {
     const float tau = __builtin_ldexpf(0.5f * (aqq - app), -__builtin_amdgcn_frexp_expf(apq)) * __builtin_amdgcn_rcpf(__builtin_amdgcn_frexp_mantf(apq));
     const float t = __builtin_copysignf(__builtin_amdgcn_rcpf(fabsf(tau) + __builtin_amdgcn_sqrtf(fmaf(tau, tau, 1.f))), tau);
