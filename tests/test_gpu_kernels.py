@@ -198,6 +198,20 @@ def test_attention_f32(atp, case, variant):
     assert err <= F32_TOL
 
 
+# (L, r, dh, standard deviation of the scores, bound in units of 2^-24)
+@pytest.mark.parametrize("case", [(400, 33, 256, 1, 4.5), (200, 300, 256, 1, 8), (500, 500, 128, 3, 9.5), (300, 200, 64, 1, 5)])
+def test_attention_f32_scores_are_short_sums(atp, case):
+    """A sum of n terms of variance v in one chain carries 2^-24/sqrt(3)·sqrt(v·n^2/2), over 256 features 6.5 units at a standard deviation of
+    1; sums of 8 or 16 features, added up, carry 2 of them (4.6 and 2 at 128 features, times 3 here).  The exponential hands that on to the
+    weights, the sums over the keys add to it."""
+    L, r, dh, sd, units = case
+    Q, K, V = (rnd((1, n, 2 * dh), 70 + i).astype(np.float32) for i, n in enumerate((L, r, r)))
+    Q *= np.float32(sd)
+    err = rel_fro(to_host(atp.attention(*(to_dev(x, "f32") for x in (Q, K, V)), 2))[0], oracle.attention(Q[0], K[0], V[0], 2))
+    print(case, err * 2 ** 24, flush=True)
+    assert err <= units * 2.0 ** -24
+
+
 # (batch, L, heads): keys dealt to four waves; 128 queries per workgroup
 @pytest.mark.parametrize("case", [(1, 40, 1), (4, 1000, 4)])
 @pytest.mark.parametrize("dead", [(32, 64), (0, 32), (0, 128), (96, 300)])
