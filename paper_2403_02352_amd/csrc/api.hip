@@ -168,7 +168,7 @@ BasesWs carve_bases(void* ws, int64_t batch, int64_t L, int64_t d, int64_t r, at
     w.Linv = (float*)c.take((size_t)batch * rp * rp * 4);
     w.dinv = (float*)c.take((size_t)batch * rp * 4);
     w.info = (int32_t*)c.take((size_t)batch * 4);
-    w.flags = (unsigned*)c.take(factor_dataflow_flag_bytes((int)batch));
+    w.flags = (unsigned*)c.take(factor_dataflow_flag_bytes((int)rp, (int)batch));
     w.total = c.off;
     return w;
 }

@@ -204,7 +204,7 @@ hipError_t factor_inverse(hipStream_t st, float* S, float* Lf, float* Y, const f
 
 // The same factorisation as ONE launch per group of items: co-resident workgroups keep their tiles in
 // registers and hand finished panel tiles to each other through global memory and per-tile flags
-// (`flags`: factor_dataflow_flag_bytes(batch) bytes, cleared by gram_prepare when passed there).
+// (`flags`: factor_dataflow_flag_bytes(r, batch) bytes, cleared by gram_prepare when passed there).
 // Covers r <= 2048 when a group of workgroups fits the chip (factor_dataflow_ok); needs every
 // workgroup of a launch resident at the same time, so it must not share the GPU with another such
 // launch.  Lf and Y receive the panel tiles (scratch).  info = -1 if a wait inside the kernel gave up.
@@ -212,7 +212,7 @@ hipError_t factor_inverse(hipStream_t st, float* S, float* Lf, float* Y, const f
 // beyond that run as further launches one after the other, which costs more than the launch-per-block-column
 // factorisation, whose launches take all items at once).
 bool factor_dataflow_ok(int r, int batch, bool whole_batch);
-size_t factor_dataflow_flag_bytes(int batch);
+size_t factor_dataflow_flag_bytes(int r, int batch);
 // polls after which a wait inside the kernel gives up (< 1: the default, far beyond any healthy wait)
 void factor_dataflow_set_spin_limit(int polls);
 hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y, const float* dinv, float* Binv,

@@ -18,6 +18,7 @@
 //     half of this file); the form used whenever the whole batch fits one launch.
 #include "common.h"
 
+#include <algorithm>
 #include <utility>
 
 namespace atp {
@@ -46,8 +47,9 @@ __device__ long long g_df_trace[1024];
 //   Binv = 0 where the factorisation never writes but the product Z·R^-1 reads: tj > ti, and, unless
 //   zero_all is set, only inside the 256-wide diagonal block (the MFMA product stops its K loop at
 //   the end of the diagonal block of a triangular operand).
-// Also clears the item's hand-over flags of the single-launch factorisation (flags may be null) and arms its exchange slots (wx: the
-// first wx_fill_words words of every item's wx_stride_words are set to the "not written yet" pattern).
+// NaN entries become the one that arithmetic makes.
+// Also clears the item's hand-over flags of the single-launch factorisation (flags may be null) and arms its exchange slots (wx: wx_words words
+// per item are set to the "not written yet" pattern).
 // HBM-bound (nparts reads of the lower triangle).  Every tile forms the 128 scale factors it needs itself: the 128·nparts diagonal
 // loads travel with the tile's own and come from L2, where a launch of its own for dinv cost 5 µs per factorisation.
 // NP = number of partial sums, a constant so that all loads of a thread are in flight together.
@@ -56,7 +58,7 @@ __global__ void __launch_bounds__(256) prepare_kernel(const float* __restrict__ 
                                                       float* __restrict__ dinv, float* __restrict__ Y, float* __restrict__ Binv,
                                                       bf16_t* __restrict__ Bh, bf16_t* __restrict__ Bl, int r, int r_true, float shift,
                                                       int zero_all, unsigned* __restrict__ flags, int flag_words, uint4* __restrict__ wx,
-                                                      int wx_stride_words, int wx_fill_words) {
+                                                      int wx_words) {
     __shared__ float sc[2][NB];
     const int b = blockIdx.z, ti = blockIdx.y, tj = blockIdx.x, tid = threadIdx.x;
     const int64_t base = (int64_t)b * r * r;
@@ -64,7 +66,7 @@ __global__ void __launch_bounds__(256) prepare_kernel(const float* __restrict__ 
         const int first = (ti * gridDim.x + tj) * 256 + tid, step = gridDim.x * gridDim.y * 256;
         for (int e = first; e < flag_words; e += step) flags[(int64_t)b * flag_words + e] = 0u;
         const uint4 unset = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-        for (int e = first; e < wx_fill_words / 4; e += step) wx[(int64_t)b * (wx_stride_words / 4) + e] = unset;
+        for (int e = first; e < wx_words / 4; e += step) wx[(int64_t)b * (wx_words / 4) + e] = unset;
     }
     const int j = tj * NB + (tid & 15) * 4;
     if (tj <= ti) {
@@ -106,6 +108,7 @@ __global__ void __launch_bounds__(256) prepare_kernel(const float* __restrict__ 
                 const float t = s[q][e] * sc[0][li], dj = sc[1][(tid & 15) * 4 + e];
                 v[e] = t * dj;
                 if (i == j + e) v[e] = i < r_true ? fmaf(t, dj, shift) : 1.f + shift;   // the diagonal rounds once
+                if (v[e] != v[e]) v[e] = __uint_as_float(0x7fc00000u);                  // (the exchange slots reserve another NaN)
             }
             *reinterpret_cast<f32x4*>(S + base + (int64_t)i * r + j) = v;
         }
@@ -206,139 +209,222 @@ __device__ __forceinline__ void elim_block(float (&reg)[32], ElimLds& L, int sel
 
 // ---------------------------------------------------------------------------
 // W = L^-T of one 64×64 symmetric positive definite tile T = L·Lᵀ, for the single-launch
-// factorisation (L itself is not needed there).  Same elimination of [T; I], four columns per step,
-// arranged for latency:
-//  * a thread is (row a, wave w); wave w owns the 4-column blocks B with B % 4 == w (16 registers);
-//  * row a of T is dead once block a/4 has been eliminated, and row a of the identity part is born in
-//    that step: the same registers hold the T row first and the row of W afterwards, so every thread has
-//    exactly one live row per step and the trailing update is half as long;
-//  * the raw values of the next block are written by their owner wave right after it has updated them,
-//    ahead of the rest of its trailing update.
-// T comes in as LDS tile `Tt` (pitch NB+1); W leaves in `Wt` (upper triangular, zeros below).
+// factorisation (L itself is not needed there).  The elimination of [T; I] above, 16 columns per stage, arranged for latency:
+//  * row a of T is dead once its 16-column block has been eliminated, and row a of the identity part is born in that stage, so
+//    64 rows are live throughout;
+//  * wave 0 eliminates the 16 columns of a stage by itself, a live row per lane.  The 16 pivot rows are held by each of its
+//    four rows of 16 lanes as well: x_k(c) reaches the lanes as the broadcast operand of the multiply-add (DPP), so a pivot
+//    costs no LDS exchange and no barrier;
+//  * the columns to the right take the 16 multipliers at once, T -= f·xᵀ on the matrix cores, a 16-row group per wave, the next
+//    stage's columns first.  The fp32 matrix instruction adds its products one by one in the order of the pivots, so every entry is the same
+//    chain of multiply-adds as column by column;
+//  * the other columns, the scaling of the final ones and their stores run in waves 1 to 3 while wave 0 is in the next stage;
+//  * the stages are one loop: the code runs cold in every workgroup, and four copies of it took 2.4 µs to fetch.
+// A chain of 64 pivots in one wave: bound by instruction issue (about 21 per pivot at 4.5 cycles).
 // ---------------------------------------------------------------------------
-struct Elim2Lds {
-    float4 raw[2][NB];  // [buffer][row]: the four block columns of the row each thread currently holds
-    float4 xs[2][NB];   // [buffer][row of T]: reduced values of the rows below the pivot block
+constexpr int EP = 20;   // row pitch of a 64×16 column block in LDS (16-byte aligned rows; reads and writes of 16 rows fall into different banks)
+struct alignas(16) Elim2Lds {
+    float raw[NB][EP];      // the 16 columns of the next stage
+    float unit[16][EP];     // rows of the identity, as they are born
+    float xs[2][NB][EP];    // [stage % 2][row]: x_k of the live rows
+    float piv[4][16];       // [stage]: the pivots
+    float ninv[4][16];      // -1/pivot, 0 where it is dropped
+    int stored;             // waves whose part of the published tile has arrived
 };
 
-// one owned block (local index M) of the trailing update of step B
-template <int B, int M>
-__device__ __forceinline__ void elim2_update(float (&reg)[16], Elim2Lds& L, int a, int w, bool pivrow, float f0, float f1,
-                                             float f2, float f3) {
-    constexpr int buf = B & 1;
-    const int c0 = 4 * (4 * M + w);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float4 d = L.xs[buf][c0 + j];
-        const float base = pivrow ? 0.f : reg[4 * M + j];    // a newborn identity row starts from zero
-        reg[4 * M + j] = fmaf(-f3, d.w, fmaf(-f2, d.z, fmaf(-f1, d.y, fmaf(-f0, d.x, base))));
-    }
-    if (4 * M + w == B + 1) L.raw[buf ^ 1][a] = make_float4(reg[4 * M], reg[4 * M + 1], reg[4 * M + 2], reg[4 * M + 3]);
-}
-
 __device__ __forceinline__ void df_st16(float* p, f32x4 v);
+__device__ __forceinline__ void df_stores_done();
 
-// `slot` (may be null): exchange slot of W, four groups of 16 columns, group q at slot + 1024·q as [row][16].
-// The four blocks of a group are final after step 4q+3, one in each wave: every thread sends its 16 bytes
-// then, so the workgroup that consumes W works through it behind this elimination, group by group.
-// `publish` (may be null): a hand-over flag whose tile stores were issued before the elimination began; they
-// have completed by the second step: every wave confirms that there (a wait that costs nothing by then),
-// and after that step's barrier one thread raises the flag, so the caller need not stall for its stores.
-template <int B>
-__device__ __forceinline__ void elim2_block(float (&reg)[16], Elim2Lds& L, int a, int w, float flag_below, int& bad_col,
-                                            float* slot, unsigned* publish) {
-    constexpr int buf = B & 1;
-    constexpr int mB = B / 4, wB = B % 4;
-    if constexpr (B == 1) {
-        if (publish) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-    __syncthreads();   // raw[buf] of block B is complete (written during the previous step)
-    if constexpr (B == 1) {
-        if (publish && a == 0 && w == 0) __hip_atomic_store(publish, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    const float4 p0 = L.raw[buf][4 * B + 0], p1 = L.raw[buf][4 * B + 1];
-    const float4 p2 = L.raw[buf][4 * B + 2], p3 = L.raw[buf][4 * B + 3];
-    float4 R = L.raw[buf][a];
-    const int ja = a - 4 * B;                 // 0..3: this thread's row is a pivot row and turns into its identity row
-    const bool pivrow = (ja >= 0 && ja < 4);
-    if (pivrow) R = make_float4(ja == 0 ? 1.f : 0.f, ja == 1 ? 1.f : 0.f, ja == 2 ? 1.f : 0.f, ja == 3 ? 1.f : 0.f);
-    const float piv0r = p0.x;
-    const float i0 = drop_rcp(piv0r);
-    const float x10 = p1.x, x20 = p2.x, x30 = p3.x;
-    const float g10 = x10 * i0, g20 = x20 * i0, g30 = x30 * i0;
-    const float piv1r = fmaf(-g10, x10, p1.y);
-    const float i1 = drop_rcp(piv1r);
-    const float x21 = fmaf(-g20, x10, p2.y);
-    const float x31 = fmaf(-g30, x10, p3.y);
-    const float g21 = x21 * i1, g31 = x31 * i1;
-    const float piv2r = fmaf(-g21, x21, fmaf(-g20, x20, p2.z));
-    const float i2 = drop_rcp(piv2r);
-    const float x32 = fmaf(-g31, x21, fmaf(-g30, x20, p3.z));
-    const float piv3r = fmaf(-x32 * i2, x32, fmaf(-g31, x31, fmaf(-g30, x30, p3.w)));
-    const float i3 = drop_rcp(piv3r);
-    const float x0 = R.x, f0 = x0 * i0;
-    const float x1 = fmaf(-f0, x10, R.y), f1 = x1 * i1;
-    const float x2 = fmaf(-f1, x21, fmaf(-f0, x20, R.z)), f2 = x2 * i2;
-    const float x3 = fmaf(-f2, x32, fmaf(-f1, x31, fmaf(-f0, x30, R.w))), f3 = x3 * i3;
-    // xs[row] is read only by the wave that owns the block column `row` lies in (the trailing update of wave w
-    // reads xs of the rows 4·blk .. 4·blk+3 of its own blocks blk): written by that same wave, it needs no block
-    // barrier; a wave's LDS accesses complete in order
-    if (w == ((a >> 2) & 3) && a >= 4 * B + 4) L.xs[buf][a] = make_float4(x0, x1, x2, x3);
-    if (bad_col < 0 && !(fminf(fminf(piv0r, piv1r), fminf(piv2r, piv3r)) >= flag_below)) {
-        if (!(piv0r >= flag_below)) bad_col = 4 * B;
-        else if (!(piv1r >= flag_below)) bad_col = 4 * B + 1;
-        else if (!(piv2r >= flag_below)) bad_col = 4 * B + 2;
-        else bad_col = 4 * B + 3;
-    }
-    if (w == wB) {   // final values of block B of the live row (rows of W; rows of L are not kept)
-        reg[4 * mB + 0] = x0 * drop_rsq(piv0r);
-        reg[4 * mB + 1] = x1 * drop_rsq(piv1r);
-        reg[4 * mB + 2] = x2 * drop_rsq(piv2r);
-        reg[4 * mB + 3] = x3 * drop_rsq(piv3r);
-    }
-    // pending blocks of wave w: local block mB only for the waves behind the owner of block B, the later
-    // ones for every wave; block B + 1 comes first in this order and its raw values are written at once
-    if (w > wB) elim2_update<B, mB>(reg, L, a, w, pivrow, f0, f1, f2, f3);
-    if constexpr (mB + 1 < 4) elim2_update<B, (mB + 1 < 4 ? mB + 1 : 3)>(reg, L, a, w, pivrow, f0, f1, f2, f3);
-    if constexpr (mB + 2 < 4) elim2_update<B, (mB + 2 < 4 ? mB + 2 : 3)>(reg, L, a, w, pivrow, f0, f1, f2, f3);
-    if constexpr (mB + 3 < 4) elim2_update<B, (mB + 3 < 4 ? mB + 3 : 3)>(reg, L, a, w, pivrow, f0, f1, f2, f3);
-    if constexpr (wB == 3) {
-        if (slot) {   // blocks 4·mB .. 4·mB+3 are final in waves 0..3; a row below its block is still a dead T row there
-            const bool dead = 4 * mB + w < (a >> 2);
-            const f32x4 v = {dead ? 0.f : reg[4 * mB], dead ? 0.f : reg[4 * mB + 1], dead ? 0.f : reg[4 * mB + 2],
-                             dead ? 0.f : reg[4 * mB + 3]};
-            df_st16(slot + 1024 * mB + 16 * a + 4 * w, v);
-        }
-    }
-    __builtin_amdgcn_sched_barrier(0);
+// lane C of each row of 16 lanes, to all lanes of that row
+template <int C>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + C, 0xf, 0xf, true));
+}
+// d += m·(lane C of the row of s).  A DPP operand must not have been written by the two instructions before; the compiler does not look into
+// these statements, so the order that keeps the distance is written out below (they are volatile and stay in it).
+template <int C>
+__device__ __forceinline__ void fma_bcast(float& d, float s, float m) {
+    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(C));
 }
 
-template <int... Bs>
-__device__ __forceinline__ void elim2_all(std::integer_sequence<int, Bs...>, float (&reg)[16], Elim2Lds& L, int a, int w,
-                                          float flag_below, int& bad_col, float* slot, unsigned* publish) {
-    (elim2_block<Bs>(reg, L, a, w, flag_below, bad_col, slot, publish), ...);
+// columns C .. 15 take the multipliers of pivot K
+template <int K, int C>
+__device__ __forceinline__ void elim2_row(float (&D)[16], float (&P)[16], float nd, float np) {
+    if constexpr (C < 16) {
+        fma_bcast<C>(D[C], D[K], nd);
+        fma_bcast<C>(P[C], D[K], np);
+        elim2_row<K, C + 1>(D, P, nd, np);
+    }
 }
 
-// all 256 threads; Tt and Wt may not alias; ends with a block barrier
-__device__ __forceinline__ void diag_inverse_factor(const float (*Tt)[NB + 1], float (*Wt)[NB + 1], Elim2Lds& L, int tid,
-                                                    float flag_below, int& bad_col, float* slot = nullptr,
-                                                    unsigned* publish = nullptr) {
-    const int a = tid & 63, w = tid >> 6;
-    float reg[16];
+// Pivot K of a stage: D the pivot rows, P the live row of the lane, ninv = -1/pivot (0: dropped); next and piv: those of pivot K+1.  Column K+1 of the pivot rows
+// comes first, and the reciprocal of the next pivot is on its way while the other columns follow.  The distances that the hardware does not
+// keep by itself: two instructions from the write of a register to its DPP read and from a compare to the select, one after a reciprocal.
+#define ATP_FMA_BCAST(d, s, m, c) "v_fmac_f32_dpp " d ", " s ", " m " row_newbcast:" c " row_mask:0xf bank_mask:0xf\n\t"
+#define ATP_DPP(op, d, s, c) op " " d ", " s " row_newbcast:" c " row_mask:0xf bank_mask:0xf\n\t"
+template <int K>
+__device__ __forceinline__ void elim2_pivot(float (&D)[16], float (&P)[16], float ninv, float& next, float& piv) {
+    float nd, np, rcp;
+    if constexpr (K <= 12) {
+        asm volatile("v_mul_f32 %[nd], %[dk], %[n]\n\tv_mul_f32 %[np], %[pk], %[n]\n\t"
+                     ATP_FMA_BCAST("%[d1]", "%[dk]", "%[nd]", "%[c1]") ATP_FMA_BCAST("%[p1]", "%[dk]", "%[np]", "%[c1]")
+                     ATP_FMA_BCAST("%[d2]", "%[dk]", "%[nd]", "%[c2]")
+                     ATP_DPP("v_rcp_f32_dpp", "%[rcp]", "%[d1]", "%[c1]") ATP_DPP("v_mov_b32_dpp", "%[piv]", "%[d1]", "%[c1]")
+                     ATP_FMA_BCAST("%[p2]", "%[dk]", "%[np]", "%[c2]")
+                     "v_cmp_lt_f32 vcc, %[drop], %[piv]\n\t"
+                     ATP_FMA_BCAST("%[d3]", "%[dk]", "%[nd]", "%[c3]") ATP_FMA_BCAST("%[p3]", "%[dk]", "%[np]", "%[c3]")
+                     "v_cndmask_b32 %[next], 0, -%[rcp], vcc"
+                     : [nd] "=&v"(nd), [np] "=&v"(np), [d1] "+v"(D[K + 1]), [p1] "+v"(P[K + 1]), [d2] "+v"(D[K + 2]), [p2] "+v"(P[K + 2]),
+                       [d3] "+v"(D[K + 3]), [p3] "+v"(P[K + 3]), [rcp] "=&v"(rcp), [piv] "=&v"(piv), [next] "=&v"(next)
+                     : [dk] "v"(D[K]), [pk] "v"(P[K]), [n] "v"(ninv), [drop] "s"(PIVOT_DROP), [c1] "n"(K + 1), [c2] "n"(K + 2), [c3] "n"(K + 3)
+                     : "vcc");
+        elim2_row<K, K + 4>(D, P, nd, np);
+    } else if constexpr (K == 13) {
+        asm volatile("v_mul_f32 %[nd], %[dk], %[n]\n\tv_mul_f32 %[np], %[pk], %[n]\n\t"
+                     ATP_FMA_BCAST("%[d1]", "%[dk]", "%[nd]", "14") ATP_FMA_BCAST("%[p1]", "%[dk]", "%[np]", "14")
+                     ATP_FMA_BCAST("%[d2]", "%[dk]", "%[nd]", "15")
+                     ATP_DPP("v_rcp_f32_dpp", "%[rcp]", "%[d1]", "14") ATP_DPP("v_mov_b32_dpp", "%[piv]", "%[d1]", "14")
+                     ATP_FMA_BCAST("%[p2]", "%[dk]", "%[np]", "15")
+                     "v_cmp_lt_f32 vcc, %[drop], %[piv]\n\ts_nop 1\n\t"
+                     "v_cndmask_b32 %[next], 0, -%[rcp], vcc"
+                     : [nd] "=&v"(nd), [np] "=&v"(np), [d1] "+v"(D[14]), [p1] "+v"(P[14]), [d2] "+v"(D[15]), [p2] "+v"(P[15]), [rcp] "=&v"(rcp),
+                       [piv] "=&v"(piv), [next] "=&v"(next)
+                     : [dk] "v"(D[13]), [pk] "v"(P[13]), [n] "v"(ninv), [drop] "s"(PIVOT_DROP)
+                     : "vcc");
+    } else {
+        asm volatile("v_mul_f32 %[nd], %[dk], %[n]\n\tv_mul_f32 %[np], %[pk], %[n]\n\t"
+                     ATP_FMA_BCAST("%[d1]", "%[dk]", "%[nd]", "15") ATP_FMA_BCAST("%[p1]", "%[dk]", "%[np]", "15")
+                     "s_nop 0\n\t"
+                     ATP_DPP("v_rcp_f32_dpp", "%[rcp]", "%[d1]", "15") ATP_DPP("v_mov_b32_dpp", "%[piv]", "%[d1]", "15")
+                     "v_cmp_lt_f32 vcc, %[drop], %[piv]\n\ts_nop 1\n\t"
+                     "v_cndmask_b32 %[next], 0, -%[rcp], vcc\n\ts_nop 1"   // (the last wait is for what follows)
+                     : [nd] "=&v"(nd), [np] "=&v"(np), [d1] "+v"(D[15]), [p1] "+v"(P[15]), [rcp] "=&v"(rcp), [piv] "=&v"(piv), [next] "=&v"(next)
+                     : [dk] "v"(D[14]), [pk] "v"(P[14]), [n] "v"(ninv), [drop] "s"(PIVOT_DROP)
+                     : "vcc");
+    }
+}
+#undef ATP_FMA_BCAST
+#undef ATP_DPP
+
+template <int... Ks>
+__device__ __forceinline__ void elim2_panel(std::integer_sequence<int, Ks...>, float (&D)[16], float (&P)[16], float (&ninv)[16], float (&piv)[16]) {
+    piv[0] = row_bcast<0>(D[0]);
+    ninv[0] = -drop_rcp(piv[0]);
+    (elim2_pivot<Ks>(D, P, ninv[Ks], ninv[Ks + 1], piv[Ks + 1]), ...);
+}
+
+// the 16-row group of the diagonal tile that a wave works on: wave 0 has the one with the least to do besides the next stage's columns
+__device__ __forceinline__ int elim2_group(int wave) { return wave < 2 ? 1 - wave : wave; }
+
+// All 256 threads.  `acc[j]`: rows 16g .. 16g+15 of T (g = elim2_group(wave)), columns 16j .. 16j+15, in the C layout of the 16×16 product
+// (column lane % 16, rows 4·(lane / 16) .. +3); only the lower 16×16 tiles are used.  Columns from `cols` on are those of the identity.
+// W leaves in `Wt` (upper triangular, zeros below) and in `slot`, the exchange slot: four groups of 16 columns, group q at slot + 1024·q, as
+// operands of the 16×16×4 product: [row / 16][(row / 4) % 4][column][row % 4].  Each is sent when its stage is over, so the workgroup that
+// consumes W works through it behind this elimination.
+// `store` is called by waves 1 to 3 in the first stage; `publish` (may be null) is the hand-over flag of what it stores, raised in the
+// second, by when the stores have completed.
+// Returns the first column whose pivot is below `flag_below`, else -1.  Ends with a block barrier.
+template <class F>
+__device__ __forceinline__ int diag_inverse_factor(const f32x4 (&acc)[4], float (*Wt)[NB + 1], Elim2Lds& L, int tid, int cols, float flag_below,
+                                                   float* slot, unsigned* publish, F store) {
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), g = elim2_group(w), l16 = lane & 15, kq = lane >> 4;
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 right[3] = {acc[1], acc[2], acc[3]};       // the column groups after the stage's
+    float A[4];
+    const int stages = cols > 48 ? 4 : (cols + 15) / 16;
+    const auto write_columns = [&](const f32x4& c) {
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+        for (int v = 0; v < 4; ++v) L.raw[16 * g + 4 * kq + v][l16] = c[v];
+    };
+    // operands of T -= f·xᵀ: lane (l16, kq) holds k = 4s + kq of row l16 of a 16-row group
+    const auto update = [&](f32x4& c, int B, int group) {
+        const float* x = &L.xs[B & 1][16 * group + l16][kq];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) reg[4 * m + j] = Tt[a][4 * (4 * m + w) + j];
-    if (w == 0) L.raw[0][a] = make_float4(reg[0], reg[1], reg[2], reg[3]);
-    elim2_all(std::make_integer_sequence<int, NB / 4>{}, reg, L, a, w, flag_below, bad_col, slot, publish);
+        for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f32_16x16x4f32(A[s], x[4 * s], c, 0, 0, 0);
+    };
+    const auto next_columns = [&](int B) {
+        const float *f = &L.xs[B & 1][16 * g + l16][kq], *n = &L.ninv[B][kq];
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+        for (int s = 0; s < 4; ++s) A[s] = f[4 * s] * n[4 * s];
+        update(right[0], B, B + 1);
+        write_columns(right[0]);
+        right[0] = right[1];
+        right[1] = right[2];
+        __syncthreads();   // the next stage's columns are in raw
+    };
+    const auto send = [&](int B, int rg) {   // columns 16B .. 16B+15 of row group rg, 0 where the rows are still those of T
+        const float scale = drop_rsq(L.piv[B][l16]);
+        f32x4 v;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = 4 * (4 * m + w) + j;
-            Wt[a][c] = (4 * m + w < (a >> 2)) ? 0.f : reg[4 * m + j];   // blocks left of the diagonal still hold the dead T row
-        }
+        for (int e = 0; e < 4; ++e) v[e] = rg <= B ? L.xs[B & 1][16 * rg + 4 * kq + e][l16] * scale : 0.f;
+        df_st16(slot + 1024 * B + 256 * rg + 4 * lane, v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Wt[16 * rg + 4 * kq + e][16 * B + l16] = v[e];
+    };
+    const auto raise = [&]() {   // the last of three waves
+        df_stores_done();
+        if (lane == 0 && atomicAdd(&L.stored, 1) == 2) __hip_atomic_store(publish, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    write_columns(acc[0]);
+    L.unit[tid >> 4][tid & 15] = (tid >> 4) == (tid & 15) ? 1.f : 0.f;
+    if (tid == 0) L.stored = 0;
+    if (tid < NB) L.piv[tid >> 4][tid & 15] = 1.f;   // stages that are left out
     __syncthreads();
+    if (w == 0) {
+#pragma unroll 1
+        for (int B = 0;; ++B) {
+            float D[16], P[16], ninv[16], piv[16];
+            // the lane's live row; group B, whose rows are born, from the identity
+            const float* dp = L.raw[16 * B + l16];
+            const float* pp = kq == B ? L.unit[l16] : L.raw[lane];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 d4 = *reinterpret_cast<const float4*>(dp + 4 * q), p4 = *reinterpret_cast<const float4*>(pp + 4 * q);
+                D[4 * q] = d4.x; D[4 * q + 1] = d4.y; D[4 * q + 2] = d4.z; D[4 * q + 3] = d4.w;
+                P[4 * q] = p4.x; P[4 * q + 1] = p4.y; P[4 * q + 2] = p4.z; P[4 * q + 3] = p4.w;
+            }
+            if (B == 1) right[0] = right[1] = zero;   // this wave's rows are born
+            if (B == 2) update(right[0], 1, 3);       // and their columns 48 .. 63 were left
+            elim2_panel(std::make_integer_sequence<int, 15>{}, D, P, ninv, piv);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                *reinterpret_cast<f32x4*>(&L.xs[B & 1][lane][4 * q]) = f32x4{P[4 * q], P[4 * q + 1], P[4 * q + 2], P[4 * q + 3]};
+                *reinterpret_cast<f32x4*>(&L.ninv[B][4 * q]) = f32x4{ninv[4 * q], ninv[4 * q + 1], ninv[4 * q + 2], ninv[4 * q + 3]};
+                *reinterpret_cast<f32x4*>(&L.piv[B][4 * q]) = f32x4{piv[4 * q], piv[4 * q + 1], piv[4 * q + 2], piv[4 * q + 3]};
+            }
+            __syncthreads();
+            if (B + 1 == stages) break;
+            next_columns(B);
+        }
+    } else {
+#pragma unroll 1
+        for (int B = 0;; ++B) {
+            if (B == 1 && publish) raise();
+            if (B > 0) {
+                if (B < 3) update(right[0], B - 1, B + 1);
+                if (B == 1) update(right[1], 0, 3);
+                send(B - 1, w);
+                if (w == 1) send(B - 1, 0);
+            } else {
+                store();
+            }
+            if (B == g) right[0] = right[1] = right[2] = zero;   // rows that are born in this stage start from zero
+            __syncthreads();
+            if (B + 1 == stages) break;
+            next_columns(B);
+        }
+    }
+    send(stages - 1, w);
+    for (int q = stages; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Wt[16 * w + 4 * kq + e][16 * q + l16] = v[e] = w == q && 4 * kq + e == l16 ? 1.f : 0.f;
+        df_st16(slot + 1024 * q + 256 * w + 4 * lane, v);
+    }
+    const uint64_t bad = __builtin_amdgcn_ballot_w64(!(L.piv[kq][l16] >= flag_below));
+    if (stages == 1 && w > 0 && publish) raise();
+    __syncthreads();
+    return bad ? (int)__builtin_ctzll(bad) : -1;
 }
 
 template <int... Bs>
@@ -608,9 +694,13 @@ __global__ void __launch_bounds__(256, 2) factor_step_kernel(float* S, float* Lf
 //   T(rho,k) = init - sum_{p<k} P(rho,p)·L(k,p)ᵀ ,   P(rho,k) = T(rho,k)·W_k ,   W_k = L_kk^-T
 // (init = S'(i,k) for S-rows, 0 for Y-rows; the sum starts at p = c for Y-row c with P(c,c) = W_c).
 // Roles inside one item's group of workgroups:
-//   spine workgroup i (one per block row) owns S'(i,i-1) and S'(i,i): applies the panels p <= i-2 as
-//     they appear, then, once W_{i-1} is published, forms L(i,i-1), the Schur complement of the diagonal
-//     tile, factorises it together with an identity tile (which yields W_i) and publishes W_i;
+//   spine workgroup i (one per block row) owns S'(i,i-2), S'(i,i-1) and S'(i,i): applies the panels p <= i-3 as
+//     they appear, forms L(i,i-2) once W_{i-2} is published, brings T(i,i-1) and T(i,i) up to panel i-2, and then, once W_{i-1} is
+//     published, forms L(i,i-1) and the Schur complement of the diagonal tile, factorises it together with an identity tile
+//     (which yields W_i) and publishes W_i.
+//     From W_{i-1} to W_i takes 9 µs at r = 1024: 6 of elimination, 0.7 for the last columns to cross, 0.8 for the quarter of L(i,i-1) and
+//     of the diagonal update that depends on them, and 1.5 by which a workgroup is late for them.  With S'(i,i-2) in a bulk
+//     workgroup, flags for every tile and the elimination in four-column steps it took 12.3 (r = 1024, batch 4: 204 -> 147 µs; 256: 55 -> 42);
 //   bulk workgroups own the remaining tiles, dealt round-robin in order of block column so that a
 //     workgroup's slots are sorted by urgency.  Step q: finalise the slots of block column q (product
 //     with W_q), publish them, then apply panel q to every later slot.
@@ -623,23 +713,25 @@ __global__ void __launch_bounds__(256, 2) factor_step_kernel(float* S, float* Lf
 constexpr int DF_SPIN_LIMIT = 1 << 22;   // polls of ~0.1-0.3 µs each: well beyond any healthy wait
 constexpr int DF_MAX_NBLK = 32;
 constexpr int DF_FLAG_WORDS = 2 * DF_MAX_NBLK * DF_MAX_NBLK + 64;   // per item; the last 64 words hold the abort word
-// Exchange slots: W_i travels from spine workgroup i to spine workgroup i+1, the one hand-over on the
-// critical path of the factorisation, without a flag and in four pieces.  The slot (a dense 64×64 tile per
-// block row, stored as four groups of 16 columns) is armed with a bit pattern no finite number has (all ones:
-// a NaN) before the launch; the producer stores a group as soon as its columns are final (columns of
-// W = L^-T become final from left to right as the elimination proceeds), the consumer loads a group until
-// none of its words shows the pattern any more and at once forms the matching 16 columns of
-// L(i+1,i) = T(i+1,i)·W_i and their share of the update of its diagonal tile.  When the last group arrives
-// only a quarter of that work is left.  A torn or partly arrived group only looks unfinished.
+// Exchange slots: what the critical path of the factorisation waits for travels without a flag.  A slot (a dense 64×64 tile) is armed with a
+// bit pattern that no number has (all ones: a NaN, and not the one that arithmetic makes; gram_prepare lets no other NaN in) before the
+// launch; a consumer loads its part until no word shows the pattern any more, so a tile that is torn or partly there only looks unfinished.
+// Against a flag (stores, wait for them, flag; poll, load) that saves two round trips through memory, 2 µs per hand-over.
+// W_i travels in four pieces: columns of W = L^-T become final from left to right as the elimination proceeds, the producer stores a group of
+// 16 columns as soon as it is final, and the next spine workgroup forms the matching 16 columns of L(i+1,i) = T(i+1,i)·W_i and their share of the
+// update of its diagonal tile at once.  When the last group arrives only a quarter of that work is left.
 constexpr unsigned DF_UNSET = 0xFFFFFFFFu;
+// tiles of the bulk workgroups: all of S' below the third diagonal and all of Y above its diagonal
+__host__ __device__ constexpr int df_bulk_tiles(int nb) { return (nb > 3 ? (nb - 2) * (nb - 3) / 2 : 0) + nb * (nb - 1) / 2; }
 constexpr int DF_SLOT_WORDS = NB * NB;
-constexpr int DF_WX_WORDS = DF_MAX_NBLK * DF_SLOT_WORDS;            // per item
+enum DfSlot { DF_SLOT_W, DF_SLOT_L1, DF_SLOT_L2, DF_SLOT_L3, DF_SLOT_T, DF_SLOTS };   // of a block row i: W_i, L(i,i-1), L(i,i-2), L(i,i-3), T(i,i-1)
+__host__ __device__ constexpr int df_wx_words(int nblk) { return nblk * DF_SLOTS * DF_SLOT_WORDS; }   // per item
 
 struct DfArgs {
     float* S; float* Lf; float* Y; const float* dinv;
     float* Binv; bf16_t* Bh; bf16_t* Bl;
     unsigned* flags;
-    float* wx;              // exchange slots, DF_WX_WORDS per item
+    float* wx;              // exchange slots, df_wx_words(nblk) per item
     int32_t* info;
     int r, nblk, item0, nbulk;
     int spin_limit;         // polls before a wait gives up
@@ -677,56 +769,104 @@ __device__ __forceinline__ void df_st16(float* p, f32x4 v) {
 }
 __device__ __forceinline__ void df_stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-constexpr int WCP = 20;   // row pitch of a 64×16 column group of W in LDS (16-byte aligned rows, the four k-slices of a read fall into different banks)
-
 __device__ __forceinline__ bool df_written(const f32x4& v) {
     return __float_as_uint(v[0]) != DF_UNSET && __float_as_uint(v[1]) != DF_UNSET && __float_as_uint(v[2]) != DF_UNSET &&
            __float_as_uint(v[3]) != DF_UNSET;
 }
 
-// Whole workgroup: load one 64×16 group of an exchange slot until every word of it has been written, then leave
-// it in `dst`.  false = gave up (spin limit or the item's abort word).  Ends with a block barrier.
-// (Taking every group that is complete at the time of a poll, four loads and a reduction per group, measured
-// slower: 225 against 204 µs per factorisation; the plain poll reacts faster.)
-__device__ __forceinline__ bool df_poll_group(float (*dst)[WCP], const float* group, unsigned* abort_w, int spin_limit,
-                                              int tid) {
-    const float* p = group + tid * 4;
-    f32x4 v;
-    for (int spins = 0;; ++spins) {
-        asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v) : "v"(p) : "memory");
-        int give_up = 0;
-        if (tid == 0 && (spins > spin_limit / 8 ||
-                         ((spins & 63) == 63 && __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))))
-            give_up = 1;
-        // two reductions: these calls return "some / every thread passed non-zero", not a combination of the values
-        if (__syncthreads_or(give_up)) return false;
-        if (__syncthreads_and(df_written(v) ? 1 : 0)) break;
+// Column groups of W on their way from an exchange slot into the registers of a wave, in the operand order that the slot holds them in: no LDS,
+// no barrier.  Group Q takes Q+1 pieces (W is upper triangular).
+struct DfW { f32x4 g0[1], g1[2], g2[3], g3[4]; };
+template <int Q>
+__device__ __forceinline__ auto& df_group(DfW& w) {
+    if constexpr (Q == 0) return w.g0;
+    else if constexpr (Q == 1) return w.g1;
+    else if constexpr (Q == 2) return w.g2;
+    else return w.g3;
+}
+template <int Q>
+__device__ __forceinline__ void df_load_group(DfW& w, const float* slot, int lane) {
+    const float* p = slot + 1024 * Q + 4 * lane;
+    auto& v = df_group<Q>(w);
+    if constexpr (Q == 0)
+        asm volatile("global_load_dwordx4 %0, %1, off sc1\n\ts_waitcnt vmcnt(0)" : "=&v"(v[0]) : "v"(p) : "memory");
+    else if constexpr (Q == 1)
+        asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %2, off offset:1024 sc1\n\ts_waitcnt vmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]) : "v"(p) : "memory");
+    else if constexpr (Q == 2)
+        asm volatile("global_load_dwordx4 %0, %3, off sc1\n\tglobal_load_dwordx4 %1, %3, off offset:1024 sc1\n\t"
+                     "global_load_dwordx4 %2, %3, off offset:2048 sc1\n\ts_waitcnt vmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]) : "v"(p) : "memory");
+    else
+        asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %4, off offset:1024 sc1\n\t"
+                     "global_load_dwordx4 %2, %4, off offset:2048 sc1\n\tglobal_load_dwordx4 %3, %4, off offset:3072 sc1\n\ts_waitcnt vmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(p) : "memory");
+}
+// all four groups in flight together
+__device__ __forceinline__ void df_load_groups(DfW& w, const float* slot, int lane) {
+    const float *p0 = slot + 4 * lane, *p1 = p0 + 1024, *p2 = p0 + 2048, *p3 = p0 + 3072;
+    asm volatile(
+        "global_load_dwordx4 %0, %10, off sc1\n\t"
+        "global_load_dwordx4 %1, %11, off sc1\n\tglobal_load_dwordx4 %2, %11, off offset:1024 sc1\n\t"
+        "global_load_dwordx4 %3, %12, off sc1\n\tglobal_load_dwordx4 %4, %12, off offset:1024 sc1\n\t"
+        "global_load_dwordx4 %5, %12, off offset:2048 sc1\n\t"
+        "global_load_dwordx4 %6, %13, off sc1\n\tglobal_load_dwordx4 %7, %13, off offset:1024 sc1\n\t"
+        "global_load_dwordx4 %8, %13, off offset:2048 sc1\n\tglobal_load_dwordx4 %9, %13, off offset:3072 sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(w.g0[0]), "=&v"(w.g1[0]), "=&v"(w.g1[1]), "=&v"(w.g2[0]), "=&v"(w.g2[1]), "=&v"(w.g2[2]), "=&v"(w.g3[0]), "=&v"(w.g3[1]),
+          "=&v"(w.g3[2]), "=&v"(w.g3[3])
+        : "v"(p0), "v"(p1), "v"(p2), "v"(p3)
+        : "memory");
+}
+template <int Q>
+__device__ __forceinline__ bool df_complete(DfW& w) {
+    const auto& v = df_group<Q>(w);
+    bool ok = true;
+#pragma unroll
+    for (int g = 0; g <= Q; ++g) ok = ok && df_written(v[g]);
+    return __all(ok);
+}
+
+// a wave's wait on an exchange slot ends without what it waits for: spin limit, or the item's abort word
+__device__ __forceinline__ bool df_gives_up(int spins, unsigned* abort_w, int spin_limit) {
+    return spins > spin_limit / 8 || ((spins & 63) == 63 && __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// One wave: until group Q has arrived.  What the last look at all of the slot (df_load_groups) found is used, so a consumer that comes late
+// takes everything in one round trip (1 µs); one that comes early polls no more than the group it waits for.
+// false = gave up (spin limit or the item's abort word).
+template <int Q>
+__device__ __forceinline__ bool df_wait_group(DfW& w, const float* slot, unsigned* abort_w, int spin_limit, int lane) {
+    if (df_complete<Q>(w)) return true;
+    df_load_groups(w, slot, lane);
+    for (int spins = 0; !df_complete<Q>(w); ++spins) {
+        df_load_group<Q>(w, slot, lane);
+        if (df_gives_up(spins, abort_w, spin_limit)) return false;
     }
-    *reinterpret_cast<f32x4*>(&dst[tid >> 2][(tid & 3) * 4]) = v;
-    __syncthreads();
     return true;
 }
 
-// Column group q of L = T·W for the wave's 16 rows (wave w: rows 16w..16w+15), 16×16×4 fp32 MFMA.
-// T row-major [row][k] (pitch LP), Wg = rows k of the group's 16 columns.  W is upper triangular: k < 16(q+1).
+// Column group Q of L = T·W for the wave's 16 rows (wave w: rows 16w..16w+15), 16×16×4 fp32 MFMA.
+// T row-major [row][k] (pitch LP).  W is upper triangular: k < 16(Q+1).
 // Lane (l16, kq): the MFMA step (g, e) contracts k = 16g + 4kq + e in lane group kq.
-// The result goes to Lm[row][16q + col] (pitch LP).
-__device__ __forceinline__ void df_l_group(float (*Lm)[LP], const float (*Tm)[LP], const float (*Wg)[WCP], int q, int w,
-                                           int l16, int kq) {
+// The result goes to Lm[row][16Q + col] (pitch LP).
+template <int Q>
+__device__ __forceinline__ void df_l_group(float (*Lm)[LP], const float (*Tm)[LP], DfW& wv, int w, int l16, int kq) {
+    const auto& v = df_group<Q>(wv);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int g = 0; g <= q; ++g) {
+#pragma unroll
+    for (int g = 0; g <= Q; ++g) {
         const float4 a4 = *reinterpret_cast<const float4*>(&Tm[16 * w + l16][16 * g + 4 * kq]);
-        const int k0 = 16 * g + 4 * kq;
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.x, Wg[k0 + 0][l16], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.y, Wg[k0 + 1][l16], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.z, Wg[k0 + 2][l16], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.w, Wg[k0 + 3][l16], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.x, v[g][0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.y, v[g][1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.z, v[g][2], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.w, v[g][3], acc, 0, 0, 0);
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) Lm[16 * w + 4 * kq + v][16 * q + l16] = acc[v];
+    for (int e = 0; e < 4; ++e) Lm[16 * w + 4 * kq + e][16 * Q + l16] = acc[e];
 }
 
-// acc[j] += L[16w.., group q]·L[16j.., group q]ᵀ for the 16×16 tiles j <= w of the wave's tile row (the lower
+// acc[j] += L[16w.., group q]·L[16j.., group q]ᵀ for the 16×16 tiles j <= w of tile row w (the lower
 // triangle is all the elimination of the diagonal tile reads)
 __device__ __forceinline__ void df_syrk_group(f32x4 (&acc)[4], const float (*Lm)[LP], int q, int w, int l16, int kq) {
     const float4 a4 = *reinterpret_cast<const float4*>(&Lm[16 * w + l16][16 * q + 4 * kq]);
@@ -738,6 +878,72 @@ __device__ __forceinline__ void df_syrk_group(f32x4 (&acc)[4], const float (*Lm)
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.y, b4.y, acc[j], 0, 0, 0);
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.z, b4.z, acc[j], 0, 0, 0);
         acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4.w, b4.w, acc[j], 0, 0, 0);
+    }
+}
+
+// Three 64×64 tiles, 16 bytes of each of 4 rows per thread and tile, and what has arrived of a W, all in flight together: one round trip.
+// The first lies in a matrix with rows of length r, of which `rows` rows exist from it on (those behind are read as its first and count as zero),
+// the others in one with rows of length ld (NB: exchange slots).
+__device__ __forceinline__ void df_load_tiles(f32x4 (&v)[12], DfW& w, const float* t0, int rows, const float* t1, const float* t2, int ld,
+                                              const float* slot, int r, int tid) {
+    const int row = tid >> 4, c4 = (tid & 15) * 4;
+    unsigned o[4], o0[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        o[q] = (unsigned)((row + 16 * q) * ld + c4) * 4u;
+        o0[q] = (unsigned)((row + 16 * q < rows ? row + 16 * q : 0) * r + c4) * 4u;
+    }
+    const unsigned w0 = (tid & 63) * 16, w1 = w0 + 4096, w2 = w0 + 8192, w3 = w0 + 12288;
+#define ATP_LD(n, off, base) "global_load_dwordx4 %" #n ", %" #off ", %" #base " sc1\n\t"
+#define ATP_LDW(n, off, imm) "global_load_dwordx4 %" #n ", %" #off ", %33 offset:" #imm " sc1\n\t"
+    asm volatile(
+        ATP_LD(0, 22, 34) ATP_LD(1, 23, 34) ATP_LD(2, 24, 34) ATP_LD(3, 25, 34)
+        ATP_LD(4, 26, 35) ATP_LD(5, 27, 35) ATP_LD(6, 28, 35) ATP_LD(7, 29, 35)
+        ATP_LD(8, 26, 36) ATP_LD(9, 27, 36) ATP_LD(10, 28, 36) ATP_LD(11, 29, 36)
+        ATP_LDW(12, 30, 0) ATP_LDW(13, 31, 0) ATP_LDW(14, 31, 1024) ATP_LDW(15, 32, 0) ATP_LDW(16, 32, 1024) ATP_LDW(17, 32, 2048)
+        ATP_LDW(18, 37, 0) ATP_LDW(19, 37, 1024) ATP_LDW(20, 37, 2048) ATP_LDW(21, 37, 3072)
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]), "=&v"(v[8]), "=&v"(v[9]),
+          "=&v"(v[10]), "=&v"(v[11]), "=&v"(w.g0[0]), "=&v"(w.g1[0]), "=&v"(w.g1[1]), "=&v"(w.g2[0]), "=&v"(w.g2[1]), "=&v"(w.g2[2]),
+          "=&v"(w.g3[0]), "=&v"(w.g3[1]), "=&v"(w.g3[2]), "=&v"(w.g3[3])
+        : "v"(o0[0]), "v"(o0[1]), "v"(o0[2]), "v"(o0[3]), "v"(o[0]), "v"(o[1]), "v"(o[2]), "v"(o[3]), "v"(w0), "v"(w1), "v"(w2), "s"(slot),
+          "s"(t0), "s"(t1), "s"(t2), "v"(w3)
+        : "memory");
+#undef ATP_LD
+#undef ATP_LDW
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (row + 16 * q >= rows) v[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+__device__ __forceinline__ void df_tile_to_lds(float (*dst)[LP], const f32x4 (&v)[12], int first, float sign, int tid) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(&dst[(tid >> 4) + 16 * q][(tid & 15) * 4]) = v[first + q] * sign;
+}
+
+// a tile of LDS into an exchange slot (row-major)
+template <int THREADS>
+__device__ __forceinline__ void df_store_slot(float* slot, const float (*src)[LP], int tid) {
+    constexpr int N = (NB * NB / 4 + THREADS - 1) / THREADS;
+    f32x4 v[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int e = (tid + j * THREADS) & (NB * NB / 4 - 1);
+        v[j] = *reinterpret_cast<const f32x4*>(&src[e >> 4][(e & 15) * 4]);
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+        if (tid + j * THREADS < NB * NB / 4) df_st16(slot + 4 * (tid + j * THREADS), v[j]);
+}
+
+// One wave's part of a tile in an exchange slot, until every word of it has been written.  false = gave up.
+__device__ __forceinline__ bool df_wait_tile(f32x4& v0, f32x4& v1, f32x4& v2, f32x4& v3, const float* slot, unsigned* abort_w, int spin_limit, int tid) {
+    const float *p0 = slot + 4 * tid, *p1 = p0 + 1024, *p2 = p0 + 2048, *p3 = p0 + 3072;
+    for (int spins = 0;; ++spins) {
+        asm volatile("global_load_dwordx4 %0, %4, off sc1\n\tglobal_load_dwordx4 %1, %5, off sc1\n\t"
+                     "global_load_dwordx4 %2, %6, off sc1\n\tglobal_load_dwordx4 %3, %7, off sc1\n\ts_waitcnt vmcnt(0)"
+                     : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3) : "v"(p0), "v"(p1), "v"(p2), "v"(p3) : "memory");
+        if (__all(df_written(v0) && df_written(v1) && df_written(v2) && df_written(v3))) return true;
+        if (df_gives_up(spins, abort_w, spin_limit)) return false;
     }
 }
 
@@ -769,12 +975,13 @@ __device__ __forceinline__ void df_tiles_to_lds(float (*da)[LP], const float* Ma
     }
 }
 
-// one thread: wait until both flags are up (f2 may equal f1); the two loads of a poll are in flight together
-__device__ __forceinline__ bool df_poll(unsigned* f1, unsigned* f2, unsigned* abort_w, int spin_limit) {
+// one thread: wait until all three flags are up (they may be the same); the loads of a poll are in flight together
+__device__ __forceinline__ bool df_poll(unsigned* f1, unsigned* f2, unsigned* f3, unsigned* abort_w, int spin_limit) {
     for (int spins = 0;; ++spins) {
         const unsigned v1 = __hip_atomic_load(f1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned v2 = __hip_atomic_load(f2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (v1 && v2) return true;
+        const unsigned v3 = __hip_atomic_load(f3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v1 && v2 && v3) return true;
         if (spins > spin_limit) return false;
         if ((spins & 255) == 255 && __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
         __builtin_amdgcn_s_sleep(1);
@@ -793,23 +1000,6 @@ __device__ __forceinline__ void df_mma(f32x16& acc, const float (*Am)[LP], const
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, bsign * b4.z, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, bsign * b4.w, acc, 0, 0, 0);
     }
-}
-
-// returns Am · W with W row-major [k][n] in LDS (the finalising product T·W_k)
-__device__ __forceinline__ f32x16 df_times_w(const float (*Am)[LP], const float (*Wm)[LP], int wr, int wc, int l32, int lh) {
-    f32x16 acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-    for (int g = 0; g < NB / 8; ++g) {
-        const float4 a4 = *reinterpret_cast<const float4*>(&Am[32 * wr + l32][8 * g + 4 * lh]);
-        const int k0 = 8 * g + 4 * lh, n = 32 * wc + l32;
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, Wm[k0 + 0][n], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, Wm[k0 + 1][n], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, Wm[k0 + 2][n], acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, Wm[k0 + 3][n], acc, 0, 0, 0);
-    }
-    return acc;
 }
 
 // accumulator (MFMA C layout: element v of a lane -> row 8*(v/4) + 4*lh + v%4, column l32 of the wave's
@@ -843,17 +1033,20 @@ __device__ __forceinline__ f32x16 df_load_acc(const float* __restrict__ M, int r
 
 // LDS tile (row-major, pitch P) -> global r×r matrix with agent-scope stores (a panel tile other workgroups
 // will read), 16-byte row pieces where the shape allows
-template <int P>
+template <int P, int THREADS = 256>
 __device__ __forceinline__ void df_store_tile(float* __restrict__ M, const float (*src)[P], int r, int r0, int c0, int tid) {
-    for (int e = tid; e < NB * NB / 4; e += 256) {
-        const int row = e >> 4, col = (e & 15) * 4;
-        const int gr = r0 + row, gc = c0 + col;
-        if (gr < r && gc < r) {
-            f32x4 v;
+    constexpr int N = (NB * NB / 4 + THREADS - 1) / THREADS;
+    f32x4 v[N];   // (out of LDS before the first store: the compiler moves no read over one)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = src[row][col + q];
-            df_st16(M + (int64_t)gr * r + gc, v);
-        }
+    for (int j = 0; j < N; ++j) {
+        const int e = tid + j * THREADS, row = (e >> 4) & (NB - 1), col = (e & 15) * 4;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[j][q] = src[row][col + q];
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        const int e = tid + j * THREADS, gr = r0 + (e >> 4), gc = c0 + (e & 15) * 4;
+        if (e < NB * NB / 4 && gr < r && gc < r) df_st16(M + (int64_t)gr * r + gc, v[j]);
     }
 }
 
@@ -902,20 +1095,26 @@ __device__ __forceinline__ void df_store_binv(const float (*src)[P], const float
     }
 }
 
+template <class F>
+__device__ __forceinline__ void for_groups(F f) {
+    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{}); f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
+}
+
 template <int NT>
 __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
     __shared__ __align__(16) float lds_a[NB * LP];
     __shared__ __align__(16) float lds_b[NB * LP];
     __shared__ __align__(16) Elim2Lds elds;
     __shared__ __align__(16) float lds_l[NB * LP];     // the product with W as it is formed, group by group
-    __shared__ __align__(16) float lds_w[NB * WCP];    // the column group of W in hand
-    __shared__ int s_ok;
+    __shared__ __align__(16) float lds_m[NB * LP], lds_t[NB * LP];
+    __shared__ int s_ok, s_gave_up;
     float (*Am)[LP] = reinterpret_cast<float (*)[LP]>(lds_a);
     float (*Bm)[LP] = reinterpret_cast<float (*)[LP]>(lds_b);
     float (*As)[NB + 1] = reinterpret_cast<float (*)[NB + 1]>(lds_a);
     float (*Bs)[NB + 1] = reinterpret_cast<float (*)[NB + 1]>(lds_b);
     float (*Am2)[LP] = reinterpret_cast<float (*)[LP]>(lds_l);
-    float (*Wg)[WCP] = reinterpret_cast<float (*)[WCP]>(lds_w);
+    float (*Lm2)[LP] = reinterpret_cast<float (*)[LP]>(lds_m);
+    float (*Tm)[LP] = reinterpret_cast<float (*)[LP]>(lds_t);
 
     const int b = a.item0 + blockIdx.y;
     const int r = a.r, nb = a.nblk;
@@ -926,19 +1125,21 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
     const float* db = a.dinv + (int64_t)b * r;
     unsigned* fl = a.flags + (int64_t)b * DF_FLAG_WORDS;
     unsigned* abort_w = fl + 2 * DF_MAX_NBLK * DF_MAX_NBLK;
-    float* wxb = a.wx + (int64_t)b * DF_WX_WORDS;
+    float* wxb = a.wx + (int64_t)b * df_wx_words(nb);
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lh = lane >> 5;
     const int wr = wave >> 1, wc = wave & 1;
     const int l16 = lane & 15, kq = lane >> 4;
+    const int grp = elim2_group(__builtin_amdgcn_readfirstlane(wave));
 
+    auto slot_of = [&](int row, DfSlot kind) { return wxb + (int64_t)(row * DF_SLOTS + kind) * DF_SLOT_WORDS; };
     // flag of the finished panel tile in stacked row `row` (S-rows 0..nb-1, Y-rows nb..2nb-1), block column p
     auto flag_of = [&](int row, int p) { return fl + row * nb + p; };
-    // whole workgroup waits for up to two flags; false = give up (abort raised)
-    auto wg_wait = [&](unsigned* f1, unsigned* f2) -> bool {
+    // whole workgroup waits for up to three flags; false = give up (abort raised)
+    auto wg_wait = [&](unsigned* f1, unsigned* f2, unsigned* f3) -> bool {
         if (tid == 0) {
-            const bool ok = df_poll(f1, f2 ? f2 : f1, abort_w, a.spin_limit);
+            const bool ok = df_poll(f1, f2, f3, abort_w, a.spin_limit);
             if (!ok) {
                 __hip_atomic_store(abort_w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if (a.info) a.info[b] = -1;
@@ -957,12 +1158,25 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
         if (tid == 0) __hip_atomic_store(f, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
 
-    // a wait on an exchange slot gave up: raise the item's abort word and flag the result
-    auto give_up = [&]() {
+    // a wait of some wave on an exchange slot gave up (looked at after a barrier): raise the item's abort word and flag the result
+    if (tid == 0) s_gave_up = 0;
+    __syncthreads();
+    auto gave_up = [&]() -> bool {
+        const int any = s_gave_up;
+        __syncthreads();      // no wave is in its next wait before all have looked
+        if (!any) return false;
         if (tid == 0) {
             __hip_atomic_store(abort_w, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (a.info) a.info[b] = -1;
         }
+        return true;
+    };
+    // column group Q of W_k; what is there of W_k before (df_load_groups, df_load_tiles) is used
+    DfW wv;
+    auto wait_group = [&](auto Q, int k) {
+        constexpr int q = decltype(Q)::value;
+        const float* slot = slot_of(k, DF_SLOT_W);
+        if (!df_wait_group<q>(wv, slot, abort_w, a.spin_limit, lane)) s_gave_up = 1;
     };
 
     const int g = blockIdx.x;
@@ -972,54 +1186,118 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
         const int r0 = i * NB;
         DF_STAMP(i * 8 + 0);
         f32x16 acc_d = df_load_acc(Sb, r, r0, r0, wr, wc, l32, lh, 1.f);
-        f32x16 acc_s;
+        f32x16 acc_s, acc_q;
         if (i > 0) acc_s = df_load_acc(Sb, r, r0, r0 - NB, wr, wc, l32, lh, 0.f);
-        for (int p = 0; p + 2 <= i; ++p) {
-            if (!wg_wait(flag_of(i, p), flag_of(i - 1, p))) return;
-            df_tiles_to_lds(Am, Lb, r0, p * NB, -1.f, Bm, Lb, r0 - NB, p * NB, true, r, tid);   // -L(i,p), L(i-1,p)
+        if (i > 1) {
+            acc_q = df_load_acc(Sb, r, r0, r0 - 2 * NB, wr, wc, l32, lh, 0.f);
+            f32x4 v[12];
+            for (int p = 0; p + 4 <= i; ++p) {
+                if (!wg_wait(flag_of(i, p), flag_of(i - 1, p), flag_of(i - 2, p))) return;
+                df_load_tiles(v, wv, Lb + (int64_t)r0 * r + p * NB, r - r0, Lb + (int64_t)(r0 - NB) * r + p * NB, Lb + (int64_t)(r0 - 2 * NB) * r + p * NB, r,
+                              slot_of(i - 2, DF_SLOT_W), r, tid);
+                df_tile_to_lds(Am, v, 0, -1.f, tid);    // -L(i,p), L(i-1,p), L(i-2,p)
+                df_tile_to_lds(Bm, v, 4, 1.f, tid);
+                df_tile_to_lds(Am2, v, 8, 1.f, tid);
+                __syncthreads();
+                df_mma(acc_q, Am, Am2, wr, wc, l32, lh, 1.f);
+                df_mma(acc_s, Am, Bm, wr, wc, l32, lh, 1.f);
+                df_mma(acc_d, Am, Am, wr, wc, l32, lh, -1.f);
+                __syncthreads();
+            }
+            // Panels i-3 and i-2 are what the next diagonal tile waits for, and in them L(i,i-2) and T(i,i-1), which workgroup i+1 waits for.
+            // Tiles of the spine come through exchange slots, those of panel i-3 in one round trip with what has arrived of W_{i-2}.
+            DF_STAMP(256 + i * 8 + 0);
+            if (i > 2) {
+                const float *l3 = slot_of(i, DF_SLOT_L3), *l2 = slot_of(i - 1, DF_SLOT_L2), *l1 = slot_of(i - 2, DF_SLOT_L1);
+                for (int spins = 0;; ++spins) {
+                    df_load_tiles(v, wv, l3, NB, l2, l1, NB, slot_of(i - 2, DF_SLOT_W), NB, tid);
+                    bool ok = true;
+#pragma unroll
+                    for (int q = 0; q < 12; ++q) ok = ok && df_written(v[q]);
+                    if (__all(ok)) break;
+                    if (df_gives_up(spins, abort_w, a.spin_limit)) { s_gave_up = 1; break; }
+                }
+                DF_STAMP(256 + i * 8 + 1);
+                df_tile_to_lds(Am, v, 0, -1.f, tid);
+                df_tile_to_lds(Bm, v, 4, 1.f, tid);
+                df_tile_to_lds(Am2, v, 8, 1.f, tid);
+                __syncthreads();
+                if (gave_up()) return;
+                df_mma(acc_q, Am, Am2, wr, wc, l32, lh, 1.f);
+                df_mma(acc_s, Am, Bm, wr, wc, l32, lh, 1.f);
+                __syncthreads();
+            } else {
+                df_load_groups(wv, slot_of(i - 2, DF_SLOT_W), lane);
+            }
+            df_acc_to_lds<LP>(Lm2, acc_q, wr, wc, l32, lh);
+            // L(i-1,i-2) is formed here for a second time, next to L(i,i-2), from the T(i-1,i-2) that workgroup i-1 sends: waiting for its
+            // L(i-1,i-2) instead puts the formation and a hand-over between W_{i-2} and W_{i-1} (12.7 µs per block row).
+            if (!df_wait_tile(v[0], v[1], v[2], v[3], slot_of(i - 1, DF_SLOT_T), abort_w, a.spin_limit, tid)) s_gave_up = 1;
+            df_tile_to_lds(Bm, v, 0, 1.f, tid);
             __syncthreads();
-            df_mma(acc_s, Am, Bm, wr, wc, l32, lh, 1.f);
-            df_mma(acc_d, Am, Am, wr, wc, l32, lh, -1.f);
+            DF_STAMP(256 + i * 8 + 2);
+            for_groups([&](auto Q) {
+                wait_group(Q, i - 2);
+                df_l_group<decltype(Q)::value>(Am2, Lm2, wv, wave, l16, kq);
+                df_l_group<decltype(Q)::value>(Tm, Bm, wv, wave, l16, kq);
+            });
             __syncthreads();
+            if (gave_up()) return;
+            DF_STAMP(256 + i * 8 + 3);
+            if (i + 1 < nb) df_store_slot<256>(slot_of(i, DF_SLOT_L2), Am2, tid);
+            df_store_tile<LP>(Lb, Am2, r, r0, r0 - 2 * NB, tid);
+            df_mma(acc_s, Am2, Tm, wr, wc, l32, lh, -1.f);
+            df_acc_to_lds<LP>(Lm2, acc_s, wr, wc, l32, lh);   // T(i,i-1)
+            wg_publish(flag_of(i, i - 2));
+            DF_STAMP(256 + i * 8 + 4);
+            if (i + 1 < nb) df_store_slot<256>(slot_of(i, DF_SLOT_T), Lm2, tid);
+            if (i > 2) df_mma(acc_d, Am, Am, wr, wc, l32, lh, -1.f);
+            df_mma(acc_d, Am2, Am2, wr, wc, l32, lh, -1.f);
         }
         DF_STAMP(i * 8 + 1);
         float (*Lm)[LP] = Am2;
         unsigned* pending = nullptr;   // flag of L(i,i-1), raised from inside the elimination
         // T_ii with the panels p <= i-2 applied (T in Bs); the panel i-1 follows below, group by group
         df_acc_to_lds<NB + 1>(Bs, acc_d, wr, wc, l32, lh);
+        f32x4 accp[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) accp[j] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (i > 0) {
-            df_acc_to_lds<LP>(Am, acc_s, wr, wc, l32, lh);   // T(i,i-1)
-            f32x4 accp[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) accp[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const float* slot = wxb + (int64_t)(i - 1) * DF_SLOT_WORDS;
-            for (int q = 0; q < 4; ++q) {
-                if (!df_poll_group(Wg, slot + 1024 * q, abort_w, a.spin_limit, tid)) {   // 16 columns of W_{i-1}
-                    give_up();
-                    return;
-                }
-                if (q == 3) DF_STAMP(i * 8 + 2);
-                df_l_group(Lm, Am, Wg, q, wave, l16, kq);          // 16 columns of L(i,i-1)
+            if (i == 1) {   // T(1,0) is the tile of S' as it is
+                df_acc_to_lds<LP>(Lm2, acc_s, wr, wc, l32, lh);
                 __syncthreads();
-                if (q == 3) df_store_tile<LP>(Lb, Lm, r, r0, r0 - NB, tid);   // stores in flight under what follows
-                df_syrk_group(accp, Lm, q, wave, l16, kq);
+                if (nb > 2) df_store_slot<256>(slot_of(1, DF_SLOT_T), Lm2, tid);
             }
-            // T_ii -= L(i,i-1)·L(i,i-1)ᵀ on the lower 16×16 tiles
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (j > wave) continue;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) Bs[16 * wave + 4 * kq + v][16 * j + l16] -= accp[j][v];
-            }
+            df_load_groups(wv, slot_of(i - 1, DF_SLOT_W), lane);
+            __syncthreads();
+            for_groups([&](auto Q) {
+                constexpr int q = decltype(Q)::value;
+                wait_group(Q, i - 1);                              // 16 columns of W_{i-1}
+                if (q == 3) DF_STAMP(i * 8 + 2);
+                df_l_group<q>(Lm, Lm2, wv, wave, l16, kq);         // 16 columns of L(i,i-1)
+                __syncthreads();
+                df_syrk_group(accp, Lm, q, grp, l16, kq);
+            });
+            if (gave_up()) return;
             pending = flag_of(i, i - 1);
             DF_STAMP(i * 8 + 3);
+        } else {
+            __syncthreads();
         }
-        __syncthreads();
+        // T_ii -= L(i,i-1)·L(i,i-1)ᵀ on the lower 16×16 tiles, into the registers that the elimination works on
+        f32x4 td[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) td[j][v] = Bs[16 * grp + 4 * kq + v][16 * j + l16] - accp[j][v];
         DF_STAMP(i * 8 + 4);
-        // W_i = L_ii^-T of the Schur complement T_ii (T in Bs, W in As)
+        // W_i = L_ii^-T of the Schur complement T_ii (W in As)
         {
-            int bad_col = -1;
-            diag_inverse_factor(Bs, As, elds, tid, a.flag_below, bad_col, wxb + (int64_t)i * DF_SLOT_WORDS, pending);
+            const int bad_col = diag_inverse_factor(td, As, elds, tid, r - r0, a.flag_below, slot_of(i, DF_SLOT_W), pending,
+                                                    [&]() {
+                                                        if (i > 0 && i + 2 < nb) df_store_slot<192>(slot_of(i, DF_SLOT_L1), Lm, tid - 64);
+                                                        if (i > 0) df_store_tile<LP, 192>(Lb, Lm, r, r0, r0 - NB, tid - 64);
+                                                    });
             if (tid == 0 && a.info && bad_col >= 0 && (r0 + bad_col) < r) atomicCAS(a.info + b, 0, r0 + bad_col + 1);
         }
         DF_STAMP(i * 8 + 5);
@@ -1033,8 +1311,8 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
 
     // ---------------------------------------------------------------------- bulk workgroup w
     const int w = g - nb;
-    const int ntiles = (nb - 1) * (nb - 1);
-    const int per = nb - 2;
+    const int ntiles = df_bulk_tiles(nb);
+    const int per = nb - 3;
     f32x16 acc[NT];
     int kcol[NT], rrow[NT];   // block column; stacked row (S-row i, or nb + c for Y-row c); kcol < 0: empty slot
 #pragma unroll
@@ -1045,12 +1323,17 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
         for (int v = 0; v < 16; ++v) acc[s][v] = 0.f;
         if (t < ntiles) {
             int k, idx;
-            if (per > 0 && t < (nb - 1) * per) { k = t / per; idx = t - k * per; }
-            else { k = nb - 1; idx = t - (nb - 1) * per; }
-            const int nS = max(nb - k - 2, 0);
+            // block column k holds the S-rows k+3 .. nb-1 and the Y-rows 0 .. k-1: nb-3 tiles up to k = nb-3, then nb-2 and nb-1
+            if (per > 0 && t < (nb - 2) * per) { k = t / per; idx = t - k * per; }
+            else {
+                idx = t - (nb > 3 ? (nb - 2) * per : 0);
+                k = nb - 2;
+                if (idx >= nb - 2) { idx -= nb - 2; k = nb - 1; }
+            }
+            const int nS = max(nb - k - 3, 0);
             kcol[s] = k;
             if (idx < nS) {
-                rrow[s] = k + 2 + idx;
+                rrow[s] = k + 3 + idx;
                 acc[s] = df_load_acc(Sb, r, rrow[s] * NB, k * NB, wr, wc, l32, lh, 0.f);
             } else {
                 rrow[s] = nb + (idx - nS);
@@ -1059,35 +1342,22 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
     }
     for (int q = 0; q < nb; ++q) {
         if (w == 0) DF_STAMP(512 + q * 4 + 0);
-        // finalise the slots of block column q:  P = T·W_q
-        // The first slot of the column takes W_q from the exchange slot, group by group behind the elimination
-        // that produces it, and leaves the whole of W_q in Bm for any further slot of the column.
-        bool have_w = false;
+        // finalise the slots of block column q:  P = T·W_q, group by group behind the elimination that produces W_q
 #pragma unroll
         for (int s = 0; s < NT; ++s) {
             if (kcol[s] != q) continue;
             const bool ykind = rrow[s] >= nb;
             const int r0 = (ykind ? rrow[s] - nb : rrow[s]) * NB;
             df_acc_to_lds<LP>(Am, acc[s], wr, wc, l32, lh);
-            if (!have_w) {
-                const float* slot = wxb + (int64_t)q * DF_SLOT_WORDS;
-                for (int g = 0; g < 4; ++g) {
-                    if (!df_poll_group(Wg, slot + 1024 * g, abort_w, a.spin_limit, tid)) {
-                        give_up();
-                        return;
-                    }
-                    *reinterpret_cast<f32x4*>(&Bm[tid >> 2][16 * g + (tid & 3) * 4]) =
-                        *reinterpret_cast<const f32x4*>(&Wg[tid >> 2][(tid & 3) * 4]);
-                    df_l_group(Am2, Am, Wg, g, wave, l16, kq);
-                }
-                have_w = true;
-                __syncthreads();
-            } else {
-                __syncthreads();
-                const f32x16 pr = df_times_w(Am, Bm, wr, wc, l32, lh);
-                df_acc_to_lds<LP>(Am2, pr, wr, wc, l32, lh);
-                __syncthreads();
-            }
+            df_load_groups(wv, slot_of(q, DF_SLOT_W), lane);
+            __syncthreads();
+            for_groups([&](auto Q) {
+                wait_group(Q, q);
+                df_l_group<decltype(Q)::value>(Am2, Am, wv, wave, l16, kq);
+            });
+            __syncthreads();
+            if (gave_up()) return;
+            if (rrow[s] == q + 3) df_store_slot<256>(slot_of(rrow[s], DF_SLOT_L3), Am2, tid);
             df_store_tile<LP>(ykind ? Yb : Lb, Am2, r, r0, q * NB, tid);
             wg_publish(flag_of(rrow[s], q));
             if (ykind) df_store_binv<LP>(Am2, db, a.Binv, a.Bh, a.Bl, boff, r, r0, q * NB, tid);
@@ -1100,7 +1370,7 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
             if (kcol[s] <= q) continue;                    // empty, finished, or just finalised
             const bool ykind = rrow[s] >= nb;
             if (ykind && rrow[s] - nb > q) continue;       // Y-row c starts at panel c
-            if (!wg_wait(flag_of(rrow[s], q), flag_of(kcol[s], q))) return;
+            if (!wg_wait(flag_of(rrow[s], q), flag_of(kcol[s], q), flag_of(kcol[s], q))) return;
             const int r0 = (ykind ? rrow[s] - nb : rrow[s]) * NB;
             df_tiles_to_lds(Am, ykind ? Yb : Lb, r0, q * NB, -1.f, Bm, Lb, kcol[s] * NB, q * NB, true, r, tid);
             __syncthreads();
@@ -1133,7 +1403,7 @@ int compute_units() {
 }
 // workgroups per item of the single-launch factorisation, 0 = shape not covered
 int dataflow_group(int nblk, int items, int& nt) {
-    const int ntiles = (nblk - 1) * (nblk - 1);
+    const int ntiles = df_bulk_tiles(nblk);
     if (nblk < 1 || nblk > DF_MAX_NBLK || items < 1) return 0;
     int room = compute_units() / items - nblk;   // bulk workgroups that fit beside the spine (one workgroup per compute unit)
     const int enough = (ntiles + 4) / 5;     // five tiles per bulk workgroup keep up with the spine; more workgroups only idle
@@ -1158,7 +1428,9 @@ bool factor_dataflow_ok(int r, int batch, bool whole_batch) {
 // per item: the flag words, then (after the flags of all items) the exchange slots
 void factor_dataflow_set_spin_limit(int polls) { g_df_spin_limit = polls >= 1 ? polls : DF_SPIN_LIMIT; }
 
-size_t factor_dataflow_flag_bytes(int batch) { return (size_t)batch * (DF_FLAG_WORDS + DF_WX_WORDS) * sizeof(unsigned); }
+size_t factor_dataflow_flag_bytes(int r, int batch) {
+    return (size_t)batch * (DF_FLAG_WORDS + df_wx_words(std::min((r + NB - 1) / NB, DF_MAX_NBLK))) * sizeof(unsigned);
+}
 
 hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y, const float* dinv, float* Binv,
                                    bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int32_t* info, float flag_below,
@@ -1196,8 +1468,8 @@ hipError_t gram_prepare(hipStream_t st, const float* Spart, int nparts, int64_t 
     const auto launch = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3(nblk, nblk, batch), dim3(256), 0, st, Spart, pstride, S, dinv, flags ? nullptr : Y, Binv, Bh, Bl, r,
                            r_true, shift, zero_all, flags, DF_FLAG_WORDS,
-                           flags ? reinterpret_cast<uint4*>(flags + (size_t)batch * DF_FLAG_WORDS) : nullptr, DF_WX_WORDS,
-                           (nblk <= DF_MAX_NBLK ? nblk : 0) * DF_SLOT_WORDS);
+                           flags ? reinterpret_cast<uint4*>(flags + (size_t)batch * DF_FLAG_WORDS) : nullptr,
+                           nblk <= DF_MAX_NBLK ? df_wx_words(nblk) : 0);
     };
     switch (nparts) {
         case 1: launch(prepare_kernel<1>); break;

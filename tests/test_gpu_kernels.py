@@ -338,6 +338,44 @@ def test_extraction_keeps_its_bits(atp, case, mode):
     assert h.hexdigest()[:16] == DIGESTS[case][mode]
 
 
+# ranks on both sides of the 16-column stages of a diagonal tile, of the 64-wide blocks, and one to eight block rows (the roles of the spine
+# workgroups change up to the fourth)
+@pytest.mark.parametrize("r", [1, 4, 15, 16, 17, 33, 48, 49, 64, 65, 81, 128, 129, 177, 193, 256, 257, 321, 449])
+def test_factorisation_at_every_edge(atp, r):
+    """One orthonormalisation against the oracle (fp32, conditioned like X·Omega of a flat spectrum: 1e-4), and the two forms of the factorisation
+    against each other: a single block is the same chain of multiply-adds in both, so the same bits; more differ by rounding, 2^-24 per
+    term of sums of up to r and the condition number (below 50) that R^-1 magnifies it by."""
+    batch, L, d = 3, 560, 470
+    X = np.stack([wl.make_X(L, d, np.sqrt(L) * np.linspace(1.0, 0.5, d), 0.0, 60 + b) for b in range(batch)]).astype(np.float32)
+    Om = wl.make_omega(d, r, 3)
+    U = []
+    for mode in (0, 1):
+        atp.set_factor_mode(mode)
+        try:
+            u, _, info, _ = atp.principal_bases(to_dev(X, "f32"), r, 0, to_dev(Om, "f32"))
+            torch.cuda.synchronize()
+        finally:
+            atp.set_factor_mode(True)
+        assert (info == 0).all()
+        U.append(to_host(u))
+    for b in range(batch):
+        Uo, _ = oracle.principal_bases(X[b].astype(np.float64), Om.astype(np.float64), 0)
+        print(r, b, rel_fro(U[1][b], Uo), rel_fro(U[1][b], U[0][b]), flush=True)
+        assert rel_fro(U[1][b], Uo) <= 1e-4
+        assert (U[0][b] == U[1][b]).all() if r <= 64 else rel_fro(U[1][b], U[0][b]) <= 50 * np.sqrt(r) * 2.0 ** -24
+
+
+def test_every_nan_is_flagged(atp):
+    """The factorisation marks what has not been handed over yet with the NaN of all ones: as an input it is a NaN like any other."""
+    X = rnd((3, 300, 280), 5).astype(np.float32)
+    for b, bits in ((0, 0xFFFFFFFF), (2, 0x7FC00000)):
+        X[b, 17, 33] = np.uint32(bits).view(np.float32)
+    _, _, info, _ = atp.principal_bases(to_dev(X, "f32"), 260, 1, to_dev(wl.make_omega(280, 260, 3), "f32"))
+    torch.cuda.synchronize()
+    print(info.tolist(), flush=True)
+    assert info[1] == 0 and info[0] > 0 and info[2] > 0
+
+
 # (L, d, r, iters): extents that are no multiple of 32, alone and together
 RAGGED_ORTH = [(300, 200, 64, 1), (161, 528, 20, 1), (515, 384, 250, 2), (1003, 440, 118, 1)]
 
