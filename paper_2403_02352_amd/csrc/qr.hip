@@ -1301,8 +1301,10 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
             if (tid == 0 && a.info && bad_col >= 0 && (r0 + bad_col) < r) atomicCAS(a.info + b, 0, r0 + bad_col + 1);
         }
         DF_STAMP(i * 8 + 5);
-        df_store_tile<NB + 1>(Yb, As, r, r0, r0, tid);
-        wg_publish(flag_of(nb + i, i));
+        if (i + 1 < nb) {   // (nobody takes the last one)
+            df_store_tile<NB + 1>(Yb, As, r, r0, r0, tid);
+            wg_publish(flag_of(nb + i, i));
+        }
         DF_STAMP(i * 8 + 6);
         df_store_binv<NB + 1>(As, db, a.Binv, a.Bh, a.Bl, boff, r, r0, r0, tid);
         DF_STAMP(i * 8 + 7);
