@@ -397,16 +397,19 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
         {
             ProfScope ps(st, ATP_K_CHOLESKY, (double)batch * r * r * r * (2.0 / 3.0), (double)batch * r * r * 16.0);
             const bool dataflow = g_factor_mode >= 1 && !pipe && factor_dataflow_ok(r, batch, g_factor_mode == 1);
-            ATP_HIP(gram_prepare(st, w.Spart, nparts, (int64_t)batch * r * r, w.S, w.dinv, w.Y, mfma ? nullptr : w.Linv,
-                                 mfma ? linv.hi() : nullptr, mfma ? linv.lo() : nullptr, r, r_true, certify ? 0.f : shift, zero_all, batch,
-                                 dataflow ? w.flags : nullptr));
-            if (dataflow)
-                ATP_HIP(factor_inverse_dataflow(st, w.S, w.Lf, w.Y, w.dinv, mfma ? nullptr : w.Linv, mfma ? linv.hi() : nullptr,
-                                                mfma ? linv.lo() : nullptr, w.flags, r, info, certify ? 1e-3f : 2e-6f, batch));
+            const float flag_below = certify ? 1e-3f : 2e-6f, sh = certify ? 0.f : shift;
+            float* b32 = mfma ? nullptr : w.Linv;
+            bf16_t *bh = mfma ? linv.hi() : nullptr, *bl = mfma ? linv.lo() : nullptr;
+            const bool single = dataflow && r <= 64;
+            if (!single)
+                ATP_HIP(gram_prepare(st, w.Spart, nparts, (int64_t)batch * r * r, w.S, w.dinv, w.Y, b32, bh, bl, r, r_true, sh, zero_all, batch,
+                                     dataflow ? w.flags : nullptr));
+            if (single)
+                ATP_HIP(factor_inverse_single(st, w.Spart, nparts, (int64_t)batch * r * r, w.dinv, b32, bh, bl, r, r_true, sh, info, flag_below, batch));
+            else if (dataflow)
+                ATP_HIP(factor_inverse_dataflow(st, w.S, w.Lf, w.Y, w.dinv, b32, bh, bl, w.flags, r, info, flag_below, batch));
             else
-                ATP_HIP(factor_inverse(st, w.S, w.Lf, w.Y, w.dinv, mfma ? nullptr : w.Linv, mfma ? linv.hi() : nullptr,
-                                       mfma ? linv.lo() : nullptr, r, info, certify ? 1e-3f : 2e-6f, batch,
-                                       pipe ? pipe_after : nullptr, &pc));
+                ATP_HIP(factor_inverse(st, w.S, w.Lf, w.Y, w.dinv, b32, bh, bl, r, info, flag_below, batch, pipe ? pipe_after : nullptr, &pc));
         }
         if (pipe) {
             hipEvent_t e = side_event();

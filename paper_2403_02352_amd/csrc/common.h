@@ -219,6 +219,10 @@ hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y
                                    bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int32_t* info, float flag_below,
                                    int batch);
 
+// gram_prepare and the factorisation in one launch of a workgroup per item, for r <= 64 (a single block row; nobody waits for anybody)
+hipError_t factor_inverse_single(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* dinv, float* Binv, bf16_t* Bh, bf16_t* Bl,
+                                 int r, int r_true, float shift, int32_t* info, float flag_below, int batch);
+
 // ---------------------------------------------------------------------------
 // attention over n_k keys (n_k = r principal keys, or L for the dense comparator)
 // ---------------------------------------------------------------------------

@@ -318,7 +318,7 @@ __device__ __forceinline__ int elim2_group(int wave) { return wave < 2 ? 1 - wav
 
 // All 256 threads.  `acc[j]`: rows 16g .. 16g+15 of T (g = elim2_group(wave)), columns 16j .. 16j+15, in the C layout of the 16×16 product
 // (column lane % 16, rows 4·(lane / 16) .. +3); only the lower 16×16 tiles are used.  Columns from `cols` on are those of the identity.
-// W leaves in `Wt` (upper triangular, zeros below) and in `slot`, the exchange slot: four groups of 16 columns, group q at slot + 1024·q, as
+// W leaves in `Wt` (upper triangular, zeros below) and in `slot` (may be null), the exchange slot: four groups of 16 columns, group q at slot + 1024·q, as
 // operands of the 16×16×4 product: [row / 16][(row / 4) % 4][column][row % 4].  Each is sent when its stage is over, so the workgroup that
 // consumes W works through it behind this elimination.
 // `store` is called by waves 1 to 3 in the first stage; `publish` (may be null) is the hand-over flag of what it stores, raised in the
@@ -357,7 +357,7 @@ __device__ __forceinline__ int diag_inverse_factor(const f32x4 (&acc)[4], float 
         f32x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = rg <= B ? L.xs[B & 1][16 * rg + 4 * kq + e][l16] * scale : 0.f;
-        df_st16(slot + 1024 * B + 256 * rg + 4 * lane, v);
+        if (slot) df_st16(slot + 1024 * B + 256 * rg + 4 * lane, v);
 #pragma unroll
         for (int e = 0; e < 4; ++e) Wt[16 * rg + 4 * kq + e][16 * B + l16] = v[e];
     };
@@ -419,7 +419,7 @@ __device__ __forceinline__ int diag_inverse_factor(const f32x4 (&acc)[4], float 
         f32x4 v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) Wt[16 * w + 4 * kq + e][16 * q + l16] = v[e] = w == q && 4 * kq + e == l16 ? 1.f : 0.f;
-        df_st16(slot + 1024 * q + 256 * w + 4 * lane, v);
+        if (slot) df_st16(slot + 1024 * q + 256 * w + 4 * lane, v);
     }
     const uint64_t bad = __builtin_amdgcn_ballot_w64(!(L.piv[kq][l16] >= flag_below));
     if (stages == 1 && w > 0 && publish) raise();
@@ -1383,6 +1383,62 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
     }
 }
 
+// One block row (r <= 64): sum of the partial Gram matrices, scaling, shift and factorisation of an item in one workgroup, the arithmetic of
+// prepare_kernel and of the spine's elimination.  What bounds such a factorisation is launches and latency: block of 128×64 with r = 32,
+// eleven of them, 305 -> 245 µs without the launch for the set-up, the arming of slots and the flags.
+__global__ void __launch_bounds__(256, 1) factor_single_kernel(const float* __restrict__ Sp, int nparts, int64_t pstride, float* __restrict__ dinv,
+                                                               float* Binv, bf16_t* Bh, bf16_t* Bl, int r, int r_true, float shift, int32_t* info,
+                                                               float flag_below) {
+    __shared__ __align__(16) float lds_a[NB * LP];
+    __shared__ __align__(16) float lds_b[NB * LP];
+    __shared__ __align__(16) Elim2Lds elds;
+    __shared__ float sc[NB];
+    float (*As)[NB + 1] = reinterpret_cast<float (*)[NB + 1]>(lds_a);
+    float (*Bs)[LP] = reinterpret_cast<float (*)[LP]>(lds_b);
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
+    const int grp = elim2_group(__builtin_amdgcn_readfirstlane(tid >> 6)), j = (tid & 15) * 4;
+    const float* src = Sp + (int64_t)b * r * r;
+    f32x4 s[4];
+    float dg = 0.f;
+    for (int p = 0; p < nparts; ++p, src += pstride) {
+        const float d = tid < r ? src[(int64_t)tid * r + tid] : 0.f;
+        dg = p ? dg + d : d;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = (tid >> 4) + 16 * q;
+            const f32x4 v = i < r && j < r ? *reinterpret_cast<const f32x4*>(src + (int64_t)i * r + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+            s[q] = p ? s[q] + v : v;
+        }
+    }
+    if (tid < NB) {
+        const float di = (dg > 0.f && dg < 3.0e38f) ? 1.0f / sqrtf(dg) : 1.0f;
+        sc[tid] = di;
+        if (tid < r) dinv[(int64_t)b * r + tid] = di;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = (tid >> 4) + 16 * q;
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float t = s[q][e] * sc[i], dj = sc[j + e];
+            v[e] = t * dj;
+            if (i == j + e) v[e] = i < r_true ? fmaf(t, dj, shift) : i < r ? 1.f + shift : 1.f;
+        }
+        *reinterpret_cast<f32x4*>(&Bs[i][j]) = v;
+    }
+    __syncthreads();
+    f32x4 td[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) td[c][v] = Bs[16 * grp + 4 * kq + v][16 * c + l16];
+    const int bad_col = diag_inverse_factor(td, As, elds, tid, r, flag_below, nullptr, nullptr, []() {});
+    if (tid == 0 && info && bad_col >= 0 && bad_col < r && info[b] == 0) info[b] = bad_col + 1;
+    df_store_binv<NB + 1>(As, sc, Binv, Bh, Bl, (int64_t)b * r * r, r, 0, 0, tid);
+}
+
 }  // namespace
 
 
@@ -1459,6 +1515,14 @@ hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y
             default: hipLaunchKernelGGL(factor_dataflow_kernel<6>, grid, block, 0, st, a); break;
         }
     }
+    return hipGetLastError();
+}
+
+hipError_t factor_inverse_single(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* dinv, float* Binv, bf16_t* Bh, bf16_t* Bl,
+                                 int r, int r_true, float shift, int32_t* info, float flag_below, int batch) {
+    if (r < 1 || r > NB || (r & 3) || nparts < 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(factor_single_kernel, dim3(batch), dim3(256), 0, st, Spart, nparts, pstride, dinv, Binv, Bh, Bl, r, r_true, shift, info,
+                       flag_below);
     return hipGetLastError();
 }
 
