@@ -1359,7 +1359,7 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
             });
             __syncthreads();
             if (gave_up()) return;
-            if (rrow[s] == q + 3) df_store_slot<256>(slot_of(rrow[s], DF_SLOT_L3), Am2, tid);
+            if (!ykind && rrow[s] == q + 3) df_store_slot<256>(slot_of(rrow[s], DF_SLOT_L3), Am2, tid);
             df_store_tile<LP>(ykind ? Yb : Lb, Am2, r, r0, q * NB, tid);
             wg_publish(flag_of(rrow[s], q));
             if (ykind) df_store_binv<LP>(Am2, db, a.Binv, a.Bh, a.Bl, boff, r, r0, q * NB, tid);

@@ -365,6 +365,19 @@ def test_factorisation_at_every_edge(atp, r):
         assert (U[0][b] == U[1][b]).all() if r <= 64 else rel_fro(U[1][b], U[0][b]) <= 50 * np.sqrt(r) * 2.0 ** -24
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r", [130, 200, 256, 330])
+def test_factorisation_stays_within_the_workspace(atp, dtype, r):
+    """The exchange slots are the last thing in the workspace: nothing behind it is written (three to six block rows, a megabyte looked at)."""
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    X, Om = to_dev(rnd((3, 400, 352), 8), dtype), to_dev(wl.make_omega(352, r, 3), "f32")
+    need = atp.binding.principal_bases_workspace(3, 400, 352, r, 1, t)
+    buf = torch.full((need + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    out = atp.principal_bases(X, r, 1, Om, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert (buf[need:] == 0xA5).all() and (out[2] == 0).all()
+
+
 def test_every_nan_is_flagged(atp):
     """The factorisation marks what has not been handed over yet with the NaN of all ones: as an input it is a NaN like any other."""
     X = rnd((3, 300, 280), 5).astype(np.float32)
