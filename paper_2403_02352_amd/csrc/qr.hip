@@ -16,6 +16,7 @@
 //  3. factor_inverse_dataflow: the same factorisation as ONE launch of co-resident workgroups that keep
 //     their tiles in registers and hand finished panel tiles to each other through global memory (second
 //     half of this file); the form used whenever the whole batch fits one launch.
+//  4. factor_inverse_single: 1 and the factorisation of a single block column (r <= 64), one workgroup per item and no hand-over.
 #include "common.h"
 
 #include <algorithm>
