@@ -736,6 +736,7 @@ struct DfArgs {
     int32_t* info;
     int r, nblk, item0, nbulk;
     int spin_limit;         // polls before a wait gives up
+    int last_by_32;         // see df_last_by_32
     float flag_below;
 };
 
@@ -826,6 +827,11 @@ __device__ __forceinline__ bool df_complete(DfW& w) {
 #pragma unroll
     for (int g = 0; g <= Q; ++g) ok = ok && df_written(v[g]);
     return __all(ok);
+}
+
+template <class F>
+__device__ __forceinline__ void for_groups(F f) {
+    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{}); f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
 }
 
 // a wave's wait on an exchange slot ends without what it waits for: spin limit, or the item's abort word
@@ -1003,6 +1009,36 @@ __device__ __forceinline__ void df_mma(f32x16& acc, const float (*Am)[LP], const
     }
 }
 
+// W as it lies in the registers of every wave -> LDS, row-major [k][n]; wave w writes column group w
+__device__ __forceinline__ void df_w_to_lds(float (*Wm)[LP], DfW& wv, int w, int l16, int kq) {
+    for_groups([&](auto Q) {
+        constexpr int q = decltype(Q)::value;
+        if (w != q) return;
+        const auto& v = df_group<q>(wv);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Wm[16 * g + 4 * kq + e][16 * q + l16] = g <= q ? v[g <= q ? g : 0][e] : 0.f;
+    });
+}
+
+// returns Am · W with W row-major [k][n] in LDS, 32×32×2 fp32 MFMA
+__device__ __forceinline__ f32x16 df_times_w(const float (*Am)[LP], const float (*Wm)[LP], int wr, int wc, int l32, int lh) {
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int g = 0; g < NB / 8; ++g) {
+        const float4 a4 = *reinterpret_cast<const float4*>(&Am[32 * wr + l32][8 * g + 4 * lh]);
+        const int k0 = 8 * g + 4 * lh, n = 32 * wc + l32;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, Wm[k0 + 0][n], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, Wm[k0 + 1][n], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, Wm[k0 + 2][n], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, Wm[k0 + 3][n], acc, 0, 0, 0);
+    }
+    return acc;
+}
+
 // accumulator (MFMA C layout: element v of a lane -> row 8*(v/4) + 4*lh + v%4, column l32 of the wave's
 // 32×32 quadrant) -> LDS tile, row-major with pitch P
 template <int P>
@@ -1094,11 +1130,6 @@ __device__ __forceinline__ void df_store_binv(const float (*src)[P], const float
             }
         }
     }
-}
-
-template <class F>
-__device__ __forceinline__ void for_groups(F f) {
-    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{}); f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
 }
 
 template <int NT>
@@ -1354,10 +1385,18 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
             df_acc_to_lds<LP>(Am, acc[s], wr, wc, l32, lh);
             df_load_groups(wv, slot_of(q, DF_SLOT_W), lane);
             __syncthreads();
+            // (the tile of df_last_by_32 is the last one dealt, so it is in the last register tile of its workgroup)
+            const bool by_32 = s == NT - 1 && a.last_by_32 && q == nb - 1 && rrow[s] == 2 * nb - 2;
             for_groups([&](auto Q) {
                 wait_group(Q, q);
-                df_l_group<decltype(Q)::value>(Am2, Am, wv, wave, l16, kq);
+                if (!by_32) df_l_group<decltype(Q)::value>(Am2, Am, wv, wave, l16, kq);
             });
+            if (by_32) {
+                df_w_to_lds(Bm, wv, wave, l16, kq);
+                __syncthreads();
+                const f32x16 pr = df_times_w(Am, Bm, wr, wc, l32, lh);
+                df_acc_to_lds<LP>(Am2, pr, wr, wc, l32, lh);
+            }
             __syncthreads();
             if (gave_up()) return;
             if (!ykind && rrow[s] == q + 3) df_store_slot<256>(slot_of(rrow[s], DF_SLOT_L3), Am2, tid);
@@ -1460,6 +1499,14 @@ int compute_units() {
     }
     return n;
 }
+// The last tile of the inverse that is a product with the last W, row nblk-2 of Y, is formed by the 32×32×2 matrix instruction where the
+// launch was once dealt so that a workgroup had two tiles of the last block column (three or four block rows, five from 29 items on 256
+// compute units), by the 16×16×4 one elsewhere.  The two add in another order, with the same precision: results keep their bits.
+// The detour through LDS comes once, at the end of the chain: 362.5 -> 363.6 µs for a basis (bf16, L = 576, d = 512, r = 256, one
+// iteration), 506 µs with and without it at batch 42.
+int df_last_by_32(int nblk, int items) {
+    return nblk >= 3 && nblk <= 5 && nblk - 1 > std::min(compute_units() / items - nblk, ((nblk - 1) * (nblk - 1) + 4) / 5);
+}
 // workgroups per item of the single-launch factorisation, 0 = shape not covered
 int dataflow_group(int nblk, int items, int& nt) {
     const int ntiles = df_bulk_tiles(nblk);
@@ -1505,6 +1552,7 @@ hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y
         a.S = S; a.Lf = Lf; a.Y = Y; a.dinv = dinv; a.Binv = Binv; a.Bh = Bh; a.Bl = Bl; a.flags = flags; a.info = info;
         a.wx = reinterpret_cast<float*>(flags + (size_t)batch * DF_FLAG_WORDS);
         a.spin_limit = g_df_spin_limit;
+        a.last_by_32 = df_last_by_32(nblk, per_launch);
         a.r = r; a.nblk = nblk; a.item0 = item0; a.nbulk = G - nblk > 0 ? G - nblk : 1; a.flag_below = flag_below;
         const dim3 grid(G, n), block(256);
         switch (nt) {

@@ -312,7 +312,11 @@ def _whole_numbers(n, seed):
 DIGESTS = {("f32", 1, 128, 64, 32, 4): ("1229367ac83f665d", "1229367ac83f665d"),
            ("f32", 2, 192, 320, 96, 1): ("a65e093e6fabd748", "2b6774bf9d5dd660"),
            ("bf16", 2, 128, 256, 64, 2): ("458e5216b2709520", "458e5216b2709520"),
-           ("bf16", 1, 512, 384, 128, 1): ("e4c095fd896ba470", "cd44cdbed4b3206e")}
+           ("bf16", 1, 512, 384, 128, 1): ("e4c095fd896ba470", "cd44cdbed4b3206e"),
+           # three, four and five block rows: the tile before the last of the inverse is formed by another instruction than the others
+           ("f32", 2, 320, 256, 160, 1): ("29fe5a667e119116", "cfc03f9069fb3883"),
+           ("bf16", 2, 512, 384, 256, 1): ("1b59f43d5971c0cc", "d0d7b1716439c964"),
+           ("bf16", 29, 640, 512, 320, 1): ("9efa08b04ccb3f6b", "1700362255381e74")}
 
 
 @pytest.mark.parametrize("mode", [0, 1])
