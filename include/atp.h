@@ -140,9 +140,10 @@ void atp_set_qr_passes(int first, int middle, int last);
 void atp_set_overlap(int on);
 
 /* How the r×r Cholesky factorisation (with inverse) inside every orthonormalisation round runs.
- * 1 (default): as ONE launch whenever r <= 2048 and the whole batch fits the chip (at r = 1024: up
- * to 4 sequences): a grid of co-resident workgroups keeps the 64×64 tiles in registers and passes
- * finished panel tiles through global memory and flags.  Every workgroup of that launch must be
+ * 1 (default): as ONE launch whenever r <= 2048 and the whole batch fits the chip (256 compute
+ * units: up to 85 sequences of r = 128, 42 of 256, 25 of 384, 16 of 512, 8 of 768, 4 of 1024 and
+ * 1152, 2 of 1536, 1 of 2048; any number up to r = 64): a grid of co-resident workgroups keeps the
+ * 64×64 tiles in registers and passes finished panel tiles through global memory and flags.  Every workgroup of that launch must be
  * resident at the same time, so while this mode is on, calls of atp_principal_bases must not
  * overlap in time with each other on one GPU (different streams or processes); a wait that gives
  * up makes the call return info = -1 for that sequence instead of hanging.  Larger batches take

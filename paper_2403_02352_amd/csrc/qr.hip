@@ -1507,12 +1507,18 @@ int compute_units() {
 int df_last_by_32(int nblk, int items) {
     return nblk >= 3 && nblk <= 5 && nblk - 1 > std::min(compute_units() / items - nblk, ((nblk - 1) * (nblk - 1) + 4) / 5);
 }
-// workgroups per item of the single-launch factorisation, 0 = shape not covered
+// Workgroups per item of the single-launch factorisation, 0 = shape not covered.  Five tiles per bulk workgroup: with three, 48 workgroups that
+// poll instead of 43 beside a spine of 16, four items of r = 1024 take 1425 µs against 1394 (bf16, L = 2112, d = 2048, one iteration), one of
+// r = 2048 2547 against 2539; short chains would like three (2 × r = 256 355 against 373, 1 × r = 1024 1123 against 1130).
+// Six tiles are what the registers hold, and a batch that needs them is taken: the launch per block column, which has no such limit, is slower
+// at every one of these shapes, 25 × r = 384 1104 against 794 µs, 16 × 512 1334 against 887, 8 × 768 1885 against 1193, 6 × 896 2175
+// against 1352, 4 × 1152 2717 against 1734, 2 × 1664 3768 against 2305 (bf16; fp32, where the products take most, 1.16 to 1.20 times), with
+// U against float64 the same to 1e-3 of its error.
 int dataflow_group(int nblk, int items, int& nt) {
     const int ntiles = df_bulk_tiles(nblk);
     if (nblk < 1 || nblk > DF_MAX_NBLK || items < 1) return 0;
     int room = compute_units() / items - nblk;   // bulk workgroups that fit beside the spine (one workgroup per compute unit)
-    const int enough = (ntiles + 4) / 5;     // five tiles per bulk workgroup keep up with the spine; more workgroups only idle
+    const int enough = (ntiles + 4) / 5;
     if (room > enough) room = enough;
     if (ntiles == 0) { nt = 1; return nblk; }
     if (room < 1) return 0;

@@ -316,7 +316,9 @@ DIGESTS = {("f32", 1, 128, 64, 32, 4): ("1229367ac83f665d", "1229367ac83f665d"),
            # three, four and five block rows: the tile before the last of the inverse is formed by another instruction than the others
            ("f32", 2, 320, 256, 160, 1): ("29fe5a667e119116", "cfc03f9069fb3883"),
            ("bf16", 2, 512, 384, 256, 1): ("1b59f43d5971c0cc", "d0d7b1716439c964"),
-           ("bf16", 29, 640, 512, 320, 1): ("9efa08b04ccb3f6b", "1700362255381e74")}
+           ("bf16", 29, 640, 512, 320, 1): ("9efa08b04ccb3f6b", "1700362255381e74"),
+           # six tiles per bulk workgroup, as many as the registers hold
+           ("f32", 19, 768, 640, 448, 1): ("43f5221234f19134", "37294b199648131a")}
 
 
 @pytest.mark.parametrize("mode", [0, 1])
@@ -367,6 +369,38 @@ def test_factorisation_at_every_edge(atp, r):
         print(r, b, rel_fro(U[1][b], Uo), rel_fro(U[1][b], U[0][b]), flush=True)
         assert rel_fro(U[1][b], Uo) <= 1e-4
         assert (U[0][b] == U[1][b]).all() if r <= 64 else rel_fro(U[1][b], U[0][b]) <= 50 * np.sqrt(r) * 2.0 ** -24
+
+
+# the largest batches that one launch takes: six tiles per bulk workgroup, 250, 256 (every compute unit) and 253 workgroups; one sequence more
+# takes the other form
+@pytest.mark.parametrize("batch,r,one_launch", [(25, 384, True), (16, 512, True), (11, 640, True), (17, 512, False)])
+def test_factorisation_of_the_largest_batches(atp, batch, r, one_launch):
+    """Modes 0 and 1 give the same bits exactly where mode 1 takes the launch per block column.  Otherwise U differs by rounding, 2^-24 per term of
+    sums of up to r and the condition number that R^-1 magnifies it by.  |U'U - I| is 7.5 to 9.5 * 2^-24 per column in both forms
+    (against float64); 15 is allowed."""
+    L, d = 2 * r + 64, 2 * r
+    X, Om = rnd((batch, L, d), 21).astype(np.float32), wl.make_omega(d, r, 3)
+    cond = max(np.linalg.cond(X[b].astype(np.float64) @ Om) for b in range(batch))
+    U = []
+    for mode in (0, 1, 1):
+        atp.set_factor_mode(mode)
+        try:
+            u, _, info, _ = atp.principal_bases(to_dev(X, "f32"), r, 0, to_dev(Om, "f32"))
+            torch.cuda.synchronize()
+        finally:
+            atp.set_factor_mode(True)
+        assert (info == 0).all()
+        U.append(u)
+    assert torch.equal(U[1], U[2]) and torch.equal(U[0], U[1]) != one_launch
+    eye, worst = torch.eye(r, dtype=torch.float64, device="cuda"), 0.0
+    for u in U[:2]:
+        orth = max(torch.linalg.norm(u[b].double().T @ u[b].double() - eye).item() for b in range(batch))
+        print(batch, r, cond, orth / np.sqrt(r) * 2 ** 24, flush=True)
+        assert orth <= 15 * np.sqrt(r) * 2.0 ** -24
+    for b in range(batch):
+        worst = max(worst, rel_fro(to_host(U[1][b]), to_host(U[0][b])))
+    print(worst, cond * np.sqrt(r) * 2.0 ** -24, flush=True)
+    assert worst <= cond * np.sqrt(r) * 2.0 ** -24
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
