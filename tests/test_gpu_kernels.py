@@ -350,7 +350,7 @@ def test_extraction_keeps_its_bits(atp, case, mode):
 def test_factorisation_at_every_edge(atp, r):
     """One orthonormalisation against the oracle (fp32, conditioned like X·Omega of a flat spectrum: 1e-4), and the two forms of the factorisation
     against each other: a single block is the same chain of multiply-adds in both, so the same bits; more differ by rounding, 2^-24 per
-    term of sums of up to r and the condition number (below 50) that R^-1 magnifies it by."""
+    term of sums of up to r and the condition number of X·Omega that R^-1 magnifies it by (7 at r = 257, 82 at 449)."""
     batch, L, d = 3, 560, 470
     X = np.stack([wl.make_X(L, d, np.sqrt(L) * np.linspace(1.0, 0.5, d), 0.0, 60 + b) for b in range(batch)]).astype(np.float32)
     Om = wl.make_omega(d, r, 3)
@@ -368,7 +368,8 @@ def test_factorisation_at_every_edge(atp, r):
         Uo, _ = oracle.principal_bases(X[b].astype(np.float64), Om.astype(np.float64), 0)
         print(r, b, rel_fro(U[1][b], Uo), rel_fro(U[1][b], U[0][b]), flush=True)
         assert rel_fro(U[1][b], Uo) <= 1e-4
-        assert (U[0][b] == U[1][b]).all() if r <= 64 else rel_fro(U[1][b], U[0][b]) <= 50 * np.sqrt(r) * 2.0 ** -24
+        cond = np.linalg.cond(X[b].astype(np.float64) @ Om)
+        assert (U[0][b] == U[1][b]).all() if r <= 64 else rel_fro(U[1][b], U[0][b]) <= cond * np.sqrt(r) * 2.0 ** -24
 
 
 # the largest batches that one launch takes: six tiles per bulk workgroup, 250, 256 (every compute unit) and 253 workgroups; one sequence more
