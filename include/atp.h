@@ -110,6 +110,8 @@ atp_status atp_init(void);
  *                                were not all resident, see atp_set_factor_mode; or
  *                                the input was not finite).  May be NULL.
  *  workspace                     device, ≥ atp_principal_bases_workspace bytes
+ *                                (a size of this build of the library, good for
+ *                                every mode: ask for it, do not store it)
  *
  * Errors: ATP_ERR_INVALID_ARG (null X/U_r/B_r, batch/L/d < 1, iters < 0, bad t,
  * misaligned pointer), ATP_ERR_BAD_RANK (r < 1 or r > min(L, d)),

@@ -136,7 +136,7 @@ struct BasesWs {
     float* Linv;     // [batch, rp, rp]
     float* dinv;     // [batch, rp]
     int32_t* info;   // [batch]
-    unsigned* flags; // hand-over flags of the single-launch factorisation
+    unsigned* flags; // hand-over flags and exchange slots of the single-launch factorisation, for the items of one launch
     BasesDims dim;
     size_t total;
 };
@@ -400,16 +400,16 @@ atp_status cholesky_qr(hipStream_t st, bool mfma, bool final_qr, bool middle, in
             const float flag_below = certify ? 1e-3f : 2e-6f, sh = certify ? 0.f : shift;
             float* b32 = mfma ? nullptr : w.Linv;
             bf16_t *bh = mfma ? linv.hi() : nullptr, *bl = mfma ? linv.lo() : nullptr;
-            const bool single = dataflow && r <= 64;
-            if (!single)
-                ATP_HIP(gram_prepare(st, w.Spart, nparts, (int64_t)batch * r * r, w.S, w.dinv, w.Y, b32, bh, bl, r, r_true, sh, zero_all, batch,
-                                     dataflow ? w.flags : nullptr));
-            if (single)
-                ATP_HIP(factor_inverse_single(st, w.Spart, nparts, (int64_t)batch * r * r, w.dinv, b32, bh, bl, r, r_true, sh, info, flag_below, batch));
-            else if (dataflow)
-                ATP_HIP(factor_inverse_dataflow(st, w.S, w.Lf, w.Y, w.dinv, b32, bh, bl, w.flags, r, info, flag_below, batch));
-            else
+            const int64_t pstride = (int64_t)batch * r * r;
+            if (dataflow && r <= 64) {
+                ATP_HIP(factor_inverse_single(st, w.Spart, nparts, pstride, w.dinv, b32, bh, bl, r, r_true, sh, info, flag_below, batch));
+            } else if (dataflow) {
+                ATP_HIP(factor_inverse_dataflow(st, w.Spart, nparts, pstride, w.S, w.dinv, w.Lf, w.Y, b32, bh, bl, w.flags, r, r_true, sh, zero_all, info,
+                                                flag_below, batch));
+            } else {
+                ATP_HIP(gram_prepare(st, w.Spart, nparts, pstride, w.S, w.dinv, w.Y, b32, bh, bl, r, r_true, sh, zero_all, batch, nullptr));
                 ATP_HIP(factor_inverse(st, w.S, w.Lf, w.Y, w.dinv, b32, bh, bl, r, info, flag_below, batch, pipe ? pipe_after : nullptr, &pc));
+            }
         }
         if (pipe) {
             hipEvent_t e = side_event();

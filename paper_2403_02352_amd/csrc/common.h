@@ -202,10 +202,11 @@ hipError_t factor_inverse(hipStream_t st, float* S, float* Lf, float* Y, const f
                           bf16_t* Bl, int r, int32_t* info, float flag_below, int batch,
                           hipError_t (*after)(void* ctx, int j) = nullptr, void* ctx = nullptr);
 
-// The same factorisation as ONE launch per group of items: co-resident workgroups keep their tiles in
-// registers and hand finished panel tiles to each other through global memory and per-tile flags
-// (`flags`: factor_dataflow_flag_bytes(r, batch) bytes, cleared by gram_prepare when passed there).
-// Covers r <= 2048 when a group of workgroups fits the chip (factor_dataflow_ok); needs every
+// gram_prepare and the same factorisation as ONE launch per group of items: co-resident workgroups keep their tiles in
+// registers and hand finished panel tiles to each other through global memory, with a flag per tile or, on the critical
+// path, through exchange slots whose content says whether it has arrived (`flags`: factor_dataflow_flag_bytes(r, batch)
+// bytes; gram_prepare clears the flags and arms the slots, for every launch anew).
+// Covers 64 < r <= 2048 when a group of workgroups fits the chip (factor_dataflow_ok); needs every
 // workgroup of a launch resident at the same time, so it must not share the GPU with another such
 // launch.  Lf and Y receive the panel tiles (scratch).  info = -1 if a wait inside the kernel gave up.
 // factor_dataflow_ok: the shape is covered; with whole_batch, also that all items fit ONE launch (items
@@ -215,9 +216,9 @@ bool factor_dataflow_ok(int r, int batch, bool whole_batch);
 size_t factor_dataflow_flag_bytes(int r, int batch);
 // polls after which a wait inside the kernel gives up (< 1: the default, far beyond any healthy wait)
 void factor_dataflow_set_spin_limit(int polls);
-hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y, const float* dinv, float* Binv,
-                                   bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int32_t* info, float flag_below,
-                                   int batch);
+hipError_t factor_inverse_dataflow(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* S, float* dinv, float* Lf, float* Y,
+                                   float* Binv, bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int r_true, float shift, int zero_all,
+                                   int32_t* info, float flag_below, int batch);
 
 // gram_prepare and the factorisation in one launch of a workgroup per item, for r <= 64 (a single block row; nobody waits for anybody)
 hipError_t factor_inverse_single(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* dinv, float* Binv, bf16_t* Bh, bf16_t* Bl,

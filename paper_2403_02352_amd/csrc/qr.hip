@@ -734,7 +734,7 @@ struct DfArgs {
     unsigned* flags;
     float* wx;              // exchange slots, df_wx_words(nblk) per item
     int32_t* info;
-    int r, nblk, item0, nbulk;
+    int r, nblk, nbulk;
     int spin_limit;         // polls before a wait gives up
     int last_by_32;         // see df_last_by_32
     float flag_below;
@@ -1148,7 +1148,7 @@ __global__ void __launch_bounds__(256, 1) factor_dataflow_kernel(DfArgs a) {
     float (*Lm2)[LP] = reinterpret_cast<float (*)[LP]>(lds_m);
     float (*Tm)[LP] = reinterpret_cast<float (*)[LP]>(lds_t);
 
-    const int b = a.item0 + blockIdx.y;
+    const int b = blockIdx.y;
     const int r = a.r, nb = a.nblk;
     const int64_t boff = (int64_t)b * r * r;
     float* Sb = a.S + boff;
@@ -1537,29 +1537,45 @@ bool factor_dataflow_ok(int r, int batch, bool whole_batch) {
     return dataflow_group(nblk, whole_batch ? batch : 1, nt) != 0;
 }
 
-// per item: the flag words, then (after the flags of all items) the exchange slots
 void factor_dataflow_set_spin_limit(int polls) { g_df_spin_limit = polls >= 1 ? polls : DF_SPIN_LIMIT; }
 
+namespace {
+// items of a launch: as many as keep every workgroup of it resident at once
+int dataflow_items(int nblk, int batch) {
+    int nt, n = std::min(batch, compute_units());
+    while (n > 0 && dataflow_group(nblk, n, nt) == 0) --n;
+    return n;
+}
+}  // namespace
+
+// for the items of one launch, which the next launch takes over: the flag words, then the exchange slots
 size_t factor_dataflow_flag_bytes(int r, int batch) {
-    return (size_t)batch * (DF_FLAG_WORDS + df_wx_words(std::min((r + NB - 1) / NB, DF_MAX_NBLK))) * sizeof(unsigned);
+    const int nblk = (r + NB - 1) / NB;
+    if (nblk < 2) return 0;   // (factor_inverse_single has nothing to hand over)
+    return (size_t)dataflow_items(nblk, batch) * (DF_FLAG_WORDS + df_wx_words(nblk)) * sizeof(unsigned);
 }
 
-hipError_t factor_inverse_dataflow(hipStream_t st, float* S, float* Lf, float* Y, const float* dinv, float* Binv,
-                                   bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int32_t* info, float flag_below,
-                                   int batch) {
-    const int nblk = (r + NB - 1) / NB;
-    // as many items per launch as keep every workgroup of the launch resident at once
-    int per_launch = batch, nt = 0, G = 0;
-    while (per_launch >= 1 && (G = dataflow_group(nblk, per_launch, nt)) == 0) --per_launch;
-    if (per_launch < 1) return hipErrorInvalidValue;
+hipError_t factor_inverse_dataflow(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* S, float* dinv, float* Lf, float* Y,
+                                   float* Binv, bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int r_true, float shift, int zero_all,
+                                   int32_t* info, float flag_below, int batch) {
+    const int nblk = (r + NB - 1) / NB, per_launch = dataflow_items(nblk, batch);
+    int nt = 0;
+    if (nblk < 2 || per_launch < 1) return hipErrorInvalidValue;
+    const int G = dataflow_group(nblk, per_launch, nt);
     for (int item0 = 0; item0 < batch; item0 += per_launch) {
-        const int n = (batch - item0 < per_launch) ? batch - item0 : per_launch;
+        const int n = std::min(batch - item0, per_launch);
+        const int64_t o = (int64_t)item0 * r * r;
         DfArgs a;
-        a.S = S; a.Lf = Lf; a.Y = Y; a.dinv = dinv; a.Binv = Binv; a.Bh = Bh; a.Bl = Bl; a.flags = flags; a.info = info;
-        a.wx = reinterpret_cast<float*>(flags + (size_t)batch * DF_FLAG_WORDS);
+        a.S = S + o; a.Lf = Lf + o; a.Y = Y + o; a.dinv = dinv + (int64_t)item0 * r;
+        a.Binv = Binv ? Binv + o : nullptr; a.Bh = Bh ? Bh + o : nullptr; a.Bl = Bl ? Bl + o : nullptr;
+        a.flags = flags; a.info = info ? info + item0 : nullptr;
+        a.wx = reinterpret_cast<float*>(flags + (size_t)n * DF_FLAG_WORDS);
         a.spin_limit = g_df_spin_limit;
         a.last_by_32 = df_last_by_32(nblk, per_launch);
-        a.r = r; a.nblk = nblk; a.item0 = item0; a.nbulk = G - nblk > 0 ? G - nblk : 1; a.flag_below = flag_below;
+        a.r = r; a.nblk = nblk; a.nbulk = G - nblk; a.flag_below = flag_below;
+        const hipError_t e = gram_prepare(st, Spart + o, nparts, pstride, a.S, dinv + (int64_t)item0 * r, a.Y, a.Binv, a.Bh, a.Bl, r, r_true, shift,
+                                          zero_all, n, flags);
+        if (e != hipSuccess) return e;
         const dim3 grid(G, n), block(256);
         switch (nt) {
             case 1: hipLaunchKernelGGL(factor_dataflow_kernel<1>, grid, block, 0, st, a); break;

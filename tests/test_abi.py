@@ -239,3 +239,18 @@ def test_factor_mode_setter_clamps(lib):
     for v in (-3, 0, 1, 2, 99):
         lib.atp_set_factor_mode(v)      # host-side setter: any value is accepted and clamped to 0..2
     lib.atp_set_factor_mode(1)
+
+
+# (batch, r, sequences whose flags and slots are reserved): a single block column, what one launch takes and one more, beyond 2048 columns
+@pytest.mark.parametrize("batch,r,items", [(1, 64, 0), (1000, 32, 0), (4, 128, 4), (85, 128, 85), (86, 128, 85), (4, 1024, 4), (8, 1024, 4),
+                                           (1, 2048, 1), (32, 2048, 1), (1, 2112, 0), (4, 4096, 0)])
+def test_workspace_holds_exchange_slots_only_for_one_launch(lib, batch, r, items):
+    """atp_principal_bases_workspace, fp32 without padding, piece by piece in blocks of 256 bytes: the flags (2112 words) and slots (5 tiles of
+    64 x 64 per 64 columns) of the single-launch factorisation come on top for the sequences that share a launch, and only where it can run."""
+    L, d = 4 * r, 2 * r
+    up = lambda n: (n + 255) // 256 * 256
+    pieces = [batch * d * L, d * r, d * r] + 4 * [batch * L * r] + 4 * [batch * d * r] + [batch * r * L, batch * r * d, 8 * batch * r * r]
+    pieces += 4 * [batch * r * r] + [batch * r, batch]
+    base = sum(up(4 * n) for n in pieces)
+    slots = up(4 * items * (2112 + (r + 63) // 64 * 5 * 4096))
+    assert lib.atp_principal_bases_workspace(batch, L, d, r, 2, F32) == base + slots

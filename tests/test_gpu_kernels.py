@@ -417,6 +417,24 @@ def test_factorisation_stays_within_the_workspace(atp, dtype, r):
     assert (buf[need:] == 0xA5).all() and (out[2] == 0).all()
 
 
+@pytest.mark.parametrize("batch,r", [(5, 64), (44, 256), (33, 330)])
+def test_factorisation_in_groups_stays_within_the_workspace(atp, batch, r):
+    """Mode 2 with batches beyond one launch (42 and 32 sequences fit), and a single block column: flags and slots are those of one launch, taken
+    over by the next, with nothing written behind them and the bits of the same sequences in one launch."""
+    X, Om = to_dev(rnd((batch, 400, 352), 8), "f32"), to_dev(wl.make_omega(352, r, 3), "f32")
+    need = atp.binding.principal_bases_workspace(batch, 400, 352, r, 1, torch.float32)
+    buf = torch.full((need + (1 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+    atp.set_factor_mode(2)
+    try:
+        U, B, info, _ = atp.principal_bases(X, r, 1, Om, workspace=buf[:need])
+        one = atp.principal_bases(X[batch - 3:].contiguous(), r, 1, Om)
+        torch.cuda.synchronize()
+    finally:
+        atp.set_factor_mode(True)
+    assert (buf[need:] == 0xA5).all() and (info == 0).all()
+    assert torch.equal(U[batch - 3:], one[0]) and torch.equal(B[batch - 3:], one[1])
+
+
 def test_every_nan_is_flagged(atp):
     """The factorisation marks what has not been handed over yet with the NaN of all ones: as an input it is a NaN like any other."""
     X = rnd((3, 300, 280), 5).astype(np.float32)
