@@ -31,10 +31,8 @@ constexpr int NB = 64;  // block size of the factorisation
 #ifdef ATP_DF_TRACE
 __device__ long long g_df_trace[1024];
 #define DF_STAMP(idx) do { if (blockIdx.y == 0 && threadIdx.x == 0) g_df_trace[idx] = wall_clock64(); } while (0)
-#define DF_CYC(idx) do { if (blockIdx.y == 0 && blockIdx.x == 1 && threadIdx.x == 0) g_df_trace[idx] = __builtin_readcyclecounter(); } while (0)
 #else
 #define DF_STAMP(idx) do { } while (0)
-#define DF_CYC(idx) do { } while (0)
 #endif
 
 // ---------------------------------------------------------------------------
@@ -1515,17 +1513,12 @@ int df_last_by_32(int nblk, int items) {
 // against 1352, 4 × 1152 2717 against 1734, 2 × 1664 3768 against 2305 (bf16; fp32, where the products take most, 1.16 to 1.20 times), with
 // U against float64 the same to 1e-3 of its error.
 int dataflow_group(int nblk, int items, int& nt) {
-    const int ntiles = df_bulk_tiles(nblk);
-    if (nblk < 1 || nblk > DF_MAX_NBLK || items < 1) return 0;
-    int room = compute_units() / items - nblk;   // bulk workgroups that fit beside the spine (one workgroup per compute unit)
-    const int enough = (ntiles + 4) / 5;
-    if (room > enough) room = enough;
-    if (ntiles == 0) { nt = 1; return nblk; }
-    if (room < 1) return 0;
-    const int nbulk = room < ntiles ? room : ntiles;
+    if (nblk < 2 || nblk > DF_MAX_NBLK || items < 1) return 0;
+    const int ntiles = df_bulk_tiles(nblk), room = compute_units() / items - nblk;   // (one workgroup per compute unit)
+    const int nbulk = std::min(room, (ntiles + 4) / 5);
+    if (nbulk < 1) return 0;
     nt = (ntiles + nbulk - 1) / nbulk;
-    if (nt > 6) return 0;
-    return nblk + nbulk;
+    return nt > 6 ? 0 : nblk + nbulk;
 }
 }  // namespace
 
@@ -1533,6 +1526,7 @@ bool factor_dataflow_ok(int r, int batch, bool whole_batch) {
     const int nblk = (r + NB - 1) / NB;
     int nt;
     if (batch < 1) return false;
+    if (nblk == 1) return true;   // factor_inverse_single: workgroups that wait for nobody
     // the whole batch in one launch, or at least one item per launch
     return dataflow_group(nblk, whole_batch ? batch : 1, nt) != 0;
 }
@@ -1551,7 +1545,6 @@ int dataflow_items(int nblk, int batch) {
 // for the items of one launch, which the next launch takes over: the flag words, then the exchange slots
 size_t factor_dataflow_flag_bytes(int r, int batch) {
     const int nblk = (r + NB - 1) / NB;
-    if (nblk < 2) return 0;   // (factor_inverse_single has nothing to hand over)
     return (size_t)dataflow_items(nblk, batch) * (DF_FLAG_WORDS + df_wx_words(nblk)) * sizeof(unsigned);
 }
 
@@ -1560,7 +1553,7 @@ hipError_t factor_inverse_dataflow(hipStream_t st, const float* Spart, int npart
                                    int32_t* info, float flag_below, int batch) {
     const int nblk = (r + NB - 1) / NB, per_launch = dataflow_items(nblk, batch);
     int nt = 0;
-    if (nblk < 2 || per_launch < 1) return hipErrorInvalidValue;
+    if (per_launch < 1) return hipErrorInvalidValue;
     const int G = dataflow_group(nblk, per_launch, nt);
     for (int item0 = 0; item0 < batch; item0 += per_launch) {
         const int n = std::min(batch - item0, per_launch);
@@ -1577,9 +1570,8 @@ hipError_t factor_inverse_dataflow(hipStream_t st, const float* Spart, int npart
                                           zero_all, n, flags);
         if (e != hipSuccess) return e;
         const dim3 grid(G, n), block(256);
-        switch (nt) {
+        switch (nt) {   // (2 does not occur: two block rows have one tile, more have at least three to a workgroup)
             case 1: hipLaunchKernelGGL(factor_dataflow_kernel<1>, grid, block, 0, st, a); break;
-            case 2: hipLaunchKernelGGL(factor_dataflow_kernel<2>, grid, block, 0, st, a); break;
             case 3: hipLaunchKernelGGL(factor_dataflow_kernel<3>, grid, block, 0, st, a); break;
             case 4: hipLaunchKernelGGL(factor_dataflow_kernel<4>, grid, block, 0, st, a); break;
             case 5: hipLaunchKernelGGL(factor_dataflow_kernel<5>, grid, block, 0, st, a); break;
