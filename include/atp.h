@@ -105,10 +105,11 @@ atp_status atp_init(void);
  *                                not be orthonormal.  A column whose pivot is at
  *                                noise level (<= 1e-6 of its scaled norm) is
  *                                dropped (zero column) rather than divided by,
- *                                so finite input gives finite output.  -1: a wait inside the
+ *                                so finite input gives finite output; input that is not
+ *                                finite gives j > 0 for its sequence.  -1: a wait inside the
  *                                single-launch factorisation gave up (its workgroups
- *                                were not all resident, see atp_set_factor_mode; or
- *                                the input was not finite).  May be NULL.
+ *                                were not all resident, see atp_set_factor_mode).
+ *                                May be NULL.
  *  workspace                     device, ≥ atp_principal_bases_workspace bytes
  *                                (a size of this build of the library, good for
  *                                every mode: ask for it, do not store it)
@@ -145,11 +146,13 @@ void atp_set_overlap(int on);
  * 1 (default): as ONE launch whenever r <= 2048 and the whole batch fits the chip (256 compute
  * units: up to 85 sequences of r = 128, 42 of 256, 25 of 384, 16 of 512, 8 of 768, 4 of 1024 and
  * 1152, 2 of 1536, 1 of 2048; any number up to r = 64): a grid of co-resident workgroups keeps the
- * 64×64 tiles in registers and passes finished panel tiles through global memory and flags.  Every workgroup of that launch must be
- * resident at the same time, so while this mode is on, calls of atp_principal_bases must not
- * overlap in time with each other on one GPU (different streams or processes); a wait that gives
- * up makes the call return info = -1 for that sequence instead of hanging.  Larger batches take
- * the launch-per-block-column form, whose launches cover all sequences at once.
+ * 64×64 tiles in registers and passes finished panel tiles through global memory, with flags or,
+ * on the critical path, as data that show by themselves that they have arrived.  Every workgroup of
+ * that launch must be resident at the same time, so while this mode is on, calls of
+ * atp_principal_bases must not overlap in time with each other on one GPU (different streams or
+ * processes); a wait that gives up makes the call return info = -1 for that sequence instead of
+ * hanging.  Larger batches take the launch-per-block-column form, whose launches cover all sequences
+ * at once.
  * 2: the single-launch form also for larger batches, as several launches one after the other
  * (measured slower than mode 0 from batch 8 on at r = 1024; kept for tests and measurements).
  * 0: one launch per 64-wide block column (no residency requirement; at small batch slower: the
@@ -159,8 +162,10 @@ void atp_set_factor_mode(int mode);
 
 /* Number of polls after which a wait inside the single-launch factorisation gives up (the call then
  * reports info = -1 for that sequence and every workgroup of it exits).  The default (any value
- * < 1 restores it) is about 4 million polls, seconds beyond any healthy wait; a tiny value makes
- * every wait give up at once, which is how the tests exercise that path.  Process-wide.  Host call. */
+ * < 1 restores it) is about 4 million polls of a flag, seconds, and an eighth as many for a wait on
+ * data, some tenths of a second: far beyond any healthy wait, which takes microseconds.  A tiny value
+ * makes every wait give up at once, which is how the tests exercise that path.  Process-wide.  Host
+ * call. */
 void atp_set_factor_spin_limit(int polls);
 
 /* Gram matrix of the SHIFTED (conditioning-only) CholeskyQR rounds on the ATP_BF16 path.

@@ -435,15 +435,54 @@ def test_factorisation_in_groups_stays_within_the_workspace(atp, batch, r):
     assert torch.equal(U[batch - 3:], one[0]) and torch.equal(B[batch - 3:], one[1])
 
 
-def test_every_nan_is_flagged(atp):
-    """The factorisation marks what has not been handed over yet with the NaN of all ones: as an input it is a NaN like any other."""
-    X = rnd((3, 300, 280), 5).astype(np.float32)
-    for b, bits in ((0, 0xFFFFFFFF), (2, 0x7FC00000)):
-        X[b, 17, 33] = np.uint32(bits).view(np.float32)
-    _, _, info, _ = atp.principal_bases(to_dev(X, "f32"), 260, 1, to_dev(wl.make_omega(280, 260, 3), "f32"))
+@pytest.mark.parametrize("bits", [0xFFFFFFFF, 0x7FFFFFFF, 0x7FC00000, 0xFFC00000])
+def test_every_nan_is_flagged(atp, bits):
+    """The factorisation marks what has not been handed over yet with the NaN of all ones, so no other entry may look like it.  The fp32 products
+    carry the bits of a NaN along: the workspace of one round shows that those of the input are the ones in the Gram matrix, and that set-up
+    leaves the one NaN 0x7fc00000 in S' whatever came in.  The call flags the sequence, with and without iterations, and no other."""
+    batch, L, d, r = 3, 300, 280, 260                     # (multiples of 4: the fp32 path pads nothing)
+    X = rnd((batch, L, d), 5).astype(np.float32)
+    X[0, 17, 33] = np.uint32(bits).view(np.float32)
+    Xd, Om = to_dev(X, "f32"), to_dev(wl.make_omega(d, r, 3), "f32")
+    assert Xd.view(torch.int32)[0, 17, 33].item() & 0xFFFFFFFF == bits
+    ws = torch.zeros(atp.binding.principal_bases_workspace(batch, L, d, r, 0, torch.float32), dtype=torch.uint8, device="cuda")
+    try:
+        atp.set_qr_passes(2, 1, 1)
+        _, _, info, _ = atp.principal_bases(Xd, r, 0, Om, workspace=ws)
+        torch.cuda.synchronize()
+    finally:
+        atp.set_qr_passes(2, 1, 2)
+    words = [batch * d * L, d * r, d * r] + 4 * [batch * L * r] + 4 * [batch * d * r] + [batch * r * L, batch * r * d]
+    at = sum((4 * n + 255) // 256 * 256 for n in words)
+    nans = []
+    for n in (batch * r * r, batch * r * r):              # the Gram matrix (of eight places for parts, fp32 takes one) and S'
+        v = ws[at:at + 4 * n].view(torch.int32).cpu().numpy().view(np.uint32)
+        nans.append(set(v[np.isnan(v.view(np.float32))].tolist()))
+        at += (8 * 4 * n + 255) // 256 * 256
+    print(hex(bits), info.tolist(), [[hex(x) for x in n] for n in nans], flush=True)
+    assert nans == [{bits}, {0x7FC00000}]
+    assert info[0] > 0 and (info[1:] == 0).all()
+    _, _, info, _ = atp.principal_bases(Xd, r, 1, Om)
     torch.cuda.synchronize()
-    print(info.tolist(), flush=True)
-    assert info[1] == 0 and info[0] > 0 and info[2] > 0
+    assert info[0] > 0 and (info[1:] == 0).all()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("r", [1, 5, 64, 65, 193, 260])
+def test_input_that_is_not_finite_gives_a_positive_info(atp, r, dtype, mode):
+    """info = -1 is kept for a wait that gave up: an infinity or a NaN gives a positive number, in every form of the factorisation
+    (the padding of the rank counts as columns here: infinity times its zeros is a NaN)."""
+    X = rnd((3, 300, 280), 5)
+    X[0, 17, 33], X[2, 299, 0] = np.inf, np.nan
+    atp.set_factor_mode(mode)
+    try:
+        _, _, info, _ = atp.principal_bases(to_dev(X, dtype), r, 1, to_dev(wl.make_omega(280, r, 3), "f32"))
+        torch.cuda.synchronize()
+    finally:
+        atp.set_factor_mode(True)
+    print(r, dtype, mode, info.tolist(), flush=True)
+    assert info[0] > 0 and info[1] == 0 and info[2] > 0
 
 
 # (L, d, r, iters): extents that are no multiple of 32, alone and together
