@@ -219,7 +219,8 @@ __device__ __forceinline__ void elim_block(float (&reg)[32], ElimLds& L, int sel
 //    chain of multiply-adds as column by column;
 //  * the other columns, the scaling of the final ones and their stores run in waves 1 to 3 while wave 0 is in the next stage;
 //  * the stages are one loop: the code runs cold in every workgroup, and four copies of it took 2.4 µs to fetch.
-// A chain of 64 pivots in one wave: bound by instruction issue (about 21 per pivot at 4.5 cycles).
+// A chain of 64 pivots: 3050 cycles per stage, 1700 of them the panel of 16 columns in one wave, bound by instruction issue (about 21 per pivot
+// at 4.5 cycles), the rest the update of the next stage's columns on the matrix cores, two barriers and two round trips through LDS.
 // ---------------------------------------------------------------------------
 constexpr int EP = 20;   // row pitch of a 64×16 column block in LDS (16-byte aligned rows; reads and writes of 16 rows fall into different banks)
 struct alignas(16) Elim2Lds {
@@ -709,7 +710,7 @@ __global__ void __launch_bounds__(256, 2) factor_step_kernel(float* S, float* Lf
 // workgroup that spins too long raises the item's abort word, sets info = -1 and exits; every other
 // wait of that item then ends as well.
 // ---------------------------------------------------------------------------
-constexpr int DF_SPIN_LIMIT = 1 << 22;   // polls of ~0.1-0.3 µs each: well beyond any healthy wait
+constexpr int DF_SPIN_LIMIT = 1 << 22;   // polls of a flag, each a round trip through memory: seconds, well beyond any healthy wait
 constexpr int DF_MAX_NBLK = 32;
 constexpr int DF_FLAG_WORDS = 2 * DF_MAX_NBLK * DF_MAX_NBLK + 64;   // per item; the last 64 words hold the abort word
 // Exchange slots: what the critical path of the factorisation waits for travels without a flag.  A slot (a dense 64×64 tile) is armed with a
@@ -832,7 +833,8 @@ __device__ __forceinline__ void for_groups(F f) {
     f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{}); f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
 }
 
-// a wave's wait on an exchange slot ends without what it waits for: spin limit, or the item's abort word
+// a wave's wait on an exchange slot ends without what it waits for: an eighth of the spin limit of a flag (a poll of data reads 1 to 22
+// pieces of 16 bytes per lane, 1 µs and more), or the item's abort word
 __device__ __forceinline__ bool df_gives_up(int spins, unsigned* abort_w, int spin_limit) {
     return spins > spin_limit / 8 || ((spins & 63) == 63 && __hip_atomic_load(abort_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
