@@ -154,7 +154,8 @@ void atp_set_overlap(int on);
  * hanging.  Larger batches take the launch-per-block-column form, whose launches cover all sequences
  * at once.
  * 2: the single-launch form also for larger batches, as several launches one after the other
- * (measured slower than mode 0 from batch 8 on at r = 1024; kept for tests and measurements).
+ * (r = 1024: 14.2 against 15.8 ms for a layer of 8 sequences, 30.1 against 29.3 for 16, 61 against
+ * 58 for 32; kept for tests and measurements).
  * 0: one launch per 64-wide block column (no residency requirement; at small batch slower: the
  * chain of launches is latency-bound).  Results of the modes agree to rounding.  Values outside
  * 0..2 are clamped.  Process-wide.  Host call. */

@@ -210,8 +210,9 @@ hipError_t factor_inverse(hipStream_t st, float* S, float* Lf, float* Y, const f
 // workgroup of a launch resident at the same time, so it must not share the GPU with another such
 // launch.  Lf and Y receive the panel tiles (scratch).  info = -1 if a wait inside the kernel gave up.
 // factor_dataflow_ok: the shape is covered; with whole_batch, also that all items fit ONE launch (items
-// beyond that run as further launches one after the other, which costs more than the launch-per-block-column
-// factorisation, whose launches take all items at once).
+// beyond that run as further launches one after the other; from four launches on that costs more than the
+// launch-per-block-column factorisation, whose launches take all items at once: r = 1024, 14 factorisations of 16 items
+// 9.2 against 8.7 ms, of 8 items 4.6 against 5.9).
 bool factor_dataflow_ok(int r, int batch, bool whole_batch);
 size_t factor_dataflow_flag_bytes(int r, int batch);
 // polls after which a wait inside the kernel gives up (< 1: the default, far beyond any healthy wait)
