@@ -1484,17 +1484,18 @@ __global__ void __launch_bounds__(256, 1) factor_single_kernel(const float* __re
 
 namespace {
 int g_df_spin_limit = DF_SPIN_LIMIT;
+constexpr int DF_MAX_CU = 256;   // an MI355X; a partition of one has fewer
 // compute units of the current device (the single-launch factorisation runs one workgroup on each and needs them
-// all resident at once); 256 on an MI355X, asked once so that a partitioned or smaller device is sized correctly
+// all resident at once), asked once so that a partitioned or smaller device is sized correctly
 int compute_units() {
     static int n = 0;
     if (n == 0) {
         int dev = 0, v = 0;
         if (hipGetDevice(&dev) == hipSuccess &&
             hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-            n = v;
+            n = std::min(v, DF_MAX_CU);
         else
-            n = 256;
+            n = DF_MAX_CU;
         (void)hipGetLastError();
     }
     return n;
@@ -1514,9 +1515,9 @@ int df_last_by_32(int nblk, int items) {
 // at every one of these shapes, 25 × r = 384 1104 against 794 µs, 16 × 512 1334 against 887, 8 × 768 1885 against 1193, 6 × 896 2175
 // against 1352, 4 × 1152 2717 against 1734, 2 × 1664 3768 against 2305 (bf16; fp32, where the products take most, 1.16 to 1.20 times), with
 // U against float64 the same to 1e-3 of its error.
-int dataflow_group(int nblk, int items, int& nt) {
+int dataflow_group(int nblk, int items, int cus, int& nt) {
     if (nblk < 2 || nblk > DF_MAX_NBLK || items < 1) return 0;
-    const int ntiles = df_bulk_tiles(nblk), room = compute_units() / items - nblk;   // (one workgroup per compute unit)
+    const int ntiles = df_bulk_tiles(nblk), room = cus / items - nblk;   // (one workgroup per compute unit)
     const int nbulk = std::min(room, (ntiles + 4) / 5);
     if (nbulk < 1) return 0;
     nt = (ntiles + nbulk - 1) / nbulk;
@@ -1530,33 +1531,35 @@ bool factor_dataflow_ok(int r, int batch, bool whole_batch) {
     if (batch < 1) return false;
     if (nblk == 1) return true;   // factor_inverse_single: workgroups that wait for nobody
     // the whole batch in one launch, or at least one item per launch
-    return dataflow_group(nblk, whole_batch ? batch : 1, nt) != 0;
+    return dataflow_group(nblk, whole_batch ? batch : 1, compute_units(), nt) != 0;
 }
 
 void factor_dataflow_set_spin_limit(int polls) { g_df_spin_limit = polls >= 1 ? polls : DF_SPIN_LIMIT; }
 
 namespace {
 // items of a launch: as many as keep every workgroup of it resident at once
-int dataflow_items(int nblk, int batch) {
-    int nt, n = std::min(batch, compute_units());
-    while (n > 0 && dataflow_group(nblk, n, nt) == 0) --n;
+int dataflow_items(int nblk, int batch, int cus) {
+    if (nblk < 2 || nblk > DF_MAX_NBLK) return 0;
+    int nt, n = std::min(batch, cus / (nblk + 1));   // (a spine and one workgroup beside it)
+    while (n > 0 && dataflow_group(nblk, n, cus, nt) == 0) --n;
     return n;
 }
 }  // namespace
 
-// for the items of one launch, which the next launch takes over: the flag words, then the exchange slots
+// For the items of one launch, which the next launch takes over: the flag words, then the exchange slots.  The size is that of a whole device,
+// which no part of one exceeds: a question about sizes does not touch the GPU.
 size_t factor_dataflow_flag_bytes(int r, int batch) {
     const int nblk = (r + NB - 1) / NB;
-    return (size_t)dataflow_items(nblk, batch) * (DF_FLAG_WORDS + df_wx_words(nblk)) * sizeof(unsigned);
+    return (size_t)dataflow_items(nblk, batch, DF_MAX_CU) * (DF_FLAG_WORDS + df_wx_words(nblk)) * sizeof(unsigned);
 }
 
 hipError_t factor_inverse_dataflow(hipStream_t st, const float* Spart, int nparts, int64_t pstride, float* S, float* dinv, float* Lf, float* Y,
                                    float* Binv, bf16_t* Bh, bf16_t* Bl, unsigned* flags, int r, int r_true, float shift, int zero_all,
                                    int32_t* info, float flag_below, int batch) {
-    const int nblk = (r + NB - 1) / NB, per_launch = dataflow_items(nblk, batch);
+    const int nblk = (r + NB - 1) / NB, cus = compute_units(), per_launch = dataflow_items(nblk, batch, cus);
     int nt = 0;
     if (per_launch < 1) return hipErrorInvalidValue;
-    const int G = dataflow_group(nblk, per_launch, nt);
+    const int G = dataflow_group(nblk, per_launch, cus, nt);
     for (int item0 = 0; item0 < batch; item0 += per_launch) {
         const int n = std::min(batch - item0, per_launch);
         const int64_t o = (int64_t)item0 * r * r;
